@@ -99,7 +99,7 @@ struct Geo {
     static constexpr int TILE = K_BYTES + V_BYTES;
     static constexpr int WAVES = NW * NP;
     static constexpr int THREADS = 64 * WAVES;
-    static constexpr int WAVES_PER_SIMD = WAVES / 4;
+    static constexpr int WAVES_PER_SIMD = D_ == 32 ? 4 : WAVES / 4;
     // tile slots in LDS: NST per query block; the selected phase copies NST - 1 steps ahead.  The 16 KB tiles of
     // d = 128 fill the LDS with two stages; four stages for the smaller tiles of d <= 64 were measured: 0.7 %
     // faster at d = 64 with 180 K tokens, 1 % slower with 57 K, 6 % slower at d = 32 -- hence two everywhere.
@@ -112,11 +112,12 @@ struct Geo {
     static constexpr int SH_IPT = T_INST >= WAVES ? T_INST / WAVES : 1;
     static constexpr int KQ = 2, VQ = 2;        // operand fragments kept in registers (rolling queues)
     static constexpr int OUT_ROW = 2 * D + 8;   // padded bf16 row of the output staging (bytes)
-    static constexpr bool GSUM_REGS = D_ <= 64; // the running gated sum fits the registers beside the accumulators
+    static constexpr bool GSUM_REGS = D_ == 64; // the running gated sum fits the registers beside the accumulators
+    static constexpr bool GSUM_LDS = D_ == 32;
     // d = 128: the running gated sum of the first GSUM_LDS_WAVES wavefronts stays in the LDS the ring leaves free
     // (8 KB each in bf16: 32 of the CU's 160 KB), the others' goes through the scratch buffer in memory
-    static constexpr int GSUM_LDS_WAVES = GSUM_REGS ? 0 : 4;
-    static constexpr int GSUM_LDS_BYTES = 32 * D_ * 2;  // per wavefront
+    static constexpr int GSUM_LDS_WAVES = GSUM_REGS ? 0 : GSUM_LDS ? WAVES : 4;
+    static constexpr int GSUM_LDS_BYTES = 32 * D_ * (GSUM_LDS ? 4 : 2);  // per wavefront
     static constexpr int LDS_BYTES = NSLOT * TILE;
     static_assert(QT == 1 || QT == 2, "");
     static_assert(WAVES % 4 == 0 && WAVES * ROWS * OUT_ROW <= LDS_BYTES, "output staging must fit in the tile slots");
@@ -851,6 +852,11 @@ __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, i
 #pragma unroll
                         for (int j = 0; j < 4; ++j) c.g[qt][dt][4 * gq + j] = v[j];
                     }
+                } else if constexpr (G::GSUM_LDS) {
+                    f32x4 *slot_lds =
+                        reinterpret_cast<f32x4 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
+                    if (branch > 0) v += *slot_lds;
+                    if (branch < 2) *slot_lds = v;
                 } else {
                     // bf16 pairs in accumulator order: 8 bytes per lane and fragment, fully coalesced; in LDS for the
                     // first wavefronts of the workgroup (behind the ring), in the scratch buffer for the others
@@ -1036,7 +1042,7 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
             }
         } else {
             // rows of the routing table: compacted through this wavefront's 512 bytes behind the tile slots
-            int *scratch = reinterpret_cast<int *>(lds + G::LDS_BYTES) + wave * 128;
+            int *scratch = reinterpret_cast<int *>(lds + G::LDS_BYTES + G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES) + wave * 128;
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
                 const int qbp = group * NP + p;
@@ -1347,7 +1353,7 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     a.groups_per_xcd = (a.groups_per_head + 7) / 8;
     // dynamic LDS: the tile slots, then 512 bytes per wavefront for compacting a routing row
     // behind the ring: the routing-row scratch of the selected phase (d <= 64) or the LDS part of the running gated sum
-    constexpr int kLds = G::LDS_BYTES + (G::GSUM_LDS_WAVES > 0 ? G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES : G::WAVES * 512);
+    constexpr int kLds = G::LDS_BYTES + G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES + (D == 128 ? 0 : G::WAVES * 512);
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern = cnt ? (wide ? reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, true>)
                                    : reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, false>))
