@@ -2,14 +2,15 @@
 // each its own softmax, combined by the gated sum, in one kernel.
 //
 // Work decomposition
-//   One 512-thread workgroup owns NP = 4 consecutive query blocks of one head and carries
-//   them through all three branches.  A wavefront holds 32 query rows (two wavefronts per
-//   query block); its state fits 256 registers, so two wavefronts run per SIMD.  In the
-//   compressed and window branches every K/V tile is copied to LDS once and used by all
-//   four query blocks (a ring of 2 NP tile slots, refilled as soon as a slot is free); in
-//   the selected branch each query block streams its own routed blocks (two stages of NP
-//   slots).  Workgroups are numbered so that each of the 8 XCDs walks a contiguous range
-//   of (head, query block) units: the L2 of an XCD then holds one head's pooled
+//   One workgroup owns NP = 2 consecutive query blocks of one head and carries them through all
+//   three branches.  A wavefront holds 32 query rows, two wavefronts a query block.  Each of the
+//   four wavefronts of a workgroup sits on its own SIMD, and as many workgroups share a CU as the
+//   registers of a wavefront allow: two at d = 128, three at d = 64, four at d = 32 (the LDS of a
+//   workgroup is sized for that).  They meet no common barrier, so one's start, epilogues, window
+//   edges and waits are filled by the others.  In the compressed branch every K/V tile is copied
+//   to LDS once and used by both query blocks; in the selected and the window branch each query
+//   block streams its own tiles.  Workgroups are numbered so that each of the 8 XCDs walks a
+//   contiguous range of (head, query block) units: the L2 of an XCD then holds one head's pooled
 //   keys/values and the neighbouring windows / routed blocks.  With grouped-query heads the
 //   query heads that share a key/value head are consecutive, hence run back to back on the
 //   same tile images.
@@ -33,13 +34,13 @@
 // Data movement
 //   K and V are repacked once per call into tile images: per (head, 32-key tile) the exact
 //   bytes of an LDS slot, K fragments then V^T fragments in MFMA operand order (see
-//   issue_shared), head-major so that one head's keys and values are one contiguous range.
+//   read_k and read_v), head-major so that one head's keys and values are one contiguous range.
 //   Tiles are copied global -> LDS with global_load_lds_dwordx4 (no VGPR staging), 1 KB
 //   contiguous on both sides per instruction, the copy instructions of a tile split over
 //   the wavefronts that share it, s_waitcnt vmcnt placed by hand, and read back as
 //   conflict-free ds_read_b128 MFMA fragments.
-//   The gated sum of the branches is carried between branches in registers at d <= 64 and, at d = 128,
-//   where they do not suffice, in a bf16 scratch tile in MFMA-fragment order (fully coalesced); the
+//   The gated sum of the branches is carried between branches in registers and LDS (fp32) at d <= 64 and, at
+//   d = 128, where they do not suffice, in a bf16 scratch tile in MFMA-fragment order (fully coalesced); the
 //   final tile goes through LDS so that the bf16 output rows are written as whole 16-byte chunks.
 #include "lsrm_internal.h"
 
@@ -57,14 +58,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxSeg = 63;
 constexpr float kMinusHuge = -1.0e30f;  // initial running maximum: finite, so no inf - inf
 
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-#define GLB_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
+// Copies 1 KB global -> LDS: lane i's 16 bytes from src + lane_off (lane_off = 16 i) to dst + 16 i.  src and dst are
+// wave-uniform.  Inline assembly on purpose: the compiler counts the builtin both as a vector-memory and as an LDS
+// operation, so that while a copy is in flight every wait for an LDS fragment becomes lgkmcnt(0), i.e. also waits for
+// the fragments requested behind it.  Who waits for the copies themselves is settled by hand (vmcnt before a barrier).
+// Measured, attention step: 0.6 % at d = 32 with 196 K tokens, 0.5 % at d = 64 with 180 K, 0.2 % at d = 128 with 428 K.
+__device__ __forceinline__ void copy_kb_to_lds(const char *src, uint32_t lane_off, const char *dst) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(lane_off), "s"(src) : "memory", "m0");
+}
 
 struct FwdArgs {
     const uint16_t *q;
     const char *kv, *kvc;  // packed tile images of (k, v) and of the pooled (kc, vc)
     const int32_t *idx;    // routing table [NB, topk]
-    const int32_t *sched;  // d = 128: the routing rows in step order, block id | owner << 28 (schedule.hip)
     const float *gates;
     int32_t seg[kMaxSeg + 1];  // window segment offsets (tokens)
     uint16_t *out;
@@ -83,13 +90,28 @@ struct FwdArgs {
     float scale_log2e, scale;
 };
 
-// NP = query blocks per workgroup, QT = 32-row query tiles per wavefront (1 or 2), so a query
+// NP = query blocks per workgroup, QT = 32-row query tiles per wavefront, so a query
 // block is held by NW = 2 / QT wavefronts.
-// LDS is a ring of 2 NP tile slots of 32 keys each (K rows, then the V^T slab).  The shared
-// phases use it as one ring; the selected phase as two stages of NP slots.
-template <int D_, int NP_, int QT_>
+// LDS is 2 NP tile slots of 32 keys each (K fragments, then V^T fragments): one ring in the compressed phase, two
+// stages of NP slots in the others; behind them the part of the running gated sum that stays on chip.
+//
+// Why workgroups of two query blocks: they used to be of four (one workgroup of eight wavefronts per CU at d >= 64),
+// with a ring of eight tiles that all shared in the compressed and window branches.  Traced at d = 64, 57 K tokens, 16
+// routed blocks, window 512: 25 % of a workgroup's time was start, epilogues and filling pipelines, with nothing else
+// on the CU, and the window's 24 shared steps cost as much as 50 compressed ones, because every query block's window
+// edges (masks, redone tiles, a pipeline filled or drained) held up the barrier of all.  Attention step, four query
+// blocks -> six of them with three wavefronts per SIMD and first copies under the epilogues -> two:
+//   16 heads of 64, 57 K tokens 1025 -> 920 -> 797 us, 180 K tokens 4.64 -> 4.12 -> 3.78 ms; 4 heads of 64, 6 K tokens
+//   52 -> 53 -> 39 us; 32 heads of 32 on 2, 196 K tokens 10.8 -> 10.7 (still four) -> 10.6 ms; 16 heads of 128, 428 K
+//   tokens 34.9 -> 34.4 (still four) -> 32.7 ms; 3 heads of 128, 2752 tokens 100 -> 98 (still four) -> 62 us.
+// It won at every size of a sweep over 12 .. 768 blocks and 1, 4, 16 heads.  What it costs is tile copies: the compressed
+// tiles are read by twice as many workgroups, and at d = 128 the routed blocks that four neighbouring rows have in
+// common (about half) are no longer copied once for all four.  Two query blocks with four stages (two workgroups per
+// CU at d = 64): 57 K tokens 860 us, 180 K 4.03 ms.  Three query blocks: two such workgroups do not share a CU at
+// three wavefronts per SIMD, since both put two wavefronts on the same two SIMDs (180 K tokens 5.12 ms).
+template <int D_>
 struct Geo {
-    static constexpr int D = D_, NP = NP_, QT = QT_;
+    static constexpr int D = D_, NP = 2, QT = 1;
     static constexpr int NW = 2 / QT;           // wavefronts per query block
     static constexpr int ROWS = 32 * QT;        // query rows per wavefront
     static constexpr int NS = D / 16;           // 16-channel slabs of the QK^T contraction
@@ -99,29 +121,26 @@ struct Geo {
     static constexpr int TILE = K_BYTES + V_BYTES;
     static constexpr int WAVES = NW * NP;
     static constexpr int THREADS = 64 * WAVES;
-    static constexpr int WAVES_PER_SIMD = D_ == 32 ? 4 : WAVES / 4;
-    // tile slots in LDS: NST per query block; the selected phase copies NST - 1 steps ahead.  The 16 KB tiles of
-    // d = 128 fill the LDS with two stages; four stages for the smaller tiles of d <= 64 were measured: 0.7 %
-    // faster at d = 64 with 180 K tokens, 1 % slower with 57 K, 6 % slower at d = 32 -- hence two everywhere.
-    static constexpr int NST = 2;
+    static constexpr int WAVES_PER_SIMD = D_ == 128 ? 2 : D_ == 64 ? 3 : 4;
+    static constexpr int NST = 2;  // stages per query block in the phases where each streams its own tiles
     static constexpr int NSLOT = NST * NP;
-    static constexpr int T_INST = TILE / 1024;  // 1 KB copy instructions per tile
-    // shared phases: copy instructions per wavefront and tile (a small tile, d = 32, has fewer
-    // instructions than the workgroup has wavefronts: the first T_INST wavefronts issue one each
-    // and the others none, whose waits for SH_IPT copies per tile are then trivially met)
-    static constexpr int SH_IPT = T_INST >= WAVES ? T_INST / WAVES : 1;
+    static constexpr int LDS_BYTES = NSLOT * TILE;
     static constexpr int KQ = 2, VQ = 2;        // operand fragments kept in registers (rolling queues)
     static constexpr int OUT_ROW = 2 * D + 8;   // padded bf16 row of the output staging (bytes)
-    static constexpr bool GSUM_REGS = D_ == 64; // the running gated sum fits the registers beside the accumulators
-    static constexpr bool GSUM_LDS = D_ == 32;
-    // d = 128: the running gated sum of the first GSUM_LDS_WAVES wavefronts stays in the LDS the ring leaves free
-    // (8 KB each in bf16: 32 of the CU's 160 KB), the others' goes through the scratch buffer in memory
-    static constexpr int GSUM_LDS_WAVES = GSUM_REGS ? 0 : GSUM_LDS ? WAVES : 4;
-    static constexpr int GSUM_LDS_BYTES = 32 * D_ * (GSUM_LDS ? 4 : 2);  // per wavefront
-    static constexpr int LDS_BYTES = NSLOT * TILE;
-    static_assert(QT == 1 || QT == 2, "");
-    static_assert(WAVES % 4 == 0 && WAVES * ROWS * OUT_ROW <= LDS_BYTES, "output staging must fit in the tile slots");
-    static_assert((T_INST % WAVES == 0 || WAVES % T_INST == 0) && T_INST % NW == 0 && NSLOT >= 7, "");
+    // The running gated sum (D / 8 fragments of four values per lane).  At d <= 64 it is fp32: the first
+    // GSUM_FRAGS_REGS fragments in registers, the others in LDS.  d = 32: all in LDS (16 KB beside 16 KB of tiles).
+    // d = 64: five of eight in LDS (20 KB beside 32 KB), which leaves 165 of the 168 registers of three wavefronts per SIMD.
+    // d = 128: bf16; that of the first GSUM_LDS_WAVES wavefronts in LDS (16 KB beside 64 KB), that of the
+    // others through the scratch buffer in memory.
+    static constexpr bool GSUM_F32 = D_ <= 64;
+    static constexpr int GSUM_FRAGS_LDS = D_ == 32 ? 4 : 5, GSUM_FRAGS_REGS = GSUM_F32 ? 4 * ND - GSUM_FRAGS_LDS : 0;
+    static constexpr int GSUM_LDS_WAVES = GSUM_F32 ? WAVES : 2;
+    static constexpr int GSUM_LDS_BYTES = GSUM_F32 ? GSUM_FRAGS_LDS * 1024 : 32 * D_ * 2;  // per wavefront
+    // all of it, in bytes; as many workgroups fit a CU's 160 KB as the registers allow
+    static constexpr int LDS_ALL = LDS_BYTES + GSUM_LDS_WAVES * GSUM_LDS_BYTES;
+    static_assert(WAVES == 4 && WAVES_PER_SIMD * LDS_ALL <= 160 * 1024, "");
+    static_assert(QT == 1 && NW == 2, "");
+    static_assert(WAVES * ROWS * OUT_ROW <= LDS_BYTES, "output staging must fit in the tile slots");
 };
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -166,10 +185,10 @@ struct WaveCtx {
     bf16x8 qf[G::QT][G::NS];
     f32x16 o[G::QT][G::ND];
     float m[G::QT], l[G::QT];
-    // running gated sum of the branches, kept in registers where they suffice (d <= 64); at d = 128 it goes
-    // through a bf16 scratch tile in global memory instead (fp32 there cost 1.8 % of the kernel for 7 % less
+    // running gated sum of the branches: the fragments kept in registers (d = 64).  At d = 128 it goes
+    // through a bf16 scratch tile in LDS or global memory instead (fp32 there cost 1.8 % of the kernel for 7 % less
     // rounding error in `out`, whose own bf16 rounding and that of the probabilities dominate either way)
-    f32x16 g[G::QT][G::GSUM_REGS ? G::ND : 1];
+    f32x4 g[G::QT][G::GSUM_FRAGS_REGS > 0 ? G::GSUM_FRAGS_REGS : 1];
     int lo[G::QT], hi[G::QT];   // valid key range of this lane's queries in mask coordinates
     uint32_t lane16;            // lane * 16: byte offset of this lane inside any 1 KB fragment or copy instruction
 };
@@ -185,17 +204,6 @@ struct WaveCtx {
 // (Gathering the K fragments straight from the caller's [N, H, d] tensor instead -- every copy
 // instruction touching 32 rows -- was measured: the attention kernel lost more than the packing
 // pass costs.)
-
-// Shared phases: the wavefronts of the workgroup split the T_INST copy instructions of a tile.
-template <class G>
-__device__ __forceinline__ void issue_shared(const WaveCtx<G> &c, const char *tile, char *slot, int wave) {
-    if (G::T_INST < G::WAVES && wave >= G::T_INST) return;
-#pragma unroll
-    for (int j = 0; j < G::SH_IPT; ++j) {
-        const int i = wave + G::WAVES * j;
-        __builtin_amdgcn_global_load_lds(GLB_PTR(tile + i * 1024 + c.lane16), LDS_PTR(slot + i * 1024), 16, 0, 0);
-    }
-}
 
 template <class G>
 __device__ __forceinline__ void reset_branch(WaveCtx<G> &c) {
@@ -441,247 +449,124 @@ __device__ __forceinline__ void pv_drain(WaveCtx<G> &c, bf16x8 (&vq)[G::VQ], con
     }
 }
 
-// Shared phase (compressed and window branches): every tile is used by all query blocks of
-// the workgroup.  Tiles go through the ring of NSLOT slots; a slot is refilled as soon as
-// every wavefront is done with it.
-//   src(t)  -> global address of the image of tile t (uniform over the workgroup)
-//   msk(t)  -> (j0, need_mask, cap) of tile t for this wavefront: keys outside the lane's [lo, hi) or at and
-//              beyond cap are masked; tiles in [mf_lo, mf_hi) need none
-// Step t runs mfma_block with QK of tile t+1, the exponentials of tile t and PV of tile t-1,
-// reloading its operand registers on the fly with the K fragments of tile t+2 and the V
-// fragments of tile t.  Once per step (one barrier) the slot of tile t-2 is refilled with
-// tile t-2+NSLOT, and after the block the row sums of tile t decide whether it must be redone
-// against a higher running maximum (close_tile).  Every wavefront runs every step: a tile outside a wavefront's own key range is
-// simply fully masked (the step body is kept unconditional on purpose -- a conditional
-// update of the accumulator tuples makes the compiler shuffle them through copies).
-// Scores and probabilities alternate between two register sets (index = tile parity), so
-// nothing is copied from step to step.
-// [w_lo, w_hi): the steps whose tiles this wavefront's queries can see at all.  Outside it the wavefront only keeps
-// the ring going (waits, barriers, its share of the copies): in the window branch the four query blocks of a
-// workgroup see 34 of the 40 tiles the workgroup streams.  w_lo is rounded down to an even step (the register set
-// of a tile is its parity).
-template <class G, typename SrcFn, typename MaskFn>
-__device__ __forceinline__ void run_shared(WaveCtx<G> &c, int n_steps, int w_lo, int w_hi, SrcFn src, MaskFn msk,
-                                           int mf_lo, int mf_hi, char *lds, int wave, int lane, float sl2) {
-    constexpr int R = G::NSLOT, QT = G::QT;
-    constexpr bool PAR = true;  // scores and probabilities alternate between two register sets by tile parity
-    if (n_steps <= 0) return;
-    w_hi = min(w_hi, n_steps);
-    w_lo = max(w_lo, 0) & ~1;
-    if (w_hi <= w_lo) w_lo = w_hi = 0;
-    auto slot = [&](int t) { return lds + (t % R) * G::TILE; };
-    auto lslot = [&](int t) { return lds + (t % R) * G::TILE + c.lane16; };  // this lane's fragment base
-    // The two wavefronts that share a SIMD (w and w + 4 of an 8-wavefront workgroup) run half a
-    // step apart: one meets the step's barrier before its MFMA block, the other after it, so
-    // one's latency-bound work between blocks coincides with the other's MFMA block.
-    const bool lag = G::WAVES == 8 && wave >= 4;
-    // (LDS reads only: no copy is in flight at the end of a phase, and the stores the previous branch's epilogue has
-    // just issued -- outputs, the gated-sum scratch -- need not have been acknowledged before the first copies of this
-    // phase go out; they are older than those copies, so the counted waits below cover them)
+// Every wavefront is done with the tile slots of the phase that ends here.
+// (LDS reads only: no copy is in flight at the end of a phase, and stores issued earlier -- outputs, the gated-sum
+// scratch -- need not have been acknowledged before the first copies of the next phase go out; they are older than
+// those copies, so the counted waits of its first steps still cover them)
+__device__ __forceinline__ void end_phase() {
     __builtin_amdgcn_s_waitcnt(kLgkmOnly);
-    wg_barrier();  // every wavefront is done with the slots (previous phase)
-    for (int t = 0; t < R && t < n_steps; ++t) issue_shared<G>(c, src(t), slot(t), wave);
-    // tiles 0, 1 and 2 must have landed before the first block reads them
-    if (n_steps >= R)
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 3) * G::SH_IPT));
-    else
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     wg_barrier();
-    bf16x8 kq[G::KQ], vq[G::VQ];
-    f32x16 S[2][QT];         // scores
-    uint32_t P[2][QT][8];    // probabilities
-    int j0, cap;  // first key of the tile; keys at or beyond `cap` are inactive slots
-    bool need_mask;
-    float psum[QT];
-
-    // One workgroup barrier per step keeps the ring consistent.  Before barrier t a wavefront has
-    // finished (at least) MFMA block t-1 and waited for its own copies of tiles <= t+3; after it,
-    // tile t+3 is complete for everyone and nobody reads tile t-2 any more, whose slot is refilled.
-    // Copies issued before the wait: tiles 0 .. t-3+R; tiles t+4 and later may stay in flight
-    // (near the end of the phase fewer are outstanding: wait for all).
-    auto sync = [&](int t) {
-        if (t >= 2 && t - 3 + R < n_steps)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 6) * G::SH_IPT));
-        else if (t == 1 && n_steps >= R)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 5) * G::SH_IPT));
-        else if (t == 0 && n_steps >= R)
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 4) * G::SH_IPT));
-        else
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        wg_barrier();
-        if (t >= 2 && t - 2 + R < n_steps) issue_shared<G>(c, src(t - 2 + R), slot(t - 2), wave);
-    };
-    // After an MFMA block: mask the scores just produced (s_next, tile t+1) where the tile needs it,
-    // and close tile t (scores s, probabilities pu: redone if their row sums say so).
-    auto post = [&](int t, const f32x16 (&s)[QT], f32x16 (&s_next)[QT], uint32_t (&pu)[QT][8]) {
-        msk(t + 1, &j0, &need_mask, &cap);
-        if (__builtin_expect(need_mask, 0)) {
-            mfma_settle();  // s_next comes from the MFMAs just issued
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) mask_scores(c.lo[qt], min(c.hi[qt], cap), s_next[qt], j0, lane);
-        }
-        close_tile<G>(c, s, pu, psum, sl2);
-    };
-    // Scores and probabilities of tile t live in S[A], P[A]: with PAR, A is the parity of t and
-    // nothing is copied from step to step; without, A = 0 and the sets are copied after a step.
-    auto rotate = [&]() {
-        if (!PAR) {
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                S[0][qt] = S[1][qt];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) P[1][qt][k] = P[0][qt][k];
-            }
-        }
-    };
-    // The same two pieces for the steps in the middle of a phase, where nothing is conditional:
-    // every copy exists and the tile needs no mask.
-    auto sync_fast = [&](int t) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((R - 6) * G::SH_IPT));
-        wg_barrier();
-        issue_shared<G>(c, src(t - 2 + R), slot(t - 2), wave);
-    };
-    auto post_fast = [&](const f32x16 (&s)[QT], uint32_t (&pu)[QT][8]) { close_tile<G>(c, s, pu, psum, sl2); };
-    // QK(t+1) || exp(t) || PV(t-1); the queues move on to K(t+2) and V(t)  (stale slots past the end: unused)
-    auto full_step = [&](auto par, auto fast, int t) {
-        constexpr int A = PAR ? decltype(par)::value : 0;
-        constexpr bool FAST = decltype(fast)::value;
-        if (lag) {
-            if constexpr (FAST) sync_fast(t); else sync(t);
-        }
-        mfma_block<G, true, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, lslot(t + 1), lslot(t + 2),
-                                  lslot(t - 1), lslot(t));
-        if (!lag) {
-            if constexpr (FAST) sync_fast(t); else sync(t);
-        }
-        if constexpr (FAST) post_fast(S[A], P[A]); else post(t, S[A], S[A ^ 1], P[A]);
-        rotate();
-    };
-    // exp(n-1) || PV(n-2); then the drain: PV of the last tile
-    auto last_step = [&](auto par, int t) {
-        constexpr int A = PAR ? decltype(par)::value : 0;
-        mfma_block<G, false, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, nullptr, nullptr,
-                                   lslot(t - 1), lslot(t));
-        close_tile<G>(c, S[A], P[A], psum, sl2);
-        pv_drain<G>(c, vq, P[A], lslot(t));
-    };
-    using Even = std::integral_constant<int, 0>;
-    using Odd = std::integral_constant<int, 1>;
-    // full steps t0 .. t1-1
-    auto run_range = [&](int t0, int t1, auto fast) {
-        int t = t0;
-        if constexpr (PAR) {
-            if (t < t1 && (t & 1) == 0) {
-                full_step(Even{}, fast, t);
-                ++t;
-            }
-            for (; t + 1 < t1; t += 2) {
-                full_step(Odd{}, fast, t);
-                full_step(Even{}, fast, t + 1);
-            }
-            if (t < t1) full_step(Odd{}, fast, t);
-        } else {
-            for (; t < t1; ++t) full_step(Even{}, fast, t);
-        }
-    };
-
-    // barriers 0 .. n_steps - 2 in all, whatever the wavefront's own range is
-    int ts = 0;  // the next barrier
-    auto idle_to = [&](int upto) {
-        for (; ts < upto; ++ts) sync(ts);
-    };
-    if (w_hi <= w_lo) {
-        idle_to(n_steps - 1);
-        return;
-    }
-    idle_to(w_lo);  // (behind barrier w_lo - 1 tiles up to w_lo + 2 are complete for everyone)
-    {
-        bf16x8 kf[G::NS];
-        read_k<G>(c, slot(w_lo), kf);
-        qk_scores<G>(c, kf, S[0]);
-    }
-    // prime the queues: first K fragments of the second tile (stale but finite data if there is none), first V
-    // fragments of the first
-#pragma unroll
-    for (int i = 0; i < G::KQ; ++i) kq[i] = *reinterpret_cast<const bf16x8 *>(lslot(w_lo + 1) + i * 1024);
-#pragma unroll
-    for (int f = 0; f < G::VQ; ++f) vq[f] = *reinterpret_cast<const bf16x8 *>(lslot(w_lo) + G::K_BYTES + f * 1024);
-    msk(w_lo, &j0, &need_mask, &cap);
-    if (need_mask) {
-        mfma_settle();  // the mask reads the scores the MFMAs above produce
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt) mask_scores(c.lo[qt], min(c.hi[qt], cap), S[0][qt], j0, lane);
-    }
-    if (w_hi - w_lo >= 2) {
-        // QK(w_lo + 1) || exp(w_lo)
-        if (lag) sync(w_lo);
-        mfma_block<G, true, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, lslot(w_lo + 1), lslot(w_lo + 2), nullptr,
-                                   nullptr);
-        if (!lag) sync(w_lo);
-        post(w_lo, S[0], S[1], P[0]);
-        rotate();
-        // full steps w_lo + 1 .. w_hi - 2; those in [t_lo, t_hi) take the unconditional path
-        const int t_end = w_hi - 1;
-        int t_lo = max(max(2, w_lo + 1), mf_lo - 1), t_hi = min(n_steps - R + 2, mf_hi - 1);
-        t_lo = min(t_lo, t_end);
-        t_hi = max(min(t_hi, t_end), t_lo);
-        run_range(w_lo + 1, t_lo, std::false_type{});
-        run_range(t_lo, t_hi, std::true_type{});
-        run_range(t_hi, t_end, std::false_type{});
-        if (PAR && (t_end & 1))
-            last_step(Odd{}, t_end);
-        else
-            last_step(Even{}, t_end);
-        ts = w_hi - 1;
-    } else {
-        mfma_block<G, false, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, nullptr, nullptr, nullptr, nullptr);
-        close_tile<G>(c, S[0], P[0], psum, sl2);
-        pv_drain<G>(c, vq, P[0], lslot(w_lo));
-        ts = w_lo;
-    }
-    idle_to(n_steps - 1);
 }
 
-// Selected phase: each query block streams its own routed blocks in 32-key tiles through its NST
-// slots; its two wavefronts split the copies, and all wavefronts meet at a workgroup barrier every step.
-// CNT: blocks may hold fewer than 64 active tokens; valid(t) is the number of active keys of tile t
-// (0..32) and the scores of the others are masked.
-// Three tiles are in flight like in the shared phases: step t of a query block runs
-// mfma_block with QK of its tile t+1, the exponentials of tile t and PV of tile t-1, so every MFMA
-// has its share of the exponentials behind it.  Tile tau lives in stage tau mod NST of the block's NST
-// slots, K and V parts copied separately.  Barrier t comes before step t; behind it K(t) and
-// V(t-2) are dead, and K(t+NST) and V(t+NST-2) are copied over them, NST-1 steps ahead of their use.
-// The operand queues are primed from LDS at the start of every step (the next tile's fragments are
-// still in flight while a step runs, so the queues cannot roll across tiles).
-// Steps 0 .. n (the last one is the PV of tile n-1); every wavefront meets barriers 0 .. n_steps.
-template <class G, bool CNT, typename SrcFn, typename OwnFn, typename ValidFn>
-__device__ __forceinline__ void run_own(WaveCtx<G> &c, int n_steps, int my_steps, SrcFn src, OwnFn own, ValidFn valid,
-                                         char *lds, int qbi, int sub, int lane, float sl2) {
-    constexpr int NP = G::NP;
-    if (n_steps <= 0) return;
+// A phase streams tiles of 32 keys through LDS, K and V parts copied separately.  Where a tile comes from, which slot
+// it lives in and who copies it is the business of a Tiles object:
+//   OwnTiles     selected and window branch: each query block streams its own tiles through NST slots of its own, its
+//                two wavefronts split the copies
+//   SharedTiles  compressed branch: both query blocks use the same tiles, which go through one ring of NSLOT slots,
+//                copied by all wavefronts together
+// Both have: n (tiles of this query block), NST (tile tau lives in slot tau mod NST), PER_STEP (copies a wavefront issues
+// per step), begin() (the first copies of the phase).  begin() is separate from run_tiles so that the epilogue of the previous
+// branch -- at the start of the kernel, the loads of the query rows and of the routing rows -- runs while the first
+// tiles are on their way.
+template <class G, typename SrcFn>
+struct OwnTiles {
+    static constexpr int NP = G::NP, NST = G::NST;
+    static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
     static_assert(G::NW == 2 && G::QT == 1, "two wavefronts per query block");
-    constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW;
-    const int n = my_steps;
-    constexpr int NST = G::NST;
     static_assert((NST & (NST - 1)) == 0 && NST >= 2, "");
-    // tile tau of this query block lives in the slot of its owner: the query block of the group that copies it (this
-    // one, unless the step schedule lets a lower-numbered query block of the group meet the same key block at the
-    // same step: the tile is then copied once and read by all of them)
-    auto stage = [&](int tau) { return lds + ((tau & (NST - 1)) * NP + own(tau)) * G::TILE; };
-    auto lstage = [&](int tau) { return stage(tau) + c.lane16; };
-    auto issue_part = [&](const char *tile, char *slot, int n_inst) {
+    const int n;  // tiles of this query block
+    const SrcFn src;  // address of the image of tile tau
+    char *const lds;
+    const int qbi, sub;
+    const uint32_t lane16;
+    __device__ __forceinline__ char *stage(int tau) const { return lds + ((tau & (NST - 1)) * NP + qbi) * G::TILE; }
+    __device__ __forceinline__ void issue_part(const char *tile, char *slot, int n_inst) const {
 #pragma unroll 8
         for (int j = 0; j < n_inst; ++j) {
             const int i = sub + G::NW * j;
-            __builtin_amdgcn_global_load_lds(GLB_PTR(tile + i * 1024 + c.lane16), LDS_PTR(slot + i * 1024), 16, 0, 0);
+            copy_kb_to_lds(tile + i * 1024, lane16, slot + i * 1024);
         }
-    };
-    auto issue_k = [&](int tau) {
-        if (own(tau) == qbi) issue_part(src(tau), stage(tau), KI);
-    };
-    auto issue_v = [&](int tau) {
-        if (own(tau) == qbi) issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
-    };
+    }
+    __device__ __forceinline__ void issue_k(int tau) const {
+        issue_part(src(tau), stage(tau), KI);
+    }
+    __device__ __forceinline__ void issue_v(int tau) const {
+        issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
+    }
+    // the first copies of the phase (the slots are free)
+    __device__ __forceinline__ void begin() const {
+#pragma unroll
+        for (int tau = 0; tau < NST; ++tau)
+            if (tau < n) issue_k(tau);
+#pragma unroll
+        for (int tau = 0; tau < NST - 2; ++tau)
+            if (tau < n) issue_v(tau);
+    }
+};
+
+template <class G, typename SrcFn>
+__device__ __forceinline__ OwnTiles<G, SrcFn> own_tiles(int n, SrcFn src, char *lds, int qbi, int sub, uint32_t lane16) {
+    return OwnTiles<G, SrcFn>{n, src, lds, qbi, sub, lane16};
+}
+
+template <class G>
+struct SharedTiles {
+    static constexpr int NST = G::NSLOT, KN = G::K_BYTES / 1024, VN = G::V_BYTES / 1024;
+    static constexpr int KI = (KN + G::WAVES - 1) / G::WAVES, VI = (VN + G::WAVES - 1) / G::WAVES;
+    static constexpr int KW = KN / KI, VW = VN / VI;  // wavefronts that copy: the first KW the K part, the last VW the V part
+    // copies per wavefront and step: both parts, or (d = 32, two instructions each) one of them
+    static constexpr int PER_STEP = KW + VW <= G::WAVES ? KI : KI + VI;
+    static_assert(KI == VI && KW == VW && (KW == G::WAVES || KW + VW == G::WAVES), "");
+    static_assert(KW * KI == KN && VW * VI == VN, "");
+    const int n;
+    const char *const base;
+    char *const lds;
+    const int wave;
+    const uint32_t lane16;
+    __device__ __forceinline__ char *stage(int tau) const { return lds + (tau & (NST - 1)) * G::TILE; }
+    __device__ __forceinline__ void issue_k(int tau) const {
+        if (KW < G::WAVES && wave >= KW) return;
+#pragma unroll
+        for (int j = 0; j < KI; ++j) {
+            const int i = wave + KW * j;
+            copy_kb_to_lds(base + (int64_t)tau * G::TILE + i * 1024, lane16, stage(tau) + i * 1024);
+        }
+    }
+    __device__ __forceinline__ void issue_v(int tau) const {
+        if (VW < G::WAVES && wave < G::WAVES - VW) return;
+#pragma unroll
+        for (int j = 0; j < VI; ++j) {
+            const int i = (VW < G::WAVES ? wave - (G::WAVES - VW) : wave) + VW * j;
+            copy_kb_to_lds(base + (int64_t)tau * G::TILE + G::K_BYTES + i * 1024, lane16, stage(tau) + G::K_BYTES + i * 1024);
+        }
+    }
+    __device__ __forceinline__ void begin() const {
+#pragma unroll
+        for (int tau = 0; tau < NST; ++tau)
+            if (tau < n) issue_k(tau);
+#pragma unroll
+        for (int tau = 0; tau < NST - 2; ++tau)
+            if (tau < n) issue_v(tau);
+    }
+};
+
+// Three tiles are in flight in a wavefront: step t runs
+// mfma_block with QK of its tile t+1, the exponentials of tile t and PV of tile t-1, so every MFMA
+// has its share of the exponentials behind it.  Scores and probabilities alternate between two register sets
+// (index = tile parity), so nothing is copied from step to step.  Barrier t comes before step t; behind it K(t) and
+// V(t-2) are dead, and K(t+NST) and V(t+NST-2) are copied over them, NST-1 steps ahead of their use.
+// The operand queues are primed from LDS at the start of every step (the next tile's fragments may
+// still be in flight while a step runs, so the queues do not roll across tiles).
+// mask_tile(t, s) masks the scores of the keys of tile t that the query block does not see.
+// Steps 0 .. n (the last one is the PV of tile n-1); every wavefront meets barriers 0 .. n_steps, the largest n of
+// the workgroup.
+template <class G, typename Tiles, typename MaskFn>
+__device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tiles &tiles, MaskFn mask_tile, float sl2) {
+    if (n_steps <= 0) return;
+    constexpr int NST = Tiles::NST;
+    const int n = tiles.n;
+    auto stage = [&](int tau) { return tiles.stage(tau); };
+    auto lstage = [&](int tau) { return tiles.stage(tau) + c.lane16; };
     // barrier t: K(t+1) and V(t-1) have landed (both were issued behind barrier t+1-NST; what the NST-2
     // barriers since then issued may stay in flight) and every LDS read of this wavefront is done.  Every
     // wavefront waits for its own copies before the barrier, so behind it the tiles are there for all
@@ -689,12 +574,12 @@ __device__ __forceinline__ void run_own(WaveCtx<G> &c, int n_steps, int my_steps
     // barrier t (K of step t, V of step t-2) are dead for all of them.
     auto sync = [&](int t) {
         if (NST > 2 && t + NST - 1 < n)
-            __builtin_amdgcn_s_waitcnt(vm_lgkm_imm((NST - 2) * (KI + VI)));
+            __builtin_amdgcn_s_waitcnt(vm_lgkm_imm((NST - 2) * Tiles::PER_STEP));
         else
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         wg_barrier();
-        if (t + NST < n) issue_k(t + NST);
-        if (t + NST - 2 < n) issue_v(t + NST - 2);
+        if (t + NST < n) tiles.issue_k(t + NST);
+        if (t + NST - 2 < n) tiles.issue_v(t + NST - 2);
     };
     bf16x8 kq[G::KQ], vq[G::VQ];
     f32x16 S[2][1];
@@ -708,28 +593,9 @@ __device__ __forceinline__ void run_own(WaveCtx<G> &c, int n_steps, int my_steps
 #pragma unroll
         for (int f = 0; f < G::VQ; ++f) vq[f] = *reinterpret_cast<const bf16x8 *>(ls + G::K_BYTES + f * 1024);
     };
-    auto mask_next = [&](int t, f32x16 &s_next) {
-        if constexpr (CNT) {
-            if (t + 1 < n) {
-                const int vld = valid(t + 1);
-                if (vld < 32) {
-                    mfma_settle();
-                    mask_scores(0, vld, s_next, 0, lane);
-                }
-            }
-        }
+    auto mask_next = [&](int t, f32x16 &s_next) {  // (an empty body where no tile can need a mask)
+        if (t + 1 < n) mask_tile(t + 1, s_next);
     };
-    // (LDS reads only: no copy is in flight at the end of a phase, and the stores the previous branch's epilogue has
-    // just issued -- outputs, the gated-sum scratch -- need not have been acknowledged before the first copies of this
-    // phase go out; they are older than those copies, so the counted waits below cover them)
-    __builtin_amdgcn_s_waitcnt(kLgkmOnly);
-    wg_barrier();  // every wavefront is done with the slots (previous phase)
-#pragma unroll
-    for (int tau = 0; tau < NST; ++tau)
-        if (tau < n) issue_k(tau);
-#pragma unroll
-    for (int tau = 0; tau < NST - 2; ++tau)
-        if (tau < n) issue_v(tau);
     __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
     wg_barrier();
     if (n > 0) {
@@ -843,20 +709,17 @@ __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, i
 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[j] = w * c.o[qt][dt][4 * gq + j];
                 if (a.gate_channels) v *= gch[8 * dt + 2 * gq];  // channels 32 dt + 8 gq + 4 hh + 0..3
-                if constexpr (G::GSUM_REGS) {
-                    if (branch > 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) v[j] += c.g[qt][dt][4 * gq + j];
+                if constexpr (G::GSUM_F32) {
+                    const int f = dt * 4 + gq;
+                    if (f < G::GSUM_FRAGS_REGS) {
+                        if (branch > 0) v += c.g[qt][f];
+                        if (branch < 2) c.g[qt][f] = v;
+                    } else {
+                        f32x4 *slot_lds = reinterpret_cast<f32x4 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) +
+                                          (f - G::GSUM_FRAGS_REGS) * 64 + lane;
+                        if (branch > 0) v += *slot_lds;
+                        if (branch < 2) *slot_lds = v;
                     }
-                    if (branch < 2) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) c.g[qt][dt][4 * gq + j] = v[j];
-                    }
-                } else if constexpr (G::GSUM_LDS) {
-                    f32x4 *slot_lds =
-                        reinterpret_cast<f32x4 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
-                    if (branch > 0) v += *slot_lds;
-                    if (branch < 2) *slot_lds = v;
                 } else {
                     // bf16 pairs in accumulator order: 8 bytes per lane and fragment, fully coalesced; in LDS for the
                     // first wavefronts of the workgroup (behind the ring), in the scratch buffer for the others
@@ -867,7 +730,7 @@ __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, i
                                   ((gtile * a.h + head) * (G::ND * 4) + dt * 4 + gq) * 64 + lane;
                     uint2 *slot_lds =
                         reinterpret_cast<uint2 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
-                    const bool in_lds = wave < G::GSUM_LDS_WAVES;
+                    const bool in_lds = G::GSUM_LDS_WAVES == G::WAVES || wave < G::GSUM_LDS_WAVES;
                     if (branch > 0) {
                         // (address spaces spelled out: one pointer that may be either would become a flat load)
                         unsigned long long raw;
@@ -983,9 +846,12 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 
     WaveCtx<G> c;
     c.lane16 = (uint32_t)lane * 16u;
-    // A fully masked step may read a slot that no copy has filled yet: make sure it holds
-    // finite values (0 * NaN would poison the accumulators).
-    for (int off = threadIdx.x * 16; off < G::LDS_BYTES; off += G::THREADS * 16)
+    // The first copies go out before anything else.  A fully masked step may read a slot that no copy has filled: make
+    // sure such slots hold finite values (0 * NaN would poison the accumulators).
+    const int n_cmp = (a.nbc + 31) / 32;
+    const SharedTiles<G> cmp_tiles{n_cmp, a.kvc + head_kvc, lds, wave, c.lane16};
+    cmp_tiles.begin();
+    for (int off = n_cmp * G::TILE + threadIdx.x * 16; off < G::LDS_BYTES; off += G::THREADS * 16)
         *reinterpret_cast<uint4 *>(lds + off) = make_uint4(0, 0, 0, 0);
     {
         // (an inactive wavefront reads the rows of block 0: finite values, results discarded)
@@ -997,6 +863,56 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
         }
     }
 
+    // ---------------- this query block's routing row, read while the first compressed tiles are copied;
+    // valid entries first: entry u sits in lane u % 64 of register u / 64
+    constexpr int NR = WIDE ? 2 : 1;
+    int packed[NR], pcount[NR], my_valid = 0, max_valid = 0;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) packed[j] = -1, pcount[j] = 0;
+    {
+        // rows of the routing table: compacted through 512 bytes per wavefront of the LDS that will hold gated sums
+        static_assert(G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES >= 512 * G::WAVES, "");
+        int *scratch = reinterpret_cast<int *>(lds + G::LDS_BYTES + wave * 512);
+        int raw[NP][NR];  // (all loads in flight together; lanes past the end of a row read its first entry)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                const int col = lane + 64 * j;
+                raw[p][j] = a.topk > 0 ? a.idx[(int64_t)min(group * NP + p, a.nb - 1) * a.topk + (col < a.topk ? col : 0)] : -1;
+            }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int qbp = group * NP + p;
+            int v[NR], n_valid = 0;
+            unsigned long long bal[NR];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                v[j] = (qbp < a.nb && lane + 64 * j < a.topk) ? raw[p][j] : -1;
+                if (v[j] >= a.nb) v[j] = -1;
+                bal[j] = __ballot(v[j] >= 0);
+                n_valid += __popcll(bal[j]);
+            }
+            max_valid = max(max_valid, n_valid);
+            if (p == qbi) {
+                int before = 0;
+#pragma unroll
+                for (int j = 0; j < NR; ++j) {
+                    if (v[j] >= 0) scratch[before + __popcll(bal[j] & ((1ull << lane) - 1ull))] = v[j];
+                    before += __popcll(bal[j]);
+                }
+                // (LDS operations of a wavefront complete in order: the reads below see the writes above)
+#pragma unroll
+                for (int j = 0; j < NR; ++j) packed[j] = lane + 64 * j < n_valid ? scratch[lane + 64 * j] : -1;
+                my_valid = n_valid;
+            }
+        }
+    }
+    if constexpr (CNT) {
+#pragma unroll
+        for (int j = 0; j < NR; ++j) pcount[j] = lane + 64 * j < my_valid ? a.count[packed[j]] : 0;
+    }
+
     // ---------------- compressed branch: all NB pooled pairs
     {
         reset_branch<G>(c);
@@ -1005,76 +921,17 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
             c.lo[qt] = 0;
             c.hi[qt] = a.nbc;
         }
-        const int n_steps = (a.nbc + 31) / 32;
-        const char *base = a.kvc + head_kvc;
-        auto src = [&](int t) { return base + t * tile_stride; };
-        auto msk = [&](int t, int *j0, bool *need, int *cap) {
-            *j0 = 32 * t;
-            *need = 32 * t + 32 > a.nbc;
-            *cap = 0x7fffffff;
+        auto mask_tile = [&](int t, f32x16 &sc) {
+            if (32 * t + 32 > a.nbc) {
+                mfma_settle();
+                mask_scores(0, a.nbc, sc, 32 * t, lane);
+            }
         };
-        run_shared<G>(c, n_steps, 0, n_steps, src, msk, 0, a.nbc / 32, lds, wave, lane, sl2);
-        if (active) finish_branch<G>(c, a, 0, row0, head, wave, lane, lds);
+        run_tiles<G>(c, n_cmp, cmp_tiles, mask_tile, sl2);
     }
 
     // ---------------- selected branch: every token of the routed blocks
     {
-        reset_branch<G>(c);
-        // this query block's routing row, valid entries first: entry u sits in lane u % 64 of register u / 64
-        constexpr int NR = WIDE ? 2 : 1;
-        int packed[NR], pcount[NR], my_valid = 0, max_valid = 0;
-#pragma unroll
-        for (int j = 0; j < NR; ++j) packed[j] = -1, pcount[j] = 0;
-        if constexpr (D == 128) {
-            // rows of the step schedule (schedule.hip): already compact, block id | owner << 28
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                int n_valid = 0;
-#pragma unroll
-                for (int j = 0; j < NR; ++j) {
-                    const int col = lane + 64 * j;
-                    const int v = col < a.topk ? a.sched[((int64_t)group * NP + p) * a.topk + col] : -1;
-                    n_valid += __popcll(__ballot(v >= 0));
-                    if (p == qbi) packed[j] = v;
-                }
-                max_valid = max(max_valid, n_valid);
-                if (p == qbi) my_valid = n_valid;
-            }
-        } else {
-            // rows of the routing table: compacted through this wavefront's 512 bytes behind the tile slots
-            int *scratch = reinterpret_cast<int *>(lds + G::LDS_BYTES + G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES) + wave * 128;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int qbp = group * NP + p;
-                int v[NR], n_valid = 0;
-                unsigned long long bal[NR];
-#pragma unroll
-                for (int j = 0; j < NR; ++j) {
-                    const int col = lane + 64 * j;
-                    v[j] = (qbp < a.nb && col < a.topk) ? a.idx[(int64_t)qbp * a.topk + col] : -1;
-                    if (v[j] >= a.nb) v[j] = -1;
-                    bal[j] = __ballot(v[j] >= 0);
-                    n_valid += __popcll(bal[j]);
-                }
-                max_valid = max(max_valid, n_valid);
-                if (p == qbi) {
-                    int before = 0;
-#pragma unroll
-                    for (int j = 0; j < NR; ++j) {
-                        if (v[j] >= 0) scratch[before + __popcll(bal[j] & ((1ull << lane) - 1ull))] = v[j];
-                        before += __popcll(bal[j]);
-                    }
-                    // (LDS operations of a wavefront complete in order: the reads below see the writes above)
-#pragma unroll
-                    for (int j = 0; j < NR; ++j) packed[j] = lane + 64 * j < n_valid ? scratch[lane + 64 * j] : -1;
-                    my_valid = n_valid;
-                }
-            }
-        }
-        if constexpr (CNT) {
-#pragma unroll
-            for (int j = 0; j < NR; ++j) pcount[j] = lane + 64 * j < my_valid ? a.count[packed[j] & 0xFFFFFF] : 0;
-        }
         // entry u of the row / of the counts (wave-uniform u)
         auto entry = [&](int u) {
             if constexpr (WIDE) {
@@ -1085,9 +942,7 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
             }
         };
         const char *base = a.kv + head_kv;
-        auto src = [&](int t) { return base + (2 * (entry(t >> 1) & 0xFFFFFF) + (t & 1)) * tile_stride; };
-        // the query block whose wavefronts copy this query block's tile of step t (always itself without a schedule)
-        auto own = [&](int t) { return D == 128 ? (entry(t >> 1) >> 28) & 3 : qbi; };
+        auto src = [&](int t) { return base + (2 * entry(t >> 1) + (t & 1)) * tile_stride; };
         auto valid = [&](int t) {  // active keys of tile t of this query block's list
             const int u = t >> 1;
             int cnt;
@@ -1099,24 +954,33 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
             }
             return min(32, max(0, cnt - 32 * (t & 1)));
         };
-        run_own<G, CNT>(c, 2 * max_valid, 2 * my_valid, src, own, valid, lds, qbi, sub, lane, sl2);
-        if (active) finish_branch<G>(c, a, 1, row0, head, wave, lane, lds);
+        auto mask_tile = [&](int t, f32x16 &sc) {
+            if constexpr (CNT) {
+                const int vld = valid(t);
+                if (vld < 32) {
+                    mfma_settle();
+                    mask_scores(0, vld, sc, 0, lane);
+                }
+            }
+        };
+        const auto tiles = own_tiles<G>(2 * my_valid, src, lds, qbi, sub, c.lane16);
+        end_phase();
+        tiles.begin();
+        if (active) finish_branch<G>(c, a, 0, row0, head, wave, lane, lds);
+        reset_branch<G>(c);
+        run_tiles<G>(c, 2 * max_valid, tiles, mask_tile, sl2);
     }
 
     // ---------------- window branch: keys j with -W/2 <= j - i < W/2 inside the segment
     {
-        reset_branch<G>(c);
-        WinRange mine = window_range(a, active ? qb : 0);
-        int st_min = 0x7fffffff, st_max = 0;
+        const WinRange mine = window_range(a, active ? qb : 0);
+        int n_max = 0;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int qbp = group * NP + p;
             if (qbp < a.nb) {
-                WinRange w = window_range(a, qbp);
-                if (w.st1 > w.st0) {
-                    st_min = min(st_min, w.st0);
-                    st_max = max(st_max, w.st1);
-                }
+                const WinRange w = window_range(a, qbp);
+                n_max = max(n_max, w.st1 - w.st0);
             }
         }
         {
@@ -1128,40 +992,40 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
                 c.hi[qt] = min(mine.seg_hi, i + half_w);
             }
         }
-        const int n_steps = st_max > st_min ? st_max - st_min : 0;
         const char *base = a.kv + head_kv;
-        auto src = [&](int t) { return base + (st_min + t) * tile_stride; };
-        auto msk = [&](int t, int *j0, bool *need, int *cap) {
-            int st = st_min + t;
-            *j0 = 32 * st;
-            *need = (32 * st < mine.full_lo) || (32 * st + 32 > mine.full_hi);  // also true outside [st0, st1)
-            *cap = 0x7fffffff;
+        auto src = [&](int t) { return base + (mine.st0 + t) * tile_stride; };
+        auto mask_tile = [&](int t, f32x16 &sc) {
+            const int j0 = 32 * (mine.st0 + t);
+            bool need = j0 < mine.full_lo || j0 + 32 > mine.full_hi;
+            int cap = 0x7fffffff;
             if constexpr (CNT) {
                 // slots of the tile's block beyond its active tokens (in own-block mode the segment already ends there)
-                if (!a.own_block && st < 2 * a.nb) {
-                    const int vld = min(32, max(0, a.count[st >> 1] - 32 * (st & 1)));
+                if (!a.own_block) {
+                    const int vld = min(32, max(0, a.count[j0 >> 6] - (j0 & 32)));
                     if (vld < 32) {
-                        *need = true;
-                        *cap = 32 * st + vld;
+                        need = true;
+                        cap = j0 + vld;
                     }
                 }
             }
+            if (need) {
+                mfma_settle();
+                mask_scores(c.lo[0], min(c.hi[0], cap), sc, j0, lane);
+            }
         };
-        // tiles wholly inside the range that every query of the block sees (none is known to be, with counts)
-        const int mf_lo = CNT ? 0 : max(0, (mine.full_lo - 32 * st_min + 31) >> 5);
-        const int mf_hi = CNT ? 0 : (mine.full_hi - 32 * st_min) >> 5;
-        // The steps of this wavefront's own query block (a query block past the end of the sequence sees nothing).
-        // Measured: attention kernel 0.5 % faster at config 4, 1.6 % at config 3, 2.5 % at config 2; 0.6 % slower at
-        // config 6 (d = 32), where the restructured loop costs more than the skipped tiles save.
-        const int w_lo = active ? mine.st0 - st_min : 0, w_hi = active ? mine.st1 - st_min : 0;
-        run_shared<G>(c, n_steps, w_lo, w_hi, src, msk, mf_lo, mf_hi, lds, wave, lane, sl2);
+        const auto tiles = own_tiles<G>(active ? mine.st1 - mine.st0 : 0, src, lds, qbi, sub, c.lane16);
+        end_phase();
+        tiles.begin();
+        if (active) finish_branch<G>(c, a, 1, row0, head, wave, lane, lds);
+        reset_branch<G>(c);
+        run_tiles<G>(c, n_max, tiles, mask_tile, sl2);
         __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         wg_barrier();  // the tile slots are about to be reused for the output rows
         if (active) finish_branch<G>(c, a, 2, row0, head, wave, lane, lds);
     }
 }
 
-// Builds the tile images (see issue_shared) of a K and a V tensor, both [n_rows, H, D] bf16:
+// Builds the tile images (see read_k, read_v) of a K and a V tensor, both [n_rows, H, D] bf16:
 // img[head][tile] = K fragments (K_BYTES) then V^T fragments (V_BYTES).
 // Rows at or beyond n_rows read as zero (their scores are masked in the attention kernel).
 // One workgroup per (64-row block, head) = two tiles.
@@ -1298,7 +1162,7 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
 }
 
 struct WsLayout {
-    size_t kv, kvc, gsum, sched, gtab, total;
+    size_t kv, kvc, gsum, gtab, total;
 };
 
 WsLayout ws_layout(const Shape &s) {
@@ -1310,10 +1174,8 @@ WsLayout ws_layout(const Shape &s) {
     w.kvc = off;
     off += align_up((size_t)((s.nbc + 31) / 32) * s.h_kv * tile, 256);
     w.gsum = off;
-    // (d = 128: bf16, the query tiles of four of a workgroup's eight wavefronts; the others' stay in LDS; in registers at d <= 64)
-    off += s.d == 128 ? align_up((size_t)((s.nb + 3) / 4) * 4 * 32 * s.h * s.d * 2, 256) : 0;
-    w.sched = off;
-    off += s.d == 128 ? sel_schedule_bytes(s) : 0;
+    // (d = 128: bf16, the query tiles of two of a workgroup's four wavefronts; the others' stay in LDS; at d <= 64 all in registers and LDS)
+    off += s.d == 128 ? align_up((size_t)((s.nb + 1) / 2) * 2 * 32 * s.h * s.d * 2, 256) : 0;
     w.gtab = off;
     off += group_tables_bytes(s);
     w.total = off > 0 ? off : 256;
@@ -1341,19 +1203,13 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     hipLaunchKernelGGL((pack_tiles<D, false>), dim3((s.nbc + 63) / 64, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
                        (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
     LSRM_HIP_CHECK(hipGetLastError());
-    if (D == 128) {
-        lsrm_status rc = launch_sel_schedule(s, a.idx, reinterpret_cast<int32_t *>(ws + w.sched), st);
-        if (rc != LSRM_OK) return rc;
-    }
-    a.sched = reinterpret_cast<const int32_t *>(ws + w.sched);
     a.kv = ws + w.kv;
     a.kvc = ws + w.kvc;
     a.gsum = reinterpret_cast<uint16_t *>(ws + w.gsum);
     a.groups_per_head = (s.nb + NP - 1) / NP;
     a.groups_per_xcd = (a.groups_per_head + 7) / 8;
-    // dynamic LDS: the tile slots, then 512 bytes per wavefront for compacting a routing row
-    // behind the ring: the routing-row scratch of the selected phase (d <= 64) or the LDS part of the running gated sum
-    constexpr int kLds = G::LDS_BYTES + G::GSUM_LDS_WAVES * G::GSUM_LDS_BYTES + (D == 128 ? 0 : G::WAVES * 512);
+    // dynamic LDS: the tile slots, then the LDS part of the running gated sum
+    constexpr int kLds = G::LDS_ALL;
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern = cnt ? (wide ? reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, true>)
                                    : reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, false>))
@@ -1449,9 +1305,11 @@ lsrm_status launch_forward(const Shape &s, const int32_t *seg_host, int n_seg, c
     a.scale_log2e = s.scale * 1.4426950408889634f;
     WsLayout w = ws_layout(s);
     char *ws = reinterpret_cast<char *>(d_ws);
-    if (s.d == 32) return launch_forward_d<Geo<32, 4, 1>>(s, seg_host, n_seg, a, d_k, d_v, d_kc, d_vc, ws, w, st, ev_start, ev_stop);
-    if (s.d == 64) return launch_forward_d<Geo<64, 4, 1>>(s, seg_host, n_seg, a, d_k, d_v, d_kc, d_vc, ws, w, st, ev_start, ev_stop);
-    return launch_forward_d<Geo<128, 4, 1>>(s, seg_host, n_seg, a, d_k, d_v, d_kc, d_vc, ws, w, st, ev_start, ev_stop);
+#define LSRM_FORWARD(DD) launch_forward_d<Geo<DD>>(s, seg_host, n_seg, a, d_k, d_v, d_kc, d_vc, ws, w, st, ev_start, ev_stop)
+    if (s.d == 32) return LSRM_FORWARD(32);
+    if (s.d == 64) return LSRM_FORWARD(64);
+    return LSRM_FORWARD(128);
+#undef LSRM_FORWARD
 }
 
 }  // namespace lsrm

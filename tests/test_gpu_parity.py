@@ -417,3 +417,16 @@ def test_error_codes(B):
         B.lsrm_nsa_compress(odd, t, t, t, t)
     assert e.value.status == B.LSRM_ERR_INVALID_ARG
     assert B.lsrm_workspace_bytes(bad, B.LSRM_WS_FORWARD) == 0
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("nb", [2, 3, 32, 33, 64, 65, 97, 128, 131, 161])
+def test_forward_pipeline_edges(B, oracle_lib, d, nb):
+    """1 .. 6 tiles of pooled pairs through the four slots of the compressed phase (whole and partly filled last
+    tiles, slots that no copy fills), an even and an odd number of query blocks for workgroups of two, windows of
+    an odd and an even number of tiles."""
+    cfg = I.small_config(name=f"f-edge-d{d}-nb{nb}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=1, d=d,
+                         topk=3, window=66 if nb % 2 else 128, seed=90 + nb)
+    _log(f"[forward] {cfg.name}")
+    assert cfg.nb == nb
+    _assert_forward(*_forward_case(B, oracle_lib, cfg), cfg.name)
