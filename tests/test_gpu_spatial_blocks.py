@@ -145,3 +145,35 @@ def test_group_arguments_are_checked(B):
     none = B.make_params(512, 0, 16, 2, 64, 3, 128)
     none.n_groups = 2         # a count without offsets
     assert B.lsrm_workspace_bytes(none, B.LSRM_WS_FORWARD) == 0
+
+
+@pytest.mark.parametrize("d,h_kv,with_counts", [(32, 1, True), (64, 3, True), (64, 2, False), (128, 5, True)])
+def test_pooling_of_spatial_blocks_edges(B, oracle_lib, d, h_kv, with_counts):
+    """Spatial blocks of 1, 2, 3, 8, 16 and 17 blocks (one pass over 128 slots, several, one past a whole number) at rows
+    of 4, 24, 16 and 80 chunks of 8 channels (16 share a workgroup); one active token in the last block."""
+    import torch
+    cfg = I.small_config(name=f"g-pool-d{d}-h{h_kv}", n_obj=64 * 47, n_views=0, grid=0, heads=h_kv, d=d, topk=1, window=64)
+    goff = np.concatenate([[0], np.cumsum([1, 2, 3, 8, 16, 17])]).astype(np.int32)
+    rng = np.random.default_rng(5)
+    cnt = None
+    if with_counts:
+        cnt = np.full(cfg.nb, 64, dtype=np.int32)
+        cnt[goff[1:] - 1] = [1, 17, 64, 33, 2, 1]
+    bits = [I.f32_to_bf16_bits(rng.standard_normal((cfg.n, h_kv, d)).astype(np.float32)) for _ in range(2)]
+    bits = _poison(cfg, cnt, *bits)
+    dev = torch.device("cuda")
+    p = B.make_params(cfg.n_obj, 0, 0, h_kv, d, 1, 64, h_kv=h_kv, group_offsets=torch.from_numpy(goff).to(dev),
+                      block_count=None if cnt is None else torch.from_numpy(cnt).to(dev))
+    k, v = (torch.from_numpy(b.view(np.int16)).to(dev).view(torch.bfloat16) for b in bits)
+    kc = torch.empty((len(goff) - 1, h_kv, d), dtype=torch.bfloat16, device=dev)
+    vc = torch.empty_like(kc)
+    _log(f"[pool] {cfg.name}")
+    B.lsrm_nsa_compress(p, k, v, kc, vc)
+    torch.cuda.synchronize()
+    active = np.arange(cfg.n) % 64 < (64 if cnt is None else np.repeat(cnt, 64))
+    for got, b in ((kc, bits[0]), (vc, bits[1])):
+        x = I.bf16_bits_to_f32(b).astype(np.float64)
+        for g in range(len(goff) - 1):
+            sl = slice(64 * goff[g], 64 * goff[g + 1])
+            ref = x[sl][active[sl]].mean(axis=0)
+            assert np.all(np.abs(got[g].double().cpu().numpy() - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
