@@ -73,8 +73,7 @@ struct BwdArgs {
     const char *img_q, *img_k, *img_v, *img_kc, *img_vc;  // tile images
     const char *img_do[3];    // images of the gradient that reaches each branch: one shared image of dout with
                               // per-head gates (the gate is folded into the exponent), gate o dout per branch
-                              // with per-channel gates
-    const uint16_t *gdo;      // per-channel gates only: [3][N][H][d] bf16, gate o dout (written by bwd_prep)
+                              // with per-channel gates (written by bwd_prep)
     float *aux;               // [3][N/32][H][64]: per query tile, 32 x (lse log2e - log2 g) then 32 x -D, rows permuted
     float *part_k, *part_v;   // [n_split][nbp][H][d] fp32 partial gradients of the pooled keys / values
     int32_t *rev_cnt, *rev_ptr, *rev_cur, *rev_idx;  // reverse routing lists
@@ -269,10 +268,16 @@ __device__ __forceinline__ void store_rows_transposed(const float (&x)[D / 32][1
 }
 
 // ---------------------------------------------------------------------------------------------
-// per (token, head): the per-branch exponent offset and D = dout . o_branch, in tile-image row order
+// per (token, head): the per-branch exponent offset and D = dout . o_branch, in tile-image row order, and the tile
+// images of the gradient rows (dout, or gate o dout per branch with per-channel gates; padding slots as zeros).
 // Threads: 8 channels each.  A workgroup takes one query tile and PREP_HB heads: thread = (head, row of the tile,
 // 16-byte chunk of the row), chunks fastest, so a row's d channels are read by d / 8 neighbouring lanes (16-byte
 // loads, contiguous per row) and the 32 table entries of a (tile, head) are written from one wavefront, side by side.
+// The images of a tile's heads are contiguous: a workgroup writes HB of them, 4 or 8 KB, in image order out of LDS (chunk
+// pitch 33 slots: neither the writes, chunks fastest, nor the reads, rows fastest, share banks).  Bound by memory:
+// dout and three branch outputs read, one or three images written, with per-channel gates 12 bytes of gates per channel.
+// Packing the images in passes of their own from dout (57 K tokens, 16 heads of 64: 40 us) or from three bf16
+// tensors that this kernel wrote (196 K tokens, 32 heads of 32: 3 x 166 us) cost one more trip through memory each.
 template <int D>
 struct PrepGeo {
     static constexpr int CH = D / 8;                            // chunks = lanes per (row, head)
@@ -282,17 +287,24 @@ struct PrepGeo {
 template <int D>
 __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
     using P = PrepGeo<D>;
-    constexpr int CH = P::CH;
-    const int c = threadIdx.x % CH, r = (threadIdx.x / CH) % 32;
+    constexpr int CH = P::CH, PITCH = 33;  // LDS slots of 16 bytes per chunk column
+    __shared__ uint4 stage[3][P::HB * CH * PITCH];
+    // (the counters of the reverse lists, which the next kernel increments: there are more threads than blocks)
+    const int64_t gid = (int64_t)blockIdx.x * P::THREADS + threadIdx.x;
+    if (gid < a.nb) a.rev_cnt[gid] = 0;
+    const int c = threadIdx.x % CH, r = (threadIdx.x / CH) % 32, hb = threadIdx.x / (CH * 32);
     const int heads_x = (a.h + P::HB - 1) / P::HB;
     const int64_t tile = blockIdx.x / heads_x;
-    const int head = (int)(blockIdx.x % heads_x) * P::HB + threadIdx.x / (CH * 32);
-    if (head >= a.h) return;  // (whole groups of CH lanes leave together)
+    const int head0 = (int)(blockIdx.x % heads_x) * P::HB;
+    const bool active = head0 + hb < a.h;  // (whole groups of CH lanes)
+    const int head = active ? head0 + hb : head0;
     const int64_t row = tile * 32 + r;
+    // a padding slot is no query: zero probabilities (offset +inf), a zero D in every branch, a zero row in the images
+    const bool padding = a.count != nullptr && (int)(row & 63) >= a.count[row >> 6];
+    const uint4 raw = *reinterpret_cast<const uint4 *>(a.dout + (row * a.h + head) * D + 8 * c);
     float dov[8];
     {
-        const uint4 w = *reinterpret_cast<const uint4 *>(a.dout + (row * a.h + head) * D + 8 * c);
-        const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+        const uint32_t u[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             dov[2 * j] = bf16_lo(u[j]);
@@ -300,8 +312,8 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
         }
     }
     const int pr = perm32(r);
-    // a padding slot is no query: zero probabilities (offset +inf) and a zero D in every branch
-    const bool padding = a.count != nullptr && (int)(row & 63) >= a.count[row >> 6];
+    const int slot = (hb * CH + c) * PITCH + (pr ^ ((c & 1) << 2));
+    if (!a.gate_channels) stage[0][slot] = padding ? make_uint4(0, 0, 0, 0) : raw;
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
         const uint4 w = *reinterpret_cast<const uint4 *>(a.out_branch + (((int64_t)b * a.n + row) * a.h + head) * D + 8 * c);
@@ -320,8 +332,7 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
                 dl += g0 * bf16_lo(u[j]) + g1 * bf16_hi(u[j]);
                 o4[j] = pack_bf16(g0, g1);
             }
-            *reinterpret_cast<uint4 *>(const_cast<uint16_t *>(a.gdo) + (((int64_t)b * a.n + row) * a.h + head) * D + 8 * c) =
-                make_uint4(o4[0], o4[1], o4[2], o4[3]);
+            stage[b][slot] = padding ? make_uint4(0, 0, 0, 0) : make_uint4(o4[0], o4[1], o4[2], o4[3]);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) dl += dov[2 * j] * bf16_lo(u[j]) + dov[2 * j + 1] * bf16_hi(u[j]);
@@ -329,7 +340,7 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
         // D of the row: the sum over its CH lanes, in a fixed order
 #pragma unroll
         for (int m = 1; m < CH; m <<= 1) dl += __shfl_xor(dl, m);
-        if (c != 0) continue;
+        if (c != 0 || !active) continue;
         const float lse = a.lse[((int64_t)b * a.n + row) * a.h + head];
         // an empty key set (lse = -inf) or a zero gate gives zero probabilities: offset +inf
         float l2 = __builtin_inff();
@@ -343,33 +354,108 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
         ax[pr] = padding ? __builtin_inff() : l2;
         ax[32 + pr] = padding ? 0.f : -dl;  // negated: the kernels start the dP accumulators from it
     }
+    __syncthreads();
+    // image of (tile, head0 + e / (32 CH)): slot e % (32 CH) = chunk column (e / 32) % CH, row slot e % 32
+    const int e = threadIdx.x, e_head = e / (32 * CH);
+    if (head0 + e_head >= a.h) return;
+    const int64_t dst = (tile * a.h + head0) * (int64_t)BGeo<D>::IMG + (int64_t)e * 16;
+    const int src = (e / 32) * PITCH + e % 32;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+        if (b == 0 || a.gate_channels) *reinterpret_cast<uint4 *>(const_cast<char *>(a.img_do[b]) + dst) = stage[b][src];
+}
+
+// ---------------------------------------------------------------------------------------------
+// Tile images of q, k, v, kc and vc in one launch (latency and launches are what a small problem pays for; a large one
+// is bound by memory: read once, written once), one workgroup per (64-row block, tensor, head), heads fastest so
+// that neighbouring workgroups read neighbouring pieces of the same rows.  Workgroups behind those count, per key
+// block, the query blocks that list it (the reverse lists' lengths).
+// Image: slot cc * 32 + rr of 16 bytes = chunk cc of tile row perm32(rr ^ 4 (cc & 1)).  Rows at or beyond the end, and
+// padding slots, read as zeros.
+template <int D>
+__global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, int64_t n_wg) {
+    constexpr int CH = D / 8, PITCH = D + 16, IMG = BGeo<D>::IMG;  // (pitch: 16-byte aligned, chunks of a row spread over the banks)
+    __shared__ __attribute__((aligned(16))) uint16_t rows[64][PITCH];
+    const int64_t wg = blockIdx.x;
+    if (wg >= n_wg) {
+        const int64_t e = (wg - n_wg) * 256 + threadIdx.x;
+        if (e < (int64_t)a.nb * a.topk) {
+            const int v = a.idx[e];
+            if (v >= 0 && v < a.nb) atomicAdd(&a.rev_cnt[v], 1);
+        }
+        return;
+    }
+    const bool pooled = wg >= n_token_wg;
+    const int y_n = pooled ? 2 * a.h_kv : a.h + 2 * a.h_kv;
+    const int64_t at = pooled ? wg - n_token_wg : wg;
+    const int64_t blk = at / y_n;
+    int head = (int)(at % y_n), h = a.h_kv;
+    const uint16_t *src;
+    const char *img;
+    if (!pooled && head < a.h) {
+        src = a.q;
+        img = a.img_q;
+        h = a.h;
+    } else {
+        if (!pooled) head -= a.h;
+        const bool second = head >= a.h_kv;
+        if (second) head -= a.h_kv;
+        src = pooled ? (second ? a.vc : a.kc) : (second ? a.v : a.k);
+        img = pooled ? (second ? a.img_vc : a.img_kc) : (second ? a.img_v : a.img_k);
+    }
+    const int64_t n_rows = pooled ? a.nbc : a.n, n_tiles = pooled ? (a.nbc + 31) / 32 : a.nt;
+    const int n_act = !pooled && a.count != nullptr ? a.count[blk] : 64;
+    constexpr int NIT = 64 * CH / 256;
+    uint4 in[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int e = threadIdx.x + 256 * it, t = e / CH, cc = e % CH;
+        const int64_t row = blk * 64 + t;
+        in[it] = row < n_rows && t < n_act ? *reinterpret_cast<const uint4 *>(src + (row * h + head) * D + cc * 8)
+                                           : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int e = threadIdx.x + 256 * it;
+        *reinterpret_cast<uint4 *>(&rows[e / CH][(e % CH) * 8]) = in[it];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int e = threadIdx.x + 256 * it, half = e / (32 * CH), q = e % (32 * CH), cc = q / 32, rr = q % 32;
+        const int64_t tile = blk * 2 + half;
+        if (tile < n_tiles)
+            *reinterpret_cast<uint4 *>(const_cast<char *>(img) + (tile * h + head) * IMG + q * 16) =
+                *reinterpret_cast<const uint4 *>(&rows[32 * half + perm32(rr ^ ((cc & 1) << 2))][cc * 8]);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
 // reverse routing lists: for every key block the query blocks that list it, ascending
-__global__ void fill_zero(int32_t *p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-__global__ void rev_count(BwdArgs a) {
-    int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= a.nb * a.topk) return;
-    int v = a.idx[e];
-    if (v >= 0 && v < a.nb) atomicAdd(&a.rev_cnt[v], 1);
-}
-__global__ __launch_bounds__(1024) void rev_scan(BwdArgs a) {
-    __shared__ int part[1024];
+// Where the lists start, and the key blocks in order of falling reverse-list length (within 1024 length classes; equal lengths in any
+// order -- it only decides which workgroup starts when).  The token-key dK/dV workgroups take their block from
+// this list: the long walks start first instead of forming the tail of the kernel, and the round-robin of
+// workgroups over the XCDs spreads them, where a contiguous range of blocks per XCD left the popular blocks
+// (say, all image blocks) to one or two XCDs.
+__global__ __launch_bounds__(1024) void rev_scan_order(BwdArgs a, int32_t *order) {
+    __shared__ int part[1024], bin[1024];
     const int t = threadIdx.x;
+    bin[t] = 0;
+    // starts of the lists: exclusive prefix sums of the lengths
     const int chunk = (a.nb + 1023) / 1024;
     const int lo = min(t * chunk, a.nb), hi = min(lo + chunk, a.nb);
     int s = 0;
     for (int i = lo; i < hi; ++i) s += a.rev_cnt[i];
     part[t] = s;
     __syncthreads();
+    for (int b = t; b < a.nb; b += 1024) atomicAdd(&bin[1023 - min(a.rev_cnt[b], 1023)], 1);  // longest first
+    __syncthreads();
+    const int own = bin[t];
     for (int off = 1; off < 1024; off <<= 1) {
-        int x = t >= off ? part[t - off] : 0;
+        const int x = t >= off ? part[t - off] : 0, y = t >= off ? bin[t - off] : 0;
         __syncthreads();
         part[t] += x;
+        bin[t] += y;
         __syncthreads();
     }
     int run = part[t] - s;  // exclusive prefix of this chunk
@@ -379,29 +465,9 @@ __global__ __launch_bounds__(1024) void rev_scan(BwdArgs a) {
         run += a.rev_cnt[i];
     }
     if (t == 1023) a.rev_ptr[a.nb] = part[1023];
-}
-// The key blocks in order of falling reverse-list length (within 1024 length classes; equal lengths in any
-// order -- it only decides which workgroup starts when).  The token-key dK/dV workgroups take their block from
-// this list: the long walks start first instead of forming the tail of the kernel, and the round-robin of
-// workgroups over the XCDs spreads them, where a contiguous range of blocks per XCD left the popular blocks
-// (say, all image blocks) to one or two XCDs.
-__global__ __launch_bounds__(1024) void rev_order(BwdArgs a, int32_t *order) {
-    __shared__ int bin[1024];
-    const int t = threadIdx.x;
-    bin[t] = 0;
+    bin[t] -= own;  // start of each class
     __syncthreads();
-    for (int b = t; b < a.nb; b += 1024) atomicAdd(&bin[min(a.rev_cnt[b], 1023)], 1);
-    __syncthreads();
-    if (t == 0) {  // start of each class, longest first
-        int run = 0;
-        for (int c = 1023; c >= 0; --c) {
-            const int n = bin[c];
-            bin[c] = run;
-            run += n;
-        }
-    }
-    __syncthreads();
-    for (int b = t; b < a.nb; b += 1024) order[atomicAdd(&bin[min(a.rev_cnt[b], 1023)], 1)] = b;
+    for (int b = t; b < a.nb; b += 1024) order[atomicAdd(&bin[1023 - min(a.rev_cnt[b], 1023)], 1)] = b;
 }
 __global__ void rev_fill(BwdArgs a) {
     int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -492,17 +558,23 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long m, int n) {
 
 // The partial gradients of the pooled keys / values, summed over the query ranges in order into range 0's slot,
 // so that the token-key workgroups read one row per pooled pair however many ranges there were.
+// (Eight ranges' rows are requested at a time: one dependent load after another took 31 us for 64 ranges.)
 __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, float *__restrict__ part_v, int n_split,
                                                  int64_t per_split) {
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= per_split) return;
+    float *part = blockIdx.y == 0 ? part_k : part_v;
+    f32x4 acc = *reinterpret_cast<const f32x4 *>(part + i);
+    int sp = 1;
+    for (; sp + 8 <= n_split; sp += 8) {
+        f32x4 x[8];
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        float *part = which == 0 ? part_k : part_v;
-        f32x4 acc = *reinterpret_cast<const f32x4 *>(part + i);
-        for (int sp = 1; sp < n_split; ++sp) acc += *reinterpret_cast<const f32x4 *>(part + sp * per_split + i);
-        *reinterpret_cast<f32x4 *>(part + i) = acc;
+        for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const f32x4 *>(part + (sp + j) * per_split + i);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc += x[j];
     }
+    for (; sp < n_split; ++sp) acc += *reinterpret_cast<const f32x4 *>(part + sp * per_split + i);
+    *reinterpret_cast<f32x4 *>(part + i) = acc;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -533,22 +605,16 @@ __global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
     const uint32_t tr_off = tr_lane_offset(lane), row_off = row_lane_offset(lane);
 
     bf16x8 qf[NS], dof[NS];
-    // the gradient rows of branch b: dout itself, or gate o dout with per-channel gates
-    // (a padding slot reads as zeros: whatever the caller left there never reaches an MFMA)
-    const bool padding = a.count != nullptr && 32 * wave + r >= a.count[qb];
-    const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    // the query rows, and the gradient rows of branch b (dout itself, or gate o dout with per-channel gates), out of
+    // their tile images: 1 KB contiguous per fragment, padding slots are zeros there
+    const int64_t img_off = ((row0 >> 5) * a.h + head) * (int64_t)G::IMG + (hh * 32 + (perm32(r) ^ (hh << 2))) * 16;
     auto load_dof = [&](int b) {
-        const uint16_t *src = a.gate_channels ? a.gdo + (int64_t)b * a.n * a.h * D : a.dout;
-        const uint16_t *drow = src + ((row0 + r) * a.h + head) * D + 8 * hh;
 #pragma unroll
-        for (int ks = 0; ks < NS; ++ks) dof[ks] = padding ? zero8 : *reinterpret_cast<const bf16x8 *>(drow + 16 * ks);
+        for (int ks = 0; ks < NS; ++ks) dof[ks] = *reinterpret_cast<const bf16x8 *>(a.img_do[b] + img_off + ks * 1024);
     };
-    {
-        const uint16_t *qrow = a.q + ((row0 + r) * a.h + head) * D + 8 * hh;
 #pragma unroll
-        for (int ks = 0; ks < NS; ++ks) qf[ks] = padding ? zero8 : *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
-        load_dof(0);
-    }
+    for (int ks = 0; ks < NS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(a.img_q + img_off + ks * 1024);
+    load_dof(0);
     float l2[3], dl[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
@@ -821,7 +887,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     const int per_xcd = (n_kb + 7) / 8;
     const int head = blockIdx.y;
     int kb;
-    if (MODE == 0) {  // token keys: longest walk first (see rev_order)
+    if (MODE == 0) {  // token keys: longest walk first (see rev_scan_order)
         if ((int)blockIdx.x >= n_kb) return;
         kb = a.order[blockIdx.x];
     } else {
@@ -1308,7 +1374,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
 }
 
 struct WsLayout {
-    size_t img_q, img_do[3], gdo, img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
+    size_t img_q, img_do[3], img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
     int n_split, nbp, tiles_per_split, hsplit, hpw;
     size_t hpart_k, hpart_v, order, gtab;
 };
@@ -1326,13 +1392,11 @@ WsLayout ws_layout(const Shape &s) {
     w.img_q = take(nt * s.h * img);
     w.img_do[0] = take(nt * s.h * img);
     if (s.gate_channels) {
-        // one image of gate o dout per branch, and the rows they are packed from
+        // one image of gate o dout per branch
         w.img_do[1] = take(nt * s.h * img);
         w.img_do[2] = take(nt * s.h * img);
-        w.gdo = take((size_t)3 * s.n * s.h * s.d * 2);
     } else {
         w.img_do[1] = w.img_do[2] = w.img_do[0];
-        w.gdo = 0;
     }
     w.img_k = take(nt * s.h_kv * img);
     w.img_v = take(nt * s.h_kv * img);
@@ -1412,34 +1476,15 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 2>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-    const int ntc = (s.nbc + 31) / 32;
-    lsrm_status rc;
     hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)(a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB))),
                        dim3(PrepGeo<D>::THREADS), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    if ((rc = launch_pack_tiles(D, a.q, a.q, ws + w.img_q, s.n, s.h, a.nt, st, true, a.count)) != LSRM_OK) return rc;
-    if (s.gate_channels) {
-        for (int b = 0; b < 3; ++b) {
-            const uint16_t *src = a.gdo + (size_t)b * s.n * s.h * D;
-            if ((rc = launch_pack_tiles(D, src, src, ws + w.img_do[b], s.n, s.h, a.nt, st, true, a.count)) != LSRM_OK) return rc;
-        }
-    } else {
-        if ((rc = launch_pack_tiles(D, a.dout, a.dout, ws + w.img_do[0], s.n, s.h, a.nt, st, true, a.count)) != LSRM_OK) return rc;
-    }
-    if ((rc = launch_pack_tiles(D, a.k, a.k, ws + w.img_k, s.n, s.h_kv, a.nt, st, true, a.count)) != LSRM_OK) return rc;
-    if ((rc = launch_pack_tiles(D, a.v, a.v, ws + w.img_v, s.n, s.h_kv, a.nt, st, true, a.count)) != LSRM_OK) return rc;
-    if ((rc = launch_pack_tiles(D, a.kc, a.kc, ws + w.img_kc, (int64_t)s.nbc, s.h_kv, ntc, st, true, nullptr)) != LSRM_OK) return rc;
-    if ((rc = launch_pack_tiles(D, a.vc, a.vc, ws + w.img_vc, (int64_t)s.nbc, s.h_kv, ntc, st, true, nullptr)) != LSRM_OK) return rc;
+    const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
+    const int64_t n_count_wg = ((int64_t)s.nb * s.topk + 255) / 256;
+    hipLaunchKernelGGL(pack_rows<D>, dim3((unsigned)(n_wg + n_count_wg)), dim3(256), 0, st, a, n_token_wg, n_wg);
+    LSRM_HIP_CHECK(hipGetLastError());
     // reverse routing lists
-    hipLaunchKernelGGL(fill_zero, dim3((s.nb + 255) / 256), dim3(256), 0, st, a.rev_cnt, s.nb);
-    LSRM_HIP_CHECK(hipGetLastError());
-    if (s.topk > 0) {
-        hipLaunchKernelGGL(rev_count, dim3((s.nb * s.topk + 255) / 256), dim3(256), 0, st, a);
-        LSRM_HIP_CHECK(hipGetLastError());
-    }
-    hipLaunchKernelGGL(rev_scan, dim3(1), dim3(1024), 0, st, a);
-    LSRM_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(rev_order, dim3(1), dim3(1024), 0, st, a, const_cast<int32_t *>(a.order));
+    hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a, const_cast<int32_t *>(a.order));
     LSRM_HIP_CHECK(hipGetLastError());
     if (s.topk > 0) {
         hipLaunchKernelGGL(rev_fill, dim3((s.nb * s.topk + 255) / 256), dim3(256), 0, st, a);
@@ -1461,7 +1506,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     LSRM_HIP_CHECK(hipGetLastError());
     if (w.n_split > 1) {
         const int64_t per_split = (int64_t)w.nbp * s.h_kv * D;
-        hipLaunchKernelGGL(sum_parts, dim3((unsigned)((per_split / 4 + 255) / 256)), dim3(256), 0, st, a.part_k, a.part_v,
+        hipLaunchKernelGGL(sum_parts, dim3((unsigned)((per_split / 4 + 255) / 256), 2), dim3(256), 0, st, a.part_k, a.part_v,
                            w.n_split, per_split);
         LSRM_HIP_CHECK(hipGetLastError());
         a.n_split = 1;  // (the kernels below read range 0's slot only)
@@ -1502,7 +1547,6 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.lse = d_lse;
     a.img_q = ws + w.img_q;
     for (int b = 0; b < 3; ++b) a.img_do[b] = ws + w.img_do[b];
-    a.gdo = s.gate_channels ? reinterpret_cast<const uint16_t *>(ws + w.gdo) : nullptr;
     a.img_k = ws + w.img_k;
     a.img_v = ws + w.img_v;
     a.img_kc = ws + w.img_kc;

@@ -1030,29 +1030,19 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 // Rows at or beyond n_rows read as zero (their scores are masked in the attention kernel).
 // One workgroup per (64-row block, head) = two tiles.
 // count (nullable, one entry per 64-row block): rows of a block at or beyond its count read as zero too.
-// ROWS_ONLY (the backward's images): only the row-order fragments of k are written, img[tile][head] is
-// K_BYTES long, and inside a fragment the 16-byte slot of (row position r, channel half hh) is
-// hh * 32 + (r ^ 4 hh) instead of hh * 32 + r (keeps the backward's transposing LDS loads off shared banks).
-// Position of the image of (tile, head), in images.  The attention kernel's images are head-major
-// (img[head][tile]): all workgroups in flight work on one head, whose keys and values are then one
-// contiguous range instead of 16 KB pieces spread over the whole buffer -- measured 3 % faster at the
-// largest shape.  The backward's row-only images are img[tile][head] (the other order changed nothing there).
-template <bool ROWS_ONLY>
-__device__ __forceinline__ int64_t image_index(int64_t tile, int head, int h, int n_tiles) {
-    return ROWS_ONLY ? tile * h + head : (int64_t)head * n_tiles + tile;
-}
-
-// POOL (with the full images only): the block averages of k and v are written as well (kc, vc [n_rows / 64, H, D]
+// The images are head-major (img[head][tile]): all workgroups in flight work on one head, whose keys and values are then one
+// contiguous range instead of 16 KB pieces spread over the whole buffer -- measured 3 % faster at the largest shape.
+//
+// POOL: the block averages of k and v are written as well (kc, vc [n_rows / 64, H, D]
 // bf16: Sec. 3.2, the compressed pair of the block), so that one pass over K and V serves both the pooling and
 // the packing.  A thread sums its rows in fp32 in token order (rows t, t + 2048 / D, ...); the partial sums of
 // the 2048 / D threads that share a channel group are added in thread order; one rounding to bf16.
-template <int D, bool ROWS_ONLY, bool POOL = false>
+template <int D, bool POOL = false>
 __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
                                                   char *__restrict__ img, int64_t n_rows, int h, int n_tiles,
                                                   const int32_t *__restrict__ count, uint16_t *__restrict__ kc = nullptr,
                                                   uint16_t *__restrict__ vc = nullptr) {
-    static_assert(!(POOL && ROWS_ONLY), "");
-    constexpr int K_BYTES = 32 * D * 2, TILE = ROWS_ONLY ? K_BYTES : K_BYTES + D * 64;
+    constexpr int K_BYTES = 32 * D * 2, TILE = K_BYTES + D * 64;
     constexpr int CH = D / 8;  // 16-byte chunks per row
     // Both tensors' rows of the block are staged in LDS, so that the images are written in image order (a wavefront
     // writes 1 KB contiguous per instruction; written straight from the loaded registers, K chunks would go out as
@@ -1060,7 +1050,7 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
     // groups that 16 lanes address in one transposing load fall in distinct banks.
     constexpr int PITCH = D + 16;
     __shared__ __attribute__((aligned(16))) uint16_t kt[64][PITCH];
-    __shared__ __attribute__((aligned(16))) uint16_t vt[ROWS_ONLY ? 1 : 64][PITCH];
+    __shared__ __attribute__((aligned(16))) uint16_t vt[64][PITCH];
     __shared__ float psum[POOL ? 2 : 1][POOL ? 256 / CH : 1][POOL ? D + 1 : 1];  // [k, v][thread group][channel]
     const int64_t blk = blockIdx.x;
     const int head = blockIdx.y;
@@ -1078,7 +1068,7 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
         vin[it] = make_uint4(0, 0, 0, 0);
         if (row < n_rows && t < n_act) {
             kin[it] = *reinterpret_cast<const uint4 *>(k + (row * h + head) * D + cc * 8);
-            if (!ROWS_ONLY) vin[it] = *reinterpret_cast<const uint4 *>(v + (row * h + head) * D + cc * 8);
+            vin[it] = *reinterpret_cast<const uint4 *>(v + (row * h + head) * D + cc * 8);
         }
     }
 #pragma unroll
@@ -1087,7 +1077,6 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
         const int t = e / CH, cc = e % CH;
         const uint4 kval = kin[it], vval = vin[it];
         *reinterpret_cast<uint4 *>(&kt[t][cc * 8]) = kval;
-        if (ROWS_ONLY) continue;
         *reinterpret_cast<uint4 *>(&vt[t][cc * 8]) = vval;
         if (POOL) {
             const uint32_t kw[4] = {kval.x, kval.y, kval.z, kval.w}, w[4] = {vval.x, vval.y, vval.z, vval.w};
@@ -1116,15 +1105,13 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
     for (int it = 0; it < NIT; ++it) {
         const int e = threadIdx.x + 256 * it;
         const int half = e / (32 * CH), q = e % (32 * CH);
-        const int cc = q / 32, rr = q % 32;
-        const int r = ROWS_ONLY ? rr ^ ((cc & 1) << 2) : rr;
+        const int cc = q / 32, r = q % 32;
         const int tt = (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
         const uint4 kval = *reinterpret_cast<const uint4 *>(&kt[32 * half + tt][cc * 8]);
         const int64_t tile = blk * 2 + half;
         if (tile < n_tiles)
-            *reinterpret_cast<uint4 *>(img + image_index<ROWS_ONLY>(tile, head, h, n_tiles) * TILE + q * 16) = kval;
+            *reinterpret_cast<uint4 *>(img + ((int64_t)head * n_tiles + tile) * TILE + q * 16) = kval;
     }
-    if (ROWS_ONLY) return;
     if (POOL) {
         if (threadIdx.x < 2 * D) {
             const int which = threadIdx.x / D, c = threadIdx.x % D;
@@ -1156,7 +1143,7 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
                      : "v"(addr), "n"(4 * PITCH * 2)
                      : "memory");
         if (tile >= n_tiles) continue;
-        *reinterpret_cast<uint4 *>(img + image_index<ROWS_ONLY>(tile, head, h, n_tiles) * TILE + K_BYTES + (f * 64 + ln) * 16) =
+        *reinterpret_cast<uint4 *>(img + ((int64_t)head * n_tiles + tile) * TILE + K_BYTES + (f * 64 + ln) * 16) =
             make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
 }
@@ -1196,11 +1183,11 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
         a.blk_seg = gt.blk_seg;
     }
     if (!s.kv_packed) {
-        hipLaunchKernelGGL((pack_tiles<D, false>), dim3(s.nb, s.h_kv), dim3(256), 0, st, d_k, d_v, ws + w.kv, s.n, s.h_kv,
+        hipLaunchKernelGGL((pack_tiles<D>), dim3(s.nb, s.h_kv), dim3(256), 0, st, d_k, d_v, ws + w.kv, s.n, s.h_kv,
                            2 * s.nb, a.count);
         LSRM_HIP_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL((pack_tiles<D, false>), dim3((s.nbc + 63) / 64, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
+    hipLaunchKernelGGL((pack_tiles<D>), dim3((s.nbc + 63) / 64, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
                        (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
     LSRM_HIP_CHECK(hipGetLastError());
     a.kv = ws + w.kv;
@@ -1226,6 +1213,22 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     return LSRM_OK;
 }
 
+lsrm_status launch_pack_tiles(int d, const uint16_t *k, const uint16_t *v, char *img, int64_t n_rows, int h, int n_tiles,
+                              hipStream_t st, const int32_t *count) {
+    const dim3 grid((n_tiles + 1) / 2, h);
+#define LSRM_PACK(DD) \
+    hipLaunchKernelGGL((pack_tiles<DD>), grid, dim3(256), 0, st, k, v, img, n_rows, h, n_tiles, count)
+    if (d == 32)
+        LSRM_PACK(32);
+    else if (d == 64)
+        LSRM_PACK(64);
+    else
+        LSRM_PACK(128);
+#undef LSRM_PACK
+    LSRM_HIP_CHECK(hipGetLastError());
+    return LSRM_OK;
+}
+
 }  // namespace
 
 size_t forward_ws_bytes(const Shape &s) { return ws_layout(s).total; }
@@ -1238,12 +1241,12 @@ lsrm_status launch_compress_pack(const Shape &s, const uint16_t *d_k, const uint
     if (s.ng > 0) {
         // a spatial block's average spans several 64-slot blocks, i.e. several workgroups of the packing pass: the
         // two are separate passes here
-        lsrm_status rc = launch_pack_tiles(s.d, d_k, d_v, img, s.n, s.h_kv, 2 * s.nb, st, false, s.count);
+        lsrm_status rc = launch_pack_tiles(s.d, d_k, d_v, img, s.n, s.h_kv, 2 * s.nb, st, s.count);
         if (rc != LSRM_OK) return rc;
         return launch_compress(s, d_k, d_v, d_kc, d_vc, st);
     }
 #define LSRM_POOL_PACK(DD) \
-    hipLaunchKernelGGL((pack_tiles<DD, false, true>), grid, dim3(256), 0, st, d_k, d_v, img, s.n, s.h_kv, 2 * s.nb, s.count, \
+    hipLaunchKernelGGL((pack_tiles<DD, true>), grid, dim3(256), 0, st, d_k, d_v, img, s.n, s.h_kv, 2 * s.nb, s.count, \
                        d_kc, d_vc)
     if (s.d == 32)
         LSRM_POOL_PACK(32);
@@ -1252,24 +1255,6 @@ lsrm_status launch_compress_pack(const Shape &s, const uint16_t *d_k, const uint
     else
         LSRM_POOL_PACK(128);
 #undef LSRM_POOL_PACK
-    LSRM_HIP_CHECK(hipGetLastError());
-    return LSRM_OK;
-}
-
-lsrm_status launch_pack_tiles(int d, const uint16_t *rows_src, const uint16_t *t_src, char *img, int64_t n_rows, int h,
-                              int n_tiles, hipStream_t st, bool rows_only, const int32_t *count) {
-    if (n_tiles <= 0) return LSRM_OK;
-    const dim3 grid((n_tiles + 1) / 2, h);
-#define LSRM_PACK(DD, RO) \
-    hipLaunchKernelGGL((pack_tiles<DD, RO>), grid, dim3(256), 0, st, rows_src, t_src, img, n_rows, h, n_tiles, count)
-    if (d == 32) {
-        if (rows_only) LSRM_PACK(32, true); else LSRM_PACK(32, false);
-    } else if (d == 64) {
-        if (rows_only) LSRM_PACK(64, true); else LSRM_PACK(64, false);
-    } else {
-        if (rows_only) LSRM_PACK(128, true); else LSRM_PACK(128, false);
-    }
-#undef LSRM_PACK
     LSRM_HIP_CHECK(hipGetLastError());
     return LSRM_OK;
 }
