@@ -14,11 +14,11 @@
 //                    (pooled, routed, window) and accumulates dQ^T in registers.
 //   bwd_dkv_kernel   one workgroup per (key block, key/value head): walks the query tiles that attend it --
 //                    MODE 1: pooled keys, every query tile of the sequence (split into ranges whose
-//                    partial sums are added in order by MODE 0); MODE 0: token keys, the query tiles
+//                    partial sums sum_parts adds in order); MODE 0: token keys, the query tiles
 //                    of the window and of the reverse routing list (query blocks in ascending order),
-//                    key blocks taken longest list first -- accumulates dK^T and dV^T in registers, adds
-//                    the pooled gradients / 64.  With grouped-query heads the heads of a group are dealt to
-//                    several workgroups, whose sums MODE 2 adds in order before finishing the rows.
+//                    longest walks first -- accumulates dK^T and dV^T in registers, adds
+//                    the pooled gradients / 64.  Long walks, and the heads of a group, are dealt to several
+//                    workgroups, whose sums sum_walks adds in order before finishing the rows.
 // Every operand tile is a "tile image" (see forward.hip): MFMA A-operand fragments in row order
 // (rows permuted so that an accumulator is directly the B operand of the next contraction); the
 // fragments of the transposed tile are read out of the same bytes in LDS (see mfma_tr).  The
@@ -91,11 +91,17 @@ struct BwdArgs {
     const int32_t *count;  // nullable [NB]: active tokens per block; the other slots are neither queries nor keys
     int nt;               // query / key tiles of 32 tokens
     int n_split, nbp, tiles_per_split;
-    // token keys with grouped-query heads: the query heads of a group are dealt to hsplit workgroups, hpw heads each,
-    // whose fp32 sums [hsplit][NB * 64][H_kv][d] a last pass adds up in order (hsplit == 1: no such pass)
-    int hsplit, hpw;
+    // Token keys: a key block's walk -- the query tiles of its window, then two per entry of its reverse list -- is dealt to
+    // several workgroups where it is long.  With grouped-query heads the query heads of a group go to hsplit
+    // workgroups, hpw heads each; and a walk of more than part_steps tiles is cut into parts of that many (cut_window = 0:
+    // the window, of unknown length, goes to the first part and is not counted).  A (key block, part) is a task;
+    // order / order_part [<= max_tasks] hold the tasks, longest first: the order the workgroups start in.  Where a block's
+    // walk is dealt out, the workgroups leave fp32 sums [hsplit][max_slots][64][H_kv][d], those of block b's parts from slot
+    // slot0[b] on, and a last pass adds them up in order: over all blocks if hsplit > 1, else over those in split_list.
+    int hsplit, hpw, part_steps, max_slots, cut_window;
     float *hpart_k, *hpart_v;
-    const int32_t *order;  // [NB] key blocks, longest reverse list first: the order the token-key workgroups start in
+    int32_t *order, *order_part, *slot0, *split_list, *task_n;  // task_n: number of tasks, length of split_list
+    int32_t *walk;  // [NB] counted tiles of every key block's walk
     float scale, sl2;
 };
 
@@ -432,42 +438,120 @@ __global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, 
 
 // ---------------------------------------------------------------------------------------------
 // reverse routing lists: for every key block the query blocks that list it, ascending
-// Where the lists start, and the key blocks in order of falling reverse-list length (within 1024 length classes; equal lengths in any
-// order -- it only decides which workgroup starts when).  The token-key dK/dV workgroups take their block from
-// this list: the long walks start first instead of forming the tail of the kernel, and the round-robin of
-// workgroups over the XCDs spreads them, where a contiguous range of blocks per XCD left the popular blocks
-// (say, all image blocks) to one or two XCDs.
-__global__ __launch_bounds__(1024) void rev_scan_order(BwdArgs a, int32_t *order) {
-    __shared__ int part[1024], bin[1024];
+// The query tiles that see key block kb in the window branch: [first, first + n).
+struct WindowTiles {
+    int first, n;
+};
+__device__ __forceinline__ WindowTiles window_tiles(const BwdArgs &a, int kb) {
+    const int k0 = kb * 64, half_w = a.window / 2;
+    int seg_lo = 0, seg_hi = 0;
+    if (a.blk_seg != nullptr) {  // the key's spatial block
+        seg_lo = a.blk_seg[2 * kb];
+        seg_hi = a.blk_seg[2 * kb + 1];
+    } else {
+        for (int s = 0; s < a.n_seg; ++s)
+            if (k0 >= a.seg[s] && k0 < a.seg[s + 1]) {
+                seg_lo = a.seg[s];
+                seg_hi = a.seg[s + 1];
+            }
+    }
+    if (a.own_block) {
+        seg_lo = k0;
+        seg_hi = k0 + 64;
+    }
+    // query i sees key j iff -W/2 <= j - i < W/2, i.e. j - W/2 < i <= j + W/2
+    const int i_lo = max(seg_lo, k0 - half_w + 1), i_hi = min(seg_hi, k0 + 63 + half_w + 1);
+    WindowTiles w;
+    w.first = i_lo / 32;
+    w.n = (half_w > 0 && i_hi > i_lo) ? (i_hi - 1) / 32 + 1 - w.first : 0;
+    return w;
+}
+// Where the lists start, and the tasks of the token-key dK/dV workgroups (see BwdArgs) in order of falling length
+// (within 1024 length classes; equal lengths in any order -- it only decides which workgroup starts when): the long
+// walks start first instead of forming the tail of the kernel, and the round-robin of workgroups over the XCDs
+// spreads them, where a contiguous range of blocks per XCD had left the popular blocks (say, all image blocks) to one or
+// two XCDs.
+__global__ __launch_bounds__(1024) void rev_scan_order(BwdArgs a) {
+    constexpr int kHeld = 4096;  // lengths kept in LDS up to this many blocks: a round trip to memory is most of this kernel
+    __shared__ int wave_total[3][16], bin[1024], n_split_blocks, held_cnt[kHeld], held_walk[kHeld];
     const int t = threadIdx.x;
+    const bool held = a.nb <= kHeld;
+    auto cnt = [&](int b) { return held ? held_cnt[b] : a.rev_cnt[b]; };
+    auto walk = [&](int b) { return held ? held_walk[b] : a.walk[b]; };
+    auto n_parts = [&](int steps) { return max(1, (steps + a.part_steps - 1) / a.part_steps); };
+    auto n_slots = [&](int steps) { return a.hsplit > 1 || steps > a.part_steps ? n_parts(steps) : 0; };
+    auto length_class = [](int steps) { return 1023 - min(steps >> 1, 1023); };
     bin[t] = 0;
-    // starts of the lists: exclusive prefix sums of the lengths
+    if (t == 0) n_split_blocks = 0;
+    for (int b = t; b < a.nb; b += 1024) {  // (an even number of window tiles: a part boundary never splits a list entry)
+        const int c = a.rev_cnt[b], w = 2 * c + (a.cut_window ? (window_tiles(a, b).n + 1) & ~1 : 0);
+        a.walk[b] = w;
+        if (held) {
+            held_cnt[b] = c;
+            held_walk[b] = w;
+        }
+    }
+    __syncthreads();
+    // starts of the lists and of the blocks' slots: exclusive prefix sums
     const int chunk = (a.nb + 1023) / 1024;
     const int lo = min(t * chunk, a.nb), hi = min(lo + chunk, a.nb);
-    int s = 0;
-    for (int i = lo; i < hi; ++i) s += a.rev_cnt[i];
-    part[t] = s;
-    __syncthreads();
-    for (int b = t; b < a.nb; b += 1024) atomicAdd(&bin[1023 - min(a.rev_cnt[b], 1023)], 1);  // longest first
+    int s = 0, sl = 0;
+    for (int i = lo; i < hi; ++i) {
+        s += cnt(i);
+        sl += n_slots(walk(i));
+    }
+    for (int b = t; b < a.nb; b += 1024) {
+        const int steps = walk(b), np = n_parts(steps);
+        if (np > 1) atomicAdd(&bin[length_class(a.part_steps)], np - 1);
+        atomicAdd(&bin[length_class(steps - (np - 1) * a.part_steps)], 1);
+    }
     __syncthreads();
     const int own = bin[t];
-    for (int off = 1; off < 1024; off <<= 1) {
-        const int x = t >= off ? part[t - off] : 0, y = t >= off ? bin[t - off] : 0;
-        __syncthreads();
-        part[t] += x;
-        bin[t] += y;
-        __syncthreads();
-    }
-    int run = part[t] - s;  // exclusive prefix of this chunk
+    // inclusive prefix sums over the threads: inside each wavefront, then over the wavefronts' totals
+    int x[3] = {s, own, sl};
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int y = __shfl_up(x[k], off);
+            if ((t & 63) >= off) x[k] += y;
+        }
+    if ((t & 63) == 63)
+        for (int k = 0; k < 3; ++k) wave_total[k][t >> 6] = x[k];
+    __syncthreads();
+    for (int w = 0; w < t >> 6; ++w)
+        for (int k = 0; k < 3; ++k) x[k] += wave_total[k][w];
+    const int part_t = x[0], bin_t = x[1], slots_t = x[2];
+    int run = part_t - s, run_slot = slots_t - sl;
     for (int i = lo; i < hi; ++i) {
         a.rev_ptr[i] = run;
         a.rev_cur[i] = run;
-        run += a.rev_cnt[i];
+        a.slot0[i] = run_slot;
+        run += cnt(i);
+        run_slot += n_slots(walk(i));
     }
-    if (t == 1023) a.rev_ptr[a.nb] = part[1023];
-    bin[t] -= own;  // start of each class
+    if (t == 1023) {
+        a.rev_ptr[a.nb] = part_t;
+        a.task_n[0] = bin_t;
+    }
+    bin[t] = bin_t - own;  // start of each class
     __syncthreads();
-    for (int b = t; b < a.nb; b += 1024) order[atomicAdd(&bin[1023 - min(a.rev_cnt[b], 1023)], 1)] = b;
+    for (int b = t; b < a.nb; b += 1024) {
+        const int steps = walk(b), np = n_parts(steps);
+        if (np > 1) {
+            const int at = atomicAdd(&bin[length_class(a.part_steps)], np - 1);
+            for (int p = 0; p < np - 1; ++p) {
+                a.order[at + p] = b;
+                a.order_part[at + p] = p;
+            }
+            a.split_list[atomicAdd(&n_split_blocks, 1)] = b;
+        }
+        const int at = atomicAdd(&bin[length_class(steps - (np - 1) * a.part_steps)], 1);
+        a.order[at] = b;
+        a.order_part[at] = np - 1;
+    }
+    __syncthreads();
+    if (t == 0) a.task_n[1] = n_split_blocks;
 }
 __global__ void rev_fill(BwdArgs a) {
     int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -887,13 +971,16 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     const int per_xcd = (n_kb + 7) / 8;
     const int head = blockIdx.y;
     int kb;
+    int part = 0;  // of the key block's walk
     if (MODE == 0) {  // token keys: longest walk first (see rev_scan_order)
-        if ((int)blockIdx.x >= n_kb) return;
+        if ((int)blockIdx.x >= a.task_n[0]) return;
         kb = a.order[blockIdx.x];
+        part = a.order_part[blockIdx.x];
     } else {
         kb = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);  // (see bwd_dq_kernel)
         if (kb >= n_kb) return;
     }
+    const int walk = MODE != 1 ? a.walk[kb] : 0;
     const int split = MODE == 1 ? blockIdx.z : 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -930,34 +1017,20 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         for (int i = 0; i < 16; ++i) acck[dt][i] = accv[dt][i] = 0.f;
 
     // ---- the query tiles that attend these keys
-    int tw = 0, wt0 = 0, ts = 0, e0 = 0, T;
+    int tw = 0, wt0 = 0, n_e = 0, e0 = 0, T = 0;  // window / pooled: first tile, how many; reverse list: first entry, how many
     if (MODE == 1) {
         wt0 = split * a.tiles_per_split;
         T = max(0, min(a.nt, wt0 + a.tiles_per_split) - wt0);
-    } else {
-        const int k0 = kb * 64;
-        int seg_lo = 0, seg_hi = 0;
-        if (a.blk_seg != nullptr) {  // the key's spatial block
-            seg_lo = a.blk_seg[2 * kb];
-            seg_hi = a.blk_seg[2 * kb + 1];
-        } else {
-            for (int s = 0; s < a.n_seg; ++s)
-                if (k0 >= a.seg[s] && k0 < a.seg[s + 1]) {
-                    seg_lo = a.seg[s];
-                    seg_hi = a.seg[s + 1];
-                }
-        }
-        if (a.own_block) {
-            seg_lo = k0;
-            seg_hi = k0 + 64;
-        }
-        // query i sees key j iff -W/2 <= j - i < W/2, i.e. j - W/2 < i <= j + W/2
-        const int i_lo = max(seg_lo, k0 - half_w + 1), i_hi = min(seg_hi, k0 + 63 + half_w + 1);
-        wt0 = i_lo / 32;
-        tw = (half_w > 0 && i_hi > i_lo) ? (i_hi - 1) / 32 + 1 - wt0 : 0;
-        e0 = a.rev_ptr[kb];
-        ts = 2 * (a.rev_ptr[kb + 1] - e0);
-        T = tw + ts;
+    } else if (MODE == 0) {
+        const WindowTiles win = window_tiles(a, kb);
+        const int lo = part * a.part_steps, hi = min(lo + a.part_steps, walk);  // this part's share of the walk
+        const int counted = a.cut_window ? (win.n + 1) & ~1 : 0;                // counted window tiles
+        const int w_lo = a.cut_window ? min(lo, win.n) : 0, w_hi = a.cut_window ? min(hi, win.n) : (part == 0 ? win.n : 0);
+        wt0 = win.first + w_lo;
+        tw = w_hi - w_lo;
+        const int e_lo = max(lo - counted, 0) >> 1, e_hi = max(hi - counted, 0) >> 1;
+        e0 = a.rev_ptr[kb] + e_lo;
+        n_e = e_hi - e_lo;
     }
     // The walk is cut into segments with one pipelined loop each: the window tiles, then the routed tiles 64
     // reverse-list entries at a time (one entry per lane, loaded before the loop).  Inside a loop nothing is loaded
@@ -1280,7 +1353,6 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         run_segment(T, std::integral_constant<int, 0>{}, [&](int t) { return wt0 + t; });
     } else if (MODE == 0) {
         run_segment(tw, std::integral_constant<int, 2>{}, [&](int t) { return wt0 + t; });
-        const int n_e = ts >> 1;  // entries of the reverse list: query blocks that route to this key block
         for (int c0 = 0; c0 < n_e; c0 += 64) {
             const int rev_held = c0 + lane < n_e ? a.rev_idx[e0 + c0 + lane] : 0;
             run_segment(2 * min(64, n_e - c0), std::integral_constant<int, 1>{}, [&](int t) {
@@ -1289,9 +1361,10 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         }
     }
 
-    if (MODE == 0 && a.hsplit > 1) {
-        // the sums over this workgroup's heads: [head range][key][head][channel] fp32; the last pass finishes the rows
-        const int64_t o = ((((int64_t)blockIdx.z * a.nb * 64) + key) * a.h_kv + head) * D;
+    if (MODE == 0 && (a.hsplit > 1 || walk > a.part_steps)) {
+        // this workgroup's sums, fp32; the last pass finishes the rows
+        const int64_t slot = (int64_t)blockIdx.z * a.max_slots + a.slot0[kb] + part;
+        const int64_t o = ((slot * 64 + 32 * wave + r) * a.h_kv + head) * D;
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
@@ -1306,24 +1379,6 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
                 *reinterpret_cast<f32x4 *>(a.hpart_v + o + 32 * dt + 8 * g + 4 * hh) = xv;
             }
         return;
-    }
-    if (MODE == 2) {
-        // last pass: the sums of the head ranges, added in order
-        for (int z = 0; z < a.hsplit; ++z) {
-            const int64_t o = ((((int64_t)z * a.nb * 64) + key) * a.h_kv + head) * D;
-#pragma unroll
-            for (int dt = 0; dt < ND; ++dt)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const f32x4 xk = *reinterpret_cast<const f32x4 *>(a.hpart_k + o + 32 * dt + 8 * g + 4 * hh);
-                    const f32x4 xv = *reinterpret_cast<const f32x4 *>(a.hpart_v + o + 32 * dt + 8 * g + 4 * hh);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        acck[dt][4 * g + j] += xk[j];
-                        accv[dt][4 * g + j] += xv[j];
-                    }
-                }
-        }
     }
     if (MODE == 1) {
         // partial sums of this query range: [split][pooled key][head][channel] fp32
@@ -1342,8 +1397,8 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
                 *reinterpret_cast<f32x4 *>(a.part_v + o + 32 * dt + 8 * g + 4 * hh) = xv;
             }
     } else {
-        // add the gradient of the pooled key / value this block went into (its query ranges in order), divided by
-        // the number of tokens that pair averaged: the block's, or its whole spatial block's
+        // add the gradient of the pooled key / value this block went into (its query ranges are added up already),
+        // divided by the number of tokens that pair averaged: the block's, or its whole spatial block's
         const int pair = a.blk_grp != nullptr ? a.blk_grp[kb] : kb;
         const float pooled_tokens = a.grp_tok != nullptr ? (float)a.grp_tok[pair] : (float)n_act;
         float xk[ND][16], xv[ND][16];
@@ -1351,12 +1406,8 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         for (int dt = 0; dt < ND; ++dt)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                f32x4 pk = {0.f, 0.f, 0.f, 0.f}, pv = {0.f, 0.f, 0.f, 0.f};
-                for (int sp = 0; sp < a.n_split; ++sp) {
-                    const int64_t o = (((int64_t)sp * a.nbp + pair) * a.h_kv + head) * D + 32 * dt + 8 * g + 4 * hh;
-                    pk += *reinterpret_cast<const f32x4 *>(a.part_k + o);
-                    pv += *reinterpret_cast<const f32x4 *>(a.part_v + o);
-                }
+                const int64_t o = ((int64_t)pair * a.h_kv + head) * D + 32 * dt + 8 * g + 4 * hh;
+                const f32x4 pk = *reinterpret_cast<const f32x4 *>(a.part_k + o), pv = *reinterpret_cast<const f32x4 *>(a.part_v + o);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     // the block average was taken over its n_act active tokens; a padding slot gets nothing
@@ -1373,10 +1424,65 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     }
 }
 
+// The rows of the key blocks whose walks were dealt out: the sums of the parts of each head range, added in order, then
+// what the token-key kernel does at the end of a walk of its own (pooled gradient, scale, rounding).  One workgroup per
+// (block, key/value head, 256 groups of four channels of a token), one such group per thread, four sums of each of dk and dv in flight:
+// bound by memory at size (196 K tokens, 2 key/value heads of 32, 8 ranges: 805 MB of sums), by its chain of loads
+// below.
+template <int D>
+__global__ __launch_bounds__(256) void sum_walks(BwdArgs a) {
+    const int head = blockIdx.y;
+    int kb = blockIdx.x;
+    if (a.hsplit == 1) {  // only the blocks whose walk was cut
+        if (kb >= a.task_n[1]) return;
+        kb = a.split_list[kb];
+    }
+    const int np = max(1, (a.walk[kb] + a.part_steps - 1) / a.part_steps), n_sums = a.hsplit * np, slot0 = a.slot0[kb];
+    const int n_act = a.count != nullptr ? a.count[kb] : 64;
+    const int pair = a.blk_grp != nullptr ? a.blk_grp[kb] : kb;
+    const float pooled_tokens = a.grp_tok != nullptr ? (float)a.grp_tok[pair] : (float)n_act;
+    const int64_t range = (int64_t)a.max_slots * 64 * a.h_kv * D, slot = (int64_t)64 * a.h_kv * D;  // in floats
+    const int e = blockIdx.z * 256 + threadIdx.x;
+    const int row = e / (D / 4), c = 4 * (e % (D / 4));
+    const int64_t in_slot = ((int64_t)row * a.h_kv + head) * D + c;
+    const int64_t o_pair = ((int64_t)pair * a.h_kv + head) * D + c;
+    const f32x4 pk = *reinterpret_cast<const f32x4 *>(a.part_k + o_pair);
+    const f32x4 pv = *reinterpret_cast<const f32x4 *>(a.part_v + o_pair);
+    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < n_sums; i += 4) {
+        f32x4 xk[4], xv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int at = min(i + j, n_sums - 1), z = at / np;  // (past the end: the last one, not added)
+            const int64_t o = z * range + (slot0 + at - z * np) * slot + in_slot;
+            xk[j] = *reinterpret_cast<const f32x4 *>(a.hpart_k + o);
+            xv[j] = *reinterpret_cast<const f32x4 *>(a.hpart_v + o);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j < n_sums) {
+                sk += xk[j];
+                sv += xv[j];
+            }
+    }
+    const float inv_cnt = row < n_act ? 1.0f / pooled_tokens : 0.f;  // a padding slot gets nothing
+    uint2 wk, wv;
+    wk.x = pack_bf16((sk[0] + pk[0] * inv_cnt) * a.scale, (sk[1] + pk[1] * inv_cnt) * a.scale);
+    wk.y = pack_bf16((sk[2] + pk[2] * inv_cnt) * a.scale, (sk[3] + pk[3] * inv_cnt) * a.scale);
+    wv.x = pack_bf16(sv[0] + pv[0] * inv_cnt, sv[1] + pv[1] * inv_cnt);
+    wv.y = pack_bf16(sv[2] + pv[2] * inv_cnt, sv[3] + pv[3] * inv_cnt);
+    const int64_t dst = (((int64_t)kb * 64 + row) * a.h_kv + head) * D + c;
+    *reinterpret_cast<uint2 *>(a.dk + dst) = wk;
+    *reinterpret_cast<uint2 *>(a.dv + dst) = wv;
+}
+
+// the shortest part a token-key walk is cut into, in query tiles
+constexpr int kMinPart = 16;
+
 struct WsLayout {
     size_t img_q, img_do[3], img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
-    int n_split, nbp, tiles_per_split, hsplit, hpw;
-    size_t hpart_k, hpart_v, order, gtab;
+    int n_split, nbp, tiles_per_split, hsplit, hpw, part_steps, max_tasks, max_slots, max_split;
+    size_t hpart_k, hpart_v, order, order_part, slot0, split_list, task_n, walk, gtab;
 };
 
 WsLayout ws_layout(const Shape &s) {
@@ -1438,23 +1544,45 @@ WsLayout ws_layout(const Shape &s) {
     }
     w.part_k = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
     w.part_v = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
-    // token keys: with grouped-query heads a workgroup would walk group x as many steps while there are group x
-    // fewer workgroups, and the longest reverse list sets the kernel's time -- deal the heads of a group to
-    // up to 8 workgroups
-    // (as long as their fp32 sums stay within 2 GiB of workspace)
-    const int grp = s.h / s.h_kv;
-    const size_t per_range = (size_t)s.nb * 64 * s.h_kv * s.d * 4 * 2;
-    const size_t fit = per_range > 0 ? ((size_t)2 << 30) / per_range : 8;
-    const int ranges = (int)(fit < 8 ? (fit < 1 ? 1 : fit) : 8);
-    w.hpw = (grp + ranges - 1) / ranges;
-    w.hsplit = (grp + w.hpw - 1) / w.hpw;
-    w.hpart_k = w.hpart_v = 0;
-    if (w.hsplit > 1) {
-        w.hpart_k = take((size_t)w.hsplit * s.nb * 64 * s.h_kv * s.d * 4);
-        w.hpart_v = take((size_t)w.hsplit * s.nb * 64 * s.h_kv * s.d * 4);
+    // Token keys.  With grouped-query heads a workgroup would walk group x as many steps while there are group x
+    // fewer workgroups, so the heads of a group are dealt to up to 8 workgroups (as long as the fp32 sums stay within
+    // 2 GiB of workspace).  And no single walk may set the kernel's time: geometric routing makes some blocks popular,
+    // and a small problem has too few walks to fill the chip, which then waits for the latency of their steps (1 to 2 us
+    // each).  A walk is cut where it would take more than half of what an evenly filled chip needs for all of them --
+    // longest first, a shorter walk never ends last -- but not below kMinPart tiles: there a workgroup's start and its
+    // sums (32 KB at d = 64, written and read) cost more than the shorter walk gains.
+    {
+        const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
+        const int grp = s.h / s.h_kv;
+        const int64_t win = s.group_window ? 0 : ((64 + s.window) / 32 + 2 + 1) & ~1;  // bounds a block's counted window
+        const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);
+        for (int ranges = 8; ranges >= 1; --ranges) {
+            w.hpw = (grp + ranges - 1) / ranges;
+            w.hsplit = (grp + w.hpw - 1) / w.hpw;
+            int64_t len = steps * s.h_kv * w.hsplit / slots / 2;
+            len = (len + 1) & ~(int64_t)1;
+            if (len < kMinPart) len = kMinPart;
+            if (len > 0x3ffffffe) len = 0x3ffffffe;
+            w.part_steps = (int)len;
+            // bounds whatever the table holds: parts beyond a block's first number at most steps / len in all, and
+            // so do the blocks that are cut
+            const int64_t more = steps / len;
+            w.max_split = (int)(more < s.nb ? more : s.nb);
+            w.max_tasks = (int)(s.nb + more);
+            w.max_slots = w.hsplit > 1 ? w.max_tasks : (int)(w.max_split + more);
+            if ((double)w.hsplit * w.max_slots * 64 * s.h_kv * s.d * 8 <= 2147483648.0) break;
+        }
     }
+    const size_t sums = (size_t)w.hsplit * w.max_slots * 64 * s.h_kv * s.d * 4;
+    w.hpart_k = take(sums);
+    w.hpart_v = take(sums);
+    w.order = take((size_t)w.max_tasks * 4);
+    w.order_part = take((size_t)w.max_tasks * 4);
+    w.slot0 = take((size_t)s.nb * 4);
+    w.split_list = take((size_t)w.max_split * 4);
+    w.task_n = take(8);
+    w.walk = take((size_t)s.nb * 4);
     w.rev_cnt = take((size_t)s.nb * 4);
-    w.order = take((size_t)s.nb * 4);
     w.rev_ptr = take((size_t)(s.nb + 1) * 4);
     w.rev_cur = take((size_t)s.nb * 4);
     w.rev_idx = take((size_t)s.nb * (s.topk > 0 ? s.topk : 1) * 4);
@@ -1473,8 +1601,6 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                                        hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
-    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 2>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
     hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)(a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB))),
                        dim3(PrepGeo<D>::THREADS), 0, st, a);
@@ -1484,7 +1610,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     hipLaunchKernelGGL(pack_rows<D>, dim3((unsigned)(n_wg + n_count_wg)), dim3(256), 0, st, a, n_token_wg, n_wg);
     LSRM_HIP_CHECK(hipGetLastError());
     // reverse routing lists
-    hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a, const_cast<int32_t *>(a.order));
+    hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     if (s.topk > 0) {
         hipLaunchKernelGGL(rev_fill, dim3((s.nb * s.topk + 255) / 256), dim3(256), 0, st, a);
@@ -1511,10 +1637,12 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
         LSRM_HIP_CHECK(hipGetLastError());
         a.n_split = 1;  // (the kernels below read range 0's slot only)
     }
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3((s.nb + 7) / 8 * 8, s.h_kv, a.hsplit), dim3(128), DKV_LDS, st, a);
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), DKV_LDS, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    if (a.hsplit > 1) {  // add up the per-head-range sums, in order, and finish the rows
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, 2>), dim3((s.nb + 7) / 8 * 8, s.h_kv), dim3(128), DKV_LDS, st, a);
+    // add up the sums of walks that were dealt out, in order, and finish their rows
+    const int n_sum_blocks = a.hsplit > 1 ? s.nb : w.max_split;
+    if (n_sum_blocks > 0) {
+        hipLaunchKernelGGL(sum_walks<D>, dim3(n_sum_blocks, s.h_kv, D / 16), dim3(256), 0, st, a);
         LSRM_HIP_CHECK(hipGetLastError());
     }
     if (ev_stop != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_stop, st));
@@ -1589,7 +1717,15 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.hpw = w.hpw;
     a.hpart_k = reinterpret_cast<float *>(ws + w.hpart_k);
     a.hpart_v = reinterpret_cast<float *>(ws + w.hpart_v);
-    a.order = reinterpret_cast<const int32_t *>(ws + w.order);
+    a.part_steps = w.part_steps;
+    a.cut_window = s.group_window ? 0 : 1;
+    a.walk = reinterpret_cast<int32_t *>(ws + w.walk);
+    a.max_slots = w.max_slots;
+    a.order = reinterpret_cast<int32_t *>(ws + w.order);
+    a.order_part = reinterpret_cast<int32_t *>(ws + w.order_part);
+    a.slot0 = reinterpret_cast<int32_t *>(ws + w.slot0);
+    a.split_list = reinterpret_cast<int32_t *>(ws + w.split_list);
+    a.task_n = reinterpret_cast<int32_t *>(ws + w.task_n);
     a.nbp = w.nbp;
     a.tiles_per_split = w.tiles_per_split;
     a.scale = s.scale;

@@ -289,3 +289,19 @@ def test_backward_full_size_is_deterministic(B, oracle_lib):
     for other in runs[1:]:
         for x, y in zip(runs[0], other):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("d,heads,h_kv", [(64, 2, 2), (32, 6, 2), (128, 1, 1)])
+def test_backward_lists_cut_into_parts(B, oracle_lib, d, heads, h_kv):
+    """Walks at the edges of the parts they are cut into (16 tiles at this size, 6 of them the window's away from the ends of
+    the sequence): lists of 4, 5, 6 and 13, 14 entries and one of an entry per row, without grouped heads (only cut
+    blocks take the summing pass) and with them (all do)."""
+    cfg = I.small_config(name=f"b-parts-d{d}", n_obj=45 * 64, n_views=1, grid=16, heads=heads, d=d, topk=6, window=96,
+                         seed=29, h_kv=h_kv)
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    idx = np.full((cfg.nb, cfg.topk), -1, dtype=np.int32)
+    for col, (block, rows) in enumerate(((3, cfg.nb), (5, 4), (7, 5), (11, 6), (12, 13), (30, 14))):
+        idx[(np.arange(rows) * 3) % cfg.nb, col] = block
+    assert [int((idx == b).sum()) for b in (3, 5, 7, 11, 12, 30)] == [49, 4, 5, 6, 13, 14]
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)
