@@ -6,7 +6,7 @@
 //   select_topk     one 256-thread workgroup per query block (object block or image
 //                   tile): evaluates the squared 2-D distance to every candidate once
 //                   (keys parked in LDS) and extracts the K smallest (distance, id)
-//                   keys by K rounds of a workgroup-wide minimum.
+//                   keys: K rounds of a minimum per wave, then a merge of the four lists.
 // and, for the four selection rules (volume/image query -> volume/image blocks):
 //   block_points    one thread per block of either modality: centroid of its 64 points.
 //   select_3d       one 256-thread workgroup per query block: a wave per view projects the
@@ -108,43 +108,91 @@ __device__ __forceinline__ float wave_min_nonneg_f32(float v) { return __uint_as
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
     const unsigned hi = (unsigned)(v >> 32), lo = (unsigned)v;
     const unsigned hi_min = wave_min_u32(hi);
-    const unsigned lo_min = wave_min_u32(hi == hi_min ? lo : 0xffffffffu);
+    // one lane holds it, unless distances tie: no second fold then
+    const unsigned long long at = __ballot(hi == hi_min);
+    const unsigned lo_min = (at & (at - 1)) == 0 ? (unsigned)__builtin_amdgcn_readlane(lo, __builtin_ctzll(at))
+                                                 : wave_min_u32(hi == hi_min ? lo : 0xffffffffu);
     return ((unsigned long long)hi_min << 32) | lo_min;
 }
 
 constexpr unsigned long long kNoKey = ~0ull;
 
+// What a lane holds of a set of distinct keys (none equal to all-ones) whose smallest are taken one by one: the two
+// smallest of its own candidates me, me + step, ... below n_cand that were not taken yet.  Only the lane that owned the
+// taken key and has none left rescans, which serialises the wave (never, up to two candidates per lane).
+struct LaneKeys {
+    unsigned long long mine, next;
+
+    template <class KeyAt>
+    __device__ __forceinline__ void scan(int me, int step, int n_cand, KeyAt key_at, bool have_floor,
+                                         unsigned long long floor_key) {
+        mine = next = kNoKey;
+        for (int c = me; c < n_cand; c += step) {
+            // (selects, no branches: written with branches the two keys were once kept in scratch memory)
+            unsigned long long key = key_at(c);
+            key = have_floor && key <= floor_key ? kNoKey : key;
+            const unsigned long long larger = key < mine ? mine : key;
+            mine = key < mine ? key : mine;
+            next = larger < next ? larger : next;
+        }
+    }
+    template <class KeyAt>
+    __device__ __forceinline__ void take(unsigned long long best, int me, int step, int n_cand, KeyAt key_at) {
+        if (mine != best) return;
+        if (next != kNoKey || n_cand <= 2 * step) {
+            mine = next;
+            next = kNoKey;
+        } else {
+            scan(me, step, n_cand, key_at, true, best);
+        }
+    }
+};
+
 // The k smallest of a set of distinct keys (none equal to all-ones), in ascending order, found by
 // one wave: lane l looks at candidates first + l', first + l' + step, ... below n_cand, where l' is
 // `me` (the lane id for a wave working alone, the thread id when the four waves of a workgroup
-// each take a quarter).  A round is one wave-wide minimum; only the lane that owned the winner
-// rescans its candidates.  emit(r, key) is called by every lane for r = 0 .. count-1; returns count.
+// each take a quarter).  A round is one wave-wide minimum.  emit(r, key) is called by every lane for
+// r = 0 .. count-1; returns count.
 template <class KeyAt, class Emit>
 __device__ __forceinline__ int wave_extract(int me, int step, int n_cand, KeyAt key_at, int k, Emit emit) {
-    auto scan = [&](bool have_floor, unsigned long long floor_key) {
-        unsigned long long best = kNoKey;
-        for (int c = me; c < n_cand; c += step) {
-            unsigned long long key = key_at(c);
-            if ((!have_floor || key > floor_key) && key < best) best = key;
-        }
-        return best;
-    };
-    unsigned long long mine = scan(false, 0);
+    LaneKeys held;
+    held.scan(me, step, n_cand, key_at, false, 0);
     int n = 0;
     for (; n < k; ++n) {
-        const unsigned long long best = wave_min_u64(mine);
+        const unsigned long long best = wave_min_u64(held.mine);
         if (best == kNoKey) break;
         emit(n, best);
-        if (mine == best) mine = scan(true, best);
+        held.take(best, me, step, n_cand, key_at);
     }
     return n;
 }
 
+// The k smallest of n_cand distinct keys (all-ones: no candidate), by one wave that counts, for each key, the smaller
+// ones: put(r, key) is called by the lane that holds the key of rank r.  Returns the number of keys put.  About four
+// instructions per 64 pairs of keys, no chain from one result to the next.
+template <class KeyAt, class Put>
+__device__ __forceinline__ int wave_rank(int lane, int n_cand, KeyAt key_at, int k, Put put) {
+    int n = 0;
+    for (int c0 = 0; c0 < n_cand; c0 += 64) {
+        const unsigned long long key = c0 + lane < n_cand ? key_at(c0 + lane) : kNoKey;
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < n_cand; ++j) rank += key_at(j) < key ? 1 : 0;
+        if (key != kNoKey && rank < k) put(rank, key);
+        n += __popcll(__ballot(key != kNoKey));
+    }
+    return n < k ? n : k;
+}
+
 // Top-k over the whole workgroup (256 threads): every wave extracts the k smallest keys of its
-// quarter into `stage` (LDS, 4 * k entries), then wave 0 merges them.  Returns, in wave 0 only,
-// the number of keys emitted; the other waves get -1 and have nothing left to do for this list.
-template <class KeyAt, class Emit>
-__device__ __forceinline__ int wg_topk(int n_cand, KeyAt key_at, int k, unsigned long long *stage, Emit emit) {
+// quarter into `stage` (LDS, 4 * k entries), then every key finds its place among all four lists -- its own position
+// plus the number of smaller keys in each of the others, by bisection -- and the lane that holds it calls put(r, key).
+// (One wave that extracted the k smallest of the 4 k again took as long as the first step, the others idle.)
+// Bound by instructions issued; with LaneKeys, wave_rank and the tile keys kept between picks: four-rule routing of 57 K
+// tokens, 8 of 512 volume blocks and 24 tiles of 6 views each, 493 -> 302 us.
+// Returns, in wave 0 only, the number of keys put; the other waves get -1 and have nothing left to do for this list.
+template <class KeyAt, class Put>
+__device__ __forceinline__ int wg_topk(int n_cand, KeyAt key_at, int k, unsigned long long *stage, Put put) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long *mine = stage + (size_t)wave * k;
     int n = wave_extract(threadIdx.x, 256, n_cand, key_at, k, [&](int r, unsigned long long key) {
@@ -152,8 +200,23 @@ __device__ __forceinline__ int wg_topk(int n_cand, KeyAt key_at, int k, unsigned
     });
     for (int r = n + lane; r < k; r += 64) mine[r] = kNoKey;
     __syncthreads();
+    for (int r = lane; r < n; r += 64) {
+        const unsigned long long key = mine[r];
+        int rank = r;
+#pragma unroll
+        for (int o = 1; o < 4; ++o) {
+            const unsigned long long *list = stage + (size_t)((wave + o) & 3) * k;
+            int below = 0;
+            for (int step = 1 << (31 - __builtin_clz(k)); step > 0; step >>= 1) {
+                const int to = below + step;
+                if (to <= k && list[to - 1] < key) below = to;
+            }
+            rank += below;
+        }
+        if (rank < k) put(rank, key);
+    }
     if (wave != 0) return -1;
-    return wave_extract(lane, 64, 4 * k, [&](int c) { return stage[c]; }, k, emit);
+    return n_cand < k ? n_cand : k;
 }
 
 // One workgroup per query block.  The squared distances of all candidates are computed once into
@@ -190,19 +253,17 @@ __global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int 
     };
     int32_t *idx_row = idx + (size_t)row * topk;
     float *d2_row = dist2_out ? dist2_out + (size_t)row * topk : nullptr;
-    auto emit = [&](int r, unsigned long long key) {
-        if ((threadIdx.x & 63) == 0) {
-            idx_row[r] = id_base + (int)(unsigned)(key & 0xffffffffu);
-            if (d2_row) d2_row[r] = __uint_as_float((unsigned)(key >> 32));
-        }
+    auto put = [&](int r, unsigned long long key) {
+        idx_row[r] = id_base + (int)(unsigned)(key & 0xffffffffu);
+        if (d2_row) d2_row[r] = __uint_as_float((unsigned)(key >> 32));
     };
     int n;
     if (cache_keys) {
         // every thread reads back only the entries it wrote itself: no barrier needed
         for (int c = threadIdx.x; c < n_cand; c += blockDim.x) d2_cache[c] = d2_of(c);
-        n = wg_topk(n_cand, [&](int c) { return make_key(d2_cache[c], (unsigned)c); }, topk, stage, emit);
+        n = wg_topk(n_cand, [&](int c) { return make_key(d2_cache[c], (unsigned)c); }, topk, stage, put);
     } else {
-        n = wg_topk(n_cand, [&](int c) { return make_key(d2_of(c), (unsigned)c); }, topk, stage, emit);
+        n = wg_topk(n_cand, [&](int c) { return make_key(d2_of(c), (unsigned)c); }, topk, stage, put);
     }
     if (n < 0) return;
     for (int k = n + (threadIdx.x & 63); k < topk; k += 64) {  // fewer candidates than topk
@@ -275,7 +336,10 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
             }
             // candidates in groups of four: pick four tiles, then fetch and measure their point sets
             // together so that the memory latency is paid once per group
-            unsigned long long floor_key = 0;
+            // every tile's key is worked out once (a division by the row length each), not once per pick
+            auto tile_key = [&](int t) { return make_key(dist2(uv, t / a.tg, t % a.tg), (unsigned)t); };
+            LaneKeys held;
+            held.scan(lane, 64, tpv, tile_key, false, 0);
             for (int c0 = 0; c0 < a.prefilter; c0 += 4) {
                 int tile[4];
                 float d[4];
@@ -283,13 +347,8 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
                 for (int u = 0; u < 4; ++u) {
                     tile[u] = -1;
                     if (c0 + u < a.prefilter) {
-                        unsigned long long best = kNoKey;
-                        for (int t = lane; t < tpv; t += 64) {
-                            unsigned long long key = make_key(dist2(uv, t / a.tg, t % a.tg), (unsigned)t);
-                            if ((c0 + u == 0 || key > floor_key) && key < best) best = key;
-                        }
-                        best = wave_min_u64(best);
-                        floor_key = best;
+                        const unsigned long long best = wave_min_u64(held.mine);
+                        held.take(best, lane, 64, tpv, tile_key);
                         tile[u] = m * tpv + (int)(unsigned)(best & 0xffffffffu);
                     }
                 }
@@ -320,20 +379,18 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
         return sqdist3(p.x, p.y, p.z, c.x, c.y, c.z);
     };
     int at = 0;
-    auto emit = [&](int r, unsigned long long key) {
-        if (lane == 0) {
-            idx_row[at + r] = (int)(unsigned)(key & 0xffffffffu);
-            if (d2_row) d2_row[at + r] = __uint_as_float((unsigned)(key >> 32));
-        }
+    auto put = [&](int r, unsigned long long key) {
+        idx_row[at + r] = (int)(unsigned)(key & 0xffffffffu);
+        if (d2_row) d2_row[at + r] = __uint_as_float((unsigned)(key >> 32));
     };
     if (kv > 0) {
         int n;
         if (a.cache_keys) {
             // every thread reads back only the entries it wrote itself
             for (int j = threadIdx.x; j < a.nb_obj; j += blockDim.x) vol_d2[j] = vol_d2_of(j);
-            n = wg_topk(a.nb_obj, [&](int j) { return make_key(vol_d2[j], (unsigned)j); }, kv, stage, emit);
+            n = wg_topk(a.nb_obj, [&](int j) { return make_key(vol_d2[j], (unsigned)j); }, kv, stage, put);
         } else {
-            n = wg_topk(a.nb_obj, [&](int j) { return make_key(vol_d2_of(j), (unsigned)j); }, kv, stage, emit);
+            n = wg_topk(a.nb_obj, [&](int j) { return make_key(vol_d2_of(j), (unsigned)j); }, kv, stage, put);
         }
         if (n < 0) return;
         at = n;
@@ -342,8 +399,18 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
         if (wave != 0) return;
     }
     // wave 0 alone: the image budget out of the surviving candidates, then the padding
-    if (ki > 0)
-        at += wave_extract(lane, 64, a.n_views * a.prefilter, [&](int c) { return img_keys[c]; }, ki, emit);
+    if (ki > 0) {
+        const int n_img = a.n_views * a.prefilter;
+        auto key_of = [&](int c) { return img_keys[c]; };
+        // Ranking costs about 4 instructions per candidate and 64 of them, an extraction about 60 per result, one
+        // waiting for the other: the line is where they are equal.
+        if ((n_img + 63) / 64 * n_img <= 16 * ki)
+            at += wave_rank(lane, n_img, key_of, ki, put);
+        else
+            at += wave_extract(lane, 64, n_img, key_of, ki, [&](int r, unsigned long long key) {
+                if (lane == 0) put(r, key);
+            });
+    }
     for (int k = at + lane; k < a.width; k += 64) {
         idx_row[k] = -1;
         if (d2_row) d2_row[k] = __builtin_inff();

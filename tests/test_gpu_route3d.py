@@ -153,3 +153,21 @@ def test_route_3d_per_token_full_size_sampled(B, oracle_lib):
     ref = oracle_lib.route_3d(pos, pimg, cams, cfg.grid, 44, 4, 8, 36, 8, 36, per_token=True, queries=pick)
     idx, d2 = G.run_route_3d(B, cfg, pos, pimg, cams, 44, 4, 8, 36, 8, 36, per_token=True)
     _same((idx[pick], d2[pick]), ref)
+
+
+@pytest.mark.parametrize("n_blocks,n_views,pre,budgets", [
+    (520, 4, 16, (64, 64, 65, 63)),      # 64 image candidates, lists of 64 and 65; some threads hold a third volume block
+    (512, 5, 16, (1, 10, 118, 9)),       # 80 image candidates: ranked for 10 results, extracted for 9
+    (1100, 5, 13, (127, 1, 33, 95)),     # 65 image candidates; lists of more than 64
+    (200, 1, 1, (128, 0, 100, 1)),       # one candidate per thread, lists longer than a quarter of the candidates
+], ids=lambda v: str(v).replace(" ", ""))
+def test_route_3d_list_lengths_at_the_edges(B, oracle_lib, n_blocks, n_views, pre, budgets):
+    """Lengths at which selection changes its course: rounds, merge of the wavefronts' lists, ranking of the tiles."""
+    cfg = I.small_config(name="r3-edge", n_obj=64 * n_blocks, n_views=n_views, grid=32, seed=n_blocks)
+    width = max(budgets[0] + budgets[1], budgets[2] + budgets[3])
+    _log(f"[route3d] {n_blocks} blocks, {n_views} views, B^i={pre} budgets={budgets}")
+    pos, cams = I.make_points(cfg), I.make_cameras(cfg)
+    pos[64 * 5:64 * 9] = pos[64:128].repeat(4, axis=0)  # coinciding centroids: distances tie, ids decide
+    pimg = I.make_points_img(cfg, cams)
+    ref = oracle_lib.route_3d(pos, pimg, cams, cfg.grid, width, pre, *budgets)
+    _same(G.run_route_3d(B, cfg, pos, pimg, cams, width, pre, *budgets), ref)
