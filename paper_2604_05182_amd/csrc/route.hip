@@ -1,14 +1,14 @@
 // 3D-aware block routing on gfx950 (Sec. 3.3 of the paper, block-level reading).
 //
 // Two kernels:
-//   project_blocks  one thread per object block: centroid of its 64 positions, then its
-//                   pinhole projection (u, v) into every view.
+//   project_blocks  one workgroup per sixteen object blocks: centroid of their 64 positions, then
+//                   its pinhole projection (u, v) into every view.
 //   select_topk     one 256-thread workgroup per query block (object block or image
 //                   tile): evaluates the squared 2-D distance to every candidate once
 //                   (keys parked in LDS) and extracts the K smallest (distance, id)
 //                   keys: K rounds of a minimum per wave, then a merge of the four lists.
 // and, for the four selection rules (volume/image query -> volume/image blocks):
-//   block_points    one thread per block of either modality: centroid of its 64 points.
+//   block_points    one workgroup per sixteen blocks of either modality: centroid of their 64 points.
 //   select_3d       one 256-thread workgroup per query block: a wave per view projects the
 //                   query point, keeps the B^i tiles with the nearest 2-D centres and
 //                   measures each one's point set (64 lanes = 64 points, minimum squared 3-D
@@ -48,21 +48,49 @@ __device__ __forceinline__ float2 project(const lsrm_camera &c, float cx, float 
     return r;
 }
 
+// Centroids of blocks b0 .. b0 + n - 1 (n <= kCentBlocks) into cent[.][0..2], by a workgroup of 256 threads: the points come
+// in whole lines into LDS, then a thread per (block, coordinate) adds its 64 values left to right.  Bound by latency:
+// with one thread per block that loaded its 192 floats itself, 768 bytes apart from its neighbours', the whole kernel
+// waited for strided loads (4096 blocks into 18 views 20 -> 4 us; a whole forward step of 6 K tokens
+// 34.8 -> 33.1 us, four-rule routing of 57 K tokens 303 -> 298 us).  The pitch of 195 puts the 48 threads of the sum in 48 banks.  point_at(b) = the first
+// coordinate of block b.
+constexpr int kCentBlocks = 16, kCentPitch = 3 * kBlock + 3;
+template <class PointAt>
+__device__ __forceinline__ void block_centroids(int b0, int n, PointAt point_at, float (&cent)[kCentBlocks][3]) {
+    __shared__ float pts[kCentBlocks * kCentPitch];
+    const int tid = threadIdx.x;
+    float v[kCentBlocks * 3 * kBlock / 256];
+#pragma unroll
+    for (int u = 0; u < kCentBlocks * 3 * kBlock / 256; ++u) {
+        const int i = u * 256 + tid, b = i / (3 * kBlock);
+        v[u] = b < n ? point_at(b0 + b)[i % (3 * kBlock)] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kCentBlocks * 3 * kBlock / 256; ++u) {
+        const int i = u * 256 + tid;
+        pts[i / (3 * kBlock) * kCentPitch + i % (3 * kBlock)] = v[u];
+    }
+    __syncthreads();
+    if (tid < 3 * kCentBlocks) {
+        const float *p = pts + tid / 3 * kCentPitch + tid % 3;
+        float s = p[0];
+#pragma unroll 16
+        for (int t = 1; t < kBlock; ++t) s = s + p[3 * t];
+        cent[tid / 3][tid % 3] = s * (1.0f / 64.0f);
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(256) void project_blocks(int nb_obj, int n_views, const float *__restrict__ pos,
                                                       const lsrm_camera *__restrict__ cams,
                                                       float2 *__restrict__ uv /* [nb_obj, n_views] */) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb_obj) return;
-    const float *p = pos + (size_t)b * kBlock * 3;
-    float sx = p[0], sy = p[1], sz = p[2];
-    for (int t = 1; t < kBlock; ++t) {
-        sx = sx + p[3 * t + 0];
-        sy = sy + p[3 * t + 1];
-        sz = sz + p[3 * t + 2];
+    __shared__ float cent[kCentBlocks][3];
+    const int b0 = blockIdx.x * kCentBlocks, n = min(kCentBlocks, nb_obj - b0);
+    block_centroids(b0, n, [&](int b) { return pos + (size_t)b * kBlock * 3; }, cent);
+    for (int i = threadIdx.x; i < n * n_views; i += 256) {
+        const float *c = cent[i / n_views];
+        uv[(size_t)b0 * n_views + i] = project(cams[i % n_views], c[0], c[1], c[2]);
     }
-    const float inv = 1.0f / 64.0f;
-    float cx = sx * inv, cy = sy * inv, cz = sz * inv;
-    for (int m = 0; m < n_views; ++m) uv[(size_t)b * n_views + m] = project(cams[m], cx, cy, cz);
 }
 
 __device__ __forceinline__ float dist2(float2 p, int ti, int tj) {
@@ -278,17 +306,18 @@ __global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int 
 // the others `pos_img`; the result is padded to float4.
 __global__ __launch_bounds__(256) void block_points(int nb_obj, int nb, const float *__restrict__ pos,
                                                     const float *__restrict__ pos_img, float4 *__restrict__ cent) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    const float *p = b < nb_obj ? pos + (size_t)b * kBlock * 3 : pos_img + (size_t)(b - nb_obj) * kBlock * 3;
-    float sx = p[0], sy = p[1], sz = p[2];
-    for (int t = 1; t < kBlock; ++t) {
-        sx = sx + p[3 * t + 0];
-        sy = sy + p[3 * t + 1];
-        sz = sz + p[3 * t + 2];
+    __shared__ float c[kCentBlocks][3];
+    const int b0 = blockIdx.x * kCentBlocks, n = min(kCentBlocks, nb - b0);
+    block_centroids(
+        b0, n,
+        [&](int b) {
+            return b < nb_obj ? pos + (size_t)b * kBlock * 3 : pos_img + (size_t)(b - nb_obj) * kBlock * 3;
+        },
+        c);
+    if ((int)threadIdx.x < n) {
+        const float *m = c[threadIdx.x];
+        cent[b0 + threadIdx.x] = make_float4(m[0], m[1], m[2], 0.0f);
     }
-    const float inv = 1.0f / 64.0f;
-    cent[b] = make_float4(sx * inv, sy * inv, sz * inv, 0.0f);
 }
 
 __device__ __forceinline__ float sqdist3(float ax, float ay, float az, float bx, float by, float bz) {
@@ -428,7 +457,7 @@ lsrm_status launch_route_3d(const Shape &s, const lsrm_route3d_params &r, const 
                             const lsrm_camera *d_cams, int32_t *d_idx, float *d_dist2, void *d_ws, hipStream_t st) {
     if (s.nb == 0 || s.topk == 0) return LSRM_OK;
     float4 *cent = reinterpret_cast<float4 *>(d_ws);
-    hipLaunchKernelGGL(block_points, dim3((s.nb + 255) / 256), dim3(256), 0, st, s.nb_obj, s.nb, d_pos, d_pos_img,
+    hipLaunchKernelGGL(block_points, dim3((s.nb + kCentBlocks - 1) / kCentBlocks), dim3(256), 0, st, s.nb_obj, s.nb, d_pos, d_pos_img,
                        cent);
     LSRM_HIP_CHECK(hipGetLastError());
     Route3d a;
@@ -498,7 +527,7 @@ lsrm_status launch_route(const Shape &s, const float *d_pos, const lsrm_camera *
                          float *d_dist2, void *d_ws, hipStream_t st) {
     float2 *uv = reinterpret_cast<float2 *>(d_ws);
     if (s.nb_obj > 0 && s.n_views > 0) {
-        int grid = (s.nb_obj + 255) / 256;
+        const int grid = (s.nb_obj + kCentBlocks - 1) / kCentBlocks;
         hipLaunchKernelGGL(project_blocks, dim3(grid), dim3(256), 0, st, s.nb_obj, s.n_views, d_pos, d_cams, uv);
         LSRM_HIP_CHECK(hipGetLastError());
     }
