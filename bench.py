@@ -31,7 +31,7 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense bf16
 # HBM bytes per launch of the attention kernel (fetched + written), from rocprofv3 FETCH_SIZE / WRITE_SIZE
 # runs of this script scaled by the same counters of a plain 1 GiB copy; the readings and the commands are
 # in profiles/nsa_forward_kernel_config4_hbm_traffic.txt.  Only the workloads that were profiled appear.
-MEASURED_HBM_BYTES = {4: 56.5e9 + 3.5e9}
+MEASURED_HBM_BYTES = {4: 82.2e9 + 3.5e9}
 
 
 def cpu_baseline(cfg, arrays, idx, target_seconds=20.0):
@@ -350,7 +350,7 @@ def main():
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
         },
     }
-    # the whole lsrm_nsa_forward call (step schedule, packing of the pooled pairs, attention kernel; with --two-pass also
+    # the whole lsrm_nsa_forward call (packing of the pooled pairs, attention kernel; with --two-pass also
     # the packing of k and v) against the same peak
     call_tflops = flops / (ms_fwd_call * 1e-3) / 1e12
     result["roofline_call"] = {"call": "lsrm_nsa_forward", "bound": "mfma", "achieved": round(call_tflops, 3),
@@ -360,12 +360,12 @@ def main():
         # At d <= 64 the softmax arithmetic, not the matrix pipe, bounds the kernel: a 32 x 32 score tile costs 8 MFMAs
         # at d = 64 (4 at d = 32) but always 1024 exponentials.  Per score element and head the kernel issues one
         # fused scale-and-subtract, one exponential (a quarter-rate instruction: 4 issue slots), one add into the row
-        # sum and half a packed bf16 conversion -- 6.5 slots; 8 are charged, the rest being the share of the
-        # per-tile work (operand address updates, overflow test of the optimistic running maximum, masks at the
-        # edges).  Peak issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz.  At d = 64 the matrix-pipe time at the
+        # sum and half a packed bf16 conversion -- 6.5 slots.  (8 were charged until the kernel passed that model's peak
+        # at d = 32: per-tile work -- addresses, overflow test of the optimistic running maximum, edge masks -- is not
+        # algorithmic.)  Peak issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz.  At d = 64 the matrix-pipe time at the
         # bf16 peak is half of the vector-pipe time at this peak, at d = 32 a quarter.
         p_all = cfg.forward_pairs(n_valid)
-        slots = 8.0 * cfg.heads * (p_all["cmp"] + p_all["sel"] + p_all["win"])
+        slots = 6.5 * cfg.heads * (p_all["cmp"] + p_all["sel"] + p_all["win"])
         peak = 256 * 4 * 16 * 2.4e9 / 1e12
         ach = slots / (ms_attn * 1e-3) / 1e12
         result["roofline"] = {"kernel": "nsa_forward_kernel", "bound": "alu", "achieved": round(ach, 3),
