@@ -35,7 +35,6 @@
 
 constexpr int kBwdNbuf = 2;         // tile buffers of the dQ kernel
 constexpr int kBwdDkvNbuf = 2;      // tile buffers of the dK/dV kernels (three, copies two steps ahead: slower, 51 -> 65 ms on the pooled keys at d = 128)
-constexpr int kBwdSplitTarget = 2048;  // pooled-key workgroups aimed at when the query range is split
 
 namespace lsrm {
 
@@ -1536,7 +1535,6 @@ WsLayout ws_layout(const Shape &s) {
                 best_n = n;
             }
         }
-        (void)kBwdSplitTarget;
         const int n_split = best_n;
         w.tiles_per_split = (int)((nt + n_split - 1) / n_split);
         w.n_split = (int)((nt + w.tiles_per_split - 1) / (w.tiles_per_split > 0 ? w.tiles_per_split : 1));
