@@ -1552,7 +1552,10 @@ WsLayout ws_layout(const Shape &s) {
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp = s.h / s.h_kv;
-        const int64_t win = s.group_window ? 0 : ((64 + s.window) / 32 + 2 + 1) & ~1;  // bounds a block's counted window
+        // bounds a block's counted window, an even number of tiles: no window leaves the sequence, however large the
+        // caller's W (an unlimited one is 2^31 - 2: 64 bits)
+        const int64_t reach = (((64 + (int64_t)s.window) / 32 + 2) + 1) & ~(int64_t)1;
+        const int64_t win = s.group_window ? 0 : reach < (int64_t)nt ? reach : (int64_t)nt;
         const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);
         for (int ranges = 8; ranges >= 1; --ranges) {
             w.hpw = (grp + ranges - 1) / ranges;
@@ -1563,7 +1566,8 @@ WsLayout ws_layout(const Shape &s) {
             if (len > 0x3ffffffe) len = 0x3ffffffe;
             w.part_steps = (int)len;
             // bounds whatever the table holds: parts beyond a block's first number at most steps / len in all, and
-            // so do the blocks that are cut
+            // so do the blocks that are cut (steps / len is below 4 slots, or 2^20 where len is at its largest: no
+            // sum below leaves 32 bits)
             const int64_t more = steps / len;
             w.max_split = (int)(more < s.nb ? more : s.nb);
             w.max_tasks = (int)(s.nb + more);

@@ -76,3 +76,22 @@ def test_host_side_argument_checks():
     cnt.d_block_count = 256            # any non-null device address: only looked at on the device
     assert B.lsrm_workspace_bytes(cnt, B.LSRM_WS_FORWARD) > 0
     assert B.lsrm_workspace_bytes(cnt, B.LSRM_WS_BACKWARD) > 0
+
+
+def test_backward_workspace_does_not_follow_the_window_beyond_the_sequence():
+    """A window larger than the sequence says "no limit" (up to 2^31 - 2, the largest even W): it asks for the workspace
+    of a window that just covers the sequence from either end."""
+    from paper_2604_05182_amd import binding as B
+    for n_obj, heads, h_kv, d, topk in ((6144, 4, 4, 64, 8), (4096, 2, 1, 64, 8), (262144, 2, 1, 64, 8), (64, 1, 1, 32, 0),
+                                        (1088, 3, 3, 128, 5)):
+        def size(window, which=B.LSRM_WS_BACKWARD, **more):
+            return B.lsrm_workspace_bytes(B.make_params(n_obj, 0, 0, heads, d, topk, window, h_kv=h_kv, **more), which)
+        covering = size(2 * n_obj)
+        assert 0 < covering < 2 ** 33
+        for window in (2 * n_obj + 2, 65536, 1 << 20, 1 << 30, 2147483582, 2147483584, 2147483646):
+            if window >= 2 * n_obj:
+                assert size(window) == covering, (n_obj, window)
+        assert size(128) <= covering
+        # the window over the own block or the spatial block has no W
+        assert size(2147483646, window_mode=1) == size(128, window_mode=1)
+        assert size(2147483646, B.LSRM_WS_FORWARD) == size(128, B.LSRM_WS_FORWARD)

@@ -305,3 +305,17 @@ def test_backward_lists_cut_into_parts(B, oracle_lib, d, heads, h_kv):
     assert [int((idx == b).sum()) for b in (3, 5, 7, 11, 12, 30)] == [49, 4, 5, 6, 13, 14]
     got, args = _case(B, oracle_lib, cfg, idx=idx)
     _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)
+
+
+@pytest.mark.parametrize("d,heads,h_kv", [(64, 2, 2), (32, 4, 1), (128, 1, 1)])
+def test_backward_unlimited_window(B, oracle_lib, d, heads, h_kv):
+    """The largest even window there is (2^31 - 2) means "the whole segment": the same gradients, bit for bit, as a window
+    of twice the sequence, and the oracle's."""
+    cfg = I.small_config(name=f"b-unlimited-d{d}", n_obj=21 * 64, n_views=1, grid=16, heads=heads, d=d, topk=3, window=64,
+                         seed=31, h_kv=h_kv)
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    got, _ = _case(B, oracle_lib, cfg, window=2147483646)
+    covering, args = _case(B, oracle_lib, cfg, window=2 * cfg.n)
+    for x, y in zip(got, covering):
+        assert np.array_equal(x, y)
+    _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)
