@@ -64,59 +64,63 @@ __global__ __launch_bounds__(256) void pool_blocks(int nb, int row_chunks /* h*d
 // block of 512 tokens is four round trips to memory; a thread adds its rows in order, the 16 partial sums of a channel are
 // added in order through LDS.  (One thread per chunk walking the whole group, one dependent load after another, took
 // 170 us for 21 K token slots in groups of up to eight blocks, a sixth of a training step; this takes 11 us.)
-// grid: (ng, ceil(row_chunks / 16), 2).
-constexpr int kPoolLanes = 16, kPoolRows = 16, kPoolDepth = 8;
-__global__ __launch_bounds__(256) void pool_groups(int row_chunks, const uint4 *__restrict__ k,
+// grid: (min(ng, kPoolMaxGrid), ceil(row_chunks / 16), 2); a workgroup takes every kPoolMaxGrid-th group (a launch holds
+// fewer than 2^32 threads in a direction: one workgroup each for the 2^24 groups of 2^30 tokens are too many).
+constexpr int kPoolLanes = 16, kPoolRows = 16, kPoolDepth = 8, kPoolMaxGrid = 1 << 16;
+__global__ __launch_bounds__(256) void pool_groups(int ng, int row_chunks, const uint4 *__restrict__ k,
                                                    const uint4 *__restrict__ v, uint4 *__restrict__ kc,
                                                    uint4 *__restrict__ vc, const int32_t *__restrict__ count,
                                                    const int32_t *__restrict__ goff) {
     __shared__ float part[kPoolRows][kPoolLanes * 8 + 1];
     __shared__ int part_tokens[kPoolRows];
-    const size_t grp = blockIdx.x;
     const int cl = threadIdx.x % kPoolLanes, rl = threadIdx.x / kPoolLanes;
     const int c = blockIdx.y * kPoolLanes + cl;
     const bool in_row = c < row_chunks;
     const uint4 *src = (blockIdx.z == 0 ? k : v) + (in_row ? c : 0);
-    const int s0 = goff[grp] * kBlock, s1 = goff[grp + 1] * kBlock;  // token slots of the group
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int tokens = 0;
-    for (int s = s0 + rl; s < s1; s += kPoolRows * kPoolDepth) {
-        bool on[kPoolDepth];
-        uint4 r[kPoolDepth];
+    for (int grp = blockIdx.x; grp < ng; grp += gridDim.x) {
+        const int s0 = goff[grp] * kBlock, s1 = goff[grp + 1] * kBlock;  // token slots of the group
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        int tokens = 0;
+        for (int s = s0 + rl; s < s1; s += kPoolRows * kPoolDepth) {
+            bool on[kPoolDepth];
+            uint4 r[kPoolDepth];
 #pragma unroll
-        for (int i = 0; i < kPoolDepth; ++i) {
-            const int si = s + i * kPoolRows;
-            on[i] = si < s1 && (count == nullptr || (si & (kBlock - 1)) < count[si / kBlock]);
+            for (int i = 0; i < kPoolDepth; ++i) {
+                const int si = s + i * kPoolRows;
+                on[i] = si < s1 && (count == nullptr || (si & (kBlock - 1)) < count[si / kBlock]);
+            }
+#pragma unroll
+            for (int i = 0; i < kPoolDepth; ++i)  // (inactive slots are never read: the caller may have left anything there)
+                r[i] = on[i] ? src[(size_t)(s + i * kPoolRows) * row_chunks] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < kPoolDepth; ++i) {
+                acc[0] += bf16_lo(r[i].x); acc[1] += bf16_hi(r[i].x);
+                acc[2] += bf16_lo(r[i].y); acc[3] += bf16_hi(r[i].y);
+                acc[4] += bf16_lo(r[i].z); acc[5] += bf16_hi(r[i].z);
+                acc[6] += bf16_lo(r[i].w); acc[7] += bf16_hi(r[i].w);
+                tokens += on[i] ? 1 : 0;
+            }
         }
 #pragma unroll
-        for (int i = 0; i < kPoolDepth; ++i)  // (inactive slots are never read: the caller may have left anything there)
-            r[i] = on[i] ? src[(size_t)(s + i * kPoolRows) * row_chunks] : make_uint4(0, 0, 0, 0);
+        for (int j = 0; j < 8; ++j) part[rl][cl * 8 + j] = acc[j];
+        if (cl == 0) part_tokens[rl] = tokens;
+        __syncthreads();
+        if (rl == 0 && in_row) {
+            int n_tok = 0;
+            for (int i = 0; i < kPoolRows; ++i) n_tok += part_tokens[i];
+            const float den = (float)(n_tok > 0 ? n_tok : 1);
+            uint32_t bits[8];
 #pragma unroll
-        for (int i = 0; i < kPoolDepth; ++i) {
-            acc[0] += bf16_lo(r[i].x); acc[1] += bf16_hi(r[i].x);
-            acc[2] += bf16_lo(r[i].y); acc[3] += bf16_hi(r[i].y);
-            acc[4] += bf16_lo(r[i].z); acc[5] += bf16_hi(r[i].z);
-            acc[6] += bf16_lo(r[i].w); acc[7] += bf16_hi(r[i].w);
-            tokens += on[i] ? 1 : 0;
+            for (int j = 0; j < 8; ++j) {
+                float sum = 0.f;
+                for (int i = 0; i < kPoolRows; ++i) sum += part[i][cl * 8 + j];
+                bits[j] = f32_to_bf16_rne(sum / den);
+            }
+            uint4 *dst = (blockIdx.z == 0 ? kc : vc) + (size_t)grp * row_chunks + c;
+            *dst = make_uint4(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16, bits[4] | bits[5] << 16, bits[6] | bits[7] << 16);
         }
+        __syncthreads();  // the partial sums have been read
     }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) part[rl][cl * 8 + j] = acc[j];
-    if (cl == 0) part_tokens[rl] = tokens;
-    __syncthreads();
-    if (rl != 0 || !in_row) return;
-    int n_tok = 0;
-    for (int i = 0; i < kPoolRows; ++i) n_tok += part_tokens[i];
-    const float den = (float)(n_tok > 0 ? n_tok : 1);
-    uint32_t bits[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        float sum = 0.f;
-        for (int i = 0; i < kPoolRows; ++i) sum += part[i][cl * 8 + j];
-        bits[j] = f32_to_bf16_rne(sum / den);
-    }
-    uint4 *dst = (blockIdx.z == 0 ? kc : vc) + grp * (size_t)row_chunks + c;
-    *dst = make_uint4(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16, bits[4] | bits[5] << 16, bits[6] | bits[7] << 16);
 }
 
 // The tables the attention kernels look blocks up in (see GroupTables): one thread per block, then one per group.
@@ -167,8 +171,9 @@ lsrm_status launch_compress(const Shape &s, const uint16_t *d_k, const uint16_t 
     if (s.nb == 0) return LSRM_OK;
     int row_chunks = s.h_kv * s.d / 8;
     if (s.ng > 0) {
-        const dim3 grid_g((unsigned)s.ng, (unsigned)((row_chunks + kPoolLanes - 1) / kPoolLanes), 2);
-        hipLaunchKernelGGL(pool_groups, grid_g, dim3(256), 0, st, row_chunks, reinterpret_cast<const uint4 *>(d_k),
+        const dim3 grid_g((unsigned)(s.ng < kPoolMaxGrid ? s.ng : kPoolMaxGrid),
+                          (unsigned)((row_chunks + kPoolLanes - 1) / kPoolLanes), 2);
+        hipLaunchKernelGGL(pool_groups, grid_g, dim3(256), 0, st, s.ng, row_chunks, reinterpret_cast<const uint4 *>(d_k),
                            reinterpret_cast<const uint4 *>(d_v), reinterpret_cast<uint4 *>(d_kc),
                            reinterpret_cast<uint4 *>(d_vc), s.count, s.goff);
         LSRM_HIP_CHECK(hipGetLastError());

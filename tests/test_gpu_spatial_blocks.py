@@ -177,3 +177,28 @@ def test_pooling_of_spatial_blocks_edges(B, oracle_lib, d, h_kv, with_counts):
             sl = slice(64 * goff[g], 64 * goff[g + 1])
             ref = x[sl][active[sl]].mean(axis=0)
             assert np.all(np.abs(got[g].double().cpu().numpy() - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
+
+
+def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B):
+    """2^30 tokens, the longest sequence the calls take, every 64-slot block a spatial block of its own: 2^24 of them.
+    (k and v are the same 64 GiB.)  All tokens of a block hold its number modulo 251 in every channel, which is its
+    mean exactly."""
+    import torch
+    nb, d = 1 << 24, 32
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GiB of free GPU memory")
+    _log(f"[pool] {nb} spatial blocks of one block")
+    dev = torch.device("cuda")
+    value = (torch.arange(nb, device=dev) % 251).to(torch.bfloat16)
+    k = torch.empty((nb * 64, 1, d), dtype=torch.bfloat16, device=dev)
+    k.view(nb, 64 * d).copy_(value[:, None].expand(nb, 64 * d))
+    goff = torch.arange(nb + 1, dtype=torch.int32, device=dev)
+    p = B.make_params(nb * 64, 0, 0, 1, d, 1, 64, group_offsets=goff)
+    kc, vc = (torch.full((nb, 1, d), -1.0, dtype=torch.bfloat16, device=dev) for _ in range(2))
+    B.lsrm_nsa_compress(p, k, k, kc, vc)
+    torch.cuda.synchronize()
+    want = value[:, None, None].expand(nb, 1, d)
+    same = torch.equal(kc, want) and torch.equal(vc, want)
+    del k, kc, vc
+    torch.cuda.empty_cache()
+    assert same
