@@ -4,7 +4,7 @@
 
 Flags: -ffp-contract=off for the routing translation unit (its distances are compared
 bit for bit), packed-fp32 code generation disabled everywhere, correctly rounded fp32
-division.  hipcc cross-compiles without a GPU.
+division, diagnostics about inline assembly (a register it may not touch) as errors.  hipcc cross-compiles without a GPU.
 """
 from __future__ import annotations
 
@@ -18,7 +18,8 @@ LIB = os.path.join(HERE, "liblsrm.so")
 SOURCES = ["api.hip", "route.hip", "compress.hip", "forward.hip", "backward.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fhip-fp32-correctly-rounded-divide-sqrt",
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+          "-Werror=inline-asm"]
 # forward.hip never produces or consumes NaNs (masked scores are -inf, running maxima start
 # finite); telling the compiler so removes the quieting copies it adds around every fmax.
 PER_FILE = {"route.hip": ["-ffp-contract=off"], "forward.hip": ["-fno-honor-nans"]}

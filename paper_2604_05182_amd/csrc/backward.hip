@@ -48,23 +48,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxSeg = 63;
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Copies 1 KB global -> LDS: lane i's 16 bytes from src + lane_off (lane_off = 16 i) to dst + 16 i.  src and dst are
-// wave-uniform.  Inline assembly on purpose: the compiler counts the builtin both as a vector-memory and as an LDS
-// operation, so that while a copy is in flight every wait for an LDS read becomes lgkmcnt(0) -- a read that an MFMA
-// needs then also waits for the reads requested behind it.  Copies it does not see leave its LDS waits counted
-// (lgkmcnt(3) in the row queue of the dQ kernel); who waits for the copies themselves is settled by hand anyway.
-// Measured, whole training step: 32 heads of 32 channels on 2, 196 K tokens 49.4 -> 48.1 ms; 16 heads of 64, 57 K
-// tokens 3.79 -> 3.73 ms; 16 heads of 128, 428 K tokens 164.7 -> 163.4 ms.
-__device__ __forceinline__ void copy_kb_to_lds(const char *src, uint32_t lane_off, const char *dst) {
-    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(lane_off), "s"(src) : "memory", "m0");
-}
-// the same with 4 bytes per lane (256 bytes in all)
-__device__ __forceinline__ void copy_256_to_lds(const void *src, uint32_t lane_off, const char *dst) {
-    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(m), "v"(lane_off), "s"(src) : "memory", "m0");
-}
-
 struct BwdArgs {
     const uint16_t *q, *k, *v, *kc, *vc, *dout, *out_branch;
     const int32_t *idx;

@@ -58,16 +58,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMaxSeg = 63;
 constexpr float kMinusHuge = -1.0e30f;  // initial running maximum: finite, so no inf - inf
 
-// Copies 1 KB global -> LDS: lane i's 16 bytes from src + lane_off (lane_off = 16 i) to dst + 16 i.  src and dst are
-// wave-uniform.  Inline assembly on purpose: the compiler counts the builtin both as a vector-memory and as an LDS
-// operation, so that while a copy is in flight every wait for an LDS fragment becomes lgkmcnt(0), i.e. also waits for
-// the fragments requested behind it.  Who waits for the copies themselves is settled by hand (vmcnt before a barrier).
-// Measured, attention step: 0.6 % at d = 32 with 196 K tokens, 0.5 % at d = 64 with 180 K, 0.2 % at d = 128 with 428 K.
-__device__ __forceinline__ void copy_kb_to_lds(const char *src, uint32_t lane_off, const char *dst) {
-    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m), "v"(lane_off), "s"(src) : "memory", "m0");
-}
-
 struct FwdArgs {
     const uint16_t *q;
     const char *kv, *kvc;  // packed tile images of (k, v) and of the pooled (kc, vc)

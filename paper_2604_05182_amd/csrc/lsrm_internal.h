@@ -32,6 +32,29 @@ lsrm_status make_shape(const lsrm_nsa_params *p, Shape *s);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Copies 1 KB global -> LDS: lane i's 16 bytes from src + lane_off (lane_off = 16 i) to dst + 16 i.  src and dst are
+// wave-uniform.  Inline assembly on purpose: the compiler counts the builtin both as a vector-memory and as an LDS
+// operation, so that while a copy is in flight every wait for an LDS read becomes lgkmcnt(0) -- a read that an MFMA
+// needs then also waits for the reads requested behind it.  Copies it does not see leave its LDS waits counted
+// (lgkmcnt(3) in the row queue of the dQ kernel); who waits for the copies themselves is settled by hand (vmcnt before a
+// barrier), and a copy in flight that the compiler does not count can only make its own vmcnt waits longer.  Measured:
+//   attention step  0.6 % at d = 32 with 196 K tokens, 0.5 % at d = 64 with 180 K, 0.2 % at d = 128 with 428 K;
+//   training step   32 heads of 32 channels on 2, 196 K tokens 49.4 -> 48.1 ms; 16 heads of 64, 57 K tokens 3.79 ->
+//                   3.73 ms; 16 heads of 128, 428 K tokens 164.7 -> 163.4 ms.
+// The LDS address goes through m0, as an input in that register: the compiler writes it and knows what it holds.  The
+// s_nop is the wait state between a scalar write of m0 and the copy that reads it, which the compiler does not add
+// inside assembly.  Nor does it add the five between a vector instruction that writes a scalar register and a memory
+// instruction that reads it: src has to come from scalar arithmetic, never straight from a readlane (true of every call).
+__device__ __forceinline__ void copy_kb_to_lds(const char *src, uint32_t lane_off, const char *dst) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(src), "{m0}"(m) : "memory");
+}
+// the same with 4 bytes per lane (256 bytes in all, lane_off = 4 i)
+__device__ __forceinline__ void copy_256_to_lds(const void *src, uint32_t lane_off, const char *dst) {
+    const uint32_t m = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(src), "{m0}"(m) : "memory");
+}
+
 #define LSRM_HIP_CHECK(expr)                         \
     do {                                             \
         hipError_t e_ = (expr);                      \
