@@ -319,3 +319,24 @@ def test_backward_unlimited_window(B, oracle_lib, d, heads, h_kv):
     for x, y in zip(got, covering):
         assert np.array_equal(x, y)
     _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)
+
+
+@pytest.mark.parametrize("d,heads,h_kv,window", [(64, 1, 1, 1024), (128, 1, 1, 962), (32, 4, 2, 962)])
+def test_backward_walks_cut_inside_the_window(B, oracle_lib, d, heads, h_kv, window):
+    """Windows of two and more parts (at this size a walk is cut every 16 tiles): parts of window tiles only, one that
+    holds the window's end and list entries, and the odd tile by which a window of an odd number of tiles falls short of
+    its even share.  Lists of 0, 1, 8 and 14 entries behind it; without grouped heads (only cut blocks take the summing
+    pass) and with them (all do)."""
+    cfg = I.small_config(name=f"b-window-parts-d{d}-w{window}", n_obj=45 * 64, n_views=1, grid=16, heads=heads, d=d, topk=3,
+                         window=window, seed=33, h_kv=h_kv)
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    # tiles that see block b in the window: queries of its segment from 64 b - W/2 + 1 to 64 b + 63 + W/2
+    b = np.arange(cfg.nb_obj)
+    first = np.maximum(0, 64 * b - window // 2 + 1) // 32
+    tiles = (np.minimum(cfg.n_obj, 64 * b + 64 + window // 2) - 1) // 32 + 1 - first
+    assert tiles.max() == {1024: 34, 962: 33}[window]
+    idx = np.full((cfg.nb, cfg.topk), -1, dtype=np.int32)
+    for col, (block, rows) in enumerate(((22, 14), (2, 8), (23, 1))):
+        idx[(np.arange(rows) * 3) % cfg.nb, col] = block
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)

@@ -202,3 +202,41 @@ def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B):
     del k, kc, vc
     torch.cuda.empty_cache()
     assert same
+
+
+@pytest.mark.parametrize("d,heads,h_kv", [(64, 2, 2), (128, 1, 1), (32, 6, 2)])
+def test_backward_lists_cut_into_parts_with_spatial_blocks(B, oracle_lib, d, heads, h_kv):
+    """The window is the spatial block: it goes uncounted to a walk's first part, and walks are cut by their lists alone
+    (every 16 tiles at this size).  Lists of 7, 8, 9, 16, 17 and 44 entries on blocks of different spatial blocks, full
+    and partly filled: whole walks, two parts and more, each finished with its own group's divisor; without grouped heads
+    (only cut blocks take the summing pass) and with them (all do)."""
+    cfg = I.small_config(name=f"g-parts-d{d}", n_obj=40 * 64, n_views=1, grid=16, heads=heads, d=d, topk=6, window=64,
+                         seed=95, h_kv=h_kv)
+    goff = np.concatenate([[0], np.cumsum([1, 8, 2, 3, 5, 8, 8, 5, 1, 1, 1, 1])]).astype(np.int32)
+    assert goff[-1] == cfg.nb == 44
+    cnt = np.full(cfg.nb, 64, dtype=np.int32)
+    cnt[goff[1:] - 1] = [40, 9, 64, 33, 1, 32, 31, 50, 64, 64, 20, 64]
+    cnt[11] = 17                         # (in the middle of a spatial block)
+    lists = {8: 7, 0: 8, 11: 9, 18: 16, 26: 17, 30: 44}
+    idx = np.full((cfg.nb, cfg.topk), -1, dtype=np.int32)
+    for col, (block, rows) in enumerate(lists.items()):
+        idx[(np.arange(rows) * 3 + col) % cfg.nb, col] = block
+    assert all(int((idx == block).sum()) == rows for block, rows in lists.items())
+    _log(f"[spatial blocks] {cfg.name}: {cfg.nb} blocks in {len(goff) - 1} spatial blocks")
+    q_bits, k_bits, v_bits = I.make_qkv(cfg)
+    gates, dout_bits = I.make_gates(cfg), I.make_dout(cfg)
+    if heads != h_kv:   # (three query heads per key/value head: see test_backward_with_spatial_blocks)
+        dout_bits = I.f32_to_bf16_bits(I.bf16_bits_to_f32(dout_bits) * np.float32(0.25))
+    q, k, v, dout = (I.bf16_bits_to_f32(a) for a in (q_bits, k_bits, v_bits, dout_bits))
+    k_bits, v_bits, dout_bits = _poison(cfg, cnt, k_bits, v_bits, dout_bits)
+    got = G.run_backward(B, cfg, q_bits, k_bits, v_bits, idx, gates, dout_bits, window_mode=1, block_count=cnt,
+                         group_offsets=goff)
+    kc, vc = oracle_lib.pool(k, cnt, goff), oracle_lib.pool(v, cnt, goff)
+    ref = oracle_lib.nsa_backward(q, k, v, kc, vc, idx, gates, cfg.seg_offsets(), cfg.window, dout, window_mode=1,
+                                  block_count=cnt, group_offsets=goff)
+    active = (np.arange(cfg.n) % 64) < np.repeat(cnt, 64)
+    for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert np.isfinite(g).all() and np.all(g[~active] == 0), name
+        ma, rl = G.attention_errors(g, r)
+        _log(f"    {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} (|ref| max {np.abs(r).max():.3e})")
+        assert ma <= G.MAX_ABS_TOL and rl <= G.REL_L2_TOL, (name, ma, rl)
