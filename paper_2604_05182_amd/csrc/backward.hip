@@ -360,11 +360,14 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
 // block, the query blocks that list it (the reverse lists' lengths).
 // Image: slot cc * 32 + rr of 16 bytes = chunk cc of tile row perm32(rr ^ 4 (cc & 1)).  Rows at or beyond the end, and
 // padding slots, read as zeros.
+// The workgroups are numbered over both directions of the grid: a launch holds fewer than 2^32 threads in a direction, which
+// three workgroups per block and head (179 M tokens, 2 heads of 32) exceed.
+constexpr int64_t kPackMaxGrid = 1 << 23;  // workgroups in the first direction
 template <int D>
 __global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, int64_t n_wg) {
     constexpr int CH = D / 8, PITCH = D + 16, IMG = BGeo<D>::IMG;  // (pitch: 16-byte aligned, chunks of a row spread over the banks)
     __shared__ __attribute__((aligned(16))) uint16_t rows[64][PITCH];
-    const int64_t wg = blockIdx.x;
+    const int64_t wg = (int64_t)blockIdx.y * kPackMaxGrid + blockIdx.x;
     if (wg >= n_wg) {
         const int64_t e = (wg - n_wg) * 256 + threadIdx.x;
         if (e < (int64_t)a.nb * a.topk) {
@@ -1591,8 +1594,10 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                        dim3(PrepGeo<D>::THREADS), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
-    const int64_t n_count_wg = ((int64_t)s.nb * s.topk + 255) / 256;
-    hipLaunchKernelGGL(pack_rows<D>, dim3((unsigned)(n_wg + n_count_wg)), dim3(256), 0, st, a, n_token_wg, n_wg);
+    const int64_t n_pack = n_wg + ((int64_t)s.nb * s.topk + 255) / 256;
+    const dim3 pack_grid((unsigned)(n_pack < kPackMaxGrid ? n_pack : kPackMaxGrid),
+                         (unsigned)((n_pack + kPackMaxGrid - 1) / kPackMaxGrid));
+    hipLaunchKernelGGL(pack_rows<D>, pack_grid, dim3(256), 0, st, a, n_token_wg, n_wg);
     LSRM_HIP_CHECK(hipGetLastError());
     // reverse routing lists
     hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a);

@@ -340,3 +340,38 @@ def test_backward_walks_cut_inside_the_window(B, oracle_lib, d, heads, h_kv, win
         idx[(np.arange(rows) * 3) % cfg.nb, col] = block
     got, args = _case(B, oracle_lib, cfg, idx=idx)
     _assert_grads(got, oracle_lib.nsa_backward(*args), cfg.name)
+
+
+def test_backward_of_more_tiles_than_one_grid_direction_holds(B):
+    """358 M tokens of one head: three images per 64-token block are more workgroups than a launch takes in one direction.
+    q, k, v, dout and the branch outputs are ones in the same memory, and every query sees itself and the key before it
+    (window 2, the other branches gated off): probabilities of a half, dq = dk = 0, and dv[j] = 1/2 from query j + 1/2
+    from query j + 1, which the last token does not have."""
+    import torch
+    nb, d = 5_600_000, 32
+    assert 3 * nb * 256 >= 2 ** 32
+    n = nb * 64
+    if torch.cuda.mem_get_info()[0] < 230 << 30:
+        pytest.skip("needs 230 GiB of free GPU memory")
+    _log(f"[backward] {nb} blocks of one head")
+    dev = torch.device("cuda")
+    goff = (torch.arange(65, device=dev) * (nb // 64)).to(torch.int32)   # (64 pooled pairs)
+    goff[-1] = nb
+    p = B.make_params(n, 0, 0, 1, d, 0, 2, group_offsets=goff)
+    branches = torch.ones((3, n, 1, d), dtype=torch.bfloat16, device=dev)
+    ones = branches[0]
+    kc = torch.ones((64, 1, d), dtype=torch.bfloat16, device=dev)
+    idx = torch.zeros((nb, 1), dtype=torch.int32, device=dev)
+    gates = torch.zeros((n, 1, 3), dtype=torch.float32, device=dev)
+    gates[:, :, 2] = 1.0
+    lse = torch.full((3, n, 1), d ** 0.5 + float(np.log(2.0)), dtype=torch.float32, device=dev)
+    dq, dv = (torch.full((n, 1, d), float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    ws = B.alloc_workspace(p, B.LSRM_WS_BACKWARD)
+    B.lsrm_nsa_backward(p, ones, ones, ones, kc, kc, idx, gates, lse, branches, ones, dq, dq, dv, ws)
+    torch.cuda.synchronize()
+    # (extremes instead of a comparison with a tensor of the same size; NaN fails both)
+    rest, last = dv[:-1], dv[-1]
+    found = [float(x) for x in (dq.min(), dq.max(), rest.min(), rest.max(), last.min(), last.max())]
+    del branches, ones, gates, lse, dq, dv, ws, rest, last
+    torch.cuda.empty_cache()
+    assert found == [0.0, 0.0, 1.0, 1.0, 0.5, 0.5]
