@@ -34,7 +34,7 @@
 // Data movement
 //   K and V are repacked once per call into tile images: per (head, 32-key tile) the exact
 //   bytes of an LDS slot, K fragments then V^T fragments in MFMA operand order (see
-//   read_k and read_v), head-major so that one head's keys and values are one contiguous range.
+//   read_k), head-major so that one head's keys and values are one contiguous range.
 //   Tiles are copied global -> LDS with global_load_lds_dwordx4 (no VGPR staging), 1 KB
 //   contiguous on both sides per instruction, the copy instructions of a tile split over
 //   the wavefronts that share it, s_waitcnt vmcnt placed by hand, and read back as
@@ -80,8 +80,7 @@ struct FwdArgs {
     float scale_log2e, scale;
 };
 
-// NP = query blocks per workgroup, QT = 32-row query tiles per wavefront, so a query
-// block is held by NW = 2 / QT wavefronts.
+// NP = query blocks per workgroup; a wavefront holds 32 query rows, NW = 2 wavefronts a query block.
 // LDS is 2 NP tile slots of 32 keys each (K fragments, then V^T fragments): one ring in the compressed phase, two
 // stages of NP slots in the others; behind them the part of the running gated sum that stays on chip.
 //
@@ -101,9 +100,9 @@ struct FwdArgs {
 // three wavefronts per SIMD, since both put two wavefronts on the same two SIMDs (180 K tokens 5.12 ms).
 template <int D_>
 struct Geo {
-    static constexpr int D = D_, NP = 2, QT = 1;
-    static constexpr int NW = 2 / QT;           // wavefronts per query block
-    static constexpr int ROWS = 32 * QT;        // query rows per wavefront
+    static constexpr int D = D_, NP = 2;
+    static constexpr int NW = 2;                // wavefronts per query block
+    static constexpr int ROWS = 32;             // query rows per wavefront
     static constexpr int NS = D / 16;           // 16-channel slabs of the QK^T contraction
     static constexpr int ND = D / 32;           // 32-channel tiles of the PV output
     static constexpr int K_BYTES = 32 * D * 2;  // 32 key rows
@@ -129,7 +128,6 @@ struct Geo {
     // all of it, in bytes; as many workgroups fit a CU's 160 KB as the registers allow
     static constexpr int LDS_ALL = LDS_BYTES + GSUM_LDS_WAVES * GSUM_LDS_BYTES;
     static_assert(WAVES == 4 && WAVES_PER_SIMD * LDS_ALL <= 160 * 1024, "");
-    static_assert(QT == 1 && NW == 2, "");
     static_assert(WAVES * ROWS * OUT_ROW <= LDS_BYTES, "output staging must fit in the tile slots");
 };
 
@@ -152,9 +150,8 @@ __device__ __forceinline__ float half_sum(float x) {
 
 // s_waitcnt immediates (vmcnt is split over bits [3:0] and [15:14], expcnt is bits [6:4],
 // lgkmcnt bits [11:8]; counters that are not waited for are left at their maxima)
-constexpr int vmcnt_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }            // vmcnt <= n
-constexpr int vm_lgkm_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0070; }          // vmcnt <= n, lgkmcnt == 0
-constexpr int kLgkmOnly = 0xC07F;                                                            // lgkmcnt == 0, vmcnt left alone
+constexpr int vm_lgkm_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0070; }  // vmcnt <= n, lgkmcnt == 0
+constexpr int kLgkmOnly = 0xC07F;                                                   // lgkmcnt == 0, vmcnt left alone
 
 // Bare workgroup barrier.  No barrier, fenced or not, waits for global -> LDS copies in flight
 // (they are counted by vmcnt, which a workgroup-scope fence leaves alone), so what must be
@@ -172,15 +169,14 @@ __device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 15\n\ts_nop 
 
 template <class G>
 struct WaveCtx {
-    bf16x8 qf[G::QT][G::NS];
-    f32x16 o[G::QT][G::ND];
-    float m[G::QT], l[G::QT];
+    bf16x8 qf[G::NS];
+    f32x16 o[G::ND];
+    float m, l;
     // running gated sum of the branches: the fragments kept in registers (d = 64).  At d = 128 it goes
     // through a bf16 scratch tile in LDS or global memory instead (fp32 there cost 1.8 % of the kernel for 7 % less
     // rounding error in `out`, whose own bf16 rounding and that of the probabilities dominate either way)
-    f32x4 g[G::QT][G::GSUM_FRAGS_REGS > 0 ? G::GSUM_FRAGS_REGS : 1];
-    int lo[G::QT], hi[G::QT];   // valid key range of this lane's queries in mask coordinates
-    uint32_t lane16;            // lane * 16: byte offset of this lane inside any 1 KB fragment or copy instruction
+    f32x4 g[G::GSUM_FRAGS_REGS > 0 ? G::GSUM_FRAGS_REGS : 1];
+    uint32_t lane16;  // lane * 16: byte offset of this lane inside any 1 KB fragment or copy instruction
 };
 
 // A tile (32 keys of one head) is stored in global memory as the exact image of its LDS slot:
@@ -197,15 +193,12 @@ struct WaveCtx {
 
 template <class G>
 __device__ __forceinline__ void reset_branch(WaveCtx<G> &c) {
+    c.m = kMinusHuge;
+    c.l = 0.f;
 #pragma unroll
-    for (int qt = 0; qt < G::QT; ++qt) {
-        c.m[qt] = kMinusHuge;
-        c.l[qt] = 0.f;
+    for (int dt = 0; dt < G::ND; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < G::ND; ++dt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) c.o[qt][dt][i] = 0.f;
-    }
+        for (int i = 0; i < 16; ++i) c.o[dt][i] = 0.f;
 }
 
 // ---- pieces of one 32-key step of one wavefront ------------------------------------------
@@ -214,27 +207,14 @@ __device__ __forceinline__ void read_k(const WaveCtx<G> &c, const char *slot, bf
 #pragma unroll
     for (int ks = 0; ks < G::NS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8 *>(slot + c.lane16 + ks * 1024);
 }
-template <class G>
-__device__ __forceinline__ void read_v(const WaveCtx<G> &c, const char *slot, bf16x8 (&vf)[G::ND][2]) {
-#pragma unroll
-    for (int dt = 0; dt < G::ND; ++dt)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-            vf[dt][ks] = *reinterpret_cast<const bf16x8 *>(slot + c.lane16 + G::K_BYTES + (ks * G::ND + dt) * 1024);
-}
 
-// S^T = K Q^T for 32 keys x the 32 queries of row tile qt
+// S^T = K Q^T for 32 keys x the wavefront's 32 queries
 template <class G>
-__device__ __forceinline__ void qk_scores(const WaveCtx<G> &c, const bf16x8 (&kf)[G::NS], f32x16 (&s)[G::QT]) {
+__device__ __forceinline__ void qk_scores(const WaveCtx<G> &c, const bf16x8 (&kf)[G::NS], f32x16 &s) {
 #pragma unroll
-    for (int qt = 0; qt < G::QT; ++qt)
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[qt][i] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < G::NS; ++ks)
-#pragma unroll
-        for (int qt = 0; qt < G::QT; ++qt)
-            s[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], c.qf[qt][ks], s[qt], 0, 0, 0);
+    for (int ks = 0; ks < G::NS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], c.qf[ks], s, 0, 0, 0);
 }
 
 // Keys outside [lo, hi) of this lane's query get a score of -inf.
@@ -271,21 +251,19 @@ __device__ __forceinline__ bool sum_overflow(float psum) {
     return __builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0;
 }
 
-// Redoes the exponentials of one tile (scores s, already masked) of row tile qt after raising m to
-// the tile's maximum; O and l (which do not yet contain this tile) are rescaled.  Rare path.
+// Redoes the exponentials of one tile (scores s, already masked) after raising m to the tile's maximum; O and l (which do not yet contain this tile) are rescaled.  Rare path.
 template <class G>
-__device__ __forceinline__ void redo_tile(WaveCtx<G> &c, int qt, const f32x16 &s, uint32_t (&pu)[8], float &psum,
-                                          float sl2) {
+__device__ __forceinline__ void redo_tile(WaveCtx<G> &c, const f32x16 &s, uint32_t (&pu)[8], float &psum, float sl2) {
     mfma_settle();  // the O accumulators (and, at the start of a phase, s itself) may still be in flight
     const float mx = half_max(lane_max(s));
-    const float m_new = fmaxf(c.m[qt], mx);
-    const float alpha = __builtin_amdgcn_exp2f((c.m[qt] - m_new) * sl2);
-    c.m[qt] = m_new;
-    c.l[qt] *= alpha;
+    const float m_new = fmaxf(c.m, mx);
+    const float alpha = __builtin_amdgcn_exp2f((c.m - m_new) * sl2);
+    c.m = m_new;
+    c.l *= alpha;
 #pragma unroll
     for (int dt = 0; dt < G::ND; ++dt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) c.o[qt][dt][i] *= alpha;
+        for (int i = 0; i < 16; ++i) c.o[dt][i] *= alpha;
     const float mc = m_new * sl2;
     float p[16];
     psum = 0.f;
@@ -300,13 +278,9 @@ __device__ __forceinline__ void redo_tile(WaveCtx<G> &c, int qt, const f32x16 &s
 
 // After the exponentials of a tile: redo where needed, then add the row sums to l.
 template <class G>
-__device__ __forceinline__ void close_tile(WaveCtx<G> &c, const f32x16 (&s)[G::QT], uint32_t (&pu)[G::QT][8],
-                                           float (&psum)[G::QT], float sl2) {
-#pragma unroll
-    for (int qt = 0; qt < G::QT; ++qt) {
-        if (__builtin_expect(sum_overflow(psum[qt]), 0)) redo_tile<G>(c, qt, s[qt], pu[qt], psum[qt], sl2);
-        c.l[qt] += psum[qt];
-    }
+__device__ __forceinline__ void close_tile(WaveCtx<G> &c, const f32x16 &s, uint32_t (&pu)[8], float &psum, float sl2) {
+    if (__builtin_expect(sum_overflow(psum), 0)) redo_tile<G>(c, s, pu, psum, sl2);
+    c.l += psum;
 }
 
 union BFrag {
@@ -327,91 +301,70 @@ union BFrag {
 // The empty asm statements pin each result to its place in the program (the compiler
 // otherwise sinks the arithmetic to its first use) and the scheduling barriers keep the
 // machine scheduler from regrouping; neither emits an instruction.
-// pu[qt][k] = bf16 pair (p[2k], p[2k+1]) of row tile qt: pu[qt][0..3] / [4..7] are the B
-// operands of the two 16-key slabs of the PV contraction.
-// The A operands come from two rolling queues of LDS fragments (kq: K rows, vq: V^T rows):
-// the MFMA that consumes fragment i is followed by the ds_read of fragment i + queue depth
-// of the same stream, which continues into the next tile (k_nxt / v_nxt), so the queues
-// enter the next block already primed.  k_cur .. v_nxt are per-lane addresses: slot + lane * 16.  LDS reads are thereby spread under the MFMAs, and
-// only a few fragments are live at a time.
+// pu[k] = bf16 pair (p[2k], p[2k+1]): pu[0..3] / [4..7] are the B operands of the two 16-key slabs of the PV
+// contraction.
+// The A operands come from two rolling queues of LDS fragments (kq: K rows, vq: V^T rows), which the caller primes with the
+// first ones: the MFMA that consumes fragment i is followed by the ds_read of fragment i + queue depth of the same
+// tile.  k_cur and v_cur are per-lane addresses: slot + lane * 16.  LDS reads are thereby spread under the MFMAs,
+// and only a few fragments are live at a time.
 template <class G, bool QK, bool PV>
-__device__ __forceinline__ void mfma_block(WaveCtx<G> &c, const f32x16 (&s)[G::QT], bf16x8 (&kq)[G::KQ],
-                                           f32x16 (&s_next)[G::QT], bf16x8 (&vq)[G::VQ],
-                                           const uint32_t (&pu_prev)[G::QT][8], uint32_t (&pu)[G::QT][8],
-                                           float (&psum)[G::QT], float sl2, const char *k_cur, const char *k_nxt,
-                                           const char *v_cur, const char *v_nxt) {
-    constexpr int QT = G::QT;
-    constexpr int NQ = QK ? G::NS * QT : 0, NPV = PV ? 2 * G::ND * QT : 0, NG = NQ + NPV;
-    constexpr int NE = 16 * QT;
-    float mc[QT], p[NE];
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        mc[qt] = c.m[qt] * sl2;
-        psum[qt] = 0.f;
-    }
+__device__ __forceinline__ void mfma_block(WaveCtx<G> &c, const f32x16 &s, bf16x8 (&kq)[G::KQ], f32x16 &s_next,
+                                           bf16x8 (&vq)[G::VQ], const uint32_t (&pu_prev)[8], uint32_t (&pu)[8],
+                                           float &psum, float sl2, const char *k_cur, const char *v_cur) {
+    constexpr int NQ = QK ? G::NS : 0, NPV = PV ? 2 * G::ND : 0, NG = NQ + NPV;
+    constexpr int NE = 16;
+    const float mc = c.m * sl2;
+    float p[NE];
+    psum = 0.f;
     if constexpr (NG == 0) {
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(s[e / 16][e % 16] * sl2 - mc[e / 16]);
-            psum[e / 16] += p[e];
+            p[e] = __builtin_amdgcn_exp2f(s[e] * sl2 - mc);
+            psum += p[e];
         }
 #pragma unroll
-        for (int k = 0; k < NE / 2; ++k) pu[k / 8][k % 8] = pack_bf16(p[2 * k], p[2 * k + 1]);
+        for (int k = 0; k < NE / 2; ++k) pu[k] = pack_bf16(p[2 * k], p[2 * k + 1]);
     } else {
         constexpr int E = NE / NG;  // exponentials per MFMA
         static_assert(E >= 1 && E * NG == NE, "");
-        BFrag pb[QT][2];
+        BFrag pb[2];
         if (PV) {
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                for (int k = 0; k < 8; ++k) pb[qt][k / 4].u[k % 4] = pu_prev[qt][k];
+            for (int k = 0; k < 8; ++k) pb[k / 4].u[k % 4] = pu_prev[k];
         }
         if (QK) {
 #pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) s_next[qt][i] = 0.f;
+            for (int i = 0; i < 16; ++i) s_next[i] = 0.f;
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             const bool do_qk = QK && (!PV || (g % 2) == 0);
             if (do_qk) {
-                const int i = PV ? g / 2 : g;
-                const int ks = i / QT, qt = i % QT;
-                s_next[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kq[ks % G::KQ], c.qf[qt][ks], s_next[qt], 0, 0, 0);
-                asm volatile("" : "+v"(s_next[qt]));
-                if (qt == QT - 1) {
-                    const int nf = ks + G::KQ;
-                    kq[ks % G::KQ] =
-                        *reinterpret_cast<const bf16x8 *>((nf < G::NS ? k_cur : k_nxt) + (nf % G::NS) * 1024);
-                }
+                const int ks = PV ? g / 2 : g;
+                s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kq[ks % G::KQ], c.qf[ks], s_next, 0, 0, 0);
+                asm volatile("" : "+v"(s_next));
+                if (ks + G::KQ < G::NS) kq[ks % G::KQ] = *reinterpret_cast<const bf16x8 *>(k_cur + (ks + G::KQ) * 1024);
             } else {
-                const int i = QK ? g / 2 : g;
-                const int f = i / QT, qt = i % QT;
+                const int f = QK ? g / 2 : g;
                 const int ks = f / G::ND, dt = f % G::ND;
-                c.o[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[f % G::VQ], pb[qt][ks].v, c.o[qt][dt], 0, 0, 0);
-                asm volatile("" : "+v"(c.o[qt][dt]));
-                if (qt == QT - 1) {
-                    const int nf = (f + G::VQ) % (2 * G::ND);
-                    vq[f % G::VQ] = *reinterpret_cast<const bf16x8 *>((f + G::VQ < 2 * G::ND ? v_cur : v_nxt) +
-                                                                      G::K_BYTES + nf * 1024);
-                }
+                c.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[f % G::VQ], pb[ks].v, c.o[dt], 0, 0, 0);
+                asm volatile("" : "+v"(c.o[dt]));
+                if (f + G::VQ < 2 * G::ND)
+                    vq[f % G::VQ] = *reinterpret_cast<const bf16x8 *>(v_cur + G::K_BYTES + (f + G::VQ) * 1024);
             }
 #pragma unroll
             for (int e = g * E; e < (g + 1) * E; ++e) {
-                p[e] = __builtin_amdgcn_exp2f(s[e / 16][e % 16] * sl2 - mc[e / 16]);
-                psum[e / 16] += p[e];
+                p[e] = __builtin_amdgcn_exp2f(s[e] * sl2 - mc);
+                psum += p[e];
                 if (e & 1) {
-                    pu[e / 16][(e % 16) / 2] = pack_bf16(p[e - 1], p[e]);
-                    asm volatile("" : "+v"(pu[e / 16][(e % 16) / 2]));
+                    pu[e / 2] = pack_bf16(p[e - 1], p[e]);
+                    asm volatile("" : "+v"(pu[e / 2]));
                 } else {
                     asm volatile("" : "+v"(p[e]));
                 }
             }
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) asm volatile("" : "+v"(psum[qt]));
+            asm volatile("" : "+v"(psum));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -419,23 +372,16 @@ __device__ __forceinline__ void mfma_block(WaveCtx<G> &c, const f32x16 (&s)[G::Q
 
 // O^T += V^T P^T of the last tile (pipeline drain): the queue holds its first fragments.
 template <class G>
-__device__ __forceinline__ void pv_drain(WaveCtx<G> &c, bf16x8 (&vq)[G::VQ], const uint32_t (&pu)[G::QT][8],
-                                         const char *v_cur) {
-    BFrag pb[G::QT][2];
+__device__ __forceinline__ void pv_drain(WaveCtx<G> &c, bf16x8 (&vq)[G::VQ], const uint32_t (&pu)[8], const char *v_cur) {
+    BFrag pb[2];
 #pragma unroll
-    for (int qt = 0; qt < G::QT; ++qt)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) pb[qt][k / 4].u[k % 4] = pu[qt][k];
+    for (int k = 0; k < 8; ++k) pb[k / 4].u[k % 4] = pu[k];
 #pragma unroll
     for (int f = 0; f < 2 * G::ND; ++f) {
         const int ks = f / G::ND, dt = f % G::ND;
-#pragma unroll
-        for (int qt = 0; qt < G::QT; ++qt)
-            c.o[qt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[f % G::VQ], pb[qt][ks].v, c.o[qt][dt], 0, 0, 0);
-        if (f + G::VQ < 2 * G::ND) {
-            const int nf = f + G::VQ;
-            vq[f % G::VQ] = *reinterpret_cast<const bf16x8 *>(v_cur + G::K_BYTES + nf * 1024);
-        }
+        c.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[f % G::VQ], pb[ks].v, c.o[dt], 0, 0, 0);
+        if (f + G::VQ < 2 * G::ND)
+            vq[f % G::VQ] = *reinterpret_cast<const bf16x8 *>(v_cur + G::K_BYTES + (f + G::VQ) * 1024);
     }
 }
 
@@ -462,7 +408,7 @@ template <class G, typename SrcFn>
 struct OwnTiles {
     static constexpr int NP = G::NP, NST = G::NST;
     static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
-    static_assert(G::NW == 2 && G::QT == 1, "two wavefronts per query block");
+    static_assert(G::NW == 2, "two wavefronts per query block");
     static_assert((NST & (NST - 1)) == 0 && NST >= 2, "");
     const int n;  // tiles of this query block
     const SrcFn src;  // address of the image of tile tau
@@ -572,9 +518,9 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         if (t + NST - 2 < n) tiles.issue_v(t + NST - 2);
     };
     bf16x8 kq[G::KQ], vq[G::VQ];
-    f32x16 S[2][1];
-    uint32_t P[2][1][8];
-    float psum[1];
+    f32x16 S[2];
+    uint32_t P[2][8];
+    float psum;
     auto prime_k = [&](const char *ls) {
 #pragma unroll
         for (int i = 0; i < G::KQ; ++i) kq[i] = *reinterpret_cast<const bf16x8 *>(ls + i * 1024);
@@ -592,7 +538,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         bf16x8 kf[G::NS];
         read_k<G>(c, stage(0), kf);
         qk_scores<G>(c, kf, S[0]);
-        mask_next(-1, S[0][0]);
+        mask_next(-1, S[0]);
     }
     auto full_step = [&](auto par, int t) {
         constexpr int A = decltype(par)::value;
@@ -600,8 +546,8 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         const char *k_nx = lstage(t + 1), *v_pv = lstage(t - 1);
         prime_k(k_nx);
         prime_v(v_pv);
-        mfma_block<G, true, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, k_nx, k_nx, v_pv, v_pv);
-        mask_next(t, S[A ^ 1][0]);
+        mfma_block<G, true, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, k_nx, v_pv);
+        mask_next(t, S[A ^ 1]);
         close_tile<G>(c, S[A], P[A], psum, sl2);
     };
     auto last_steps = [&](auto par, int t) {  // t = n - 1 >= 1: exp(t) || PV(t-1), then the PV of tile t
@@ -609,7 +555,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         sync(t);
         const char *v_pv = lstage(t - 1);
         prime_v(v_pv);
-        mfma_block<G, false, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, nullptr, nullptr, v_pv, v_pv);
+        mfma_block<G, false, true>(c, S[A], kq, S[A ^ 1], vq, P[A ^ 1], P[A], psum, sl2, nullptr, v_pv);
         close_tile<G>(c, S[A], P[A], psum, sl2);
         sync(t + 1);
         const char *v_last = lstage(t);
@@ -623,8 +569,8 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         sync(0);
         const char *k1 = lstage(1);
         prime_k(k1);
-        mfma_block<G, true, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, k1, k1, nullptr, nullptr);
-        mask_next(0, S[1][0]);
+        mfma_block<G, true, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, k1, nullptr);
+        mask_next(0, S[1]);
         close_tile<G>(c, S[0], P[0], psum, sl2);
         int t = 1;
         for (; t + 2 < n; t += 2) {
@@ -642,7 +588,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         done = n + 1;
     } else if (n == 1) {
         sync(0);
-        mfma_block<G, false, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, nullptr, nullptr, nullptr, nullptr);
+        mfma_block<G, false, false>(c, S[0], kq, S[1], vq, P[1], P[0], psum, sl2, nullptr, nullptr);
         close_tile<G>(c, S[0], P[0], psum, sl2);
         sync(1);
         const char *v_last = lstage(0);
@@ -666,90 +612,86 @@ __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, i
     constexpr int D = G::D;
     const int r = lane & 31, hh = lane >> 5;
     char *tr = lds + wave * G::ROWS * G::OUT_ROW;  // output staging region of this wavefront
-#pragma unroll
-    for (int qt = 0; qt < G::QT; ++qt) {
-        const int64_t row = row0 + 32 * qt + r;
-        const float l_tot = half_sum(c.l[qt]);
-        const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-        const float w = a.gate_channels ? inv : a.gates[(row * a.h + head) * 3 + branch] * inv;
-        // per-channel gates of this row, branch and head: D floats
-        const f32x4 *gch = reinterpret_cast<const f32x4 *>(a.gates + ((row * 3 + branch) * a.h + head) * D) + hh;
-        if (a.lse != nullptr && hh == 0) {
-            float v = l_tot > 0.f ? c.m[qt] * a.scale + __logf(l_tot) : -__builtin_inff();
-            a.lse[((int64_t)branch * a.n + row) * a.h + head] = v;
-        }
-        if (a.out_branch != nullptr) {
-#pragma unroll
-            for (int dt = 0; dt < G::ND; ++dt) {
-                uint16_t *dst = a.out_branch + (((int64_t)branch * a.n + row) * a.h + head) * D + 32 * dt + 4 * hh;
-#pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    uint2 w2;
-                    w2.x = pack_bf16(c.o[qt][dt][4 * gq + 0] * inv, c.o[qt][dt][4 * gq + 1] * inv);
-                    w2.y = pack_bf16(c.o[qt][dt][4 * gq + 2] * inv, c.o[qt][dt][4 * gq + 3] * inv);
-                    *reinterpret_cast<uint2 *>(dst + 8 * gq) = w2;
-                }
-            }
-        }
+    const int64_t row = row0 + r;
+    const float l_tot = half_sum(c.l);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    const float w = a.gate_channels ? inv : a.gates[(row * a.h + head) * 3 + branch] * inv;
+    // per-channel gates of this row, branch and head: D floats
+    const f32x4 *gch = reinterpret_cast<const f32x4 *>(a.gates + ((row * 3 + branch) * a.h + head) * D) + hh;
+    if (a.lse != nullptr && hh == 0) {
+        float v = l_tot > 0.f ? c.m * a.scale + __logf(l_tot) : -__builtin_inff();
+        a.lse[((int64_t)branch * a.n + row) * a.h + head] = v;
+    }
+    if (a.out_branch != nullptr) {
 #pragma unroll
         for (int dt = 0; dt < G::ND; ++dt) {
+            uint16_t *dst = a.out_branch + (((int64_t)branch * a.n + row) * a.h + head) * D + 32 * dt + 4 * hh;
 #pragma unroll
             for (int gq = 0; gq < 4; ++gq) {
-                f32x4 v;
+                uint2 w2;
+                w2.x = pack_bf16(c.o[dt][4 * gq + 0] * inv, c.o[dt][4 * gq + 1] * inv);
+                w2.y = pack_bf16(c.o[dt][4 * gq + 2] * inv, c.o[dt][4 * gq + 3] * inv);
+                *reinterpret_cast<uint2 *>(dst + 8 * gq) = w2;
+            }
+        }
+    }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = w * c.o[qt][dt][4 * gq + j];
-                if (a.gate_channels) v *= gch[8 * dt + 2 * gq];  // channels 32 dt + 8 gq + 4 hh + 0..3
-                if constexpr (G::GSUM_F32) {
-                    const int f = dt * 4 + gq;
-                    if (f < G::GSUM_FRAGS_REGS) {
-                        if (branch > 0) v += c.g[qt][f];
-                        if (branch < 2) c.g[qt][f] = v;
-                    } else {
-                        f32x4 *slot_lds = reinterpret_cast<f32x4 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) +
-                                          (f - G::GSUM_FRAGS_REGS) * 64 + lane;
-                        if (branch > 0) v += *slot_lds;
-                        if (branch < 2) *slot_lds = v;
-                    }
+    for (int dt = 0; dt < G::ND; ++dt) {
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            f32x4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = w * c.o[dt][4 * gq + j];
+            if (a.gate_channels) v *= gch[8 * dt + 2 * gq];  // channels 32 dt + 8 gq + 4 hh + 0..3
+            if constexpr (G::GSUM_F32) {
+                const int f = dt * 4 + gq;
+                if (f < G::GSUM_FRAGS_REGS) {
+                    if (branch > 0) v += c.g[f];
+                    if (branch < 2) c.g[f] = v;
                 } else {
-                    // bf16 pairs in accumulator order: 8 bytes per lane and fragment, fully coalesced; in LDS for the
-                    // first wavefronts of the workgroup (behind the ring), in the scratch buffer for the others
-                    static_assert(G::QT == 1, "");
-                    // (the scratch buffer holds the query tiles of wavefronts GSUM_LDS_WAVES .. WAVES - 1 only)
-                    const int64_t gtile = (row0 / (32 * G::WAVES)) * (G::WAVES - G::GSUM_LDS_WAVES) + (wave - G::GSUM_LDS_WAVES);
-                    uint2 *slot = reinterpret_cast<uint2 *>(a.gsum) +
-                                  ((gtile * a.h + head) * (G::ND * 4) + dt * 4 + gq) * 64 + lane;
-                    uint2 *slot_lds =
-                        reinterpret_cast<uint2 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
-                    const bool in_lds = G::GSUM_LDS_WAVES == G::WAVES || wave < G::GSUM_LDS_WAVES;
-                    if (branch > 0) {
-                        // (address spaces spelled out: one pointer that may be either would become a flat load)
-                        unsigned long long raw;
-                        if (in_lds)
-                            raw = *(const __attribute__((address_space(3))) unsigned long long *)slot_lds;
-                        else
-                            raw = *(const __attribute__((address_space(1))) unsigned long long *)slot;
-                        const uint2 pv = make_uint2((uint32_t)raw, (uint32_t)(raw >> 32));
-                        v[0] += __uint_as_float(pv.x << 16);
-                        v[1] += __uint_as_float(pv.x & 0xffff0000u);
-                        v[2] += __uint_as_float(pv.y << 16);
-                        v[3] += __uint_as_float(pv.y & 0xffff0000u);
-                    }
-                    if (branch < 2) {
-                        uint2 w2;
-                        w2.x = pack_bf16(v[0], v[1]);
-                        w2.y = pack_bf16(v[2], v[3]);
-                        if (in_lds)
-                            *slot_lds = w2;
-                        else
-                            *slot = w2;
-                    }
+                    f32x4 *slot_lds = reinterpret_cast<f32x4 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) +
+                                      (f - G::GSUM_FRAGS_REGS) * 64 + lane;
+                    if (branch > 0) v += *slot_lds;
+                    if (branch < 2) *slot_lds = v;
                 }
-                if (branch == 2) {
+            } else {
+                // bf16 pairs in accumulator order: 8 bytes per lane and fragment, fully coalesced; in LDS for the
+                // first wavefronts of the workgroup (behind the ring), in the scratch buffer for the others
+                // (the scratch buffer holds the query tiles of wavefronts GSUM_LDS_WAVES .. WAVES - 1 only)
+                const int64_t gtile = (row0 / (32 * G::WAVES)) * (G::WAVES - G::GSUM_LDS_WAVES) + (wave - G::GSUM_LDS_WAVES);
+                uint2 *slot = reinterpret_cast<uint2 *>(a.gsum) +
+                              ((gtile * a.h + head) * (G::ND * 4) + dt * 4 + gq) * 64 + lane;
+                uint2 *slot_lds =
+                    reinterpret_cast<uint2 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
+                const bool in_lds = G::GSUM_LDS_WAVES == G::WAVES || wave < G::GSUM_LDS_WAVES;
+                if (branch > 0) {
+                    // (address spaces spelled out: one pointer that may be either would become a flat load)
+                    unsigned long long raw;
+                    if (in_lds)
+                        raw = *(const __attribute__((address_space(3))) unsigned long long *)slot_lds;
+                    else
+                        raw = *(const __attribute__((address_space(1))) unsigned long long *)slot;
+                    const uint2 pv = make_uint2((uint32_t)raw, (uint32_t)(raw >> 32));
+                    v[0] += __uint_as_float(pv.x << 16);
+                    v[1] += __uint_as_float(pv.x & 0xffff0000u);
+                    v[2] += __uint_as_float(pv.y << 16);
+                    v[3] += __uint_as_float(pv.y & 0xffff0000u);
+                }
+                if (branch < 2) {
                     uint2 w2;
                     w2.x = pack_bf16(v[0], v[1]);
                     w2.y = pack_bf16(v[2], v[3]);
-                    *reinterpret_cast<uint2 *>(tr + (32 * qt + r) * G::OUT_ROW + (32 * dt + 8 * gq + 4 * hh) * 2) = w2;
+                    if (in_lds)
+                        *slot_lds = w2;
+                    else
+                        *slot = w2;
                 }
+            }
+            if (branch == 2) {
+                uint2 w2;
+                w2.x = pack_bf16(v[0], v[1]);
+                w2.y = pack_bf16(v[2], v[3]);
+                *reinterpret_cast<uint2 *>(tr + r * G::OUT_ROW + (32 * dt + 8 * gq + 4 * hh) * 2) = w2;
             }
         }
     }
@@ -845,12 +787,9 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
         *reinterpret_cast<uint4 *>(lds + off) = make_uint4(0, 0, 0, 0);
     {
         // (an inactive wavefront reads the rows of block 0: finite values, results discarded)
+        const uint16_t *qrow = a.q + ((row0 + r) * a.h + head) * D + 8 * hh;
 #pragma unroll
-        for (int qt = 0; qt < G::QT; ++qt) {
-            const uint16_t *qrow = a.q + ((row0 + 32 * qt + r) * a.h + head) * D + 8 * hh;
-#pragma unroll
-            for (int ks = 0; ks < G::NS; ++ks) c.qf[qt][ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
-        }
+        for (int ks = 0; ks < G::NS; ++ks) c.qf[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
     }
 
     // ---------------- this query block's routing row, read while the first compressed tiles are copied;
@@ -906,11 +845,6 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
     // ---------------- compressed branch: all NB pooled pairs
     {
         reset_branch<G>(c);
-#pragma unroll
-        for (int qt = 0; qt < G::QT; ++qt) {
-            c.lo[qt] = 0;
-            c.hi[qt] = a.nbc;
-        }
         auto mask_tile = [&](int t, f32x16 &sc) {
             if (32 * t + 32 > a.nbc) {
                 mfma_settle();
@@ -973,15 +907,9 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
                 n_max = max(n_max, w.st1 - w.st0);
             }
         }
-        {
-            const int half_w = a.window / 2;
-#pragma unroll
-            for (int qt = 0; qt < G::QT; ++qt) {
-                const int i = (int)row0 + 32 * qt + r;
-                c.lo[qt] = max(mine.seg_lo, i - half_w);
-                c.hi[qt] = min(mine.seg_hi, i + half_w);
-            }
-        }
+        // the keys that this lane's query sees
+        const int i = (int)row0 + r, half_w = a.window / 2;
+        const int lo = max(mine.seg_lo, i - half_w), hi = min(mine.seg_hi, i + half_w);
         const char *base = a.kv + head_kv;
         auto src = [&](int t) { return base + (mine.st0 + t) * tile_stride; };
         auto mask_tile = [&](int t, f32x16 &sc) {
@@ -1000,7 +928,7 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
             }
             if (need) {
                 mfma_settle();
-                mask_scores(c.lo[0], min(c.hi[0], cap), sc, j0, lane);
+                mask_scores(lo, min(hi, cap), sc, j0, lane);
             }
         };
         const auto tiles = own_tiles<G>(active ? mine.st1 - mine.st0 : 0, src, lds, qbi, sub, c.lane16);
@@ -1015,7 +943,7 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
     }
 }
 
-// Builds the tile images (see read_k, read_v) of a K and a V tensor, both [n_rows, H, D] bf16:
+// Builds the tile images (see WaveCtx) of a K and a V tensor, both [n_rows, H, D] bf16:
 // img[head][tile] = K fragments (K_BYTES) then V^T fragments (V_BYTES).
 // Rows at or beyond n_rows read as zero (their scores are masked in the attention kernel).
 // One workgroup per (64-row block, head) = two tiles.
