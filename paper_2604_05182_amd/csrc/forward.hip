@@ -778,13 +778,11 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 
     WaveCtx<G> c;
     c.lane16 = (uint32_t)lane * 16u;
-    // The first copies go out before anything else.  A fully masked step may read a slot that no copy has filled: make
-    // sure such slots hold finite values (0 * NaN would poison the accumulators).
+    // The first copies go out before anything else.  (Slots that no copy fills hold anything: run_tiles reads the tiles of
+    // the phase only.)
     const int n_cmp = (a.nbc + 31) / 32;
     const SharedTiles<G> cmp_tiles{n_cmp, a.kvc + head_kvc, lds, wave, c.lane16};
     cmp_tiles.begin();
-    for (int off = n_cmp * G::TILE + threadIdx.x * 16; off < G::LDS_BYTES; off += G::THREADS * 16)
-        *reinterpret_cast<uint4 *>(lds + off) = make_uint4(0, 0, 0, 0);
     {
         // (an inactive wavefront reads the rows of block 0: finite values, results discarded)
         const uint16_t *qrow = a.q + ((row0 + r) * a.h + head) * D + 8 * hh;
