@@ -72,7 +72,7 @@ struct BwdArgs {
     int gate_channels;  // gates are [N, 3, H, d]
     const int32_t *count;  // nullable [NB]: active tokens per block; the other slots are neither queries nor keys
     int nt;               // query / key tiles of 32 tokens
-    int n_split, nbp, tiles_per_split;
+    int nbp, tiles_per_split;
     // Token keys: a key block's walk -- the query tiles of its window, then two per entry of its reverse list -- is dealt to
     // several workgroups where it is long.  With grouped-query heads the query heads of a group go to hsplit
     // workgroups, hpw heads each; and a walk of more than part_steps tiles is cut into parts of that many (cut_window = 0:
@@ -952,7 +952,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     constexpr int TILE = 2 * G::ROW + 1024;  // (table padded to keep the next buffer aligned)
     static_assert(2 * 32 * G::OUT_ROW <= kBwdDkvNbuf * TILE, "output staging fits in the tile buffers");
     extern __shared__ __attribute__((aligned(1024))) char lds[];  // kBwdDkvNbuf * TILE bytes
-    const int n_kb = MODE != 1 ? a.nb : a.nbp / 64;
+    const int n_kb = MODE == 0 ? a.nb : a.nbp / 64;
     const int per_xcd = (n_kb + 7) / 8;
     const int head = blockIdx.y;
     int kb;
@@ -965,7 +965,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         kb = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);  // (see bwd_dq_kernel)
         if (kb >= n_kb) return;
     }
-    const int walk = MODE != 1 ? a.walk[kb] : 0;
+    const int walk = MODE == 0 ? a.walk[kb] : 0;
     const int split = MODE == 1 ? blockIdx.z : 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -974,17 +974,17 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     const uint32_t tr_off = tr_lane_offset(lane), row_off = row_lane_offset(lane);
     const int64_t key0 = (int64_t)kb * 64 + 32 * wave;  // token index (MODE 0) or pooled-key index (MODE 1)
     const int64_t key = key0 + r;
-    const int64_t limit = MODE != 1 ? a.n : (int64_t)a.nbc;
+    const int64_t limit = MODE == 0 ? a.n : (int64_t)a.nbc;
     const int half_w = a.window / 2;
     // MODE 0 with per-block counts: a padding slot is nobody's key (its probabilities are zeroed) and gets a zero gradient
-    const int n_act = MODE != 1 && a.count != nullptr ? a.count[kb] : 64;
+    const int n_act = MODE == 0 && a.count != nullptr ? a.count[kb] : 64;
     const bool key_active = MODE == 1 || 32 * wave + r < n_act;
 
     bf16x8 kB[NS], vB[NS];
     {
         const int64_t krow_i = key < limit ? key : limit - 1;  // (rows past the end are masked below)
-        const uint16_t *krow = (MODE != 1 ? a.k : a.kc) + (krow_i * a.h_kv + head) * D + 8 * hh;
-        const uint16_t *vrow = (MODE != 1 ? a.v : a.vc) + (krow_i * a.h_kv + head) * D + 8 * hh;
+        const uint16_t *krow = (MODE == 0 ? a.k : a.kc) + (krow_i * a.h_kv + head) * D + 8 * hh;
+        const uint16_t *vrow = (MODE == 0 ? a.v : a.vc) + (krow_i * a.h_kv + head) * D + 8 * hh;
 #pragma unroll
         for (int ks = 0; ks < NS; ++ks) {
             kB[ks] = *reinterpret_cast<const bf16x8 *>(krow + 16 * ks);
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     if (MODE == 1) {
         wt0 = split * a.tiles_per_split;
         T = max(0, min(a.nt, wt0 + a.tiles_per_split) - wt0);
-    } else if (MODE == 0) {
+    } else {
         const WindowTiles win = window_tiles(a, kb);
         const int lo = part * a.part_steps, hi = min(lo + a.part_steps, walk);  // this part's share of the walk
         const int counted = a.cut_window ? (win.n + 1) & ~1 : 0;                // counted window tiles
@@ -1028,9 +1028,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     // the step in its interleaved form (step_interleaved below).  Not at d = 64: there it needs more than the 168
     // registers of three wavefronts per SIMD, and with two it measured slower (config 5: 1.12 -> 1.25 ms).
     constexpr bool INTERLEAVE = D != 64;
-    constexpr int NB = kBwdDkvNbuf;  // tile buffers: the copies run NB - 1 steps ahead of the arithmetic
-    constexpr int IPW = G::ROW / 1024;    // copy instructions per wavefront and step (wavefront 0: one more, the table)
-    static_assert(NB == 2 || NB == 3, "");
+    static_assert(kBwdDkvNbuf == 2, "the copies of a step go out one step ahead");
     // br_c: the branch whose probabilities these are (0 compressed, 1 selected, 2 window); tile_fn(t): the t-th query
     // tile of the segment (arithmetic on registers only); every tile is met by the grp query heads of this key/value
     // head in turn
@@ -1294,28 +1292,18 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
 
         __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         __syncthreads();  // both wavefronts are done with the buffers (previous segment)
-        for (int i = 0; i < NB - 1 && i < U; ++i) {
-            issue(t_nxt, gh_nxt, lds + i * TILE);
-            advance(t_nxt, gh_nxt);
-        }
-        for (int u = 0, slot = 0; u < U; ++u, advance(t, gh), slot = slot + 1 == NB ? 0 : slot + 1) {
+        issue(t_nxt, gh_nxt, lds);
+        advance(t_nxt, gh_nxt);
+        for (int u = 0, slot = 0; u < U; ++u, advance(t, gh), slot ^= 1) {
             // The barrier alone does not wait for copies in flight (they are counted by vmcnt, which a
             // workgroup-scope fence leaves alone): every wavefront first waits for its own share of the
-            // step's tile -- the copies of the next step may stay in flight -- then the barrier publishes
-            // all shares; it also tells that everyone is done with the buffer refilled next.
-            if (NB == 3 && u + 1 < U) {
-                if (wave == 0)
-                    __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(IPW + 1));
-                else
-                    __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(IPW));
-            } else {
-                __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
-            }
+            // step's tile, then the barrier publishes all shares; it also tells that everyone is done with the
+            // buffer refilled next.
+            __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
             wg_barrier();
             auto issue_next = [&]() {
-                if (u + NB - 1 < U) {
-                    const int fill = slot == 0 ? NB - 1 : slot - 1;  // the buffer of step u - 1 = that of step u + NB - 1
-                    issue(t_nxt, gh_nxt, lds + fill * TILE);
+                if (u + 1 < U) {
+                    issue(t_nxt, gh_nxt, lds + (slot ^ 1) * TILE);  // the buffer of step u - 1
                     advance(t_nxt, gh_nxt);
                 }
             };
@@ -1336,7 +1324,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     };
     if (MODE == 1) {
         run_segment(T, std::integral_constant<int, 0>{}, [&](int t) { return wt0 + t; });
-    } else if (MODE == 0) {
+    } else {
         run_segment(tw, std::integral_constant<int, 2>{}, [&](int t) { return wt0 + t; });
         for (int c0 = 0; c0 < n_e; c0 += 64) {
             const int rev_held = c0 + lane < n_e ? a.rev_idx[e0 + c0 + lane] : 0;
@@ -1625,7 +1613,6 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
         hipLaunchKernelGGL(sum_parts, dim3((unsigned)((per_split / 4 + 255) / 256), 2), dim3(256), 0, st, a.part_k, a.part_v,
                            w.n_split, per_split);
         LSRM_HIP_CHECK(hipGetLastError());
-        a.n_split = 1;  // (the kernels below read range 0's slot only)
     }
     hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), DKV_LDS, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
@@ -1702,7 +1689,6 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.own_block = s.own_block;
     a.n_seg = n_seg;
     a.nt = s.nb * 2;
-    a.n_split = w.n_split;
     a.hsplit = w.hsplit;
     a.hpw = w.hpw;
     a.hpart_k = reinterpret_cast<float *>(ws + w.hpart_k);
