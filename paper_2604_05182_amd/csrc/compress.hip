@@ -59,67 +59,103 @@ __global__ __launch_bounds__(256) void pool_blocks(int nb, int row_chunks /* h*d
 }
 
 // Spatial blocks of several 64-slot blocks (Sec. 3.2: volume blocks of up to 512 active tokens): one pair per
-// group, the mean over the active tokens of all its blocks.  One workgroup per (group, 16 chunks of 8 channels): 16
-// threads side by side read 256 contiguous bytes of a row, 16 such rows are read at a time, eight deep, so that a
-// block of 512 tokens is four round trips to memory; a thread adds its rows in order, the 16 partial sums of a channel are
-// added in order through LDS.  (One thread per chunk walking the whole group, one dependent load after another, took
-// 170 us for 21 K token slots in groups of up to eight blocks, a sixth of a training step; this takes 11 us.)
-// grid: (min(ng, kPoolMaxGrid), ceil(row_chunks / 16), 2); a workgroup takes every kPoolMaxGrid-th group (a launch holds
-// fewer than 2^32 threads in a direction: one workgroup each for the 2^24 groups of 2^30 tokens are too many).
-constexpr int kPoolLanes = 16, kPoolRows = 16, kPoolDepth = 8, kPoolMaxGrid = 1 << 16;
+// group, the mean over the active tokens of all its blocks.  A workgroup takes SIDE groups side by side and LANES chunks of 8
+// channels of their rows; the threads of a group read 256 / (LANES SIDE) of its rows at a time, DEPTH deep.  However many
+// that are, a channel's sum is that of sixteen partial sums in order, the i-th over the slots i, i + 16, ... of
+// the group: a thread adds its rows in registers, then they go through LDS and a thread per channel adds them up.  The
+// same bits in every layout, chosen by the shape alone (see launch_compress):
+//   <16, 1, 8>   16 rows of 256 bytes at a time: 512 tokens in four round trips to memory.  What a few long groups need, where
+//                the latency of the chain (offsets, rows, sums) is all there is.
+//   <4, 4, 8>, <8, 2, 8>   rows of 4 or 8 chunks (a head or two of 32 channels, one of 64), which would leave 12 or 8 of
+//                16 lanes idle.  8 chunks only where groups are short (under two blocks on average): with two
+//                blocks a group, one group fills the loads in flight (16 M tokens of a head of 64: 680 us alone, 720 side by side).
+//   <64, 1, 16>  1 KB of a row per wavefront, a whole 64-slot block in flight, the sets of chunks numbered fastest: neighbouring
+//                workgroups read neighbouring pieces of the same rows.  What many groups of wide rows need, which the
+//                memory bounds (428 K tokens, 16 heads of 128, 3.5 GB: 597 us = 5.9 TB/s, 676 with <16, 1, 8>).  Not
+//                for few: 256 groups there 25.9 instead of 21.5 us, 500 of them 43.8 instead of 40.5.
+// One thread per chunk that walked the whole group, the form before the first of these, took 158 us for 197 K tokens of
+// 2 heads of 32 in groups of eight blocks (9), 26.8 us for 1 M tokens of one head of 32 in single blocks (21.5; 52 with
+// <16, 1, 8>) and 628 us for the 3.5 GB above.
+// A workgroup loops where there are more units than kPoolMaxGrid: a launch holds fewer than 2^32 threads in a direction, and
+// there can be 2^24 groups.
+constexpr int kPoolSums = 16, kPoolMaxGrid = 1 << 22;
+constexpr int64_t kPoolWideFrom = 1 << 17;  // groups times chunks of a row
+template <int LANES, int SIDE, int DEPTH>
 __global__ __launch_bounds__(256) void pool_groups(int ng, int row_chunks, const uint4 *__restrict__ k,
                                                    const uint4 *__restrict__ v, uint4 *__restrict__ kc,
                                                    uint4 *__restrict__ vc, const int32_t *__restrict__ count,
                                                    const int32_t *__restrict__ goff) {
-    __shared__ float part[kPoolRows][kPoolLanes * 8 + 1];
-    __shared__ int part_tokens[kPoolRows];
-    const int cl = threadIdx.x % kPoolLanes, rl = threadIdx.x / kPoolLanes;
-    const int c = blockIdx.y * kPoolLanes + cl;
+    constexpr int COLS = LANES * SIDE, ROWS = 256 / COLS, CHANNELS = COLS * 8, PER = (CHANNELS + 255) / 256;
+    constexpr int SUMS = kPoolSums / ROWS;  // of the partial sums, how many a thread holds: rows rl + ROWS m, m mod SUMS
+    constexpr bool SETS_FIRST = LANES == 64;
+    static_assert(SUMS * ROWS == kPoolSums && DEPTH % SUMS == 0, "");
+    __shared__ __attribute__((aligned(16))) float part[ROWS][CHANNELS + 4];  // (a pitch of whole 16-byte pieces)
+    __shared__ int part_tokens[ROWS][SIDE];
+    const int cl = threadIdx.x % COLS, rl = threadIdx.x / COLS;
+    const int n_sets = SETS_FIRST ? row_chunks / LANES : 1, set = SETS_FIRST ? blockIdx.x % n_sets : blockIdx.y;
+    const int c0 = set * LANES, c = c0 + cl % LANES;
     const bool in_row = c < row_chunks;
-    const uint4 *src = (blockIdx.z == 0 ? k : v) + (in_row ? c : 0);
-    for (int grp = blockIdx.x; grp < ng; grp += gridDim.x) {
+    const uint4 *src = (blockIdx.z == 0 ? k : v) + c;
+    const int stride = (int)(gridDim.x / n_sets) * SIDE;
+    for (int g0 = blockIdx.x / n_sets * SIDE; g0 < ng; g0 += stride) {
+        const int grp = SIDE == 1 ? g0 : min(g0 + cl / LANES, ng - 1);   // (past the end: the last group again, not stored)
         const int s0 = goff[grp] * kBlock, s1 = goff[grp + 1] * kBlock;  // token slots of the group
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        int tokens = 0;
-        for (int s = s0 + rl; s < s1; s += kPoolRows * kPoolDepth) {
-            bool on[kPoolDepth];
-            uint4 r[kPoolDepth];
+        float acc[SUMS][8];
 #pragma unroll
-            for (int i = 0; i < kPoolDepth; ++i) {
-                const int si = s + i * kPoolRows;
-                on[i] = si < s1 && (count == nullptr || (si & (kBlock - 1)) < count[si / kBlock]);
+        for (int m = 0; m < SUMS; ++m)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[m][j] = 0.f;
+        int tokens = 0;
+        for (int s = s0 + rl; s < s1; s += ROWS * DEPTH) {
+            bool on[DEPTH];
+            uint4 r[DEPTH];
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                const int si = s + i * ROWS;
+                on[i] = in_row && si < s1 && (count == nullptr || (si & (kBlock - 1)) < count[si / kBlock]);
             }
 #pragma unroll
-            for (int i = 0; i < kPoolDepth; ++i)  // (inactive slots are never read: the caller may have left anything there)
-                r[i] = on[i] ? src[(size_t)(s + i * kPoolRows) * row_chunks] : make_uint4(0, 0, 0, 0);
+            for (int i = 0; i < DEPTH; ++i)  // (inactive slots are never read: the caller may have left anything there)
+                r[i] = on[i] ? src[(size_t)(s + i * ROWS) * row_chunks] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < kPoolDepth; ++i) {
-                acc[0] += bf16_lo(r[i].x); acc[1] += bf16_hi(r[i].x);
-                acc[2] += bf16_lo(r[i].y); acc[3] += bf16_hi(r[i].y);
-                acc[4] += bf16_lo(r[i].z); acc[5] += bf16_hi(r[i].z);
-                acc[6] += bf16_lo(r[i].w); acc[7] += bf16_hi(r[i].w);
+            for (int i = 0; i < DEPTH; ++i) {
+                float(&x)[8] = acc[i % SUMS];
+                x[0] += bf16_lo(r[i].x); x[1] += bf16_hi(r[i].x);
+                x[2] += bf16_lo(r[i].y); x[3] += bf16_hi(r[i].y);
+                x[4] += bf16_lo(r[i].z); x[5] += bf16_hi(r[i].z);
+                x[6] += bf16_lo(r[i].w); x[7] += bf16_hi(r[i].w);
                 tokens += on[i] ? 1 : 0;
             }
         }
+        if (cl % LANES == 0) part_tokens[rl][cl / LANES] = tokens;
+        float sum[PER];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) part[rl][cl * 8 + j] = acc[j];
-        if (cl == 0) part_tokens[rl] = tokens;
-        __syncthreads();
-        if (rl == 0 && in_row) {
-            int n_tok = 0;
-            for (int i = 0; i < kPoolRows; ++i) n_tok += part_tokens[i];
-            const float den = (float)(n_tok > 0 ? n_tok : 1);
-            uint32_t bits[8];
+        for (int m = 0; m < SUMS; ++m) {
+            if (m > 0) __syncthreads();  // the sums before these have been read
+            float4 *row = reinterpret_cast<float4 *>(&part[rl][cl * 8]);
+            row[0] = make_float4(acc[m][0], acc[m][1], acc[m][2], acc[m][3]);
+            row[1] = make_float4(acc[m][4], acc[m][5], acc[m][6], acc[m][7]);
+            __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                float sum = 0.f;
-                for (int i = 0; i < kPoolRows; ++i) sum += part[i][cl * 8 + j];
-                bits[j] = f32_to_bf16_rne(sum / den);
+            for (int u = 0; u < PER; ++u) {
+                const int ch = u * 256 + threadIdx.x;
+                if (m == 0) sum[u] = 0.f;
+                if (CHANNELS % 256 != 0 && ch >= CHANNELS) continue;
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) sum[u] += part[i][ch];
             }
-            uint4 *dst = (blockIdx.z == 0 ? kc : vc) + (size_t)grp * row_chunks + c;
-            *dst = make_uint4(bits[0] | bits[1] << 16, bits[2] | bits[3] << 16, bits[4] | bits[5] << 16, bits[6] | bits[7] << 16);
         }
-        __syncthreads();  // the partial sums have been read
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int ch = u * 256 + threadIdx.x, side = ch / (LANES * 8), channel = c0 * 8 + ch % (LANES * 8);
+            if (ch >= CHANNELS || g0 + side >= ng || channel >= row_chunks * 8) continue;
+            int n_tok = 0;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) n_tok += part_tokens[i][side];
+            reinterpret_cast<uint16_t *>(blockIdx.z == 0 ? kc : vc)[(size_t)(g0 + side) * row_chunks * 8 + channel] =
+                (uint16_t)f32_to_bf16_rne(sum[u] / (float)(n_tok > 0 ? n_tok : 1));
+        }
+        if (g0 + stride < ng) __syncthreads();  // the partial sums have been read
     }
 }
 
@@ -171,11 +207,20 @@ lsrm_status launch_compress(const Shape &s, const uint16_t *d_k, const uint16_t 
     if (s.nb == 0) return LSRM_OK;
     int row_chunks = s.h_kv * s.d / 8;
     if (s.ng > 0) {
-        const dim3 grid_g((unsigned)(s.ng < kPoolMaxGrid ? s.ng : kPoolMaxGrid),
-                          (unsigned)((row_chunks + kPoolLanes - 1) / kPoolLanes), 2);
-        hipLaunchKernelGGL(pool_groups, grid_g, dim3(256), 0, st, s.ng, row_chunks, reinterpret_cast<const uint4 *>(d_k),
-                           reinterpret_cast<const uint4 *>(d_v), reinterpret_cast<uint4 *>(d_kc),
-                           reinterpret_cast<uint4 *>(d_vc), s.count, s.goff);
+        const bool wide = row_chunks % 64 == 0 && (int64_t)s.ng * row_chunks >= kPoolWideFrom;
+        const bool short_groups = s.nb < 2 * (int64_t)s.ng;
+        const int lanes = wide ? 64 : row_chunks <= 4 ? 4 : row_chunks <= 8 && short_groups ? 8 : 16;
+        const int side = wide ? 1 : 16 / lanes, n_sets = (row_chunks + lanes - 1) / lanes;
+        const int units = (s.ng + side - 1) / side;
+        const int most = !wide ? kPoolMaxGrid : n_sets < kPoolMaxGrid ? kPoolMaxGrid / n_sets : 1;
+        const unsigned grid_x = units < most ? units : most;
+        const auto kernel = wide         ? pool_groups<64, 1, 16>
+                            : lanes == 4 ? pool_groups<4, 4, 8>
+                            : lanes == 8 ? pool_groups<8, 2, 8>
+                                         : pool_groups<16, 1, 8>;
+        hipLaunchKernelGGL(kernel, wide ? dim3(grid_x * n_sets, 1, 2) : dim3(grid_x, n_sets, 2), dim3(256), 0, st, s.ng,
+                           row_chunks, reinterpret_cast<const uint4 *>(d_k), reinterpret_cast<const uint4 *>(d_v),
+                           reinterpret_cast<uint4 *>(d_kc), reinterpret_cast<uint4 *>(d_vc), s.count, s.goff);
         LSRM_HIP_CHECK(hipGetLastError());
         return LSRM_OK;
     }

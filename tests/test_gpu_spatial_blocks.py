@@ -179,6 +179,48 @@ def test_pooling_of_spatial_blocks_edges(B, oracle_lib, d, h_kv, with_counts):
             assert np.all(np.abs(got[g].double().cpu().numpy() - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
 
 
+@pytest.mark.parametrize("d,h_kv,n_groups,max_size", [
+    (32, 1, 10, 8),       # rows of 4 chunks: four groups side by side, two of the last four missing
+    (64, 1, 7, 1), (32, 2, 9, 2),  # of 8, short groups: two side by side, one missing
+    (32, 2, 7, 17),       # of 8, long groups: one, half of the lanes idle
+    (32, 3, 6, 3),        # of 12
+    (128, 4, 2048, 3),    # of 64, as many groups as the wide form starts from
+    (64, 24, 700, 3),     # of 192, wide: three sets of chunks
+    (128, 4, 2047, 2),    # one group less
+], ids=lambda v: str(v))
+def test_pooling_of_spatial_blocks_layouts(B, d, h_kv, n_groups, max_size):
+    """Every layout of the pooling kernel, at the shapes where its workgroups are partly filled."""
+    import torch
+    rng = np.random.default_rng(n_groups + max_size)
+    sizes = rng.integers(1, max_size + 1, size=n_groups)
+    sizes[-1] = max_size
+    goff = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    nb = int(goff[-1])
+    cnt = np.full(nb, 64, dtype=np.int32)
+    cnt[goff[1:] - 1] = rng.integers(1, 65, size=n_groups)
+    _log(f"[pool] {n_groups} groups in {nb} blocks, {h_kv} heads of {d}")
+    dev = torch.device("cuda")
+    gen = torch.Generator(device=dev).manual_seed(n_groups)
+    k, v = (torch.randn((nb * 64, h_kv, d), generator=gen, device=dev, dtype=torch.bfloat16) for _ in range(2))
+    slot = torch.arange(nb * 64, device=dev) % 64
+    active = slot < torch.from_numpy(cnt).to(dev).repeat_interleave(64)
+    k[~active] = float("nan")   # (whatever sits in padding slots is never read)
+    v[~active] = float("inf")
+    p = B.make_params(nb * 64, 0, 0, h_kv, d, 1, 64, h_kv=h_kv, group_offsets=torch.from_numpy(goff).to(dev),
+                      block_count=torch.from_numpy(cnt).to(dev))
+    kc = torch.full((n_groups, h_kv, d), -1.0, dtype=torch.bfloat16, device=dev)
+    vc = torch.full_like(kc, -1.0)
+    B.lsrm_nsa_compress(p, k, v, kc, vc)
+    torch.cuda.synchronize()
+    group = torch.from_numpy(np.repeat(np.arange(n_groups), 64 * sizes)).to(dev)
+    tokens = torch.zeros(n_groups, dtype=torch.float64, device=dev).index_add_(0, group, active.double())
+    for got, x in ((kc, k), (vc, v)):
+        x = torch.where(active[:, None, None], x, torch.zeros_like(x)).double()
+        ref = torch.zeros((n_groups, h_kv, d), dtype=torch.float64, device=dev).index_add_(0, group, x)
+        ref /= tokens[:, None, None]
+        assert bool(((got.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-6).all())
+
+
 def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B):
     """2^30 tokens, the longest sequence the calls take, every 64-slot block a spatial block of its own: 2^24 of them.
     (k and v are the same 64 GiB.)  All tokens of a block hold its number modulo 251 in every channel, which is its
