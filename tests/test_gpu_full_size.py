@@ -2,10 +2,10 @@
 (config 4: the benchmark's; config 6: the paper's head shape; config 3 shapes for the backward), in the launch
 configuration the benchmark times.  The oracle cannot finish these sizes, so it evaluates samples:
 
-forward   first and last block of every segment, 8 random query blocks for every combination of (position of
-          the block inside its workgroup's group of 4, which of the 8 contiguous ranges of groups -- one per
-          XCD -- the group falls in), and the blocks on either side of every range boundary: about 300 query
-          blocks at config 4, all heads, every output element of those blocks;
+forward   first and last block of every segment, 8 random query blocks for every combination of (block id mod 4:
+          both positions in a workgroup of two query blocks, in even and odd workgroups; which of the 8
+          contiguous ranges of the sequence -- one per XCD -- the block falls in), and the blocks on either side of
+          every range boundary: about 300 query blocks at config 4, all heads, every output element of those blocks;
 backward  dq on sampled query blocks, dk and dv on sampled key blocks (a popular one, i.e. one with the
           longest reverse routing list, among them) to which every query of the sequence contributes.
 

@@ -325,8 +325,8 @@ def test_forward_wide_routing_rows(B, oracle_lib, d, topk, with_counts):
 
 @pytest.mark.parametrize("d,topk", [(64, 6), (128, 9), (32, 5)])
 def test_forward_rows_that_share_and_repeat_blocks(B, oracle_lib, d, topk):
-    """Routing rows built to stress the step schedule of the selected branch: the four rows of a workgroup
-    identical, overlapping in part (pairs, triples), disjoint, a block listed twice or three times in a row
+    """Rows of the routing table that neighbours share or not, four at a time (two workgroups of two query blocks):
+    identical, overlapping in part, disjoint, a block listed twice or three times in a row
     (it is attended that many times) while its neighbours list it once, holes in the middle of rows, rows of
     different lengths, an empty row."""
     cfg = I.small_config(name=f"f-share-d{d}", n_obj=1088, n_views=3, grid=24, heads=2, d=d, topk=topk, window=64,
@@ -360,6 +360,26 @@ def test_forward_rows_that_share_and_repeat_blocks(B, oracle_lib, d, topk):
                 if r - g == 3:
                     idx[r] = -1
     _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx), cfg.name)
+
+
+@pytest.mark.parametrize("d,topk,with_counts", [(64, 9, False), (128, 5, False), (32, 7, False), (128, 100, True)])
+def test_forward_rows_of_a_workgroup_of_different_lengths(B, oracle_lib, d, topk, with_counts):
+    """The two query blocks of a workgroup meet the barriers of the longer one's selected branch: a full row beside an
+    empty one, one entry beside all, lengths one apart, either way round; and the odd block at the end, which
+    has a workgroup to itself, full and empty."""
+    lengths = [topk, 0, 0, topk, 1, topk, topk, 1, topk - 1, topk, 2, 1, 0, 1, 0, 0]
+    for last in (topk, 0):
+        cfg = I.small_config(name=f"f-lengths-d{d}-last{last}", n_obj=64 * 112, n_views=1, grid=8, heads=2, d=d, topk=topk,
+                             window=96, seed=83)
+        assert cfg.nb == 113
+        rows = (lengths * 7 + [last])
+        rng = np.random.default_rng(19)
+        idx = np.full((cfg.nb, topk), -1, dtype=np.int32)
+        for r, n in enumerate(rows):   # (holes anywhere in the row)
+            idx[r, np.sort(rng.choice(topk, size=n, replace=False))] = rng.choice(cfg.nb, size=n, replace=False)
+        _log(f"[forward] {cfg.name}")
+        cnt = _block_counts(cfg, 11) if with_counts else None
+        _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
 
 
 @pytest.mark.parametrize("n_obj,n_views", [(0, 3), (640, 0)])
