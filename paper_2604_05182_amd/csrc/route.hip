@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
         }
     }
 
-    // volume rule: per-wave extraction, merged by wave 0 (the barrier inside also publishes img_keys)
+    // volume rule: per-wave extraction, every wave places its own keys (the barrier inside also publishes img_keys)
     int32_t *idx_row = idx + (size_t)row * a.width;
     float *d2_row = dist2_out ? dist2_out + (size_t)row * a.width : nullptr;
     auto vol_d2_of = [&](int j) {
