@@ -77,8 +77,8 @@ __global__ __launch_bounds__(256) void pool_blocks(int nb, int row_chunks /* h*d
 // 2 heads of 32 in groups of eight blocks (9), 26.8 us for 1 M tokens of one head of 32 in single blocks (21.5; 52 with
 // <16, 1, 8>) and 628 us for the 3.5 GB above.
 // A workgroup loops where there are more units than kPoolMaxGrid: a launch holds fewer than 2^32 threads in a direction, and
-// there can be 2^24 groups.
-constexpr int kPoolSums = 16, kPoolMaxGrid = 1 << 22;
+// there can be 2^24 groups.  (Not at fewer: 131 K groups of two blocks, one head of 64, 700 us in two turns, 645 to 680 in one.)
+constexpr int kPoolSums = 16, kPoolMaxGrid = 1 << 20;
 constexpr int64_t kPoolWideFrom = 1 << 17;  // groups times chunks of a row
 template <int LANES, int SIDE, int DEPTH>
 __global__ __launch_bounds__(256) void pool_groups(int ng, int row_chunks, const uint4 *__restrict__ k,

@@ -221,25 +221,26 @@ def test_pooling_of_spatial_blocks_layouts(B, d, h_kv, n_groups, max_size):
         assert bool(((got.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-6).all())
 
 
-def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B):
-    """2^30 tokens, the longest sequence the calls take, every 64-slot block a spatial block of its own: 2^24 of them.
+@pytest.mark.parametrize("nb,h_kv,d", [(1 << 24, 1, 32), ((1 << 20) + 3, 1, 128), ((1 << 20) + 3, 4, 128)])
+def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B, nb, h_kv, d):
+    """2^30 tokens, the longest sequence the calls take, every 64-slot block a spatial block of its own: 2^24 of them;
+    and a few more of rows of 16 and 64 chunks than there are workgroups, so that some take two in turn.
     (k and v are the same 64 GiB.)  All tokens of a block hold its number modulo 251 in every channel, which is its
     mean exactly."""
     import torch
-    nb, d = 1 << 24, 32
     if torch.cuda.mem_get_info()[0] < 80 << 30:
         pytest.skip("needs 80 GiB of free GPU memory")
     _log(f"[pool] {nb} spatial blocks of one block")
     dev = torch.device("cuda")
     value = (torch.arange(nb, device=dev) % 251).to(torch.bfloat16)
-    k = torch.empty((nb * 64, 1, d), dtype=torch.bfloat16, device=dev)
-    k.view(nb, 64 * d).copy_(value[:, None].expand(nb, 64 * d))
+    k = torch.empty((nb * 64, h_kv, d), dtype=torch.bfloat16, device=dev)
+    k.view(nb, 64 * h_kv * d).copy_(value[:, None].expand(nb, 64 * h_kv * d))
     goff = torch.arange(nb + 1, dtype=torch.int32, device=dev)
-    p = B.make_params(nb * 64, 0, 0, 1, d, 1, 64, group_offsets=goff)
-    kc, vc = (torch.full((nb, 1, d), -1.0, dtype=torch.bfloat16, device=dev) for _ in range(2))
+    p = B.make_params(nb * 64, 0, 0, h_kv, d, 1, 64, group_offsets=goff)
+    kc, vc = (torch.full((nb, h_kv, d), -1.0, dtype=torch.bfloat16, device=dev) for _ in range(2))
     B.lsrm_nsa_compress(p, k, k, kc, vc)
     torch.cuda.synchronize()
-    want = value[:, None, None].expand(nb, 1, d)
+    want = value[:, None, None].expand(nb, h_kv, d)
     same = torch.equal(kc, want) and torch.equal(vc, want)
     del k, kc, vc
     torch.cuda.empty_cache()
