@@ -14,6 +14,7 @@
 //                   measures each one's point set (64 lanes = 64 points, minimum squared 3-D
 //                   distance); the workgroup then extracts the nearest volume blocks by
 //                   centre distance and the nearest of the surviving tiles.
+//   select_3d_many  the same for many queries (per token): 16 lanes a query.
 // The whole file is built with floating-point contraction off: every product and sum
 // below is rounded to fp32 exactly as written, which is what makes the indices
 // reproducible bit for bit.  Plain ALU work, latency bound and tiny next to attention.
@@ -446,6 +447,323 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
     }
 }
 
+// The same selection for many queries (57 K tokens of a scene, say): a workgroup takes kManyQueries of them that follow one
+// another, 16 lanes a query, so that a minimum over a query's lanes is four data-parallel-primitive steps without a scalar
+// read, four queries a wavefront side by side.  select_3d gives a workgroup to a query: chains of minima over 64
+// lanes, most lanes with nothing of their own.  Bound by instructions issued (the vector pipe is busy all the time), as
+// that one is, with a fifth of them per query: what several queries have in common is done once.
+// 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query.
+// 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query.
+constexpr int kManyQueries = 16;
+constexpr int kNearList = 128, kNearFrom = 48;  // listed blocks of a query, the largest volume budget that a list is made for
+constexpr int kCommonList = 256, kCommonFrom = 256;  // listed blocks of a workgroup, the fewest blocks it is made from
+
+// Minimum over the 16 lanes of a row; every lane of the row gets it.
+__device__ __forceinline__ unsigned row_min_u32(unsigned v) {
+    return row_fold(v, [](unsigned a, unsigned b) { return a < b ? a : b; });
+}
+__device__ __forceinline__ unsigned row_max_u32(unsigned v) {
+    return row_fold(v, [](unsigned a, unsigned b) { return a > b ? a : b; });
+}
+__device__ __forceinline__ unsigned long long row_min_u64(unsigned long long v) {
+    const unsigned hi = (unsigned)(v >> 32), lo = (unsigned)v;
+    const unsigned hi_min = row_min_u32(hi);
+    return ((unsigned long long)hi_min << 32) | row_min_u32(hi == hi_min ? lo : 0xffffffffu);
+}
+
+struct __attribute__((packed, aligned(4))) FourPoints {
+    float v[12];
+};
+
+// The window of 4 x 4 tiles of a view around a projection in which its nearest tiles are looked for.  Squares and sums round
+// monotonically, so a tile outside the window is no nearer than `beside`, the smallest of the tiles just outside its four
+// borders in the row or column of the window's smallest difference: tiles of the window that are strictly nearer than
+// that are the nearest of the view.  beside < 0: no tile of the view is a candidate.
+struct TileWindow {
+    float u, v, beside;
+    int first;  // first row << 16 | first column
+};
+__device__ __forceinline__ TileWindow tile_window(float2 uv, int tg) {
+    TileWindow w;
+    w.u = uv.x;
+    w.v = uv.y;
+    w.beside = -1.0f;
+    w.first = 0;
+    if (dist2(uv, 0, 0) == __builtin_inff()) return w;
+    const int top = max(tg - 4, 0);
+    const float fi = floorf((fminf(fmaxf(uv.y, -1.0e6f), 1.0e6f) - 4.0f) * 0.125f);
+    const float fj = floorf((fminf(fmaxf(uv.x, -1.0e6f), 1.0e6f) - 4.0f) * 0.125f);
+    const int i0 = min(max((int)fi - 1, 0), top), j0 = min(max((int)fj - 1, 0), top);
+    auto du2_at = [&](int j) { const float du = uv.x - (float)(8 * j + 4); return du * du; };
+    auto dv2_at = [&](int i) { const float dv = uv.y - (float)(8 * i + 4); return dv * dv; };
+    float du2 = du2_at(j0), dv2 = dv2_at(i0);
+    for (int t = 1; t < min(4, tg); ++t) {
+        du2 = fminf(du2, du2_at(j0 + t));
+        dv2 = fminf(dv2, dv2_at(i0 + t));
+    }
+    w.beside = __builtin_inff();
+    if (i0 > 0) w.beside = fminf(w.beside, du2 + dv2_at(i0 - 1));
+    if (i0 + 4 < tg) w.beside = fminf(w.beside, du2 + dv2_at(i0 + 4));
+    if (j0 > 0) w.beside = fminf(w.beside, du2_at(j0 - 1) + dv2);
+    if (j0 + 4 < tg) w.beside = fminf(w.beside, du2_at(j0 + 4) + dv2);
+    w.first = i0 << 16 | j0;
+    return w;
+}
+
+// Dynamic LDS: [Q][n_views] windows, [Q][n_views * prefilter] keys, [Q][width] ids and distances.
+template <int Q>
+__global__ __launch_bounds__(16 * Q) void select_3d_many(Route3d a, int n_queries, const float4 *__restrict__ cent,
+                                                         const float *__restrict__ pos, const float *__restrict__ pos_img,
+                                                         const lsrm_camera *__restrict__ cams, int32_t *__restrict__ idx,
+                                                         float *__restrict__ dist2_out) {
+    extern __shared__ unsigned long long lds_base[];
+    __shared__ float4 points[Q], common[kCommonList];
+    __shared__ unsigned long long near_keys[Q * kNearList];
+    __shared__ int n_common;
+    __shared__ unsigned wave_bound[Q / 4];
+    const int n_img = a.n_views * a.prefilter;
+    TileWindow *windows = reinterpret_cast<TileWindow *>(lds_base);
+    unsigned long long *img_keys = reinterpret_cast<unsigned long long *>(windows + Q * a.n_views);
+    int *out_idx = reinterpret_cast<int *>(img_keys + Q * n_img);
+    float *out_d2 = reinterpret_cast<float *>(out_idx + Q * a.width);
+    const int q0 = blockIdx.x * Q, nq = min(Q, n_queries - q0);
+    const int g = threadIdx.x >> 4, l = threadIdx.x & 15, lane = threadIdx.x & 63;
+    const int tpv = a.tg * a.tg, n_obj_rows = a.per_token ? a.n_obj : a.nb_obj;
+    const bool any_img = a.k_v2i > 0 || a.k_i2i > 0;
+    const int kv_max = max(a.k_v2v, a.k_i2v);
+    if ((int)threadIdx.x < Q) {
+        const int row = q0 + min((int)threadIdx.x, nq - 1);
+        if (a.per_token) {
+            const float *q = row < a.n_obj ? pos + (size_t)row * 3 : pos_img + (size_t)(row - a.n_obj) * 3;
+            points[threadIdx.x] = make_float4(q[0], q[1], q[2], 0.0f);
+        } else {
+            points[threadIdx.x] = cent[row];
+        }
+    }
+    if (threadIdx.x == 0) n_common = 0;
+    for (int i = threadIdx.x; i < nq * a.width; i += 16 * Q) {
+        out_idx[i] = -1;
+        out_d2[i] = __builtin_inff();
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; any_img && i < nq * a.n_views; i += 16 * Q) {
+        const int q = i / a.n_views;
+        const float4 p = points[q];
+        windows[i] = tile_window(project(cams[i - q * a.n_views], p.x, p.y, p.z), a.tg);
+    }
+
+    // The volume blocks that any of the workgroup's queries can select.  With R the largest distance of a query from the
+    // middle one and D a bound on that one's kv-th smallest block distance, every query has kv blocks within D + R, and
+    // those lie within D + 2 R of the middle one.  (Distances are off by less than 1e-6 of themselves, far below the
+    // allowance; one that is not finite leaves the list empty.)
+    const bool listing = kv_max > 0 && kv_max <= kNearFrom && a.nb_obj >= kCommonFrom;
+    bool listed = false;
+    if (listing) {
+        const float4 p0 = points[nq / 2], pl = points[l & (Q - 1)];
+        const float r2 = __uint_as_float(row_max_u32(__float_as_uint(sqdist3(p0.x, p0.y, p0.z, pl.x, pl.y, pl.z))));
+        auto d2_bits = [&](int j) {
+            const float4 c = cent[j];
+            return __float_as_uint(sqdist3(p0.x, p0.y, p0.z, c.x, c.y, c.z));
+        };
+        unsigned m = ~0u, bound = 0;
+        for (int j = threadIdx.x; j < a.nb_obj; j += 16 * Q) m = min(m, d2_bits(j));
+        for (int r = 0; r < kv_max; ++r) {  // (equal ones go together: the bound is then a larger one)
+            bound = wave_min_u32(m);
+            m = m == bound ? ~0u : m;
+        }
+        if (lane == 0) wave_bound[threadIdx.x >> 6] = bound;
+        __syncthreads();
+        for (int w = 0; w < Q / 4; ++w) bound = min(bound, wave_bound[w]);
+        const float reach = (sqrtf(__uint_as_float(bound)) + 2.0f * sqrtf(r2)) * 1.0001f + 1.0e-17f, reach2 = reach * reach;
+        if (reach2 < __builtin_inff()) {
+            for (int j = threadIdx.x; j < a.nb_obj; j += 16 * Q)
+                if (__uint_as_float(d2_bits(j)) <= reach2) {
+                    const int at = atomicAdd(&n_common, 1);
+                    if (at < kCommonList) {
+                        float4 c = cent[j];
+                        c.w = __int_as_float(j);
+                        common[at] = c;
+                    }
+                }
+            listed = true;
+        }
+    }
+    __syncthreads();
+    if (n_common > kCommonList) listed = false;
+    if (g >= nq) return;  // (from here on a query's lanes are on their own; the last barrier is behind)
+
+    const float4 p = points[g];
+    const bool obj_row = q0 + g < n_obj_rows;
+    const int kv = obj_row ? a.k_v2v : a.k_i2v, ki = obj_row ? a.k_v2i : a.k_i2i;
+    unsigned long long *keys = img_keys + g * n_img;
+    auto put = [&](int at, unsigned long long key) {
+        out_idx[g * a.width + at] = (int)(unsigned)(key & 0xffffffffu);
+        out_d2[g * a.width + at] = __uint_as_float((unsigned)(key >> 32));
+    };
+
+    // image rule, first two steps: the prefilter nearest tiles of every view by 2-D distance, then their point sets (four
+    // points per lane)
+    for (int m = 0; ki > 0 && m < a.n_views; ++m) {
+        const TileWindow w = windows[g * a.n_views + m];
+        const float2 uv = make_float2(w.u, w.v);
+        unsigned long long *out = keys + m * a.prefilter;
+        if (w.beside < 0.0f) {
+            for (int c = l; c < a.prefilter; c += 16) out[c] = kNoKey;
+            continue;
+        }
+        auto point_set = [&](int tile) {
+            return *reinterpret_cast<const FourPoints *>(pos_img + ((size_t)tile * kBlock + 4 * l) * 3);
+        };
+        auto measure = [&](int c, int tile, const FourPoints &pts) {
+            unsigned d = 0xffffffffu;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                d = min(d, __float_as_uint(sqdist3(p.x, p.y, p.z, pts.v[3 * i], pts.v[3 * i + 1], pts.v[3 * i + 2])));
+            d = row_min_u32(d);
+            if (l == 0) out[c] = ((unsigned long long)d << 32) | (unsigned)(a.nb_obj + tile);
+        };
+        bool found = false;
+        if (a.prefilter <= 4) {
+            const int i0 = w.first >> 16, j0 = w.first & 0xffff, ti = i0 + (l >> 2), tj = j0 + (l & 3);
+            unsigned key = ti < a.tg && tj < a.tg ? __float_as_uint(dist2(uv, ti, tj)) : 0xffffffffu, last = 0;
+            int tile[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                tile[r] = 0;
+                if (r < a.prefilter) {
+                    last = row_min_u32(key);
+                    const int at = (int)row_min_u32(key == last ? (unsigned)l : 16u);  // (lanes are in the order of the tiles)
+                    tile[r] = m * tpv + (i0 + (at >> 2)) * a.tg + j0 + (at & 3);
+                    key = l == at ? 0xffffffffu : key;
+                }
+            }
+            found = last < __float_as_uint(w.beside);
+            if (found) {
+                FourPoints pts[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pts[r] = point_set(tile[r]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r < a.prefilter) measure(r, tile[r], pts[r]);
+            }
+        }
+        if (!found) {
+            auto tile_key = [&](int t) { return make_key(dist2(uv, t / a.tg, t % a.tg), (unsigned)t); };
+            LaneKeys held;
+            held.scan(l, 16, tpv, tile_key, false, 0);
+            for (int c = 0; c < a.prefilter; ++c) {
+                const unsigned long long best = row_min_u64(held.mine);
+                held.take(best, l, 16, tpv, tile_key);
+                const int tile = m * tpv + (int)(unsigned)(best & 0xffffffffu);
+                measure(c, tile, point_set(tile));
+            }
+        }
+    }
+
+    // volume rule
+    const int n_vol = min(kv, a.nb_obj);
+    if (n_vol > 0) {
+        auto key_of = [&](int j) {
+            const float4 c = cent[j];
+            return ((unsigned long long)__float_as_uint(sqdist3(p.x, p.y, p.z, c.x, c.y, c.z)) << 32) | (unsigned)j;
+        };
+        // The blocks (those of the list, or all) are dealt to 4 x 16 sets; the kv-th smallest of the sets' smallest distances
+        // bounds the kv-th smallest of all, and few blocks are below it (about 64 ln(64 / (64 - kv)) of many).  Those are listed
+        // and ranked.  More of them than the list holds (equal distances, say): the blocks are taken one by one.
+        int n_near = kNearList + 1;
+        unsigned long long *near = near_keys + g * kNearList;
+        auto narrow = [&](int n_src, auto src_key) {
+            unsigned m[4] = {~0u, ~0u, ~0u, ~0u};
+            for (int j0 = l; j0 < n_src; j0 += 64) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j = j0 + 16 * u;
+                    const unsigned x = (unsigned)(src_key(min(j, n_src - 1)) >> 32);
+                    m[u] = j < n_src ? min(m[u], x) : m[u];
+                }
+            }
+            unsigned bound = 0;
+            for (int r = 0; r < kv; ++r) {  // (equal ones go together, as above)
+                bound = row_min_u32(min(min(m[0], m[1]), min(m[2], m[3])));
+#pragma unroll
+                for (int u = 0; u < 4; ++u) m[u] = m[u] == bound ? ~0u : m[u];
+            }
+            n_near = 0;
+            const int row_shift = threadIdx.x & 48;
+            for (int j0 = l; j0 - l < n_src; j0 += 16) {
+                const unsigned long long key = src_key(min(j0, n_src - 1));
+                const bool on = j0 < n_src && (unsigned)(key >> 32) <= bound;
+                const unsigned in_row = (unsigned)(__ballot(on) >> row_shift) & 0xffffu;
+                if (in_row != 0) {
+                    const int at = n_near + __popc(in_row & ((1u << l) - 1u));
+                    if (on && at < kNearList) near[at] = key;
+                    n_near += __popc(in_row);
+                }
+            }
+        };
+        if (listed)
+            narrow(n_common, [&](int i) {
+                const float4 c = common[i];
+                return ((unsigned long long)__float_as_uint(sqdist3(p.x, p.y, p.z, c.x, c.y, c.z)) << 32) |
+                       (unsigned)__float_as_int(c.w);
+            });
+        else if (kv <= kNearFrom)
+            narrow(a.nb_obj, key_of);
+        if (n_near <= kNearList) {
+            // (LDS operations of a wavefront complete in order, and a query's lanes are in one wavefront)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int c = l; c < n_near; c += 16) {
+                const unsigned long long key = near[c];
+                int rank = 0;
+#pragma unroll 4
+                for (int j = 0; j < n_near; ++j) rank += near[j] < key ? 1 : 0;
+                if (rank < n_vol) put(rank, key);
+            }
+        } else {
+            LaneKeys held;
+            held.scan(l, 16, a.nb_obj, key_of, false, 0);
+            for (int r = 0; r < n_vol; ++r) {
+                const unsigned long long best = row_min_u64(held.mine);
+                if (l == 0) put(r, best);
+                held.take(best, l, 16, a.nb_obj, key_of);
+            }
+        }
+    }
+
+    // image rule: the budget out of the surviving candidates
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (ki > 0) {
+        // ranking costs about 4 instructions per candidate and 16 of them, an extraction about 25 per result: the line is
+        // where they are equal
+        if ((n_img + 15) / 16 * n_img <= 6 * ki + 64) {
+            for (int c = l; c < n_img; c += 16) {
+                const unsigned long long key = keys[c];
+                int rank = 0;
+#pragma unroll 4
+                for (int j = 0; j < n_img; ++j) rank += keys[j] < key ? 1 : 0;
+                if (key != kNoKey && rank < ki) put(n_vol + rank, key);
+            }
+        } else {
+            auto key_of = [&](int c) { return keys[c]; };
+            LaneKeys held;
+            held.scan(l, 16, n_img, key_of, false, 0);
+            for (int r = 0; r < ki; ++r) {
+                const unsigned long long best = row_min_u64(held.mine);
+                if (best == kNoKey) break;
+                if (l == 0) put(n_vol + r, best);
+                held.take(best, l, 16, n_img, key_of);
+            }
+        }
+    }
+    // the row, 64 bytes at a time
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const size_t row0 = (size_t)(q0 + g) * a.width;
+    for (int i = l; i < a.width; i += 16) {
+        idx[row0 + i] = out_idx[g * a.width + i];
+        if (dist2_out) dist2_out[row0 + i] = out_d2[g * a.width + i];
+    }
+}
+
 }  // namespace
 
 size_t route3d_ws_bytes(const Shape &s) {
@@ -481,6 +799,18 @@ lsrm_status launch_route_3d(const Shape &s, const lsrm_route3d_params &r, const 
     a.cache_keys = vol_bytes + cand_bytes <= 60 * 1024 ? 1 : 0;
     const size_t lds = cand_bytes + (a.cache_keys ? vol_bytes : 0);
     const unsigned n_queries = r.per_token ? (unsigned)s.n : (unsigned)s.nb;
+    // A query's 16 lanes do in turn what select_3d gives to 256: many queries are needed to fill the chip, and the more
+    // blocks there are to look at the more of them.  Measured, select_3d and select_3d_many: 57344 queries of 512 blocks
+    // 322 and 87 us, 70144 of 1024 936 and 331, 12288 of 64 128 and 64, 4096 of 64 16 and 11, 1280 of 16 11 and 11; but 640
+    // of 512 11 and 21, 3072 of 2048 57 and 80, 4672 of 4096 71 and 108.
+    const size_t many_lds = kManyQueries * (16 * (size_t)s.n_views + 8 * (size_t)s.n_views * a.prefilter + 8 * (size_t)s.topk);
+    if (n_queries >= 2048u + 2u * s.nb_obj && many_lds <= 40 * 1024) {
+        hipLaunchKernelGGL(select_3d_many<kManyQueries>, dim3((n_queries + kManyQueries - 1) / kManyQueries),
+                           dim3(16 * kManyQueries), many_lds, st, a, (int)n_queries, cent, d_pos, d_pos_img, d_cams, d_idx,
+                           d_dist2);
+        LSRM_HIP_CHECK(hipGetLastError());
+        return LSRM_OK;
+    }
     hipLaunchKernelGGL(select_3d, dim3(n_queries), dim3(256), lds, st, a, cent, d_pos, d_pos_img, d_cams, d_idx,
                        d_dist2);
     LSRM_HIP_CHECK(hipGetLastError());

@@ -171,3 +171,38 @@ def test_route_3d_list_lengths_at_the_edges(B, oracle_lib, n_blocks, n_views, pr
     pimg = I.make_points_img(cfg, cams)
     ref = oracle_lib.route_3d(pos, pimg, cams, cfg.grid, width, pre, *budgets)
     _same(G.run_route_3d(B, cfg, pos, pimg, cams, width, pre, *budgets), ref)
+
+
+@pytest.mark.parametrize("n_blocks,n_views,grid,pre,budgets,scene", [
+    (256, 2, 24, 4, (8, 8, 8, 8), "plain"),        # the fewest blocks that a common list is made from; windows of the whole view
+    (255, 3, 16, 3, (48, 9, 3, 9), "plain"),       # no common list; the largest volume budget that a list is made for
+    (300, 1, 72, 4, (49, 4, 20, 3), "plain"),      # one budget above it
+    (320, 2, 64, 5, (6, 10, 7, 9), "plain"),       # more tiles per view than a window is searched for
+    (260, 18, 16, 1, (0, 18, 5, 0), "plain"),      # one-sided budgets
+    (272, 20, 40, 4, (4, 60, 12, 80), "plain"),    # 80 candidate tiles: extracted for 60 results, ranked for 80
+    (264, 2, 48, 4, (8, 8, 8, 8), "far"),          # projections far outside the images: distances tie after rounding
+    (264, 2, 48, 4, (8, 8, 8, 8), "tied"),         # blocks and queries that coincide: lists overflow, ids decide
+    (264, 2, 48, 4, (8, 8, 8, 8), "holes"),        # blocks and queries whose squared distances overflow
+    (5, 18, 96, 4, (4, 9, 3, 11), "blocks"),       # block queries, 2597 of them: an odd number, fewer blocks than lanes
+], ids=lambda v: str(v).replace(" ", ""))
+def test_route_3d_many_queries(B, oracle_lib, n_blocks, n_views, grid, pre, budgets, scene):
+    """Enough queries for the kernel that gives 16 lanes to each, at the sizes where it changes its course."""
+    cfg = I.small_config(name="r3-many", n_obj=64 * n_blocks, n_views=n_views, grid=grid, seed=n_blocks, near_views=1)
+    width = max(budgets[0] + budgets[1], budgets[2] + budgets[3])
+    _log(f"[route3d] many queries: {n_blocks} blocks, {n_views} views of {grid}, B^i={pre} budgets={budgets} {scene}")
+    pos, cams = I.make_points(cfg), I.make_cameras(cfg)
+    if scene == "far":
+        pos *= np.float32(3e4)
+    elif scene == "tied":
+        pos[64 * 20:64 * 220] = pos[64:128].repeat(200, axis=0)
+    elif scene == "holes":
+        pos[::64 * 7] = 1e30
+    pimg = I.make_points_img(cfg, cams)
+    per_token = scene != "blocks"
+    n = cfg.n if per_token else cfg.nb
+    assert n >= 2048 + 2 * cfg.nb_obj
+    rng = np.random.default_rng(3)
+    pick = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, size=600)]))
+    ref = oracle_lib.route_3d(pos, pimg, cams, cfg.grid, width, pre, *budgets, per_token=per_token, queries=pick)
+    idx, d2 = G.run_route_3d(B, cfg, pos, pimg, cams, width, pre, *budgets, per_token=per_token)
+    _same((idx[pick], d2[pick]), ref)
