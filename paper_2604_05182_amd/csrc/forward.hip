@@ -44,6 +44,7 @@
 //   final tile goes through LDS so that the bf16 output rows are written as whole 16-byte chunks.
 #include "lsrm_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lsrm {
@@ -77,6 +78,7 @@ struct FwdArgs {
     int own_block;      // the window branch sees the query's own block (App. A) instead of a sliding window
     const int32_t *count;  // nullable [NB]: active tokens per block (its first count[b] slots)
     int groups_per_head, groups_per_xcd;  // query-block groups of one head, and the share of one XCD
+    int teams[3];  // nsa_forward_teams: teams of each branch
     float scale_log2e, scale;
 };
 
@@ -152,6 +154,20 @@ __device__ __forceinline__ float half_sum(float x) {
 // lgkmcnt bits [11:8]; counters that are not waited for are left at their maxima)
 constexpr int vm_lgkm_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0070; }  // vmcnt <= n, lgkmcnt == 0
 constexpr int kLgkmOnly = 0xC07F;                                                   // lgkmcnt == 0, vmcnt left alone
+
+// Waits until at most n copies of UNIT instructions each are in flight, n <= MAX at run time (wave-uniform).
+template <int UNIT, int MAX>
+__device__ __forceinline__ void wait_copies(int n) {
+    if constexpr (MAX == 0) {
+        __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
+    } else {
+        static_assert(UNIT * MAX < 64, "vmcnt has six bits");
+        if (n >= MAX)
+            __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(UNIT * MAX));
+        else
+            wait_copies<UNIT, MAX - 1>(n);
+    }
+}
 
 // Bare workgroup barrier.  No barrier, fenced or not, waits for global -> LDS copies in flight
 // (they are counted by vmcnt, which a workgroup-scope fence leaves alone), so what must be
@@ -407,6 +423,7 @@ __device__ __forceinline__ void end_phase() {
 template <class G, typename SrcFn>
 struct OwnTiles {
     static constexpr int NP = G::NP, NST = G::NST;
+    static constexpr bool EXACT = false;
     static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
     static_assert(G::NW == 2, "two wavefronts per query block");
     static_assert((NST & (NST - 1)) == 0 && NST >= 2, "");
@@ -447,6 +464,7 @@ __device__ __forceinline__ OwnTiles<G, SrcFn> own_tiles(int n, SrcFn src, char *
 
 template <class G>
 struct SharedTiles {
+    static constexpr bool EXACT = false;
     static constexpr int NST = G::NSLOT, KN = G::K_BYTES / 1024, VN = G::V_BYTES / 1024;
     static constexpr int KI = (KN + G::WAVES - 1) / G::WAVES, VI = (VN + G::WAVES - 1) / G::WAVES;
     static constexpr int KW = KN / KI, VW = VN / VI;  // wavefronts that copy: the first KW the K part, the last VW the V part
@@ -511,6 +529,8 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
     auto sync = [&](int t) {
         if (NST > 2 && t + NST - 1 < n)
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm((NST - 2) * Tiles::PER_STEP));
+        else if constexpr (Tiles::EXACT)
+            wait_copies<Tiles::KI, Tiles::MOST>(tiles.in_flight(t));
         else
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         wg_barrier();
@@ -532,7 +552,10 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
     auto mask_next = [&](int t, f32x16 &s_next) {  // (an empty body where no tile can need a mask)
         if (t + 1 < n) mask_tile(t + 1, s_next);
     };
-    __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
+    if constexpr (Tiles::EXACT)
+        wait_copies<Tiles::KI, Tiles::MOST>(n > 0 ? tiles.in_flight_first() : 0);
+    else
+        __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
     wg_barrier();
     if (n > 0) {
         bf16x8 kf[G::NS];
@@ -941,6 +964,266 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
     }
 }
 
+// The same layer for few query blocks: the three branches run beside each other instead of one after the other, in one workgroup
+// per query block and head (or two query blocks).  NT teams of two wavefronts share the tiles of a query block: every
+// branch has teams of its own, the longest branches the most (FwdArgs::teams), and a team streams a contiguous part of its
+// branch's tiles.  All run the same code (the tiles' addresses and masks differ), so that its instructions are fetched once
+// and not three times.  The teams' running maxima, sums and outputs meet in LDS in fp32.
+// A lone workgroup of nsa_forward_kernel is a chain: 6 K tokens, 4 heads of 64, 8 routed blocks, window 512
+// (3 + 16 + 18 steps) took 39.5 K cycles, 3.1 K of them for the routing row, 4.1 / 8.7 / 13.9 K for the branches at 500 to 800 a step, 2 to
+// 3 K for each epilogue, on SIMDs with one wavefront or none.
+// Attention step, nsa_forward_kernel and this: that problem 19.9 -> 14.8 us; 43 blocks, 3 heads of 128, 9 routed blocks, window
+// 192: 33.8 -> 15.6 us (what remains is the copies' latency, two stages deep: 2000 cycles a step, 1400 without copies).
+template <class G, int NB_, int NT_, int NST_>
+struct Teams {
+    static constexpr int NB = NB_, NT = NT_, NST = NST_;  // query blocks of a workgroup; teams of one; stages of a team
+    static constexpr int THREADS = 64 * G::NW * NT * NB;
+    static constexpr int PITCH = G::D + 4;  // floats of a row of a team's result: 16-byte aligned, rows spread over the banks
+    static constexpr int TILES_BYTES = NB * NT * NST * G::TILE, SUM_BYTES = NB * NT * kBlock * (PITCH + 2) * 4;
+    static constexpr int LDS_ALL = TILES_BYTES > SUM_BYTES ? TILES_BYTES : SUM_BYTES;
+    static constexpr int WAVES_PER_SIMD = (THREADS / 64 + 3) / 4;  // (one workgroup per CU)
+    static_assert(LDS_ALL <= 160 * 1024 && NT >= 3, "");
+};
+
+template <class G, class TM, typename SrcFn>
+struct TeamTiles {
+    static constexpr int NST = TM::NST;
+    static constexpr bool EXACT = true;
+    static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
+    const int n;
+    const SrcFn src;
+    char *const lds;  // the slots of the team
+    const int sub;
+    const uint32_t lane16;
+    __device__ __forceinline__ char *stage(int tau) const { return lds + (tau & (NST - 1)) * G::TILE; }
+    __device__ __forceinline__ void issue_part(const char *tile, char *slot, int n_inst) const {
+#pragma unroll 8
+        for (int j = 0; j < n_inst; ++j) {
+            const int i = sub + G::NW * j;
+            copy_kb_to_lds(tile + i * 1024, lane16, slot + i * 1024);
+        }
+    }
+    __device__ __forceinline__ void issue_k(int tau) const { issue_part(src(tau), stage(tau), KI); }
+    __device__ __forceinline__ void issue_v(int tau) const {
+        issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
+    }
+    // in the order K(0), K(1), V(0), K(2), V(1), ..
+    __device__ __forceinline__ void begin() const {
+#pragma unroll
+        for (int tau = 0; tau < NST; ++tau) {
+            if (tau < n) issue_k(tau);
+            if (tau >= 1 && tau < NST - 1 && tau - 1 < n) issue_v(tau - 1);
+        }
+    }
+    // Copies that may be in flight at barrier t, in units of KI instructions: behind K(t + 1) and V(t - 1) those of K(t + 2 ..) and
+    // V(t ..) that were issued before it; ahead of the first step all but K(0).
+    static constexpr int MOST = 2 * NST - 3;
+    static_assert(KI == VI, "");
+    __device__ __forceinline__ int in_flight(int t) const { return min(NST - 2, max(0, n - 2 - t)) + min(NST - 2, max(0, n - t)); }
+    __device__ __forceinline__ int in_flight_first() const { return min(NST - 1, n - 1) + min(NST - 2, n); }
+};
+
+template <class G, class TM, bool CNT, bool WIDE>
+__global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forward_teams(FwdArgs a) {
+    constexpr int D = G::D, NB = TM::NB, NT = TM::NT;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;  // (numbered as above)
+    const int head = slot_id / a.groups_per_xcd;
+    const int group = xcd * a.groups_per_xcd + slot_id % a.groups_per_xcd;
+    if (group >= a.groups_per_head) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int team = wave % NT, sub = wave / NT % G::NW, qbi = wave / (NT * G::NW);
+    const int branch = team < a.teams[0] ? 0 : team < a.teams[0] + a.teams[1] ? 1 : 2;
+    const int part = branch == 0 ? team : branch == 1 ? team - a.teams[0] : team - a.teams[0] - a.teams[1];
+    const int n_parts = a.teams[branch];
+    const int r = lane & 31, hh = lane >> 5;
+    const int qb = min(group * NB + qbi, a.nb - 1);  // (the last group may be short: its last wavefronts have no keys)
+    const bool active = group * NB + qbi < a.nb;
+    const int64_t row0 = (int64_t)qb * 64 + G::ROWS * sub, row = row0 + r;
+    const int kvh = head / a.group;
+    const float sl2 = a.scale_log2e;
+    char *const slots = lds + (qbi * NT + team) * TM::NST * G::TILE;
+
+    // the routing row, valid entries first (entry u in lane u % 64 of register u / 64), compacted in the part of the branch's
+    // slots that this wavefront copies to
+    constexpr int NR = WIDE ? 2 : 1;
+    int packed[NR], pcount[NR], n_valid = 0;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) packed[j] = -1, pcount[j] = 0;
+    if (branch == 1) {
+        int *scratch = reinterpret_cast<int *>(slots + sub * 1024);
+        int v[NR];
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            v[j] = lane + 64 * j < a.topk ? a.idx[(int64_t)qb * a.topk + lane + 64 * j] : -1;
+            if (v[j] >= a.nb) v[j] = -1;
+        }
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const unsigned long long bal = __ballot(v[j] >= 0);
+            if (v[j] >= 0) scratch[n_valid + __popcll(bal & ((1ull << lane) - 1ull))] = v[j];
+            n_valid += __popcll(bal);
+        }
+        // (LDS operations of a wavefront complete in order: the reads see the writes)
+#pragma unroll
+        for (int j = 0; j < NR; ++j) packed[j] = lane + 64 * j < n_valid ? scratch[lane + 64 * j] : -1;
+        if constexpr (CNT) {
+#pragma unroll
+            for (int j = 0; j < NR; ++j) pcount[j] = lane + 64 * j < n_valid ? a.count[packed[j]] : 0;
+        }
+    }
+    WaveCtx<G> c;
+    c.lane16 = (uint32_t)lane * 16u;
+    const uint16_t *qrow = a.q + (row * a.h + head) * D + 8 * hh;
+#pragma unroll
+    for (int ks = 0; ks < G::NS; ++ks) c.qf[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
+    auto of_row = [&](const int (&x)[NR], int u) {  // (u is wave-uniform)
+        const int e0 = __builtin_amdgcn_readlane(x[0], u & 63);
+        if constexpr (WIDE) {
+            const int e1 = __builtin_amdgcn_readlane(x[NR - 1], u & 63);
+            return u < 64 ? e0 : e1;
+        } else {
+            return e0;
+        }
+    };
+
+    // the keys of this team: tiles first .. first + n - 1 of an image, or entries of the routing row; lane's query sees [lo, hi),
+    // all queries [full_lo, full_hi)
+    const WinRange win = window_range(a, qb);
+    const int n_cmp = (a.nbc + 31) / 32;
+    const bool cmp = branch == 0;
+    const int n_branch = !active ? 0 : cmp ? n_cmp : branch == 1 ? 2 * n_valid : win.st1 - win.st0;
+    const int t0 = n_branch * part / n_parts, n = n_branch * (part + 1) / n_parts - t0;
+    const int i = (int)row, half_w = a.window / 2;
+    const int first = (cmp ? 0 : branch == 1 ? 0 : win.st0) + t0;
+    const int full_lo = cmp ? 0 : win.full_lo, full_hi = cmp ? a.nbc : win.full_hi;
+    const int lo = cmp ? 0 : max(win.seg_lo, i - half_w), hi = cmp ? a.nbc : min(win.seg_hi, i + half_w);
+    // no fewer steps than any wavefront of the workgroup has
+    int n_win = win.st1 - win.st0;
+    if (NB == 2) {
+        const WinRange other = window_range(a, min(group * NB + 1 - qbi, a.nb - 1));
+        n_win = max(n_win, other.st1 - other.st0);
+    }
+    const int n_steps = max(max((n_cmp + a.teams[0] - 1) / a.teams[0], (2 * a.topk + a.teams[1] - 1) / a.teams[1]),
+                            (n_win + a.teams[2] - 1) / a.teams[2]);
+    const char *base = cmp ? a.kvc + (int64_t)kvh * n_cmp * G::TILE : a.kv + (int64_t)kvh * (2 * a.nb) * G::TILE;
+    auto src = [&](int t) {
+        const int tile = branch == 1 ? 2 * of_row(packed, (first + t) >> 1) + ((first + t) & 1) : first + t;
+        return base + (int64_t)tile * G::TILE;
+    };
+    auto mask_tile = [&](int t, f32x16 &sc) {
+        int j0 = 32 * (first + t), from = lo, to = hi;
+        bool need = j0 < full_lo || j0 + 32 > full_hi;
+        if (branch == 1) {
+            need = false;
+            if constexpr (CNT) {
+                to = min(32, max(0, of_row(pcount, (first + t) >> 1) - 32 * ((first + t) & 1)));
+                need = to < 32;
+                j0 = from = 0;
+            }
+        } else if constexpr (CNT) {
+            if (branch == 2 && !a.own_block) {
+                const int vld = min(32, max(0, a.count[j0 >> 6] - (j0 & 32)));
+                if (vld < 32) {
+                    need = true;
+                    to = min(hi, j0 + vld);
+                }
+            }
+        }
+        if (need) {
+            mfma_settle();
+            mask_scores(from, to, sc, j0, lane);
+        }
+    };
+    const TeamTiles<G, TM, decltype(src)> tiles{n, src, slots, sub, c.lane16};
+    tiles.begin();
+    // A thread finishes 8 channels of NIT rows: their gates are requested now.
+    constexpr int CH = D / 8, NIT = (NB * kBlock * CH + TM::THREADS - 1) / TM::THREADS;
+    const int n_rows = kBlock * min(NB, a.nb - group * NB);
+    const int64_t out0 = (int64_t)group * NB * kBlock;
+    float gate[NIT][3];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int rr = (threadIdx.x + TM::THREADS * it) / CH;
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+            gate[it][b] = !a.gate_channels && rr < n_rows ? a.gates[((out0 + rr) * a.h + head) * 3 + b] : 1.f;
+    }
+    reset_branch<G>(c);
+    run_tiles<G>(c, n_steps, tiles, mask_tile, sl2);
+
+    // The teams of a branch bring their results to the branch's maximum and sum.
+    float *sums = reinterpret_cast<float *>(lds);     // [query block][team][row][PITCH]
+    float *ml = sums + NB * NT * kBlock * TM::PITCH;  // [query block][team][row][2]: running maximum, row sum
+    const int my_row = (qbi * NT + team) * kBlock + G::ROWS * sub + r;
+    const float l_part = half_sum(c.l);
+    __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
+    wg_barrier();  // (the tile slots are reused)
+    if (hh == 0) {
+        ml[2 * my_row] = c.m;
+        ml[2 * my_row + 1] = l_part;
+    }
+    __syncthreads();
+    float m = c.m, l = l_part, f = 1.f;
+    if (n_parts > 1) {
+        const int of_branch = my_row - part * kBlock;
+        m = kMinusHuge;
+        for (int j = 0; j < n_parts; ++j) m = fmaxf(m, ml[2 * (of_branch + j * kBlock)]);
+        l = 0.f;
+        for (int j = 0; j < n_parts; ++j) {
+            const int at = of_branch + j * kBlock;
+            l += ml[2 * at + 1] * __builtin_amdgcn_exp2f((ml[2 * at] - m) * sl2);
+        }
+        f = __builtin_amdgcn_exp2f((c.m - m) * sl2);
+    }
+    f = l > 0.f ? f / l : 0.f;
+    if (a.lse != nullptr && part == 0 && hh == 0 && active)
+        a.lse[((int64_t)branch * a.n + row) * a.h + head] = l > 0.f ? m * a.scale + __logf(l) : -__builtin_inff();
+#pragma unroll
+    for (int dt = 0; dt < G::ND; ++dt)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq)
+            *reinterpret_cast<f32x4 *>(sums + my_row * TM::PITCH + 32 * dt + 8 * gq + 4 * hh) =
+                f32x4{f * c.o[dt][4 * gq], f * c.o[dt][4 * gq + 1], f * c.o[dt][4 * gq + 2], f * c.o[dt][4 * gq + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int e = threadIdx.x + TM::THREADS * it, rr = e / CH, ch = e % CH;
+        if (rr >= n_rows) break;
+        const float *at = sums + (rr / kBlock * NT * kBlock + rr % kBlock) * TM::PITCH + 8 * ch;
+        f32x4 part_of[NT][2], total[2], of_branch[2];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q4 = 0; q4 < 2; ++q4) part_of[j][q4] = *reinterpret_cast<const f32x4 *>(at + j * kBlock * TM::PITCH + 4 * q4);
+        int b = 0, end = a.teams[0];  // branch of team j and the first team of the next one
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const bool opens = j == 0 || j == end;
+            if (j > 0 && j == end) end += a.teams[++b];
+#pragma unroll
+            for (int q4 = 0; q4 < 2; ++q4) of_branch[q4] = opens ? part_of[j][q4] : of_branch[q4] + part_of[j][q4];
+            if (j + 1 < end) continue;
+            if (a.out_branch != nullptr)
+                *reinterpret_cast<uint4 *>(a.out_branch + (((int64_t)b * a.n + out0 + rr) * a.h + head) * D + ch * 8) =
+                    make_uint4(pack_bf16(of_branch[0][0], of_branch[0][1]), pack_bf16(of_branch[0][2], of_branch[0][3]),
+                               pack_bf16(of_branch[1][0], of_branch[1][1]), pack_bf16(of_branch[1][2], of_branch[1][3]));
+            const float g = b == 0 ? gate[it][0] : b == 1 ? gate[it][1] : gate[it][2];
+#pragma unroll
+            for (int q4 = 0; q4 < 2; ++q4) {
+                f32x4 v = of_branch[q4] * g;
+                if (a.gate_channels)
+                    v *= *reinterpret_cast<const f32x4 *>(a.gates + (((out0 + rr) * 3 + b) * a.h + head) * D + ch * 8 + 4 * q4);
+                total[q4] = b == 0 ? v : total[q4] + v;
+            }
+        }
+        *reinterpret_cast<uint4 *>(a.out + ((out0 + rr) * a.h + head) * D + ch * 8) =
+            make_uint4(pack_bf16(total[0][0], total[0][1]), pack_bf16(total[0][2], total[0][3]),
+                       pack_bf16(total[1][0], total[1][1]), pack_bf16(total[1][2], total[1][3]));
+    }
+}
+
 // Builds the tile images (see WaveCtx) of a K and a V tensor, both [n_rows, H, D] bf16:
 // img[head][tile] = K fragments (K_BYTES) then V^T fragments (V_BYTES).
 // Rows at or beyond n_rows read as zero (their scores are masked in the attention kernel).
@@ -1109,21 +1392,51 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     a.kv = ws + w.kv;
     a.kvc = ws + w.kvc;
     a.gsum = reinterpret_cast<uint16_t *>(ws + w.gsum);
-    a.groups_per_head = (s.nb + NP - 1) / NP;
+    // Few query blocks: the branches beside each other, where all workgroups fit the 256 CUs together, one or two query blocks each.
+    // Measured (us, the general kernel and teams of one / of two query blocks), 64 blocks x 4 heads: d = 32 18.5 and 14.7 / 17.7, d = 64
+    // 21.7 and 15.3 / 19.3, d = 128 35.6 and 21.0; 65 x 4: 19.0 and 24.1 / 17.8, 22.1 and 25.3 / 19.8, 37.3 and 36.3 (a second
+    // round of workgroups); 254 x 2: 28.4 and 34.1 / 26.5, 31.7 and 35.4 / 29.0; 258 x 2: 31.5 and 43.7 / 40.3, 36.8 and 46.1 / 45.6,
+    // 59.4 and 67.9.  (At d = 128 a wavefront's registers leave no room for the twelve of two query blocks.)
+    using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2>;
+    using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2>;
+    const int64_t blocks = (int64_t)s.nb * s.h;
+    const int nb_wg = blocks <= 256 ? 1 : blocks <= 256 * Two::NB ? 2 : 0;  // query blocks of a workgroup of teams
+    if (nb_wg > 0) {
+        // every branch one team, the others where the longest part is
+        const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
+        for (int &t : a.teams) t = 1;
+        for (int extra = (nb_wg == 1 ? One::NT : Two::NT) - 3; extra > 0; --extra) {
+            int most = 0;
+            for (int b = 1; b < 3; ++b)
+                if ((int64_t)tiles[b] * a.teams[most] > (int64_t)tiles[most] * a.teams[b]) most = b;
+            ++a.teams[most];
+        }
+    }
+    a.groups_per_head = nb_wg == 0 ? (s.nb + NP - 1) / NP : (s.nb + nb_wg - 1) / nb_wg;
     a.groups_per_xcd = (a.groups_per_head + 7) / 8;
-    // dynamic LDS: the tile slots, then the LDS part of the running gated sum
-    constexpr int kLds = G::LDS_ALL;
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
-    const void *kern = cnt ? (wide ? reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, true>)
-                                   : reinterpret_cast<const void *>(&nsa_forward_kernel<G, true, false>))
-                           : (wide ? reinterpret_cast<const void *>(&nsa_forward_kernel<G, false, true>)
-                                   : reinterpret_cast<const void *>(&nsa_forward_kernel<G, false, false>));
+    const void *kern;
+    int lds, threads;
+#define LSRM_KERNEL(...) \
+    (cnt ? (wide ? reinterpret_cast<const void *>(&__VA_ARGS__, true, true>) : reinterpret_cast<const void *>(&__VA_ARGS__, true, false>)) \
+         : (wide ? reinterpret_cast<const void *>(&__VA_ARGS__, false, true>) : reinterpret_cast<const void *>(&__VA_ARGS__, false, false>)))
+    if (nb_wg == 1) {
+        kern = LSRM_KERNEL(nsa_forward_teams<G, One);
+        lds = One::LDS_ALL, threads = One::THREADS;
+    } else if (nb_wg == 2) {
+        kern = LSRM_KERNEL(nsa_forward_teams<G, Two);
+        lds = Two::LDS_ALL, threads = Two::THREADS;
+    } else {
+        kern = LSRM_KERNEL(nsa_forward_kernel<G);
+        lds = G::LDS_ALL, threads = G::THREADS;  // the tile slots, then the LDS part of the running gated sum
+    }
+#undef LSRM_KERNEL
     // (set on every launch: cheap, and right whichever device is current and whichever thread calls)
-    LSRM_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLds));
+    LSRM_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
     const dim3 grid(8 * a.groups_per_xcd * s.h);
     void *kargs[] = {&a};
-    LSRM_HIP_CHECK(hipLaunchKernel(kern, grid, dim3(G::THREADS), kargs, kLds, st));
+    LSRM_HIP_CHECK(hipLaunchKernel(kern, grid, dim3(threads), kargs, lds, st));
     LSRM_HIP_CHECK(hipGetLastError());
     if (ev_stop != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_stop, st));
     return LSRM_OK;

@@ -450,3 +450,31 @@ def test_forward_pipeline_edges(B, oracle_lib, d, nb):
     _log(f"[forward] {cfg.name}")
     assert cfg.nb == nb
     _assert_forward(*_forward_case(B, oracle_lib, cfg), cfg.name)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("nb,heads,h_kv,topk,window,with_counts,channels", [
+    (64, 4, 2, 7, 192, False, False),    # 256 (block, head) pairs: the most that get a workgroup each
+    (65, 4, 4, 4, 64, True, False),      # 260: two to a workgroup, the last one alone (d = 128: the general kernel)
+    (128, 4, 1, 9, 320, False, True),    # 512: the most that go two to a workgroup
+    (171, 3, 3, 6, 130, False, False),   # 513: the general kernel, an odd number of blocks
+    (6, 86, 1, 3, 66, True, False),      # 516, less than a tile of pooled pairs
+    (33, 2, 1, 90, 2, True, True),       # nearly all teams on a long routing row, the window one or two tiles
+    (40, 1, 1, 1, 4096, False, False),   # nearly all teams on the window
+    (250, 1, 1, 2, 64, False, False),    # nearly all teams on the pooled pairs
+    (2, 1, 1, 2, 2, False, False),       # more teams than tiles
+])
+def test_forward_few_and_many_query_blocks(B, oracle_lib, d, nb, heads, h_kv, topk, window, with_counts, channels):
+    """Both sides of the numbers of query blocks at which workgroups change: teams that share a branch's tiles, teams and
+    whole branches without any, routing rows of every length."""
+    cfg = I.small_config(name=f"f-teams-d{d}-nb{nb}-h{heads}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=heads, d=d,
+                         topk=topk, window=window, seed=nb, h_kv=h_kv, gate_channels=channels)
+    assert cfg.nb == nb
+    rng = np.random.default_rng(nb)
+    idx = np.full((nb, topk), -1, dtype=np.int32)
+    for r in range(nb):
+        n = min((0, 1, topk // 2, topk)[r % 4], nb)
+        idx[r, np.sort(rng.choice(topk, size=n, replace=False))] = rng.choice(nb, size=n, replace=False)
+    _log(f"[forward] {cfg.name}")
+    cnt = _block_counts(cfg, 12) if with_counts else None
+    _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
