@@ -453,7 +453,6 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
 // lanes, most lanes with nothing of their own.  Bound by instructions issued (the vector pipe is busy all the time), as
 // that one is, with a fifth of them per query: what several queries have in common is done once.
 // 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query.
-// 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query.
 constexpr int kManyQueries = 16;
 constexpr int kNearList = 128, kNearFrom = 48;  // listed blocks of a query, the largest volume budget that a list is made for
 constexpr int kCommonList = 256, kCommonFrom = 256;  // listed blocks of a workgroup, the fewest blocks it is made from
