@@ -19,6 +19,8 @@
 //                    longest walks first -- accumulates dK^T and dV^T in registers, adds
 //                    the pooled gradients / 64.  Long walks, and the heads of a group, are dealt to several
 //                    workgroups, whose sums sum_walks adds in order before finishing the rows.
+// Small problems go through three launches instead (bwd_prepare_small, bwd_walks_small, sum_walks): their walks run beside each
+// other, and all sums of token keys meet the pooled gradients in the last one.
 // Every operand tile is a "tile image" (see forward.hip): MFMA A-operand fragments in row order
 // (rows permuted so that an accumulator is directly the B operand of the next contraction); the
 // fragments of the transposed tile are read out of the same bytes in LDS (see mfma_tr).  The
@@ -273,17 +275,15 @@ struct PrepGeo {
     static constexpr int THREADS = HB * 32 * CH;
 };
 template <int D>
-__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
+using PrepStage = uint4[3][PrepGeo<D>::HB * PrepGeo<D>::CH * 33];
+template <int D>
+__device__ __forceinline__ void prep_rows(const BwdArgs &a, PrepStage<D> &stage, int64_t wg) {
     using P = PrepGeo<D>;
     constexpr int CH = P::CH, PITCH = 33;  // LDS slots of 16 bytes per chunk column
-    __shared__ uint4 stage[3][P::HB * CH * PITCH];
-    // (the counters of the reverse lists, which the next kernel increments: there are more threads than blocks)
-    const int64_t gid = (int64_t)blockIdx.x * P::THREADS + threadIdx.x;
-    if (gid < a.nb) a.rev_cnt[gid] = 0;
     const int c = threadIdx.x % CH, r = (threadIdx.x / CH) % 32, hb = threadIdx.x / (CH * 32);
     const int heads_x = (a.h + P::HB - 1) / P::HB;
-    const int64_t tile = blockIdx.x / heads_x;
-    const int head0 = (int)(blockIdx.x % heads_x) * P::HB;
+    const int64_t tile = wg / heads_x;
+    const int head0 = (int)(wg % heads_x) * P::HB;
     const bool active = head0 + hb < a.h;  // (whole groups of CH lanes)
     const int head = active ? head0 + hb : head0;
     const int64_t row = tile * 32 + r;
@@ -352,6 +352,14 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
     for (int b = 0; b < 3; ++b)
         if (b == 0 || a.gate_channels) *reinterpret_cast<uint4 *>(const_cast<char *>(a.img_do[b]) + dst) = stage[b][src];
 }
+template <int D>
+__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
+    __shared__ PrepStage<D> stage;
+    // (the counters of the reverse lists, which the next kernel increments: there are more threads than blocks)
+    const int64_t gid = (int64_t)blockIdx.x * PrepGeo<D>::THREADS + threadIdx.x;
+    if (gid < a.nb) a.rev_cnt[gid] = 0;
+    prep_rows<D>(a, stage, blockIdx.x);
+}
 
 // ---------------------------------------------------------------------------------------------
 // Tile images of q, k, v, kc and vc in one launch (latency and launches are what a small problem pays for; a large one
@@ -364,18 +372,10 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
 // three workgroups per block and head (179 M tokens, 2 heads of 32) exceed.
 constexpr int64_t kPackMaxGrid = 1 << 23;  // workgroups in the first direction
 template <int D>
-__global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, int64_t n_wg) {
-    constexpr int CH = D / 8, PITCH = D + 16, IMG = BGeo<D>::IMG;  // (pitch: 16-byte aligned, chunks of a row spread over the banks)
-    __shared__ __attribute__((aligned(16))) uint16_t rows[64][PITCH];
-    const int64_t wg = (int64_t)blockIdx.y * kPackMaxGrid + blockIdx.x;
-    if (wg >= n_wg) {
-        const int64_t e = (wg - n_wg) * 256 + threadIdx.x;
-        if (e < (int64_t)a.nb * a.topk) {
-            const int v = a.idx[e];
-            if (v >= 0 && v < a.nb) atomicAdd(&a.rev_cnt[v], 1);
-        }
-        return;
-    }
+using PackStage = uint16_t[64][D + 16];  // (pitch: 16-byte aligned, chunks of a row spread over the banks)
+template <int D, int THREADS>
+__device__ __forceinline__ void pack_block(const BwdArgs &a, PackStage<D> &rows, int64_t n_token_wg, int64_t wg) {
+    constexpr int CH = D / 8, IMG = BGeo<D>::IMG;
     const bool pooled = wg >= n_token_wg;
     const int y_n = pooled ? 2 * a.h_kv : a.h + 2 * a.h_kv;
     const int64_t at = pooled ? wg - n_token_wg : wg;
@@ -396,29 +396,44 @@ __global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, 
     }
     const int64_t n_rows = pooled ? a.nbc : a.n, n_tiles = pooled ? (a.nbc + 31) / 32 : a.nt;
     const int n_act = !pooled && a.count != nullptr ? a.count[blk] : 64;
-    constexpr int NIT = 64 * CH / 256;
+    constexpr int NIT = 64 * CH / THREADS;
     uint4 in[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int e = threadIdx.x + 256 * it, t = e / CH, cc = e % CH;
+        const int e = threadIdx.x + THREADS * it, t = e / CH, cc = e % CH;
         const int64_t row = blk * 64 + t;
         in[it] = row < n_rows && t < n_act ? *reinterpret_cast<const uint4 *>(src + (row * h + head) * D + cc * 8)
                                            : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int e = threadIdx.x + 256 * it;
+        const int e = threadIdx.x + THREADS * it;
         *reinterpret_cast<uint4 *>(&rows[e / CH][(e % CH) * 8]) = in[it];
     }
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int e = threadIdx.x + 256 * it, half = e / (32 * CH), q = e % (32 * CH), cc = q / 32, rr = q % 32;
+        const int e = threadIdx.x + THREADS * it, half = e / (32 * CH), q = e % (32 * CH), cc = q / 32, rr = q % 32;
         const int64_t tile = blk * 2 + half;
         if (tile < n_tiles)
             *reinterpret_cast<uint4 *>(const_cast<char *>(img) + (tile * h + head) * IMG + q * 16) =
                 *reinterpret_cast<const uint4 *>(&rows[32 * half + perm32(rr ^ ((cc & 1) << 2))][cc * 8]);
     }
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void pack_rows(BwdArgs a, int64_t n_token_wg, int64_t n_wg) {
+    __shared__ __attribute__((aligned(16))) PackStage<D> rows;
+    const int64_t wg = (int64_t)blockIdx.y * kPackMaxGrid + blockIdx.x;
+    if (wg >= n_wg) {
+        const int64_t e = (wg - n_wg) * 256 + threadIdx.x;
+        if (e < (int64_t)a.nb * a.topk) {
+            const int v = a.idx[e];
+            if (v >= 0 && v < a.nb) atomicAdd(&a.rev_cnt[v], 1);
+        }
+        return;
+    }
+    pack_block<D, 256>(a, rows, n_token_wg, wg);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -610,6 +625,87 @@ __global__ void rev_sort_serial(BwdArgs a) {
     }
 }
 
+// Everything that the walks of a small problem need, in one launch: gradient rows and tables (prep_rows), tile images (pack_block)
+// and, one workgroup per key block, the reverse list, its place and the tasks of the block.  As five launches that is
+// 6 + 5 + 7 + 4 + 4 us and the gaps between them for 6 K tokens of 4 heads of 64, most of them with a few workgroups.
+// A workgroup counts all entries of the table by itself (in LDS), which gives it the lists and tasks ahead of its own without
+// another launch, then writes its list by going through the table once more: ascending, and the same in every run, as it
+// is.  The tasks are in the order of the blocks: there are few enough to start together.
+constexpr int kSmallBlocks = 640, kSmallEntries = 16384;  // the most blocks and table entries: two passes of 64 steps a workgroup
+template <int D>
+__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare_small(BwdArgs a, int64_t n_prep, int64_t n_token_wg, int64_t n_pack) {
+    constexpr int THREADS = PrepGeo<D>::THREADS, WAVES = THREADS / 64;
+    __shared__ union {
+        PrepStage<D> prep;
+        __attribute__((aligned(16))) PackStage<D> pack;
+        struct {
+            int count[kSmallBlocks], of_wave[WAVES], before[3][WAVES];
+        } rev;
+    } lds;
+    if (blockIdx.x < n_prep) {
+        prep_rows<D>(a, lds.prep, blockIdx.x);
+        return;
+    }
+    if (blockIdx.x < n_prep + n_pack) {
+        pack_block<D, THREADS>(a, lds.pack, n_token_wg, blockIdx.x - n_prep);
+        return;
+    }
+    const int kb = (int)(blockIdx.x - n_prep - n_pack), t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int n_entries = a.nb * a.topk, per_wave = (n_entries + WAVES - 1) / WAVES;
+    const int e0 = min(wave * per_wave, n_entries), e1 = min(e0 + per_wave, n_entries);
+    for (int b = t; b < a.nb; b += THREADS) lds.rev.count[b] = 0;
+    __syncthreads();
+    int mine = 0;  // entries of this wavefront's part of the table that name kb
+    for (int e = e0 + lane; e - lane < e1; e += 64) {
+        const int v = e < e1 ? a.idx[e] : -1;
+        if (v >= 0 && v < a.nb) atomicAdd(&lds.rev.count[v], 1);
+        mine += __popcll(__ballot(v == kb));
+    }
+    if (lane == 0) lds.rev.of_wave[wave] = mine;
+    __syncthreads();
+    auto walk_of = [&](int b) { return 2 * lds.rev.count[b] + (a.cut_window ? (window_tiles(a, b).n + 1) & ~1 : 0); };
+    auto parts_of = [&](int steps) { return max(1, (steps + a.part_steps - 1) / a.part_steps); };
+    // entries and tasks of the blocks before kb (and, for the last block, of all)
+    int x[2] = {0, 0};
+    for (int b = t; b < kb; b += THREADS) {
+        x[0] += lds.rev.count[b];
+        x[1] += parts_of(walk_of(b));
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        for (int off = 32; off > 0; off >>= 1) x[k] += __shfl_xor(x[k], off);
+        if (lane == 0) lds.rev.before[k][wave] = x[k];
+    }
+    __syncthreads();
+    int ptr = 0, task = 0, at = 0;
+    for (int w = 0; w < WAVES; ++w) {
+        ptr += lds.rev.before[0][w];
+        task += lds.rev.before[1][w];
+        at += w < wave ? lds.rev.of_wave[w] : 0;
+    }
+    const int steps = walk_of(kb), np = parts_of(steps);
+    for (int p = t; p < np; p += THREADS) {
+        a.order[task + p] = kb;
+        a.order_part[task + p] = p;
+    }
+    if (t == 0) {
+        a.walk[kb] = steps;
+        a.slot0[kb] = task;
+        a.rev_ptr[kb] = ptr;
+        if (kb == a.nb - 1) {
+            a.rev_ptr[a.nb] = ptr + lds.rev.count[kb];
+            a.task_n[0] = task + np;
+        }
+    }
+    at += ptr;
+    for (int e = e0 + lane; e - lane < e1; e += 64) {
+        const bool on = e < e1 && a.idx[e] == kb;
+        const unsigned long long m = __ballot(on);
+        if (on) a.rev_idx[at + __popcll(m & ((1ull << lane) - 1ull))] = e / a.topk;
+        at += __popcll(m);
+    }
+}
+
 // Position of the n-th (from 0) set bit of m; 0 <= result <= 63 whatever n is (meaningful for n < popcount(m)).
 __device__ __forceinline__ int nth_set_bit(unsigned long long m, int n) {
     int pos = 0;
@@ -649,20 +745,21 @@ __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, flo
 // ---------------------------------------------------------------------------------------------
 // dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head)
 // WIDE: routing rows of 65..128 entries (two per lane of the list holder instead of one).
+// lds: DQ_LDS bytes.  wg, head: numbers of the workgroup.
+template <int D>
+constexpr int DQ_LDS = kBwdNbuf * 2 * BGeo<D>::ROW;
 template <int D, bool WIDE>
-__global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
-    // (at d = 128 the 256-register budget of two workgroups per SIMD still holds: 64 accumulator registers)
+__device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int head) {
     using G = BGeo<D>;
     constexpr int NS = G::NS, ND = G::ND;
     constexpr int TILE = 2 * G::ROW;     // K rows | V rows (K^T is read out of the K rows, see mfma_tr)
     constexpr int NBUF = kBwdNbuf;  // tile buffers: copies run NBUF - 1 tiles ahead
     static_assert((G::ROW / 1024) % 2 == 0, "");
     static_assert(2 * 32 * G::OUT_ROW <= NBUF * TILE, "output staging fits in the tile buffers");
-    __shared__ __attribute__((aligned(1024))) char lds[NBUF * TILE];
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD a contiguous range of
     // blocks so that neighbouring blocks (overlapping windows, similar routed sets) share its L2
     const int per_xcd = (a.nb + 7) / 8;
-    const int qb = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), head = blockIdx.y;
+    const int qb = (wg & 7) * per_xcd + (wg >> 3);
     if (qb >= a.nb) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -939,34 +1036,42 @@ __global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
         for (int i = 0; i < 16; ++i) x[dt][i] = acc[dt][i] * a.scale;
     store_rows_transposed<D>(x, lds + wave * 32 * G::OUT_ROW, a.dq + (row0 * a.h + head) * D, (int64_t)a.h * D, lane);
 }
+template <int D, bool WIDE>
+__global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
+    // (at d = 128 the 256-register budget of two workgroups per SIMD still holds: 64 accumulator registers)
+    __shared__ __attribute__((aligned(1024))) char lds[DQ_LDS<D>];
+    dq_walk<D, WIDE>(a, lds, blockIdx.x, blockIdx.y);
+}
 
 // ---------------------------------------------------------------------------------------------
 // dK, dV: one workgroup (2 wavefronts x 32 keys) per (key block, head[, query range])
 // blockIdx.y is the key/value head; the query tiles of each of its `group` query heads are walked in turn.
 // (d = 128: the two [128 x 32] accumulator sets alone take 128 registers, so one workgroup per SIMD.)
-template <int D, int MODE>
-__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArgs a) {
+// SUMS (MODE 0): every walk leaves fp32 sums for a last pass, which is also where the pooled gradients come in.
+// lds: DKV_LDS bytes.  wg, head, z: numbers of the workgroup.
+template <int D>
+constexpr int DKV_LDS = kBwdDkvNbuf * (2 * BGeo<D>::ROW + 1024);
+template <int D, int MODE, bool SUMS = false>
+__device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, int head, int z) {
     using G = BGeo<D>;
     constexpr int NS = G::NS, ND = G::ND;
     constexpr int AUX = 2 * G::ROW;          // Q rows | dO rows | table (64 floats); Q^T and dO^T: see mfma_tr
     constexpr int TILE = 2 * G::ROW + 1024;  // (table padded to keep the next buffer aligned)
     static_assert(2 * 32 * G::OUT_ROW <= kBwdDkvNbuf * TILE, "output staging fits in the tile buffers");
-    extern __shared__ __attribute__((aligned(1024))) char lds[];  // kBwdDkvNbuf * TILE bytes
     const int n_kb = MODE == 0 ? a.nb : a.nbp / 64;
     const int per_xcd = (n_kb + 7) / 8;
-    const int head = blockIdx.y;
     int kb;
     int part = 0;  // of the key block's walk
     if (MODE == 0) {  // token keys: longest walk first (see rev_scan_order)
-        if ((int)blockIdx.x >= a.task_n[0]) return;
-        kb = a.order[blockIdx.x];
-        part = a.order_part[blockIdx.x];
+        if (wg >= a.task_n[0]) return;
+        kb = a.order[wg];
+        part = a.order_part[wg];
     } else {
-        kb = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);  // (see bwd_dq_kernel)
+        kb = (wg & 7) * per_xcd + (wg >> 3);  // (see dq_walk)
         if (kb >= n_kb) return;
     }
     const int walk = MODE == 0 ? a.walk[kb] : 0;
-    const int split = MODE == 1 ? blockIdx.z : 0;
+    const int split = MODE == 1 ? z : 0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, hh = lane >> 5;
@@ -1022,7 +1127,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     // into registers from global memory: the wait for such a load would also wait for every tile copy in flight.
     // the query heads of the group this workgroup walks: all of them, or (token keys, heads dealt to hsplit
     // workgroups) its share
-    const int gh0 = MODE == 0 && a.hsplit > 1 ? (int)blockIdx.z * a.hpw : 0;
+    const int gh0 = MODE == 0 && a.hsplit > 1 ? z * a.hpw : 0;
     const int grp = MODE == 0 && a.hsplit > 1 ? min(a.group, gh0 + a.hpw) - gh0 : a.group;
     constexpr bool VGPR_CHAINS = D == 128;  // (the kernel has one wavefront per SIMD: see mfma_v)
     // the step in its interleaved form (step_interleaved below).  Not at d = 64: there it needs more than the 168
@@ -1334,9 +1439,9 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
         }
     }
 
-    if (MODE == 0 && (a.hsplit > 1 || walk > a.part_steps)) {
+    if (MODE == 0 && (SUMS || a.hsplit > 1 || walk > a.part_steps)) {
         // this workgroup's sums, fp32; the last pass finishes the rows
-        const int64_t slot = (int64_t)blockIdx.z * a.max_slots + a.slot0[kb] + part;
+        const int64_t slot = (int64_t)z * a.max_slots + a.slot0[kb] + part;
         const int64_t o = ((slot * 64 + 32 * wave + r) * a.h_kv + head) * D;
 #pragma unroll
         for (int dt = 0; dt < ND; ++dt)
@@ -1353,6 +1458,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
             }
         return;
     }
+    if (SUMS) return;
     if (MODE == 1) {
         // partial sums of this query range: [split][pooled key][head][channel] fp32
         const int64_t o = (((int64_t)split * a.nbp + key) * a.h_kv + head) * D;
@@ -1397,16 +1503,50 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArg
     }
 }
 
+template <int D, int MODE>
+__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    dkv_walk<D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+// The three kinds of walks of a small problem in one launch: none of them fills the chip, and none needs another's results (the
+// gradients of the pooled pairs meet those of the token keys in finish_small).  Workgroups: token keys first, dQ, pooled keys; each
+// kind's number is a multiple of 8 (XCDs).
+template <int D, bool WIDE>
+__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdArgs a, int n_tasks, int n_dkv, int n_dq_x, int n_dq, int n_pooled_x) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    // (divided in vector registers: readfirstlane tells the compiler that the numbers are uniform all the same)
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    int wg = blockIdx.x;
+    if (wg < n_dkv) {
+        const int y = uniform(wg / n_tasks), z = uniform(y / a.h_kv);
+        if (z >= a.hsplit) return;  // (the number was rounded up to eight)
+        dkv_walk<D, 0, true>(a, lds, wg - y * n_tasks, y - z * a.h_kv, z);
+        return;
+    }
+    wg -= n_dkv;
+    if (wg < n_dq) {
+        const int y = uniform(wg / n_dq_x);
+        dq_walk<D, WIDE>(a, lds, wg - y * n_dq_x, y);
+        return;
+    }
+    wg -= n_dq;
+    const int y = uniform(wg / n_pooled_x), z = uniform(y / a.h_kv);
+    dkv_walk<D, 1>(a, lds, wg - y * n_pooled_x, y - z * a.h_kv, z);
+}
+
 // The rows of the key blocks whose walks were dealt out: the sums of the parts of each head range, added in order, then
 // what the token-key kernel does at the end of a walk of its own (pooled gradient, scale, rounding).  One workgroup per
 // (block, key/value head, 256 groups of four channels of a token), one such group per thread, four sums of each of dk and dv in flight:
 // bound by memory at size (196 K tokens, 2 key/value heads of 32, 8 ranges: 805 MB of sums), by its chain of loads
 // below.
-template <int D>
-__global__ __launch_bounds__(256) void sum_walks(BwdArgs a) {
+// SMALL (behind bwd_walks_small): the rows of all blocks; the pooled gradient is still in n_split parts, which a workgroup adds up first,
+// 256 / (D / 2) threads to a group of four channels.
+template <int D, bool SMALL>
+__global__ __launch_bounds__(256) void sum_walks(BwdArgs a, int n_split) {
     const int head = blockIdx.y;
     int kb = blockIdx.x;
-    if (a.hsplit == 1) {  // only the blocks whose walk was cut
+    if (!SMALL && a.hsplit == 1) {  // only the blocks whose walk was cut
         if (kb >= a.task_n[1]) return;
         kb = a.split_list[kb];
     }
@@ -1419,8 +1559,29 @@ __global__ __launch_bounds__(256) void sum_walks(BwdArgs a) {
     const int row = e / (D / 4), c = 4 * (e % (D / 4));
     const int64_t in_slot = ((int64_t)row * a.h_kv + head) * D + c;
     const int64_t o_pair = ((int64_t)pair * a.h_kv + head) * D + c;
-    const f32x4 pk = *reinterpret_cast<const f32x4 *>(a.part_k + o_pair);
-    const f32x4 pv = *reinterpret_cast<const f32x4 *>(a.part_v + o_pair);
+    f32x4 pk, pv;
+    if constexpr (SMALL) {
+        constexpr int COLS = D / 2, GROUPS = 256 / COLS;  // columns of four channels: of dk, then of dv
+        __shared__ f32x4 parts[GROUPS][COLS];
+        const int col = threadIdx.x % COLS, g = threadIdx.x / COLS;
+        const float *from = (col < D / 4 ? a.part_k : a.part_v) + ((int64_t)pair * a.h_kv + head) * D + 4 * (col % (D / 4));
+        const int64_t per_split = (int64_t)a.nbp * a.h_kv * D;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int sp = g; sp < n_split; sp += GROUPS) sum += *reinterpret_cast<const f32x4 *>(from + sp * per_split);
+        parts[g][col] = sum;
+        __syncthreads();
+        pk = parts[0][c / 4];
+        pv = parts[0][D / 4 + c / 4];
+#pragma unroll 4
+        for (int j = 1; j < GROUPS; ++j) {
+            pk += parts[j][c / 4];
+            pv += parts[j][D / 4 + c / 4];
+        }
+    } else {
+        pk = *reinterpret_cast<const f32x4 *>(a.part_k + o_pair);
+        pv = *reinterpret_cast<const f32x4 *>(a.part_v + o_pair);
+    }
     f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
     for (int i = 0; i < n_sums; i += 4) {
         f32x4 xk[4], xv[4];
@@ -1452,9 +1613,24 @@ __global__ __launch_bounds__(256) void sum_walks(BwdArgs a) {
 // the shortest part a token-key walk is cut into, in query tiles
 constexpr int kMinPart = 16;
 
+// Whether a backward goes through the launches of small problems.  They save eight of eleven launches and the ends of three
+// kernels; they cost fp32 sums of every walk, walks that do not start in order of length and, at d = 128, dQ walks with one
+// wavefront per SIMD.  Backward, general / small (us), blocks x heads (on key/value heads):
+//   d = 32   96 x 4 95 / 51, 192 x 8 174 / 130, 548 x 4 353 / 311, 337 x 8 (2) 355 / 301, 160 x 32 (16) 400 / 343; 896 x 8 777 / 809,
+//            512 x 16 752 / 776
+//   d = 64   96 x 4 119 / 65, 192 x 8 260 / 224, 548 x 4 533 / 507, 337 x 8 (2) 525 / 485, 160 x 32 (16) 662 / 614; 896 x 2 410 / 420,
+//            512 x 16 1249 / 1323
+//   d = 128  96 x 4 181 / 135, 132 x 1 134 / 93, 192 x 6 430 / 402; 192 x 8 425 / 431, 512 x 2 404 / 434, 160 x 32 (2) 1995 / 2098
+bool small_backward(const Shape &s) {
+    const int64_t entries = (int64_t)s.nb * s.topk;
+    if (s.topk <= 0 || entries > kSmallEntries || s.nb > kSmallBlocks) return false;
+    return s.d == 128 ? s.nb <= 256 && s.nb * s.h <= 1280 : s.nb * s.h_kv <= 3072;
+}
+
 struct WsLayout {
     size_t img_q, img_do[3], img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
     int n_split, nbp, tiles_per_split, hsplit, hpw, part_steps, max_tasks, max_slots, max_split;
+    bool small;  // bwd_prepare_small, bwd_walks_small
     size_t hpart_k, hpart_v, order, order_part, slot0, split_list, task_n, walk, gtab;
 };
 
@@ -1484,6 +1660,7 @@ WsLayout ws_layout(const Shape &s) {
     w.aux = take((size_t)3 * nt * s.h * 64 * 4);
     // pooled keys: enough query ranges to fill the chip
     w.nbp = (s.nbc + 63) / 64 * 64;
+    w.small = small_backward(s);
     const int wgs = (w.nbp / 64) * s.h_kv;
     // The query tiles are cut into n ranges, one workgroup per (64 pooled keys, key/value head, range), all equally
     // long.  The chip runs `slots` of them at a time (256 CUs x the workgroups per CU that the kernel's registers
@@ -1545,7 +1722,7 @@ WsLayout ws_layout(const Shape &s) {
             const int64_t more = steps / len;
             w.max_split = (int)(more < s.nb ? more : s.nb);
             w.max_tasks = (int)(s.nb + more);
-            w.max_slots = w.hsplit > 1 ? w.max_tasks : (int)(w.max_split + more);
+            w.max_slots = w.hsplit > 1 || w.small ? w.max_tasks : (int)(w.max_split + more);
             if ((double)w.hsplit * w.max_slots * 64 * s.h_kv * s.d * 8 <= 2147483648.0) break;
         }
     }
@@ -1570,18 +1747,36 @@ WsLayout ws_layout(const Shape &s) {
 template <int D>
 lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
-    using G = BGeo<D>;
-    constexpr int DKV_LDS = kBwdDkvNbuf * (2 * G::ROW + 1024);
-    // (set on every call: cheap, and right whichever device is current and whichever thread calls)
-    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 0>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
-    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS));
-    if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-    hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)(a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB))),
-                       dim3(PrepGeo<D>::THREADS), 0, st, a);
-    LSRM_HIP_CHECK(hipGetLastError());
+    const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
+    if (w.small) {
+        if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
+        hipLaunchKernelGGL(bwd_prepare_small<D>, dim3((unsigned)(n_prep + n_wg + s.nb)), dim3(PrepGeo<D>::THREADS), 0, st, a, n_prep,
+                           n_token_wg, n_wg);
+        LSRM_HIP_CHECK(hipGetLastError());
+        auto eights = [](int64_t x) { return (x + 7) / 8 * 8; };
+        const int n_dq_x = (int)eights(s.nb), n_pooled_x = (int)eights(w.nbp / 64);
+        const int64_t n_dkv = eights((int64_t)w.max_tasks * s.h_kv * a.hsplit), n_dq = (int64_t)n_dq_x * s.h;
+        const int64_t n_walks = n_dkv + n_dq + (int64_t)n_pooled_x * s.h_kv * w.n_split;
+        constexpr int LDS = DKV_LDS<D> > DQ_LDS<D> ? DKV_LDS<D> : DQ_LDS<D>;
+        auto walks = s.topk > 64 ? &bwd_walks_small<D, true> : &bwd_walks_small<D, false>;
+        // (set on every call: cheap, and right whichever device is current and whichever thread calls)
+        LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(walks), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
+        hipLaunchKernelGGL(walks, dim3((unsigned)n_walks), dim3(128), LDS, st, a, w.max_tasks, (int)n_dkv, n_dq_x, (int)n_dq,
+                           n_pooled_x);
+        LSRM_HIP_CHECK(hipGetLastError());
+        hipLaunchKernelGGL((sum_walks<D, true>), dim3(s.nb, s.h_kv, D / 16), dim3(256), 0, st, a, w.n_split);
+        LSRM_HIP_CHECK(hipGetLastError());
+        if (ev_stop != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_stop, st));
+        return LSRM_OK;
+    }
+    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 0>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
+    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
+    if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
+    hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
+    LSRM_HIP_CHECK(hipGetLastError());
     const int64_t n_pack = n_wg + ((int64_t)s.nb * s.topk + 255) / 256;
     const dim3 pack_grid((unsigned)(n_pack < kPackMaxGrid ? n_pack : kPackMaxGrid),
                          (unsigned)((n_pack + kPackMaxGrid - 1) / kPackMaxGrid));
@@ -1605,7 +1800,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     else
         hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / 64 + 7) / 8 * 8, s.h_kv, w.n_split), dim3(128), DKV_LDS, st,
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / 64 + 7) / 8 * 8, s.h_kv, w.n_split), dim3(128), DKV_LDS<D>, st,
                        a);
     LSRM_HIP_CHECK(hipGetLastError());
     if (w.n_split > 1) {
@@ -1614,12 +1809,12 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                            w.n_split, per_split);
         LSRM_HIP_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), DKV_LDS, st, a);
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), DKV_LDS<D>, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     // add up the sums of walks that were dealt out, in order, and finish their rows
     const int n_sum_blocks = a.hsplit > 1 ? s.nb : w.max_split;
     if (n_sum_blocks > 0) {
-        hipLaunchKernelGGL(sum_walks<D>, dim3(n_sum_blocks, s.h_kv, D / 16), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((sum_walks<D, false>), dim3(n_sum_blocks, s.h_kv, D / 16), dim3(256), 0, st, a, w.n_split);
         LSRM_HIP_CHECK(hipGetLastError());
     }
     if (ev_stop != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_stop, st));

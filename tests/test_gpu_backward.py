@@ -1,6 +1,7 @@
 """GPU parity of lsrm_nsa_backward against the CPU oracle's analytic gradients, element by
 element on small cases and on a sample of blocks and heads at the full size of config 5.
 Tolerance as for the forward: max-abs <= 2e-2 and relative L2 <= 5e-3 per gradient tensor."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -375,3 +376,28 @@ def test_backward_of_more_tiles_than_one_grid_direction_holds(B):
     del branches, ones, gates, lse, dq, dv, ws, rest, last
     torch.cuda.empty_cache()
     assert found == [0.0, 0.0, 1.0, 1.0, 0.5, 0.5]
+
+
+@pytest.mark.parametrize("d,heads,h_kv,n_blocks,channels", [(64, 2, 2, 148, False), (32, 3, 1, 133, True), (128, 1, 1, 140, False)])
+def test_backward_same_problem_on_both_sides_of_the_small_ones(B, oracle_lib, d, heads, h_kv, n_blocks, channels):
+    """A table of few entries goes through the joint launches of small problems, the same table with columns of holes up to more
+    than 16384 entries through the general ones: both against the oracle.  Popular blocks (walks of many parts), blocks
+    that nobody lists, a block listed twice in a row, rows of holes."""
+    topk, wide = 4, 127
+    cfg = I.small_config(name=f"b-routes-d{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
+                         window=160, seed=77, h_kv=h_kv, gate_channels=channels)
+    assert cfg.nb == n_blocks and n_blocks * topk <= 16384 < n_blocks * wide
+    rng = np.random.default_rng(6)
+    idx = np.stack([rng.choice(cfg.nb // 2, size=topk, replace=False) for _ in range(cfg.nb)]).astype(np.int32)
+    idx[:, 0] = 5          # every row: a walk of many parts
+    idx[::3, 1] = 5        # and twice in some
+    idx[1::4, 2:] = -1
+    idx[7] = -1
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    ref = oracle_lib.nsa_backward(*args)
+    _assert_grads(got, ref, cfg.name + " small")
+    holes = np.full((cfg.nb, wide - topk), -1, dtype=np.int32)
+    padded = dataclasses.replace(cfg, topk=wide)
+    got, _ = _case(B, oracle_lib, padded, idx=np.concatenate([idx[:, :2], holes, idx[:, 2:]], axis=1))
+    _assert_grads(got, ref, cfg.name + " general")
