@@ -1236,11 +1236,10 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
 // bf16: Sec. 3.2, the compressed pair of the block), so that one pass over K and V serves both the pooling and
 // the packing.  A thread sums its rows in fp32 in token order (rows t, t + 2048 / D, ...); the partial sums of
 // the 2048 / D threads that share a channel group are added in thread order; one rounding to bf16.
-template <int D, bool POOL = false>
-__global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
-                                                  char *__restrict__ img, int64_t n_rows, int h, int n_tiles,
-                                                  const int32_t *__restrict__ count, uint16_t *__restrict__ kc = nullptr,
-                                                  uint16_t *__restrict__ vc = nullptr) {
+template <int D, bool POOL>
+__device__ __forceinline__ void pack_block(const int64_t blk, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+                                           char *__restrict__ img, int64_t n_rows, int h, int n_tiles,
+                                           const int32_t *__restrict__ count, uint16_t *__restrict__ kc, uint16_t *__restrict__ vc) {
     constexpr int K_BYTES = 32 * D * 2, TILE = K_BYTES + D * 64;
     constexpr int CH = D / 8;  // 16-byte chunks per row
     // Both tensors' rows of the block are staged in LDS, so that the images are written in image order (a wavefront
@@ -1251,7 +1250,6 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
     __shared__ __attribute__((aligned(16))) uint16_t kt[64][PITCH];
     __shared__ __attribute__((aligned(16))) uint16_t vt[64][PITCH];
     __shared__ float psum[POOL ? 2 : 1][POOL ? 256 / CH : 1][POOL ? D + 1 : 1];  // [k, v][thread group][channel]
-    const int64_t blk = blockIdx.x;
     const int head = blockIdx.y;
     const int n_act = count != nullptr ? count[blk] : 64;
     float ak[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, av[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1346,6 +1344,24 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
             make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
 }
+template <int D, bool POOL = false>
+__global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+                                                  char *__restrict__ img, int64_t n_rows, int h, int n_tiles,
+                                                  const int32_t *__restrict__ count, uint16_t *__restrict__ kc = nullptr,
+                                                  uint16_t *__restrict__ vc = nullptr) {
+    pack_block<D, POOL>(blockIdx.x, k, v, img, n_rows, h, n_tiles, count, kc, vc);
+}
+// Keys and values and the pooled pairs in one launch: the workgroups behind the nb blocks take the pairs, nbc of them.
+template <int D>
+__global__ __launch_bounds__(256) void pack_both(int nb, int nbc, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+                                                 char *__restrict__ img, const uint16_t *__restrict__ kc,
+                                                 const uint16_t *__restrict__ vc, char *__restrict__ img_c, int h,
+                                                 const int32_t *__restrict__ count) {
+    const bool pairs = (int)blockIdx.x >= nb;
+    pack_block<D, false>(pairs ? blockIdx.x - nb : blockIdx.x, pairs ? kc : k, pairs ? vc : v, pairs ? img_c : img,
+                         pairs ? nbc : (int64_t)nb * kBlock, h, pairs ? (nbc + 31) / 32 : 2 * nb, pairs ? nullptr : count, nullptr,
+                         nullptr);
+}
 
 struct WsLayout {
     size_t kv, kvc, gsum, gtab, total;
@@ -1381,13 +1397,13 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
         if (rc != LSRM_OK) return rc;
         a.blk_seg = gt.blk_seg;
     }
-    if (!s.kv_packed) {
-        hipLaunchKernelGGL((pack_tiles<D>), dim3(s.nb, s.h_kv), dim3(256), 0, st, d_k, d_v, ws + w.kv, s.n, s.h_kv,
-                           2 * s.nb, a.count);
-        LSRM_HIP_CHECK(hipGetLastError());
-    }
-    hipLaunchKernelGGL((pack_tiles<D>), dim3((s.nbc + 63) / 64, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
-                       (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
+    const int pair_blocks = (s.nbc + 63) / 64;
+    if (!s.kv_packed)
+        hipLaunchKernelGGL(pack_both<D>, dim3(s.nb + pair_blocks, s.h_kv), dim3(256), 0, st, s.nb, s.nbc, d_k, d_v, ws + w.kv, d_kc,
+                           d_vc, ws + w.kvc, s.h_kv, a.count);
+    else
+        hipLaunchKernelGGL((pack_tiles<D>), dim3(pair_blocks, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
+                           (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
     LSRM_HIP_CHECK(hipGetLastError());
     a.kv = ws + w.kv;
     a.kvc = ws + w.kvc;

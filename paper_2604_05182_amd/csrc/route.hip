@@ -252,10 +252,10 @@ __device__ __forceinline__ int wg_topk(int n_cand, KeyAt key_at, int k, unsigned
 // LDS (the candidate id is the array index), then extracted with wg_topk.  `cache_keys` is false
 // when they do not fit: distances are then recomputed on every scan (same results, slower).
 // Dynamic LDS: [n_cand floats if cache_keys, padded to 8 bytes][4 * topk keys].
-__global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int tg, int topk, int cache_keys,
-                                                   const float2 *__restrict__ uv, int32_t *__restrict__ idx,
-                                                   float *__restrict__ dist2_out) {
-    extern __shared__ unsigned long long lds_base[];
+// obj_uv(m): projection of an object query into view m; tile_uv(b): that of object block b into the view qm of a tile query.
+template <class ObjUv, class TileUv>
+__device__ __forceinline__ void select_row(int nb_obj, int n_views, int tg, int topk, int cache_keys, ObjUv obj_uv, TileUv tile_uv,
+                                           unsigned long long *lds_base, int32_t *__restrict__ idx, float *__restrict__ dist2_out) {
     const int row = blockIdx.x;  // query block
     const int tpv = tg * tg;
     const int n_tiles = n_views * tpv;
@@ -276,9 +276,9 @@ __global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int 
     auto d2_of = [&](int c) {
         if (obj_row) {
             int m = c / tpv, r = c % tpv;
-            return dist2(uv[(size_t)row * n_views + m], r / tg, r % tg);
+            return dist2(obj_uv(m), r / tg, r % tg);
         }
-        return dist2(uv[(size_t)c * n_views + qm], qi, qj);
+        return dist2(tile_uv(c, qm), qi, qj);
     };
     int32_t *idx_row = idx + (size_t)row * topk;
     float *d2_row = dist2_out ? dist2_out + (size_t)row * topk : nullptr;
@@ -299,6 +299,67 @@ __global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int 
         idx_row[k] = -1;
         if (d2_row) d2_row[k] = __builtin_inff();
     }
+}
+
+__global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int tg, int topk, int cache_keys,
+                                                   const float2 *__restrict__ uv, int32_t *__restrict__ idx,
+                                                   float *__restrict__ dist2_out) {
+    extern __shared__ unsigned long long lds_base[];
+    select_row(
+        nb_obj, n_views, tg, topk, cache_keys, [&](int m) { return uv[(size_t)blockIdx.x * n_views + m]; },
+        [&](int b, int m) { return uv[(size_t)b * n_views + m]; }, lds_base, idx, dist2_out);
+}
+
+// The same without project_blocks, for few object blocks: a workgroup works out the projections it needs by itself (an object
+// query's own into every view, a tile query's of all blocks into its view), by the same sums.  A launch less, where that
+// is most of the time: 25 blocks, 2 views 4.8 and 4.4 us and the gap between them -> 6.9 us; with 64 blocks a step of 6 K tokens gained nothing.
+constexpr int kRouteFew = 32, kRouteFewRows = 256;  // object blocks (25 KB of points in LDS); queries, as every tile's reads all points
+__global__ __launch_bounds__(256) void select_topk_few(int nb_obj, int n_views, int tg, int topk, int cache_keys,
+                                                       const float *__restrict__ pos, const lsrm_camera *__restrict__ cams,
+                                                       int32_t *__restrict__ idx, float *__restrict__ dist2_out) {
+    extern __shared__ unsigned long long lds_base[];
+    __shared__ float pts[kRouteFew * kCentPitch], cent[kRouteFew][3];
+    __shared__ float2 uv[kRouteFew];  // of an object query per view (as many as there are threads for, else worked out again)
+    const int row = blockIdx.x, tid = threadIdx.x;
+    const bool obj_row = row < nb_obj;
+    const int b0 = obj_row ? row : 0, n = obj_row ? 1 : nb_obj;
+    constexpr int NIT = kRouteFew * 3 * kBlock / 4 / 256;
+    // (a block's points are 768 bytes: sixteen-byte loads where the whole array allows them)
+    float v[NIT][4];
+    const float *src = pos + (size_t)b0 * kBlock * 3;
+#pragma unroll
+    for (int u = 0; u < NIT; ++u) {
+        const int i = 4 * (u * 256 + tid);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] = i < n * 3 * kBlock ? src[i + j] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < NIT; ++u) {
+        const int i = 4 * (u * 256 + tid), b = i / (3 * kBlock);  // (192 is a multiple of four: one block)
+        if (b < n) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pts[b * kCentPitch + i % (3 * kBlock) + j] = v[u][j];
+        }
+    }
+    __syncthreads();
+    if (tid < 3 * n) {
+        const float *p = pts + tid / 3 * kCentPitch + tid % 3;
+        float s = p[0];
+#pragma unroll 16
+        for (int t = 1; t < kBlock; ++t) s = s + p[3 * t];
+        cent[tid / 3][tid % 3] = s * (1.0f / 64.0f);
+    }
+    __syncthreads();
+    const int qm = obj_row ? 0 : (row - nb_obj) / (tg * tg);
+    if (obj_row ? tid < min(n_views, kRouteFew) : tid < n) {
+        const float *c = cent[obj_row ? 0 : tid];
+        uv[tid] = project(cams[obj_row ? tid : qm], c[0], c[1], c[2]);
+    }
+    __syncthreads();
+    select_row(
+        nb_obj, n_views, tg, topk, cache_keys,
+        [&](int m) { return m < kRouteFew ? uv[m] : project(cams[m], cent[0][0], cent[0][1], cent[0][2]); },
+        [&](int b, int) { return uv[b]; }, lds_base, idx, dist2_out);
 }
 
 // ---------------------------------------------------------------- four selection rules (Sec. 3.3)
@@ -855,7 +916,8 @@ size_t route_ws_bytes(const Shape &s) {
 lsrm_status launch_route(const Shape &s, const float *d_pos, const lsrm_camera *d_cams, int32_t *d_idx,
                          float *d_dist2, void *d_ws, hipStream_t st) {
     float2 *uv = reinterpret_cast<float2 *>(d_ws);
-    if (s.nb_obj > 0 && s.n_views > 0) {
+    const bool few = s.nb_obj > 0 && s.nb_obj <= kRouteFew && s.nb <= kRouteFewRows && s.n_views > 0 && s.topk > 0;
+    if (s.nb_obj > 0 && s.n_views > 0 && !few) {
         const int grid = (s.nb_obj + kCentBlocks - 1) / kCentBlocks;
         hipLaunchKernelGGL(project_blocks, dim3(grid), dim3(256), 0, st, s.nb_obj, s.n_views, d_pos, d_cams, uv);
         LSRM_HIP_CHECK(hipGetLastError());
@@ -865,8 +927,14 @@ lsrm_status launch_route(const Shape &s, const float *d_pos, const lsrm_camera *
         const size_t stage_bytes = 4 * (size_t)s.topk * sizeof(unsigned long long);
         const size_t cache_bytes = (size_t)((max_cand + 1) / 2) * sizeof(unsigned long long);
         // default dynamic-LDS limit; beyond it distances are recomputed
-        const int cache_keys = cache_bytes + stage_bytes <= 60 * 1024 ? 1 : 0;
+        const int cache_keys = cache_bytes + stage_bytes <= (few ? 12 : 60) * 1024 ? 1 : 0;
         const size_t lds = stage_bytes + (cache_keys ? cache_bytes : 0);
+        if (few) {
+            hipLaunchKernelGGL(select_topk_few, dim3(s.nb), dim3(256), lds, st, s.nb_obj, s.n_views, s.grid / 8, s.topk,
+                               cache_keys, d_pos, d_cams, d_idx, d_dist2);
+            LSRM_HIP_CHECK(hipGetLastError());
+            return LSRM_OK;
+        }
         hipLaunchKernelGGL(select_topk, dim3(s.nb), dim3(256), lds, st, s.nb_obj, s.n_views,
                            s.grid / 8, s.topk, cache_keys, uv, d_idx, d_dist2);
         LSRM_HIP_CHECK(hipGetLastError());

@@ -48,6 +48,29 @@ def test_route_bit_exact(B, oracle_lib, cfg):
     assert np.array_equal(d2.view(np.uint32), ref_d2.view(np.uint32))
 
 
+@pytest.mark.parametrize("blocks,views,grid,topk", [(32, 4, 48, 40), (33, 2, 16, 5), (1, 3, 16, 2), (31, 40, 16, 128),
+                                                    (32, 14, 32, 9), (32, 15, 32, 9)])
+def test_route_few_object_blocks(B, oracle_lib, blocks, views, grid, topk):
+    """Both sides of the sizes up to which a query's workgroup works out the projections by itself: 32 object blocks, 256
+    queries; more views than projections are kept of; points that start at any multiple of four bytes."""
+    cfg = I.small_config(name=f"r-few{blocks}", n_obj=64 * blocks, n_views=views, grid=grid, topk=topk, seed=8)
+    _log(f"[route] {cfg.name} nb={cfg.nb}")
+    pos, cams = I.make_points(cfg), I.make_cameras(cfg)
+    ref_idx, ref_d2 = oracle_lib.route(pos, cams, cfg.grid, cfg.topk)
+    import torch
+    p = G.params_for(B, cfg)
+    d_cams = torch.from_numpy(cams).cuda()
+    for shift in (0, 1):
+        held = torch.empty(pos.size + shift, dtype=torch.float32, device="cuda")
+        d_pos = held[shift:].view(pos.shape)
+        d_pos.copy_(torch.from_numpy(pos))
+        idx = torch.full((cfg.nb, cfg.topk), -7, dtype=torch.int32, device="cuda")
+        d2 = torch.full((cfg.nb, cfg.topk), -1.0, dtype=torch.float32, device="cuda")
+        B.lsrm_route_blocks(p, d_pos, d_cams, idx, d2, B.alloc_workspace(p, B.LSRM_WS_ROUTE))
+        assert np.array_equal(idx.cpu().numpy(), ref_idx)
+        assert np.array_equal(d2.cpu().numpy().view(np.uint32), ref_d2.view(np.uint32))
+
+
 def test_route_ties_and_behind_camera(B, oracle_lib):
     cfg = I.small_config(name="r-hand", n_obj=128, n_views=1, grid=16, topk=4)
     pos = np.zeros((128, 3), dtype=np.float32)
@@ -79,6 +102,26 @@ def test_compress(B, oracle_lib, cfg):
     _, _, kc, vc = G.run_compress(B, cfg, k_bits, v_bits)
     for got, bits in ((kc, k_bits), (vc, v_bits)):
         ref = oracle_lib.pool(I.bf16_bits_to_f32(bits))
+        got = G.bf16_host(got)
+        # one rounding to bf16 (relative 2^-9) plus fp32 summation noise
+        assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
+
+
+@pytest.mark.parametrize("n_blocks,heads,d,with_counts", [(1, 1, 32, True), (23, 3, 32, True), (128, 16, 128, False),
+                                                          (129, 16, 128, True), (2049, 1, 32, False)])
+def test_compress_few_and_many_blocks(B, oracle_lib, n_blocks, heads, d, with_counts):
+    """Both sides of 2^15 chunks of 8 channels and of 2048 blocks, rows that are no multiple of 16 chunks."""
+    cfg = I.small_config(name=f"p-few{n_blocks}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, seed=45)
+    assert cfg.nb == n_blocks
+    _log(f"[compress] {cfg.name}")
+    cnt = np.random.default_rng(13).integers(1, 65, size=cfg.nb).astype(np.int32) if with_counts else None
+    _, k_bits, v_bits = I.make_qkv(cfg)
+    if with_counts:
+        k_bits = k_bits.copy()
+        k_bits[(np.arange(cfg.n) % 64) >= np.repeat(cnt, 64)] = 0x7FC0
+    _, _, kc, vc = G.run_compress(B, cfg, k_bits, v_bits, cnt)
+    for got, bits in ((kc, k_bits), (vc, v_bits)):
+        ref = oracle_lib.pool(I.bf16_bits_to_f32(bits), cnt)
         got = G.bf16_host(got)
         # one rounding to bf16 (relative 2^-9) plus fp32 summation noise
         assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
