@@ -19,7 +19,7 @@
 //                    longest walks first -- accumulates dK^T and dV^T in registers, adds
 //                    the pooled gradients / 64.  Long walks, and the heads of a group, are dealt to several
 //                    workgroups, whose sums sum_walks adds in order before finishing the rows.
-// Small problems go through three launches instead (bwd_prepare_small, bwd_walks_small, sum_walks): their walks run beside each
+// Small problems go through three launches instead (bwd_prepare, bwd_walks_small, sum_walks): their walks run beside each
 // other, and all sums of token keys meet the pooled gradients in the last one.
 // Every operand tile is a "tile image" (see forward.hip): MFMA A-operand fragments in row order
 // (rows permuted so that an accumulator is directly the B operand of the next contraction); the
@@ -625,21 +625,24 @@ __global__ void rev_sort_serial(BwdArgs a) {
     }
 }
 
-// Everything that the walks of a small problem need, in one launch: gradient rows and tables (prep_rows), tile images (pack_block)
-// and, one workgroup per key block, the reverse list, its place and the tasks of the block.  As five launches that is
-// 6 + 5 + 7 + 4 + 4 us and the gaps between them for 6 K tokens of 4 heads of 64, most of them with a few workgroups.
-// A workgroup counts all entries of the table by itself (in LDS), which gives it the lists and tasks ahead of its own without
-// another launch, then writes its list by going through the table once more: ascending, and the same in every run, as it
-// is.  The tasks are in the order of the blocks: there are few enough to start together.
-constexpr int kSmallBlocks = 640, kSmallEntries = 16384;  // the most blocks and table entries: two passes of 64 steps a workgroup
+// Everything that the walks need where the routing table is small, in one launch: gradient rows and tables (prep_rows), tile images
+// (pack_block) and, one workgroup per key block, the reverse list, its place and the block's tasks.  As five launches
+// that is 6 + 5 + 7 + 4 + 4 us and the gaps between them for 6 K tokens of 4 heads of 64, most of them with a few workgroups; here 8.7 us.
+// A workgroup counts all entries of the table by itself (in LDS), which tells it the lists, parts and lengths of all other
+// blocks without another launch, then writes its list by going through the table once more: ascending, and the same in every
+// run, as it is.  Eight loads of the table in flight to a wavefront: a pass of 16 K entries is eight round trips.
+// Tasks as rev_scan_order puts them: longest first, whole parts, then the blocks' last parts.  all_slots: sums for every walk
+// (bwd_walks_small), not only for those that are dealt out.
+constexpr int kTableBlocks = 768, kTableEntries = 16384;  // (see small_table)
 template <int D>
-__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare_small(BwdArgs a, int64_t n_prep, int64_t n_token_wg, int64_t n_pack) {
-    constexpr int THREADS = PrepGeo<D>::THREADS, WAVES = THREADS / 64;
+__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare(BwdArgs a, int64_t n_prep, int64_t n_token_wg, int64_t n_pack,
+                                                                    int all_slots) {
+    constexpr int THREADS = PrepGeo<D>::THREADS, WAVES = THREADS / 64, DEEP = 8, SUMS = 6;
     __shared__ union {
         PrepStage<D> prep;
         __attribute__((aligned(16))) PackStage<D> pack;
         struct {
-            int count[kSmallBlocks], of_wave[WAVES], before[3][WAVES];
+            int count[kTableBlocks], of_wave[WAVES], sum[SUMS][WAVES];
         } rev;
     } lds;
     if (blockIdx.x < n_prep) {
@@ -653,57 +656,76 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare_small(BwdArgs
     const int kb = (int)(blockIdx.x - n_prep - n_pack), t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int n_entries = a.nb * a.topk, per_wave = (n_entries + WAVES - 1) / WAVES;
     const int e0 = min(wave * per_wave, n_entries), e1 = min(e0 + per_wave, n_entries);
+    // the entries [e0, e1) of this wavefront, 64 at a time: take(first entry, this lane's, -1 past the end)
+    auto each = [&](auto take) {
+        for (int e = e0; e < e1; e += 64 * DEEP) {
+            int v[DEEP];
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j) v[j] = e + 64 * j + lane < e1 ? a.idx[e + 64 * j + lane] : -1;
+#pragma unroll
+            for (int j = 0; j < DEEP; ++j) take(e + 64 * j, v[j]);
+        }
+    };
     for (int b = t; b < a.nb; b += THREADS) lds.rev.count[b] = 0;
     __syncthreads();
     int mine = 0;  // entries of this wavefront's part of the table that name kb
-    for (int e = e0 + lane; e - lane < e1; e += 64) {
-        const int v = e < e1 ? a.idx[e] : -1;
+    each([&](int, int v) {
         if (v >= 0 && v < a.nb) atomicAdd(&lds.rev.count[v], 1);
         mine += __popcll(__ballot(v == kb));
-    }
+    });
     if (lane == 0) lds.rev.of_wave[wave] = mine;
     __syncthreads();
     auto walk_of = [&](int b) { return 2 * lds.rev.count[b] + (a.cut_window ? (window_tiles(a, b).n + 1) & ~1 : 0); };
     auto parts_of = [&](int steps) { return max(1, (steps + a.part_steps - 1) / a.part_steps); };
-    // entries and tasks of the blocks before kb (and, for the last block, of all)
-    int x[2] = {0, 0};
-    for (int b = t; b < kb; b += THREADS) {
-        x[0] += lds.rev.count[b];
-        x[1] += parts_of(walk_of(b));
+    const int steps = walk_of(kb), np = parts_of(steps), last = steps - (np - 1) * a.part_steps;
+    // of the blocks before kb: entries, slots of sums, whole parts, cut blocks; of all: whole parts, last parts that go before kb's
+    int x[SUMS] = {0, 0, 0, 0, 0, 0};
+    for (int b = t; b < a.nb; b += THREADS) {
+        const int w = walk_of(b), n = parts_of(w), rest = w - (n - 1) * a.part_steps;
+        const bool before = b < kb;
+        x[0] += before ? lds.rev.count[b] : 0;
+        x[1] += before && (all_slots || a.hsplit > 1 || n > 1) ? n : 0;
+        x[2] += before ? n - 1 : 0;
+        x[3] += before && n > 1 ? 1 : 0;
+        x[4] += n - 1;
+        x[5] += rest > last || (rest == last && before) ? 1 : 0;
     }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < SUMS; ++k) {
         for (int off = 32; off > 0; off >>= 1) x[k] += __shfl_xor(x[k], off);
-        if (lane == 0) lds.rev.before[k][wave] = x[k];
+        if (lane == 0) lds.rev.sum[k][wave] = x[k];
     }
     __syncthreads();
-    int ptr = 0, task = 0, at = 0;
+    int at = 0;
+#pragma unroll
+    for (int k = 0; k < SUMS; ++k) x[k] = 0;
     for (int w = 0; w < WAVES; ++w) {
-        ptr += lds.rev.before[0][w];
-        task += lds.rev.before[1][w];
+#pragma unroll
+        for (int k = 0; k < SUMS; ++k) x[k] += lds.rev.sum[k][w];
         at += w < wave ? lds.rev.of_wave[w] : 0;
     }
-    const int steps = walk_of(kb), np = parts_of(steps);
     for (int p = t; p < np; p += THREADS) {
-        a.order[task + p] = kb;
-        a.order_part[task + p] = p;
+        const int task = p < np - 1 ? x[2] + p : x[4] + x[5];
+        a.order[task] = kb;
+        a.order_part[task] = p;
     }
     if (t == 0) {
         a.walk[kb] = steps;
-        a.slot0[kb] = task;
-        a.rev_ptr[kb] = ptr;
+        a.slot0[kb] = x[1];
+        a.rev_ptr[kb] = x[0];
+        if (np > 1) a.split_list[x[3]] = kb;
         if (kb == a.nb - 1) {
-            a.rev_ptr[a.nb] = ptr + lds.rev.count[kb];
-            a.task_n[0] = task + np;
+            a.rev_ptr[a.nb] = x[0] + lds.rev.count[kb];
+            a.task_n[0] = x[4] + a.nb;
+            a.task_n[1] = x[3] + (np > 1 ? 1 : 0);
         }
     }
-    at += ptr;
-    for (int e = e0 + lane; e - lane < e1; e += 64) {
-        const bool on = e < e1 && a.idx[e] == kb;
-        const unsigned long long m = __ballot(on);
-        if (on) a.rev_idx[at + __popcll(m & ((1ull << lane) - 1ull))] = e / a.topk;
+    at += x[0];
+    each([&](int e, int v) {
+        const unsigned long long m = __ballot(v == kb);
+        if (v == kb) a.rev_idx[at + __popcll(m & ((1ull << lane) - 1ull))] = (e + lane) / a.topk;
         at += __popcll(m);
-    }
+    });
 }
 
 // Position of the n-th (from 0) set bit of m; 0 <= result <= 63 whatever n is (meaningful for n < popcount(m)).
@@ -1613,24 +1635,31 @@ __global__ __launch_bounds__(256) void sum_walks(BwdArgs a, int n_split) {
 // the shortest part a token-key walk is cut into, in query tiles
 constexpr int kMinPart = 16;
 
+// Whether bwd_prepare does what else takes five launches: few enough table entries to be counted by every block's workgroup, and a
+// grid that one direction holds.  Backward, five launches / bwd_prepare (us; blocks x heads, entries): 96 x 4, 768 118 / 99; 192 x 8 of
+// 128, 1536 430 / 412; 337 x 8 (2), 6740 532 / 511; 544 x 32 (2), 16320 3972 / 3935; 896 x 2, 14336 431 / 423; 896 x 8 1327 / 1319; 1020 x 4,
+// 16320 805 / 805; 2024 x 1, 16192 550 / 564.
+bool small_table(const Shape &s) {
+    return s.topk > 0 && s.nb <= kTableBlocks && (int64_t)s.nb * s.topk <= kTableEntries && (int64_t)s.nb * s.h <= 1 << 20;
+}
+
 // Whether a backward goes through the launches of small problems.  They save eight of eleven launches and the ends of three
-// kernels; they cost fp32 sums of every walk, walks that do not start in order of length and, at d = 128, dQ walks with one
+// kernels; they cost fp32 sums of every walk and, at d = 128, dQ walks with one
 // wavefront per SIMD.  Backward, general / small (us), blocks x heads (on key/value heads):
-//   d = 32   96 x 4 95 / 51, 192 x 8 174 / 130, 548 x 4 353 / 311, 337 x 8 (2) 355 / 301, 160 x 32 (16) 400 / 343; 896 x 8 777 / 809,
+//   d = 32   96 x 4 95 / 51, 192 x 8 174 / 130, 548 x 4 353 / 311, 337 x 8 (2) 357 / 296, 160 x 32 (16) 400 / 343; 896 x 8 777 / 809,
 //            512 x 16 752 / 776
-//   d = 64   96 x 4 119 / 65, 192 x 8 260 / 224, 548 x 4 533 / 507, 337 x 8 (2) 525 / 485, 160 x 32 (16) 662 / 614; 896 x 2 410 / 420,
+//   d = 64   96 x 4 119 / 65, 192 x 8 260 / 224, 548 x 4 533 / 507, 337 x 8 (2) 532 / 471, 160 x 32 (16) 662 / 614; 896 x 2 410 / 420,
 //            512 x 16 1249 / 1323
 //   d = 128  96 x 4 181 / 135, 132 x 1 134 / 93, 192 x 6 430 / 402; 192 x 8 425 / 431, 512 x 2 404 / 434, 160 x 32 (2) 1995 / 2098
 bool small_backward(const Shape &s) {
-    const int64_t entries = (int64_t)s.nb * s.topk;
-    if (s.topk <= 0 || entries > kSmallEntries || s.nb > kSmallBlocks) return false;
+    if (!small_table(s) || s.nb > 640 || (int64_t)s.nb * s.h > 1 << 16) return false;
     return s.d == 128 ? s.nb <= 256 && s.nb * s.h <= 1280 : s.nb * s.h_kv <= 3072;
 }
 
 struct WsLayout {
     size_t img_q, img_do[3], img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
     int n_split, nbp, tiles_per_split, hsplit, hpw, part_steps, max_tasks, max_slots, max_split;
-    bool small;  // bwd_prepare_small, bwd_walks_small
+    bool small;  // bwd_walks_small
     size_t hpart_k, hpart_v, order, order_part, slot0, split_list, task_n, walk, gtab;
 };
 
@@ -1749,11 +1778,14 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                               hipEvent_t ev_stop) {
     const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
-    if (w.small) {
-        if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-        hipLaunchKernelGGL(bwd_prepare_small<D>, dim3((unsigned)(n_prep + n_wg + s.nb)), dim3(PrepGeo<D>::THREADS), 0, st, a, n_prep,
-                           n_token_wg, n_wg);
+    const bool table = small_table(s);
+    if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
+    if (table) {
+        hipLaunchKernelGGL(bwd_prepare<D>, dim3((unsigned)(n_prep + n_wg + s.nb)), dim3(PrepGeo<D>::THREADS), 0, st, a, n_prep,
+                           n_token_wg, n_wg, w.small ? 1 : 0);
         LSRM_HIP_CHECK(hipGetLastError());
+    }
+    if (w.small) {
         auto eights = [](int64_t x) { return (x + 7) / 8 * 8; };
         const int n_dq_x = (int)eights(s.nb), n_pooled_x = (int)eights(w.nbp / 64);
         const int64_t n_dkv = eights((int64_t)w.max_tasks * s.h_kv * a.hsplit), n_dq = (int64_t)n_dq_x * s.h;
@@ -1774,26 +1806,27 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                                        hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
-    if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-    hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
-    LSRM_HIP_CHECK(hipGetLastError());
-    const int64_t n_pack = n_wg + ((int64_t)s.nb * s.topk + 255) / 256;
-    const dim3 pack_grid((unsigned)(n_pack < kPackMaxGrid ? n_pack : kPackMaxGrid),
-                         (unsigned)((n_pack + kPackMaxGrid - 1) / kPackMaxGrid));
-    hipLaunchKernelGGL(pack_rows<D>, pack_grid, dim3(256), 0, st, a, n_token_wg, n_wg);
-    LSRM_HIP_CHECK(hipGetLastError());
-    // reverse routing lists
-    hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a);
-    LSRM_HIP_CHECK(hipGetLastError());
-    if (s.topk > 0) {
-        hipLaunchKernelGGL(rev_fill, dim3((s.nb * s.topk + 255) / 256), dim3(256), 0, st, a);
+    if (!table) {
+        hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
         LSRM_HIP_CHECK(hipGetLastError());
-        const size_t bitmap = (size_t)((s.nb + 31) / 32) * 4;
-        if (bitmap <= 48 * 1024)
-            hipLaunchKernelGGL(rev_sort, dim3(s.nb), dim3(64), bitmap, st, a);
-        else
-            hipLaunchKernelGGL(rev_sort_serial, dim3((s.nb + 63) / 64), dim3(64), 0, st, a);
+        const int64_t n_pack = n_wg + ((int64_t)s.nb * s.topk + 255) / 256;
+        const dim3 pack_grid((unsigned)(n_pack < kPackMaxGrid ? n_pack : kPackMaxGrid),
+                             (unsigned)((n_pack + kPackMaxGrid - 1) / kPackMaxGrid));
+        hipLaunchKernelGGL(pack_rows<D>, pack_grid, dim3(256), 0, st, a, n_token_wg, n_wg);
         LSRM_HIP_CHECK(hipGetLastError());
+        // reverse routing lists
+        hipLaunchKernelGGL(rev_scan_order, dim3(1), dim3(1024), 0, st, a);
+        LSRM_HIP_CHECK(hipGetLastError());
+        if (s.topk > 0) {
+            hipLaunchKernelGGL(rev_fill, dim3((s.nb * s.topk + 255) / 256), dim3(256), 0, st, a);
+            LSRM_HIP_CHECK(hipGetLastError());
+            const size_t bitmap = (size_t)((s.nb + 31) / 32) * 4;
+            if (bitmap <= 48 * 1024)
+                hipLaunchKernelGGL(rev_sort, dim3(s.nb), dim3(64), bitmap, st, a);
+            else
+                hipLaunchKernelGGL(rev_sort_serial, dim3((s.nb + 63) / 64), dim3(64), 0, st, a);
+            LSRM_HIP_CHECK(hipGetLastError());
+        }
     }
     if (s.topk > 64)
         hipLaunchKernelGGL((bwd_dq_kernel<D, true>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);

@@ -401,3 +401,27 @@ def test_backward_same_problem_on_both_sides_of_the_small_ones(B, oracle_lib, d,
     padded = dataclasses.replace(cfg, topk=wide)
     got, _ = _case(B, oracle_lib, padded, idx=np.concatenate([idx[:, :2], holes, idx[:, 2:]], axis=1))
     _assert_grads(got, ref, cfg.name + " general")
+
+
+@pytest.mark.parametrize("n_blocks,topk", [(768, 3), (769, 3), (300, 54), (300, 55)])
+def test_backward_preparation_on_both_sides_of_its_sizes(B, oracle_lib, n_blocks, topk):
+    """Up to 768 blocks and 16384 table entries one launch prepares the walks, above that five do (with more pairs of a block
+    and a head than the joint launches of small problems take): a popular block, whose walk has many parts, and
+    rows with holes; sampled against the oracle, and the same twice."""
+    cfg = I.small_config(name=f"b-table{n_blocks}-{topk}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=11, d=32, topk=topk,
+                         window=64, seed=78)
+    assert cfg.nb == n_blocks and cfg.nb * cfg.heads > 3072
+    rng = np.random.default_rng(9)
+    idx = np.full((cfg.nb, topk), -1, dtype=np.int32)
+    idx[:, :3] = rng.integers(0, cfg.nb, size=(cfg.nb, 3))
+    idx[:, topk - 1] = 17
+    idx[::5, 0] = -1
+    qblocks, kblocks, heads = [0, 17, cfg.nb - 2, cfg.nb - 1], [0, 5, 17, cfg.nb - 2, cfg.nb - 1], [0, 10]
+    _log(f"[backward] {cfg.name} nb={cfg.nb} entries={cfg.nb * topk}")
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    ref = oracle_lib.nsa_backward_sampled(*args, qblocks, kblocks, heads)
+    rows_q, rows_k = ((np.asarray(b)[:, None] * 64 + np.arange(64)[None]).reshape(-1) for b in (qblocks, kblocks))
+    _assert_grads((got[0][rows_q][:, heads], got[1][rows_k][:, heads], got[2][rows_k][:, heads]), ref, cfg.name)
+    again, _ = _case(B, oracle_lib, cfg, idx=idx)
+    for x, y in zip(got, again):
+        assert np.array_equal(x, y)
