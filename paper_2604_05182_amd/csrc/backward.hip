@@ -74,7 +74,7 @@ struct BwdArgs {
     int gate_channels;  // gates are [N, 3, H, d]
     const int32_t *count;  // nullable [NB]: active tokens per block; the other slots are neither queries nor keys
     int nt;               // query / key tiles of 32 tokens
-    int nbp, tiles_per_split;
+    int nbp, tiles_per_split, n_split;  // pooled keys, rounded up; the query ranges of their walks
     // Token keys: a key block's walk -- the query tiles of its window, then two per entry of its reverse list -- is dealt to
     // several workgroups where it is long.  With grouped-query heads the query heads of a group go to hsplit
     // workgroups, hpw heads each; and a walk of more than part_steps tiles is cut into parts of that many (cut_window = 0:
@@ -1070,7 +1070,7 @@ __global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
 // blockIdx.y is the key/value head; the query tiles of each of its `group` query heads are walked in turn.
 // (d = 128: the two [128 x 32] accumulator sets alone take 128 registers, so one workgroup per SIMD.)
 // SUMS (MODE 0): every walk leaves fp32 sums for a last pass, which is also where the pooled gradients come in.
-// lds: DKV_LDS bytes.  wg, head, z: numbers of the workgroup.
+// lds: DKV_LDS bytes.  wg: place in the order of tasks, or group of 64 pooled keys; z: head range, or range of query tiles.
 template <int D>
 constexpr int DKV_LDS = kBwdDkvNbuf * (2 * BGeo<D>::ROW + 1024);
 template <int D, int MODE, bool SUMS = false>
@@ -1080,17 +1080,12 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     constexpr int AUX = 2 * G::ROW;          // Q rows | dO rows | table (64 floats); Q^T and dO^T: see mfma_tr
     constexpr int TILE = 2 * G::ROW + 1024;  // (table padded to keep the next buffer aligned)
     static_assert(2 * 32 * G::OUT_ROW <= kBwdDkvNbuf * TILE, "output staging fits in the tile buffers");
-    const int n_kb = MODE == 0 ? a.nb : a.nbp / 64;
-    const int per_xcd = (n_kb + 7) / 8;
-    int kb;
+    int kb = wg;
     int part = 0;  // of the key block's walk
     if (MODE == 0) {  // token keys: longest walk first (see rev_scan_order)
         if (wg >= a.task_n[0]) return;
         kb = a.order[wg];
         part = a.order_part[wg];
-    } else {
-        kb = (wg & 7) * per_xcd + (wg >> 3);  // (see dq_walk)
-        if (kb >= n_kb) return;
     }
     const int walk = MODE == 0 ? a.walk[kb] : 0;
     const int split = MODE == 1 ? z : 0;
@@ -1525,17 +1520,39 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     }
 }
 
+// Number of a workgroup among the walks of pooled keys -> group of 64 keys, key/value head, range of query tiles; false: none left.
+// Equal shares of all walks for the XCDs, and to each the key groups of one (head, range) beside each other: they read the same
+// query tiles, at the same pace, so that its L2 fetches those about once.  (Dealing the key groups of every (head, range) to
+// the XCDs leaves some with nothing where there are few: of three groups, five of eight.  Backward, that / this, us, blocks x
+// heads: d = 128, 192 x 8 404 / 363, 337 x 8 (2) 974 / 909, 896 x 2 731 / 654, 896 x 8 2549 / 2440, 4096 x 8 22570 / 21930; d = 64, 192 x
+// 8 222 / 206, 896 x 8 1287 / 1224.)
+__device__ bool pooled_walk(const BwdArgs &a, int wg, int *group, int *head, int *z) {
+    const int n_groups = a.nbp / 64, n = n_groups * a.h_kv * a.n_split, item = (wg & 7) * ((n + 7) / 8) + (wg >> 3);
+    if (item >= n) return false;
+    // (divided in vector registers: readfirstlane tells the compiler that the numbers are uniform all the same)
+    const int y = __builtin_amdgcn_readfirstlane(item / n_groups);
+    *z = __builtin_amdgcn_readfirstlane(y / a.h_kv);
+    *head = y - *z * a.h_kv;
+    *group = item - y * n_groups;
+    return true;
+}
+
 template <int D, int MODE>
 __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    dkv_walk<D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+    if constexpr (MODE == 0) {
+        dkv_walk<D, 0>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+    } else {
+        int group, head, z;
+        if (pooled_walk(a, blockIdx.x, &group, &head, &z)) dkv_walk<D, 1>(a, lds, group, head, z);
+    }
 }
 
 // The three kinds of walks of a small problem in one launch: none of them fills the chip, and none needs another's results (the
 // gradients of the pooled pairs meet those of the token keys in finish_small).  Workgroups: token keys first, dQ, pooled keys; each
 // kind's number is a multiple of 8 (XCDs).
 template <int D, bool WIDE>
-__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdArgs a, int n_tasks, int n_dkv, int n_dq_x, int n_dq, int n_pooled_x) {
+__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdArgs a, int n_tasks, int n_dkv, int n_dq_x, int n_dq) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     // (divided in vector registers: readfirstlane tells the compiler that the numbers are uniform all the same)
     auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
@@ -1553,8 +1570,8 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
         return;
     }
     wg -= n_dq;
-    const int y = uniform(wg / n_pooled_x), z = uniform(y / a.h_kv);
-    dkv_walk<D, 1>(a, lds, wg - y * n_pooled_x, y - z * a.h_kv, z);
+    int group, head, z;
+    if (pooled_walk(a, wg, &group, &head, &z)) dkv_walk<D, 1>(a, lds, group, head, z);
 }
 
 // The rows of the key blocks whose walks were dealt out: the sums of the parts of each head range, added in order, then
@@ -1787,15 +1804,14 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     }
     if (w.small) {
         auto eights = [](int64_t x) { return (x + 7) / 8 * 8; };
-        const int n_dq_x = (int)eights(s.nb), n_pooled_x = (int)eights(w.nbp / 64);
+        const int n_dq_x = (int)eights(s.nb);
         const int64_t n_dkv = eights((int64_t)w.max_tasks * s.h_kv * a.hsplit), n_dq = (int64_t)n_dq_x * s.h;
-        const int64_t n_walks = n_dkv + n_dq + (int64_t)n_pooled_x * s.h_kv * w.n_split;
+        const int64_t n_walks = n_dkv + n_dq + eights((int64_t)w.nbp / 64 * s.h_kv * w.n_split);
         constexpr int LDS = DKV_LDS<D> > DQ_LDS<D> ? DKV_LDS<D> : DQ_LDS<D>;
         auto walks = s.topk > 64 ? &bwd_walks_small<D, true> : &bwd_walks_small<D, false>;
         // (set on every call: cheap, and right whichever device is current and whichever thread calls)
         LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(walks), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
-        hipLaunchKernelGGL(walks, dim3((unsigned)n_walks), dim3(128), LDS, st, a, w.max_tasks, (int)n_dkv, n_dq_x, (int)n_dq,
-                           n_pooled_x);
+        hipLaunchKernelGGL(walks, dim3((unsigned)n_walks), dim3(128), LDS, st, a, w.max_tasks, (int)n_dkv, n_dq_x, (int)n_dq);
         LSRM_HIP_CHECK(hipGetLastError());
         hipLaunchKernelGGL((sum_walks<D, true>), dim3(s.nb, s.h_kv, D / 16), dim3(256), 0, st, a, w.n_split);
         LSRM_HIP_CHECK(hipGetLastError());
@@ -1833,7 +1849,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     else
         hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / 64 + 7) / 8 * 8, s.h_kv, w.n_split), dim3(128), DKV_LDS<D>, st,
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / 64 * s.h_kv * w.n_split + 7) / 8 * 8), dim3(128), DKV_LDS<D>, st,
                        a);
     LSRM_HIP_CHECK(hipGetLastError());
     if (w.n_split > 1) {
@@ -1932,6 +1948,7 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.task_n = reinterpret_cast<int32_t *>(ws + w.task_n);
     a.nbp = w.nbp;
     a.tiles_per_split = w.tiles_per_split;
+    a.n_split = w.n_split;
     a.scale = s.scale;
     a.sl2 = s.scale * kLog2e;
     if (s.d == 32) return launch_backward_d<32>(s, a, w, ws, st, ev_start, ev_stop);

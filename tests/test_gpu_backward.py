@@ -425,3 +425,22 @@ def test_backward_preparation_on_both_sides_of_its_sizes(B, oracle_lib, n_blocks
     again, _ = _case(B, oracle_lib, cfg, idx=idx)
     for x, y in zip(got, again):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("d,n_blocks,heads,h_kv", [(128, 64, 21, 3), (128, 65, 21, 3), (128, 128, 21, 7), (128, 129, 11, 11), (128, 193, 7, 7),
+                                                   (128, 65, 3, 3), (64, 300, 11, 11), (32, 129, 26, 13)])
+def test_backward_pooled_keys_at_the_edges_of_their_groups(B, oracle_lib, d, n_blocks, heads, h_kv):
+    """Numbers of pooled keys around those a workgroup takes (64, 128), and of walks that eight does not divide, above the limits of
+    the joint launches and once below: sampled against the oracle, first and last blocks, keys and heads."""
+    cfg = I.small_config(name=f"b-pooled{n_blocks}-{heads}-{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=4,
+                         window=96, seed=79, h_kv=h_kv)
+    assert cfg.nb == n_blocks
+    rng = np.random.default_rng(10)
+    idx = np.stack([rng.choice(cfg.nb, size=4, replace=False) for _ in range(cfg.nb)]).astype(np.int32)
+    blocks, some = sorted({0, 63, min(64, cfg.nb - 1), cfg.nb - 2, cfg.nb - 1}), sorted({0, heads // 2, heads - 1})
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    kv = sorted({h // (heads // h_kv) for h in some})
+    ref = oracle_lib.nsa_backward_sampled(*args, blocks, blocks, some, kv_heads=kv)
+    rows = (np.asarray(blocks)[:, None] * 64 + np.arange(64)[None]).reshape(-1)
+    _assert_grads((got[0][rows][:, some], got[1][rows][:, kv], got[2][rows][:, kv]), ref, cfg.name)
