@@ -126,14 +126,14 @@ __device__ __forceinline__ void mfma_v(f32x16 &d, bf16x8 a, bf16x8 b) {
 }
 __device__ __forceinline__ void mfma_v_settle(f32x16 &d) { asm volatile("s_nop 15\n\ts_nop 7" : "+v"(d)); }
 
-// copies n_kb KB, contiguous on both sides, global -> LDS; the two wavefronts of the workgroup split it
-template <int N_KB>
+// copies n_kb KB, contiguous on both sides, global -> LDS; the WV wavefronts of the workgroup split it
+template <int N_KB, int WV = 2>
 __device__ __forceinline__ void copy_kb(const char *src, char *dst, int wave, uint32_t lane16) {
-    static_assert(N_KB % 2 == 0, "");
+    static_assert(N_KB % WV == 0, "");
     src += wave * 1024;
     dst += wave * 1024;
 #pragma unroll
-    for (int i = 0; i < N_KB; i += 2)
+    for (int i = 0; i < N_KB; i += WV)
         copy_kb_to_lds(src + i * 1024, lane16, dst + i * 1024);
 }
 
@@ -1066,20 +1066,27 @@ __global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// dK, dV: one workgroup (2 wavefronts x 32 keys) per (key block, head[, query range])
-// blockIdx.y is the key/value head; the query tiles of each of its `group` query heads are walked in turn.
-// (d = 128: the two [128 x 32] accumulator sets alone take 128 registers, so one workgroup per SIMD.)
+// dK, dV: one workgroup (WV wavefronts x 32 keys) per (key block or group of pooled keys, key/value head, range of query
+// heads or of query tiles); the query tiles of each of the `group` query heads of a key/value head are walked in turn.
 // SUMS (MODE 0): every walk leaves fp32 sums for a last pass, which is also where the pooled gradients come in.
-// lds: DKV_LDS bytes.  wg: place in the order of tasks, or group of 64 pooled keys; z: head range, or range of query tiles.
-template <int D>
-constexpr int DKV_LDS = kBwdDkvNbuf * (2 * BGeo<D>::ROW + 1024);
-template <int D, int MODE, bool SUMS = false>
+// V_LDS: the value fragments of a wavefront's keys are read from LDS in every step instead of held in 32 registers.  At
+// d = 128, where the two [128 x 32] sets of sums alone take 128, that is what lets two wavefronts share a SIMD (223 registers,
+// in the plain order of a step), each filling the other's waits.  Done for pooled keys, with four wavefronts to a workgroup: they
+// share a tile's copies, and two workgroups' buffers and values fit the LDS of a CU.  Backward before / after, ms, blocks x
+// heads: 512 x 16 2.45 / 2.41, 2560 x 8 10.7 / 10.1, 4096 x 16 (2) 43.9 / 42.2, 6704 x 16 127.9 / 117.7; 192 x 8 0.363 / 0.370
+// (193 to 255 keys are as many steps as 256).  Not done for the token keys: 9 registers more than there are, and the last of
+// these took 121 to 122 ms either way; nor in the joint launch of small problems (192 x 6 305 / 300 us, 132 x 1 61 / 65).
+// lds: DKV_LDS bytes.  wg: place in the order of tasks, or group of 32 * WV pooled keys; z: head range, or range of query tiles.
+template <int D, int WV, bool V_LDS>
+constexpr int DKV_LDS = kBwdDkvNbuf * (2 * BGeo<D>::ROW + 1024) + (V_LDS ? WV * BGeo<D>::ROW : 0);
+template <int D, int MODE, bool SUMS, int WV, bool V_LDS>
 __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, int head, int z) {
     using G = BGeo<D>;
     constexpr int NS = G::NS, ND = G::ND;
     constexpr int AUX = 2 * G::ROW;          // Q rows | dO rows | table (64 floats); Q^T and dO^T: see mfma_tr
     constexpr int TILE = 2 * G::ROW + 1024;  // (table padded to keep the next buffer aligned)
     static_assert(2 * 32 * G::OUT_ROW <= kBwdDkvNbuf * TILE, "output staging fits in the tile buffers");
+    static_assert(MODE == 1 || WV == 2, "a block of token keys");
     int kb = wg;
     int part = 0;  // of the key block's walk
     if (MODE == 0) {  // token keys: longest walk first (see rev_scan_order)
@@ -1094,7 +1101,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     const int r = lane & 31, hh = lane >> 5;
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const uint32_t tr_off = tr_lane_offset(lane), row_off = row_lane_offset(lane);
-    const int64_t key0 = (int64_t)kb * 64 + 32 * wave;  // token index (MODE 0) or pooled-key index (MODE 1)
+    const int64_t key0 = (int64_t)kb * (32 * WV) + 32 * wave;  // token index (MODE 0) or pooled-key index (MODE 1)
     const int64_t key = key0 + r;
     const int64_t limit = MODE == 0 ? a.n : (int64_t)a.nbc;
     const int half_w = a.window / 2;
@@ -1103,6 +1110,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     const bool key_active = MODE == 1 || 32 * wave + r < n_act;
 
     bf16x8 kB[NS], vB[NS];
+    char *const v_own = lds + kBwdDkvNbuf * TILE + wave * G::ROW + lane * 16;  // V_LDS: this lane's part of fragment 0, its own only
     {
         const int64_t krow_i = key < limit ? key : limit - 1;  // (rows past the end are masked below)
         const uint16_t *krow = (MODE == 0 ? a.k : a.kc) + (krow_i * a.h_kv + head) * D + 8 * hh;
@@ -1115,6 +1123,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
                 const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
                 kB[ks] = vB[ks] = zero8;
             }
+            if constexpr (V_LDS) *reinterpret_cast<bf16x8 *>(v_own + ks * 1024) = vB[ks];
         }
     }
     f32x16 acck[ND], accv[ND];
@@ -1146,10 +1155,10 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     // workgroups) its share
     const int gh0 = MODE == 0 && a.hsplit > 1 ? z * a.hpw : 0;
     const int grp = MODE == 0 && a.hsplit > 1 ? min(a.group, gh0 + a.hpw) - gh0 : a.group;
-    constexpr bool VGPR_CHAINS = D == 128;  // (the kernel has one wavefront per SIMD: see mfma_v)
-    // the step in its interleaved form (step_interleaved below).  Not at d = 64: there it needs more than the 168
+    constexpr bool VGPR_CHAINS = D == 128 && !V_LDS;  // (the kernel has one wavefront per SIMD: see mfma_v)
+    // the step in its interleaved form (step_interleaved below).  Not with two wavefronts per SIMD; not at d = 64: there it needs more than the 168
     // registers of three wavefronts per SIMD, and with two it measured slower (config 5: 1.12 -> 1.25 ms).
-    constexpr bool INTERLEAVE = D != 64;
+    constexpr bool INTERLEAVE = D != 64 && !V_LDS;
     static_assert(kBwdDkvNbuf == 2, "the copies of a step go out one step ahead");
     // br_c: the branch whose probabilities these are (0 compressed, 1 selected, 2 window); tile_fn(t): the t-th query
     // tile of the segment (arithmetic on registers only); every tile is met by the grp query heads of this key/value
@@ -1164,8 +1173,8 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
             // (tile, head) index in 32 bits, byte offsets by shifts: a 64-bit multiply is several scalar instructions
             const uint32_t ih = (uint32_t)tile_fn(t) * (uint32_t)a.h + (uint32_t)(head * a.group + gh0 + gh);
             const int64_t off = (int64_t)ih * G::IMG;
-            copy_kb<G::ROW / 1024>(a.img_q + off, buf, wave, lane16);
-            copy_kb<G::ROW / 1024>(img_do + off, buf + G::ROW, wave, lane16);
+            copy_kb<G::ROW / 1024, WV>(a.img_q + off, buf, wave, lane16);
+            copy_kb<G::ROW / 1024, WV>(img_do + off, buf + G::ROW, wave, lane16);
             if (wave == 0)
                 copy_256_to_lds(aux_br + (int64_t)ih * 64, lane16 >> 2, buf + AUX);
         };
@@ -1220,7 +1229,8 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
                 if constexpr (VGPR_CHAINS)
                     mfma_v(x.dp, rows, vB[ks]);
                 else
-                    x.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows, vB[ks], x.dp, 0, 0, 0);
+                    x.dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        rows, V_LDS ? *reinterpret_cast<const bf16x8 *>(v_own + ks * 1024) : vB[ks], x.dp, 0, 0, 0);
             }
         };
         // P = exp2(S scale log2e - offset), the offsets of the query rows from the first half of the table
@@ -1435,6 +1445,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
                 // (the plain order: scores, exponentials, dV, dP, dK; at d = 64 the interleaved one does not fit the
                 // registers of three wavefronts per SIMD)
                 issue_next();
+                if (WV > 2 && key0 >= a.nbc) continue;  // (no keys in the last workgroup: copies and barriers only)
                 Tile x;
                 ph_scores(x, lds + slot * TILE, tile_fn(t));
                 ph_exp(x);
@@ -1520,14 +1531,19 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     }
 }
 
-// Number of a workgroup among the walks of pooled keys -> group of 64 keys, key/value head, range of query tiles; false: none left.
+// Wavefronts of a workgroup that takes pooled keys.
+template <int D>
+constexpr int kPooledWaves = D == 128 ? 4 : 2;
+
+// Number of a workgroup among the walks of pooled keys -> group of 32 * WV keys, key/value head, range of query tiles; false: none left.
 // Equal shares of all walks for the XCDs, and to each the key groups of one (head, range) beside each other: they read the same
 // query tiles, at the same pace, so that its L2 fetches those about once.  (Dealing the key groups of every (head, range) to
 // the XCDs leaves some with nothing where there are few: of three groups, five of eight.  Backward, that / this, us, blocks x
 // heads: d = 128, 192 x 8 404 / 363, 337 x 8 (2) 974 / 909, 896 x 2 731 / 654, 896 x 8 2549 / 2440, 4096 x 8 22570 / 21930; d = 64, 192 x
 // 8 222 / 206, 896 x 8 1287 / 1224.)
+template <int WV>
 __device__ bool pooled_walk(const BwdArgs &a, int wg, int *group, int *head, int *z) {
-    const int n_groups = a.nbp / 64, n = n_groups * a.h_kv * a.n_split, item = (wg & 7) * ((n + 7) / 8) + (wg >> 3);
+    const int n_groups = a.nbp / (32 * WV), n = n_groups * a.h_kv * a.n_split, item = (wg & 7) * ((n + 7) / 8) + (wg >> 3);
     if (item >= n) return false;
     // (divided in vector registers: readfirstlane tells the compiler that the numbers are uniform all the same)
     const int y = __builtin_amdgcn_readfirstlane(item / n_groups);
@@ -1538,13 +1554,14 @@ __device__ bool pooled_walk(const BwdArgs &a, int wg, int *group, int *head, int
 }
 
 template <int D, int MODE>
-__global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_dkv_kernel(BwdArgs a) {
+__global__ __launch_bounds__(MODE == 0 ? 128 : 64 * kPooledWaves<D>, (D == 128 ? MODE == 0 ? 1 : 2 : 3)) void bwd_dkv_kernel(BwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     if constexpr (MODE == 0) {
-        dkv_walk<D, 0>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
+        dkv_walk<D, 0, false, 2, false>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
     } else {
         int group, head, z;
-        if (pooled_walk(a, blockIdx.x, &group, &head, &z)) dkv_walk<D, 1>(a, lds, group, head, z);
+        if (!pooled_walk<kPooledWaves<D>>(a, blockIdx.x, &group, &head, &z)) return;
+        dkv_walk<D, 1, false, kPooledWaves<D>, D == 128>(a, lds, group, head, z);
     }
 }
 
@@ -1560,7 +1577,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
     if (wg < n_dkv) {
         const int y = uniform(wg / n_tasks), z = uniform(y / a.h_kv);
         if (z >= a.hsplit) return;  // (the number was rounded up to eight)
-        dkv_walk<D, 0, true>(a, lds, wg - y * n_tasks, y - z * a.h_kv, z);
+        dkv_walk<D, 0, true, 2, false>(a, lds, wg - y * n_tasks, y - z * a.h_kv, z);
         return;
     }
     wg -= n_dkv;
@@ -1571,7 +1588,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
     }
     wg -= n_dq;
     int group, head, z;
-    if (pooled_walk(a, wg, &group, &head, &z)) dkv_walk<D, 1>(a, lds, group, head, z);
+    if (pooled_walk<2>(a, wg, &group, &head, &z)) dkv_walk<D, 1, false, 2, false>(a, lds, group, head, z);
 }
 
 // The rows of the key blocks whose walks were dealt out: the sums of the parts of each head range, added in order, then
@@ -1705,20 +1722,21 @@ WsLayout ws_layout(const Shape &s) {
     w.img_vc = take(ntc * s.h_kv * img);
     w.aux = take((size_t)3 * nt * s.h * 64 * 4);
     // pooled keys: enough query ranges to fill the chip
-    w.nbp = (s.nbc + 63) / 64 * 64;
     w.small = small_backward(s);
-    const int wgs = (w.nbp / 64) * s.h_kv;
-    // The query tiles are cut into n ranges, one workgroup per (64 pooled keys, key/value head, range), all equally
+    const int wg_keys = s.d == 128 && !w.small ? 32 * kPooledWaves<128> : 64;  // pooled keys of a workgroup
+    w.nbp = (s.nbc + wg_keys - 1) / wg_keys * wg_keys;
+    const int wgs = (w.nbp / wg_keys) * s.h_kv;
+    // The query tiles are cut into n ranges, one workgroup per (wg_keys pooled keys, key/value head, range), all equally
     // long.  The chip runs `slots` of them at a time (256 CUs x the workgroups per CU that the kernel's registers
     // allow), so the kernel takes ceil(workgroups / slots) rounds of (tiles per range) x (query heads per key/value
     // head) steps; every range also costs its partial sums, written here and read back by the token-key kernel.
-    // n minimises that: e.g. at 1680 workgroups per range and 512 slots, two ranges run 7 rounds where 6.6 would
-    // do, seven ranges run 23 rounds of a seventh the length (6 % less).
+    // n minimises that: e.g. at 848 workgroups per range and 512 slots, one range runs 2 rounds where 1.66 would
+    // do, three ranges run 5 rounds of a third of the length (17 % less).
     {
-        const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);
+        const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp_q = s.h / s.h_kv;
         const double range_bytes = (double)w.nbp * s.h_kv * s.d * 4 * 2 * 2;
-        const double step_seconds = 1.1e-6 * s.d / 128, range_steps = range_bytes / 4e12 / step_seconds;
+        const double step_seconds = wg_keys == 128 ? 1.9e-6 : 1.1e-6 * s.d / 128, range_steps = range_bytes / 4e12 / step_seconds;
         double best = 0;
         int best_n = 1;
         for (int n = 1; n <= 64; ++n) {
@@ -1793,6 +1811,7 @@ WsLayout ws_layout(const Shape &s) {
 template <int D>
 lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
+    constexpr int LDS_TOKENS = DKV_LDS<D, 2, false>, LDS_POOLED = DKV_LDS<D, kPooledWaves<D>, D == 128>;
     const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
     const bool table = small_table(s);
@@ -1807,7 +1826,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
         const int n_dq_x = (int)eights(s.nb);
         const int64_t n_dkv = eights((int64_t)w.max_tasks * s.h_kv * a.hsplit), n_dq = (int64_t)n_dq_x * s.h;
         const int64_t n_walks = n_dkv + n_dq + eights((int64_t)w.nbp / 64 * s.h_kv * w.n_split);
-        constexpr int LDS = DKV_LDS<D> > DQ_LDS<D> ? DKV_LDS<D> : DQ_LDS<D>;
+        constexpr int LDS_WALK = DKV_LDS<D, 2, false>, LDS = LDS_WALK > DQ_LDS<D> ? LDS_WALK : DQ_LDS<D>;
         auto walks = s.topk > 64 ? &bwd_walks_small<D, true> : &bwd_walks_small<D, false>;
         // (set on every call: cheap, and right whichever device is current and whichever thread calls)
         LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(walks), hipFuncAttributeMaxDynamicSharedMemorySize, LDS));
@@ -1819,9 +1838,9 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
         return LSRM_OK;
     }
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 0>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS_TOKENS));
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, DKV_LDS<D>));
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS_POOLED));
     if (!table) {
         hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
         LSRM_HIP_CHECK(hipGetLastError());
@@ -1849,8 +1868,8 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     else
         hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / 64 * s.h_kv * w.n_split + 7) / 8 * 8), dim3(128), DKV_LDS<D>, st,
-                       a);
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / (32 * kPooledWaves<D>) * s.h_kv * w.n_split + 7) / 8 * 8),
+                       dim3(64 * kPooledWaves<D>), LDS_POOLED, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     if (w.n_split > 1) {
         const int64_t per_split = (int64_t)w.nbp * s.h_kv * D;
@@ -1858,7 +1877,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
                            w.n_split, per_split);
         LSRM_HIP_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), DKV_LDS<D>, st, a);
+    hipLaunchKernelGGL((bwd_dkv_kernel<D, 0>), dim3(w.max_tasks, s.h_kv, a.hsplit), dim3(128), LDS_TOKENS, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     // add up the sums of walks that were dealt out, in order, and finish their rows
     const int n_sum_blocks = a.hsplit > 1 ? s.nb : w.max_split;
