@@ -58,40 +58,35 @@ __global__ __launch_bounds__(256) void pool_blocks(int nb, int row_chunks /* h*d
     *dst = o;
 }
 
-// The same where pool_blocks would be a few workgroups: a workgroup per block and sixteen chunks, sixteen
-// threads to a chunk with four rows each, their sums added in order through LDS.  43 blocks, 3 heads of 128: 7.6 -> 3.3 us.  The
-// line is where nothing is left to gain: 300 blocks, 8 heads of 128 13.8 and 12.6 us, 896, 16 of 128 85 and 99 us; 16000, one of 32
-// 20.2 and 23.7 us (three quarters of the threads idle).
+// The same sums where pool_blocks would be a few workgroups: a workgroup per block and sixteen chunks, sixteen threads to a
+// chunk with four rows each in flight, which go into LDS as they are; then a thread per channel adds its 64 values in token order,
+// so that a block's pair has the same bits however many blocks a call has.  (Bound by latency; sixteen partial sums a channel,
+// a shorter chain, took 2.6 us where this takes 2.9, 43 blocks, 3 heads of 128, and rounded differently.)  Workgroups of one block
+// beside each other: whole rows are read at about the same time.  pool_blocks / this, us, blocks x heads: d = 128, 43 x 3 6.9 / 2.9; d = 64, 128 x 16
+// 7.3 / 4.8, 160 x 16 9.8 / 8.5, 512 x 8 12.6 / 11.8, 128 x 32 12.4 / 11.8, 64 x 64 15.8 / 11.7; the line is where little is left to gain.
 constexpr int64_t kPoolFew = 1 << 15;  // chunks in all
 constexpr int kPoolFewBlocks = 2048;
 __global__ __launch_bounds__(256) void pool_blocks_few(int row_chunks, const uint4 *__restrict__ k, const uint4 *__restrict__ v,
                                                        uint4 *__restrict__ kc, uint4 *__restrict__ vc,
                                                        const int32_t *__restrict__ count) {
-    __shared__ __attribute__((aligned(16))) float part[16][16 * 8 + 4];
-    const size_t b = blockIdx.x;
-    const int cl = threadIdx.x % 16, rl = threadIdx.x / 16, c = blockIdx.y * 16 + cl;
+    __shared__ uint4 rows[kBlock][16];
+    const size_t b = blockIdx.y;
+    const int cl = threadIdx.x % 16, rl = threadIdx.x / 16, c = blockIdx.x * 16 + cl;
     const uint4 *src = (blockIdx.z == 0 ? k : v) + b * kBlock * (size_t)row_chunks + min(c, row_chunks - 1);
     const int n_act = count != nullptr ? count[b] : kBlock;
     uint4 r[kBlock / 16];
 #pragma unroll
     for (int i = 0; i < kBlock / 16; ++i)
         r[i] = rl + 16 * i < n_act ? src[(size_t)(rl + 16 * i) * row_chunks] : make_uint4(0, 0, 0, 0);
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < kBlock / 16; ++i) {
-        acc[0] += bf16_lo(r[i].x); acc[1] += bf16_hi(r[i].x);
-        acc[2] += bf16_lo(r[i].y); acc[3] += bf16_hi(r[i].y);
-        acc[4] += bf16_lo(r[i].z); acc[5] += bf16_hi(r[i].z);
-        acc[6] += bf16_lo(r[i].w); acc[7] += bf16_hi(r[i].w);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) part[rl][8 * cl + j] = acc[j];
+    for (int i = 0; i < kBlock / 16; ++i) rows[rl + 16 * i][cl] = r[i];
     __syncthreads();
-    const int ch = threadIdx.x, chunk = blockIdx.y * 16 + ch / 8;
+    const int ch = threadIdx.x, chunk = blockIdx.x * 16 + ch / 8;
     if (ch >= 128 || chunk >= row_chunks) return;
+    const uint16_t *column = reinterpret_cast<const uint16_t *>(rows) + ch;
     float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum += part[i][ch];
+    for (int t = 0; t < kBlock; ++t) sum += __uint_as_float((uint32_t)column[t * 128] << 16);
     uint16_t *dst = reinterpret_cast<uint16_t *>((blockIdx.z == 0 ? kc : vc) + b * (size_t)row_chunks + chunk);
     dst[ch % 8] = (uint16_t)f32_to_bf16_rne(sum / (float)n_act);
 }
@@ -263,7 +258,7 @@ lsrm_status launch_compress(const Shape &s, const uint16_t *d_k, const uint16_t 
         return LSRM_OK;
     }
     if (s.nb <= kPoolFewBlocks && (int64_t)s.nb * row_chunks <= kPoolFew) {
-        hipLaunchKernelGGL(pool_blocks_few, dim3(s.nb, (row_chunks + 15) / 16, 2), dim3(256), 0, st, row_chunks,
+        hipLaunchKernelGGL(pool_blocks_few, dim3((row_chunks + 15) / 16, s.nb, 2), dim3(256), 0, st, row_chunks,
                            reinterpret_cast<const uint4 *>(d_k), reinterpret_cast<const uint4 *>(d_v),
                            reinterpret_cast<uint4 *>(d_kc), reinterpret_cast<uint4 *>(d_vc), s.count);
         LSRM_HIP_CHECK(hipGetLastError());

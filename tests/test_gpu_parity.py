@@ -127,6 +127,37 @@ def test_compress_few_and_many_blocks(B, oracle_lib, n_blocks, heads, d, with_co
         assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-6)
 
 
+@pytest.mark.parametrize("n_blocks,heads,d,with_counts", [(1, 1, 32, True), (23, 3, 32, False), (43, 3, 128, True),
+                                                          (128, 16, 128, False), (129, 16, 128, False), (2049, 1, 32, False)])
+def test_compress_adds_in_token_order(B, n_blocks, heads, d, with_counts):
+    """Bit for bit the fp32 sum left to right, divided and rounded once, whichever kernel takes the call: rows that
+    cancel up to a hundredth or so, so that another order of the sum has other leading digits."""
+    cfg = I.small_config(name=f"p-order{n_blocks}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, seed=46)
+    rng = np.random.default_rng(14)
+    cnt = rng.integers(1, 65, size=cfg.nb).astype(np.int32) if with_counts else None
+    _log(f"[compress] {cfg.name}")
+
+    def rows():
+        x = (rng.standard_normal((cfg.nb, 64, heads * d)) * 2.0 ** rng.integers(0, 12, size=(cfg.nb, 64, 1))).astype(np.float32)
+        x[:, 32:] = -x[:, 31::-1]
+        x[:, ::9] *= np.float32(2.0 ** -12)
+        return I.f32_to_bf16_bits(x).reshape(cfg.n, heads, d)
+
+    def in_order(bits):
+        x = I.bf16_bits_to_f32(bits).reshape(cfg.nb, 64, heads, d)
+        act = np.full(cfg.nb, 64) if cnt is None else cnt
+        acc = np.zeros((cfg.nb, heads, d), dtype=np.float32)
+        for t in range(64):
+            acc = acc + np.where((t < act)[:, None, None], x[:, t], np.float32(0))
+        return I.f32_to_bf16_bits(acc / act[:, None, None].astype(np.float32))
+
+    k_bits, v_bits = rows(), rows()
+    _, _, kc, vc = G.run_compress(B, cfg, k_bits, v_bits, cnt)
+    for got, bits in ((kc, k_bits), (vc, v_bits)):
+        ref = I.bf16_bits_to_f32(in_order(bits)).reshape(cfg.nb, heads, d)
+        assert np.array_equal(G.bf16_host(got).view(np.uint32), ref.view(np.uint32))
+
+
 # ----------------------------------------------------------------------------- forward
 def _forward_case(B, oracle_lib, cfg, idx=None, seg="default", scale=0.0, qblocks=None, window=None, window_mode=0,
                   block_count=None):
