@@ -77,7 +77,7 @@ struct FwdArgs {
     int gate_channels;  // gates are [N, 3, H, d] (one per output channel) instead of [N, H, 3]
     int own_block;      // the window branch sees the query's own block (App. A) instead of a sliding window
     const int32_t *count;  // nullable [NB]: active tokens per block (its first count[b] slots)
-    int groups_per_head, groups_per_xcd;  // query-block groups of one head, and the share of one XCD
+    int groups_per_head, groups_per_xcd;  // query-block groups of one head, and the share of one XCD (nsa_forward_teams: of all heads)
     int teams[3];  // nsa_forward_teams: teams of each branch
     float scale_log2e, scale;
 };
@@ -1027,10 +1027,12 @@ template <class G, class TM, bool CNT, bool WIDE>
 __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forward_teams(FwdArgs a) {
     constexpr int D = G::D, NB = TM::NB, NT = TM::NT;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;  // (numbered as above)
-    const int head = slot_id / a.groups_per_xcd;
-    const int group = xcd * a.groups_per_xcd + slot_id % a.groups_per_xcd;
-    if (group >= a.groups_per_head) return;
+    // Equal shares of all workgroups for the XCDs, of 32 CUs each: the chip holds them together only if none gets more.  (An eighth
+    // of every head's, rounded up, is 36 for 17 blocks x 12 heads; with packing, general kernel, that deal, this one, us: d = 32 26.6, 29.8,
+    // 16.8; 9 x 28 26.7, 30.8, 17.3; one block x 256 heads of 64 59.9, 80.3, 16.7.)
+    const int item = (blockIdx.x & 7) * a.groups_per_xcd + (blockIdx.x >> 3);
+    const int head = item / a.groups_per_head, group = item - head * a.groups_per_head;
+    if (head >= a.h) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int team = wave % NT, sub = wave / NT % G::NW, qbi = wave / (NT * G::NW);
@@ -1412,11 +1414,12 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // Measured (us, the general kernel and teams of one / of two query blocks), 64 blocks x 4 heads: d = 32 18.5 and 14.7 / 17.7, d = 64
     // 21.7 and 15.3 / 19.3, d = 128 35.6 and 21.0; 65 x 4: 19.0 and 24.1 / 17.8, 22.1 and 25.3 / 19.8, 37.3 and 36.3 (a second
     // round of workgroups); 254 x 2: 28.4 and 34.1 / 26.5, 31.7 and 35.4 / 29.0; 258 x 2: 31.5 and 43.7 / 40.3, 36.8 and 46.1 / 45.6,
-    // 59.4 and 67.9.  (At d = 128 a wavefront's registers leave no room for the twelve of two query blocks.)
+    // 59.4 and 67.9.  Workgroups are what counts, two query blocks or an odd one: 17 x 30 are 270.
+    // (At d = 128 a wavefront's registers leave no room for the twelve of two query blocks.)
     using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2>;
     using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2>;
-    const int64_t blocks = (int64_t)s.nb * s.h;
-    const int nb_wg = blocks <= 256 ? 1 : blocks <= 256 * Two::NB ? 2 : 0;  // query blocks of a workgroup of teams
+    // query blocks of a workgroup of teams
+    const int nb_wg = (int64_t)s.nb * s.h <= 256 ? 1 : Two::NB == 2 && (int64_t)(s.nb + 1) / 2 * s.h <= 256 ? 2 : 0;
     if (nb_wg > 0) {
         // every branch one team, the others where the longest part is
         const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
@@ -1429,7 +1432,7 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
         }
     }
     a.groups_per_head = nb_wg == 0 ? (s.nb + NP - 1) / NP : (s.nb + nb_wg - 1) / nb_wg;
-    a.groups_per_xcd = (a.groups_per_head + 7) / 8;
+    a.groups_per_xcd = nb_wg == 0 ? (a.groups_per_head + 7) / 8 : (a.groups_per_head * s.h + 7) / 8;
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern;
     int lds, threads;
@@ -1450,7 +1453,7 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // (set on every launch: cheap, and right whichever device is current and whichever thread calls)
     LSRM_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-    const dim3 grid(8 * a.groups_per_xcd * s.h);
+    const dim3 grid(8 * a.groups_per_xcd * (nb_wg == 0 ? s.h : 1));
     void *kargs[] = {&a};
     LSRM_HIP_CHECK(hipLaunchKernel(kern, grid, dim3(threads), kargs, lds, st));
     LSRM_HIP_CHECK(hipGetLastError());

@@ -532,6 +532,12 @@ def test_forward_pipeline_edges(B, oracle_lib, d, nb):
     (65, 4, 4, 4, 64, True, False),      # 260: two to a workgroup, the last one alone (d = 128: the general kernel)
     (128, 4, 1, 9, 320, False, True),    # 512: the most that go two to a workgroup
     (171, 3, 3, 6, 130, False, False),   # 513: the general kernel, an odd number of blocks
+    (17, 15, 3, 5, 128, True, False),    # 255: one XCD has a workgroup less than the others
+    (3, 29, 29, 4, 64, False, True),     # 87, dealt to the XCDs eleven and ten
+    (51, 9, 9, 5, 96, False, False),     # 26 workgroups a head, the last of one block: 234 in all
+    (51, 10, 5, 5, 96, True, False),     # 260 of those, though 510 pairs: the general kernel
+    (1, 256, 8, 1, 64, False, False),    # one block, a workgroup a head
+    (1, 257, 1, 1, 64, False, False),    # the same, one too many
     (6, 86, 1, 3, 66, True, False),      # 516, less than a tile of pooled pairs
     (33, 2, 1, 90, 2, True, True),       # nearly all teams on a long routing row, the window one or two tiles
     (40, 1, 1, 1, 4096, False, False),   # nearly all teams on the window
