@@ -831,6 +831,27 @@ size_t route3d_ws_bytes(const Shape &s) {
     return align_up(n > 0 ? n : 256, 256);
 }
 
+// Whether select_3d_many is the faster one (all figures: us, select_3d / select_3d_many).
+static bool many_pay(const Route3d &a, unsigned n_queries) {
+    constexpr unsigned kFillsChip = 6144;  // queries, 24 for every CU, from which the slower parts below pay at all
+    const int n_img = a.n_views * a.prefilter, k_vol = min(max(a.k_v2v, a.k_i2v), a.nb_obj), k_img = max(a.k_v2i, a.k_i2i);
+    // A query's 16 lanes do in turn what select_3d gives to 256: many queries are needed to fill the chip, and the more
+    // blocks there are to look at, or candidate tiles, the more of them.  57344 queries of 512 blocks 322 / 87, 70144 of 1024
+    // 936 / 331, 12288 of 64 128 / 64, 4096 of 64 16 / 11, 1280 of 16 11 / 11; but 640 of 512 11 / 21, 3072 of 2048 57 / 80,
+    // 4672 of 4096 71 / 108.  64 of 120 tiles, 4384 queries 99 / 95; of 160, 2592 queries 80 / 109.
+    if (n_queries < (k_img > 0 && n_img > 64 ? 4096u : 2048u) + 2u * a.nb_obj) return false;
+    // Above kNearFrom there is no list of near blocks, they are taken one by one.  Of 64 blocks 48 92 / 22, 49 94 / 46, 64 113 / 57,
+    // of 256 blocks 64 317 / 279; but of 128 blocks 96 113 / 125, of 512 49 671 / 802, of 2048 49 2301 / 6544; 2656 queries of 64
+    // blocks, 49 59 / 67.
+    if (k_vol > kNearFrom && (k_vol > 64 || a.nb_obj > 256 || n_queries < kFillsChip)) return false;
+    // Above four tiles a view there is no window, all tiles are looked at.  Eight of 64 tiles a view 410 / 212, of 144 798 / 206; but
+    // of 256, four views, 323 / 505; 2320 queries, eight of 144 57 / 108, 4384, five of 144 116 / 127.
+    if (k_img > 0 && a.prefilter > 4 && (a.tg > 12 || n_queries < kFillsChip)) return false;
+    // Too many candidates to rank and too many results to take one by one.  64 of 144 532 / 393, 120 of 96 958 / 652; but 120
+    // of 144 558 / 769.
+    return k_img <= 64 || n_img <= 96;
+}
+
 lsrm_status launch_route_3d(const Shape &s, const lsrm_route3d_params &r, const float *d_pos, const float *d_pos_img,
                             const lsrm_camera *d_cams, int32_t *d_idx, float *d_dist2, void *d_ws, hipStream_t st) {
     if (s.nb == 0 || s.topk == 0) return LSRM_OK;
@@ -859,12 +880,8 @@ lsrm_status launch_route_3d(const Shape &s, const lsrm_route3d_params &r, const 
     a.cache_keys = vol_bytes + cand_bytes <= 60 * 1024 ? 1 : 0;
     const size_t lds = cand_bytes + (a.cache_keys ? vol_bytes : 0);
     const unsigned n_queries = r.per_token ? (unsigned)s.n : (unsigned)s.nb;
-    // A query's 16 lanes do in turn what select_3d gives to 256: many queries are needed to fill the chip, and the more
-    // blocks there are to look at the more of them.  Measured, select_3d and select_3d_many: 57344 queries of 512 blocks
-    // 322 and 87 us, 70144 of 1024 936 and 331, 12288 of 64 128 and 64, 4096 of 64 16 and 11, 1280 of 16 11 and 11; but 640
-    // of 512 11 and 21, 3072 of 2048 57 and 80, 4672 of 4096 71 and 108.
     const size_t many_lds = kManyQueries * (16 * (size_t)s.n_views + 8 * (size_t)s.n_views * a.prefilter + 8 * (size_t)s.topk);
-    if (n_queries >= 2048u + 2u * s.nb_obj && many_lds <= 40 * 1024) {
+    if (many_lds <= 40 * 1024 && many_pay(a, n_queries)) {
         hipLaunchKernelGGL(select_3d_many<kManyQueries>, dim3((n_queries + kManyQueries - 1) / kManyQueries),
                            dim3(16 * kManyQueries), many_lds, st, a, (int)n_queries, cent, d_pos, d_pos_img, d_cams, d_idx,
                            d_dist2);

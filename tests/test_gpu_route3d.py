@@ -176,7 +176,14 @@ def test_route_3d_list_lengths_at_the_edges(B, oracle_lib, n_blocks, n_views, pr
 @pytest.mark.parametrize("n_blocks,n_views,grid,pre,budgets,scene", [
     (256, 2, 24, 4, (8, 8, 8, 8), "plain"),        # the fewest blocks that a common list is made from; windows of the whole view
     (255, 3, 16, 3, (48, 9, 3, 9), "plain"),       # no common list; the largest volume budget that a list is made for
-    (300, 1, 72, 4, (49, 4, 20, 3), "plain"),      # one budget above it
+    (300, 1, 72, 4, (49, 4, 20, 3), "plain"),      # one budget above it, of too many blocks: the other kernel
+    (256, 1, 72, 4, (49, 4, 64, 3), "plain"),      # budgets above it, of the most blocks that still take this kernel
+    (256, 1, 72, 4, (65, 4, 64, 3), "plain"),      # and of one result more: the other kernel
+    (256, 1, 96, 8, (4, 5, 6, 7), "plain"),        # eight of 144 tiles of a view
+    (256, 1, 104, 8, (4, 5, 6, 7), "plain"),       # of 169: the other kernel
+    (64, 12, 64, 8, (4, 70, 4, 96), "plain"),      # 70 and all of 96 candidate tiles
+    (64, 33, 24, 3, (4, 70, 4, 64), "plain"),      # of 99: the other kernel
+    (64, 33, 24, 3, (4, 33, 4, 64), "plain"),      # 64 of 99
     (320, 2, 64, 5, (6, 10, 7, 9), "plain"),       # more tiles per view than a window is searched for
     (260, 18, 16, 1, (0, 18, 5, 0), "plain"),      # one-sided budgets
     (272, 20, 40, 4, (4, 60, 12, 80), "plain"),    # 80 candidate tiles: extracted for 60 results, ranked for 80
