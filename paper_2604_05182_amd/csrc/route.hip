@@ -314,7 +314,7 @@ __global__ __launch_bounds__(256) void select_topk(int nb_obj, int n_views, int 
 // query's own into every view, a tile query's of all blocks into its view), by the same sums.  A launch less, where that
 // is most of the time: 25 blocks, 2 views 4.8 and 4.4 us and the gap between them -> 6.9 us; with 64 blocks a step of 6 K tokens gained nothing.
 constexpr int kRouteFew = 32, kRouteFewRows = 256;  // object blocks (25 KB of points in LDS); queries, as every tile's reads all points
-__global__ __launch_bounds__(256) void select_topk_few(int nb_obj, int n_views, int tg, int topk, int cache_keys,
+__global__ __launch_bounds__(256) void select_topk_few(int nb_obj, int n_views, int tg, int topk,
                                                        const float *__restrict__ pos, const lsrm_camera *__restrict__ cams,
                                                        int32_t *__restrict__ idx, float *__restrict__ dist2_out) {
     extern __shared__ unsigned long long lds_base[];
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void select_topk_few(int nb_obj, int n_views, 
     }
     __syncthreads();
     select_row(
-        nb_obj, n_views, tg, topk, cache_keys,
+        nb_obj, n_views, tg, topk, 1,
         [&](int m) { return m < kRouteFew ? uv[m] : project(cams[m], cent[0][0], cent[0][1], cent[0][2]); },
         [&](int b, int) { return uv[b]; }, lds_base, idx, dist2_out);
 }
@@ -944,11 +944,11 @@ lsrm_status launch_route(const Shape &s, const float *d_pos, const lsrm_camera *
         const size_t stage_bytes = 4 * (size_t)s.topk * sizeof(unsigned long long);
         const size_t cache_bytes = (size_t)((max_cand + 1) / 2) * sizeof(unsigned long long);
         // default dynamic-LDS limit; beyond it distances are recomputed
-        const int cache_keys = cache_bytes + stage_bytes <= (few ? 12 : 60) * 1024 ? 1 : 0;
+        const int cache_keys = cache_bytes + stage_bytes <= 60 * 1024 ? 1 : 0;
         const size_t lds = stage_bytes + (cache_keys ? cache_bytes : 0);
-        if (few) {
-            hipLaunchKernelGGL(select_topk_few, dim3(s.nb), dim3(256), lds, st, s.nb_obj, s.n_views, s.grid / 8, s.topk,
-                               cache_keys, d_pos, d_cams, d_idx, d_dist2);
+        if (few) {  // (at most 5 KB: the keys are always kept)
+            hipLaunchKernelGGL(select_topk_few, dim3(s.nb), dim3(256), lds, st, s.nb_obj, s.n_views, s.grid / 8, s.topk, d_pos,
+                               d_cams, d_idx, d_dist2);
             LSRM_HIP_CHECK(hipGetLastError());
             return LSRM_OK;
         }
