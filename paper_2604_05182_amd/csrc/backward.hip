@@ -1071,11 +1071,11 @@ __global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
 // SUMS (MODE 0): every walk leaves fp32 sums for a last pass, which is also where the pooled gradients come in.
 // V_LDS: the value fragments of a wavefront's keys are read from LDS in every step instead of held in 32 registers.  At
 // d = 128, where the two [128 x 32] sets of sums alone take 128, that is what lets two wavefronts share a SIMD (223 registers,
-// in the plain order of a step), each filling the other's waits.  Done for pooled keys, with four wavefronts to a workgroup: they
-// share a tile's copies, and two workgroups' buffers and values fit the LDS of a CU.  Backward before / after, ms, blocks x
-// heads: 512 x 16 2.45 / 2.41, 2560 x 8 10.7 / 10.1, 4096 x 16 (2) 43.9 / 42.2, 6704 x 16 127.9 / 117.7; 192 x 8 0.363 / 0.370
-// (193 to 255 keys are as many steps as 256).  Not done for the token keys: 9 registers more than there are, and the last of
-// these took 121 to 122 ms either way; nor in the joint launch of small problems (192 x 6 305 / 300 us, 132 x 1 61 / 65).
+// in the plain order of a step), each filling the other's waits.  Done for many pooled keys (kPooledWide), with four wavefronts to a
+// workgroup: they share a tile's copies, and two workgroups' buffers and values fit the LDS of a CU.  Backward before / after, ms,
+// blocks x heads: 512 x 16 2.45 / 2.41, 2560 x 8 10.7 / 10.1, 4096 x 16 (2) 43.9 / 42.2, 6704 x 16 127.9 / 117.7.  Not done for
+// the token keys: 9 registers more than there are, and the last of these took 121 to 122 ms either way; nor in the joint launch
+// of small problems (192 x 6 305 / 300 us, 132 x 1 61 / 65).
 // lds: DKV_LDS bytes.  wg: place in the order of tasks, or group of 32 * WV pooled keys; z: head range, or range of query tiles.
 template <int D, int WV, bool V_LDS>
 constexpr int DKV_LDS = kBwdDkvNbuf * (2 * BGeo<D>::ROW + 1024) + (V_LDS ? WV * BGeo<D>::ROW : 0);
@@ -1531,9 +1531,12 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
     }
 }
 
-// Wavefronts of a workgroup that takes pooled keys.
-template <int D>
-constexpr int kPooledWaves = D == 128 ? 4 : 2;
+// Pooled keys from which a workgroup of four wavefronts takes 128 of them, two to a SIMD with the values in LDS (d = 128 only, not
+// in the joint launch).  Fewer keys leave it short of work, or its second half without keys.  Backward with 64 / with 128
+// keys to a workgroup, us, blocks x heads: 64 x 32 597 / 607, 128 x 16 586 / 598, 192 x 8 466 / 477, 257 x 4 401 / 411, 300 x 2 255 / 265, 400 x 1
+// 203 / 206, 64 groups of 256 x 8 469 / 481; 448 x 8 1103 / 1100, 512 x 2 339 / 345, 520 x 8 1314 / 1312, 700 x 8 1843 / 1802, 896 x 8
+// 2469 / 2391, 1500 x 4 2514 / 2405.
+constexpr int kPooledWide = 512;
 
 // Number of a workgroup among the walks of pooled keys -> group of 32 * WV keys, key/value head, range of query tiles; false: none left.
 // Equal shares of all walks for the XCDs, and to each the key groups of one (head, range) beside each other: they read the same
@@ -1553,15 +1556,15 @@ __device__ bool pooled_walk(const BwdArgs &a, int wg, int *group, int *head, int
     return true;
 }
 
-template <int D, int MODE>
-__global__ __launch_bounds__(MODE == 0 ? 128 : 64 * kPooledWaves<D>, (D == 128 ? MODE == 0 ? 1 : 2 : 3)) void bwd_dkv_kernel(BwdArgs a) {
+template <int D, int MODE, int WV = 2>
+__global__ __launch_bounds__(64 * WV, (D == 128 ? WV / 2 : 3)) void bwd_dkv_kernel(BwdArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     if constexpr (MODE == 0) {
         dkv_walk<D, 0, false, 2, false>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
     } else {
         int group, head, z;
-        if (!pooled_walk<kPooledWaves<D>>(a, blockIdx.x, &group, &head, &z)) return;
-        dkv_walk<D, 1, false, kPooledWaves<D>, D == 128>(a, lds, group, head, z);
+        if (!pooled_walk<WV>(a, blockIdx.x, &group, &head, &z)) return;
+        dkv_walk<D, 1, false, WV, WV == 4>(a, lds, group, head, z);
     }
 }
 
@@ -1692,7 +1695,7 @@ bool small_backward(const Shape &s) {
 
 struct WsLayout {
     size_t img_q, img_do[3], img_k, img_v, img_kc, img_vc, aux, part_k, part_v, rev_cnt, rev_ptr, rev_cur, rev_idx, total;
-    int n_split, nbp, tiles_per_split, hsplit, hpw, part_steps, max_tasks, max_slots, max_split;
+    int n_split, nbp, wg_keys, tiles_per_split, hsplit, hpw, part_steps, max_tasks, max_slots, max_split;
     bool small;  // bwd_walks_small
     size_t hpart_k, hpart_v, order, order_part, slot0, split_list, task_n, walk, gtab;
 };
@@ -1723,7 +1726,7 @@ WsLayout ws_layout(const Shape &s) {
     w.aux = take((size_t)3 * nt * s.h * 64 * 4);
     // pooled keys: enough query ranges to fill the chip
     w.small = small_backward(s);
-    const int wg_keys = s.d == 128 && !w.small ? 32 * kPooledWaves<128> : 64;  // pooled keys of a workgroup
+    const int wg_keys = w.wg_keys = s.d == 128 && !w.small && s.nbc >= kPooledWide ? 128 : 64;  // pooled keys of a workgroup
     w.nbp = (s.nbc + wg_keys - 1) / wg_keys * wg_keys;
     const int wgs = (w.nbp / wg_keys) * s.h_kv;
     // The query tiles are cut into n ranges, one workgroup per (wg_keys pooled keys, key/value head, range), all equally
@@ -1811,7 +1814,7 @@ WsLayout ws_layout(const Shape &s) {
 template <int D>
 lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
-    constexpr int LDS_TOKENS = DKV_LDS<D, 2, false>, LDS_POOLED = DKV_LDS<D, kPooledWaves<D>, D == 128>;
+    constexpr int LDS_TOKENS = DKV_LDS<D, 2, false>;
     const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
     const bool table = small_table(s);
@@ -1839,8 +1842,6 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     }
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 0>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_TOKENS));
-    LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 1>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, LDS_POOLED));
     if (!table) {
         hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
         LSRM_HIP_CHECK(hipGetLastError());
@@ -1868,9 +1869,18 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     else
         hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
-    hipLaunchKernelGGL((bwd_dkv_kernel<D, 1>), dim3((w.nbp / (32 * kPooledWaves<D>) * s.h_kv * w.n_split + 7) / 8 * 8),
-                       dim3(64 * kPooledWaves<D>), LDS_POOLED, st, a);
-    LSRM_HIP_CHECK(hipGetLastError());
+    auto pooled = [&](auto *kernel, int lds) -> lsrm_status {
+        LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        hipLaunchKernelGGL(kernel, dim3((w.nbp / w.wg_keys * s.h_kv * w.n_split + 7) / 8 * 8), dim3(2 * w.wg_keys), lds, st, a);
+        LSRM_HIP_CHECK(hipGetLastError());
+        return LSRM_OK;
+    };
+    lsrm_status rc;
+    if constexpr (D == 128)
+        rc = w.wg_keys == 128 ? pooled(&bwd_dkv_kernel<D, 1, 4>, DKV_LDS<D, 4, true>) : pooled(&bwd_dkv_kernel<D, 1>, LDS_TOKENS);
+    else
+        rc = pooled(&bwd_dkv_kernel<D, 1>, LDS_TOKENS);
+    if (rc != LSRM_OK) return rc;
     if (w.n_split > 1) {
         const int64_t per_split = (int64_t)w.nbp * s.h_kv * D;
         hipLaunchKernelGGL(sum_parts, dim3((unsigned)((per_split / 4 + 255) / 256), 2), dim3(256), 0, st, a.part_k, a.part_v,

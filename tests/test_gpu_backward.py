@@ -428,10 +428,12 @@ def test_backward_preparation_on_both_sides_of_its_sizes(B, oracle_lib, n_blocks
 
 
 @pytest.mark.parametrize("d,n_blocks,heads,h_kv", [(128, 64, 21, 3), (128, 65, 21, 3), (128, 128, 21, 7), (128, 129, 11, 11), (128, 193, 7, 7),
-                                                   (128, 65, 3, 3), (64, 300, 11, 11), (32, 129, 26, 13)])
+                                                   (128, 65, 3, 3), (64, 300, 11, 11), (32, 129, 26, 13), (128, 511, 2, 2),
+                                                   (128, 512, 4, 2), (128, 513, 2, 1), (128, 575, 1, 1), (128, 609, 2, 2)])
 def test_backward_pooled_keys_at_the_edges_of_their_groups(B, oracle_lib, d, n_blocks, heads, h_kv):
-    """Numbers of pooled keys around those a workgroup takes (64, 128), and of walks that eight does not divide, above the limits of
-    the joint launches and once below: sampled against the oracle, first and last blocks, keys and heads."""
+    """Numbers of pooled keys around those a workgroup takes (64; 128 from 512 keys on at d = 128, the last workgroup with one
+    to four wavefronts that have any), and of walks that eight does not divide, above the limits of the joint launches and
+    once below: sampled against the oracle, first and last blocks, keys and heads."""
     cfg = I.small_config(name=f"b-pooled{n_blocks}-{heads}-{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=4,
                          window=96, seed=79, h_kv=h_kv)
     assert cfg.nb == n_blocks
