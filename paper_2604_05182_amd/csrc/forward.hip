@@ -1115,16 +1115,22 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
         return base + (int64_t)tile * G::TILE;
     };
     auto mask_tile = [&](int t, f32x16 &sc) {
-        int j0 = 32 * (first + t), from = lo, to = hi;
-        bool need = j0 < full_lo || j0 + 32 > full_hi;
+        // (masks of their own for the selected branch: with counts most tiles need one, and one bound is half the work of two; 171 x 2 of
+        // d = 32, 64 partly filled blocks routed, 113 -> 94 us)
         if (branch == 1) {
-            need = false;
             if constexpr (CNT) {
-                to = min(32, max(0, of_row(pcount, (first + t) >> 1) - 32 * ((first + t) & 1)));
-                need = to < 32;
-                j0 = from = 0;
+                const int vld = min(32, max(0, of_row(pcount, (first + t) >> 1) - 32 * ((first + t) & 1)));
+                if (vld < 32) {
+                    mfma_settle();
+                    mask_scores(0, vld, sc, 0, lane);
+                }
             }
-        } else if constexpr (CNT) {
+            return;
+        }
+        const int j0 = 32 * (first + t);
+        int to = hi;
+        bool need = j0 < full_lo || j0 + 32 > full_hi;
+        if constexpr (CNT) {
             if (branch == 2 && !a.own_block) {
                 const int vld = min(32, max(0, a.count[j0 >> 6] - (j0 & 32)));
                 if (vld < 32) {
@@ -1135,7 +1141,7 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
         }
         if (need) {
             mfma_settle();
-            mask_scores(from, to, sc, j0, lane);
+            mask_scores(lo, to, sc, j0, lane);
         }
     };
     const TeamTiles<G, TM, decltype(src)> tiles{n, src, slots, sub, c.lane16};
