@@ -1424,11 +1424,18 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // (At d = 128 a wavefront's registers leave no room for the twelve of two query blocks.)
     using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2>;
     using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2>;
+    const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
+    const int64_t longest = std::max(tiles[0], std::max(tiles[1], tiles[2])), all = (int64_t)tiles[0] + tiles[1] + tiles[2];
+    // Of two query blocks every branch has one team.  Where one is nearly all there is and long, the others' ends save less than
+    // two stages of tiles instead of three cost (with packing, general kernel / teams, us: 171 x 2 of d = 32, rows of 92, window 64 79 / 83, of 128
+    // 101 / 110, with counts 164 / 178; of 64, window 512 63 / 61, of 32, window 64 41 / 39).
+    const bool one_branch = longest > 96 && 8 * longest > 7 * all;
     // query blocks of a workgroup of teams
-    const int nb_wg = (int64_t)s.nb * s.h <= 256 ? 1 : Two::NB == 2 && (int64_t)(s.nb + 1) / 2 * s.h <= 256 ? 2 : 0;
+    const int nb_wg = (int64_t)s.nb * s.h <= 256                                            ? 1
+                      : Two::NB == 2 && !one_branch && (int64_t)(s.nb + 1) / 2 * s.h <= 256 ? 2
+                                                                                            : 0;
     if (nb_wg > 0) {
         // every branch one team, the others where the longest part is
-        const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
         for (int &t : a.teams) t = 1;
         for (int extra = (nb_wg == 1 ? One::NT : Two::NT) - 3; extra > 0; --extra) {
             int most = 0;

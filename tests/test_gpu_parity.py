@@ -536,6 +536,9 @@ def test_forward_pipeline_edges(B, oracle_lib, d, nb):
     (3, 29, 29, 4, 64, False, True),     # 87, dealt to the XCDs eleven and ten
     (51, 9, 9, 5, 96, False, False),     # 26 workgroups a head, the last of one block: 234 in all
     (51, 10, 5, 5, 96, True, False),     # 260 of those, though 510 pairs: the general kernel
+    (86, 5, 1, 49, 64, True, False),     # two to a workgroup, but nearly all tiles are the routing row's: the general kernel
+    (86, 5, 1, 49, 640, True, False),    # a window long enough beside that row
+    (86, 5, 1, 48, 2, False, False),     # a row short enough
     (1, 256, 8, 1, 64, False, False),    # one block, a workgroup a head
     (1, 257, 1, 1, 64, False, False),    # the same, one too many
     (6, 86, 1, 3, 66, True, False),      # 516, less than a tile of pooled pairs
