@@ -2,6 +2,7 @@
 tokens), given as groups of consecutive 64-slot blocks: one compressed pair per spatial block, the own-block window
 over the whole spatial block, gradients handed back to all its active tokens.  Compress, forward and backward
 against the oracle, element by element."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -70,7 +71,10 @@ def _poison(cfg, cnt, *bits):
 
 @pytest.mark.parametrize("d,heads,h_kv,window_mode,with_counts", [(64, 2, 2, 1, False), (128, 2, 2, 1, True),
                                                                   (64, 4, 2, 0, True), (32, 4, 1, 1, True),
-                                                                  (128, 3, 3, 0, False)])
+                                                                  (128, 3, 3, 0, False),
+                                                                  # more than 256 workgroups: the general kernel
+                                                                  (64, 10, 2, 1, False), (128, 6, 2, 1, True), (64, 12, 2, 0, True),
+                                                                  (32, 12, 1, 1, True), (128, 6, 3, 0, False)])
 def test_forward_with_spatial_blocks(B, oracle_lib, d, heads, h_kv, window_mode, with_counts):
     cfg = I.small_config(name=f"g-fwd-d{d}-w{window_mode}-cnt{int(with_counts)}", n_obj=2368, n_views=2, grid=24,
                          heads=heads, d=d, topk=6, window=160, seed=91, h_kv=h_kv)
@@ -132,6 +136,107 @@ def test_backward_with_spatial_blocks(B, oracle_lib, d, heads, h_kv, window_mode
         inactive = (np.arange(cfg.n) % 64) >= np.repeat(cnt, 64)
         for g in got:
             assert np.all(g[inactive] == 0)
+
+
+def _heads(x, n_copies, axis):
+    return np.ascontiguousarray(np.concatenate([x] * n_copies, axis=axis))
+
+
+@pytest.mark.parametrize("d,heads,h_kv,window_mode,grouped_blocks,channels", [
+    (64, 2, 2, 1, True, False), (64, 4, 2, 0, False, True), (32, 2, 2, 0, True, False), (32, 4, 2, 1, True, True),
+    (32, 2, 2, 1, False, False), (128, 2, 2, 1, True, False), (128, 4, 2, 0, True, True), (128, 2, 2, 1, False, False)])
+def test_backward_options_on_every_set_of_launches(B, oracle_lib, d, heads, h_kv, window_mode, grouped_blocks, channels):
+    """Active counts, both windows, blocks alone and in spatial blocks, with a block that every row lists (walks of many
+    parts): the joint launches of a small problem; the general kernels behind five launches of preparation (holes in the
+    table up to more than 16384 entries); the general kernels behind one (copies of the heads)."""
+    cfg = I.small_config(name=f"g-sets-d{d}-h{heads}-w{window_mode}-g{int(grouped_blocks)}", n_obj=64 * 139, n_views=1, grid=8,
+                         heads=heads, d=d, topk=4, window=160, seed=97, h_kv=h_kv, gate_channels=channels)
+    assert cfg.nb == 140
+    goff, idx, cnt = _case(cfg, 7, True, cfg.topk, min_count=8)
+    idx[:, 1] = np.where(np.arange(cfg.nb) % 5 == 0, -1, 11)
+    if not grouped_blocks:
+        goff = None
+        cnt = np.random.default_rng(8).integers(8, 65, size=cfg.nb).astype(np.int32)
+        cnt[:4] = (32, 33, 64, 31)
+    _log(f"[sets of launches] {cfg.name}")
+    q_bits, k_bits, v_bits = I.make_qkv(cfg)
+    gates, dout_bits = I.make_gates(cfg), I.make_dout(cfg)
+    # (a popular block and a group of heads add up gradients: keep them at the magnitude the absolute bar was set for)
+    dout_bits = I.f32_to_bf16_bits(I.bf16_bits_to_f32(dout_bits) * np.float32(0.5 * h_kv / heads))
+    q, k, v, dout = (I.bf16_bits_to_f32(a) for a in (q_bits, k_bits, v_bits, dout_bits))
+    k_bits, v_bits, dout_bits = _poison(cfg, cnt, k_bits, v_bits, dout_bits)
+    ref = oracle_lib.nsa_backward(q, k, v, oracle_lib.pool(k, cnt, goff), oracle_lib.pool(v, cnt, goff), idx, gates,
+                                  cfg.seg_offsets(), cfg.window, dout, window_mode=window_mode, block_count=cnt,
+                                  group_offsets=goff)
+    active = (np.arange(cfg.n) % 64) < np.repeat(cnt, 64)
+
+    def check(cfg, idx, copies, tag):
+        got = G.run_backward(B, cfg, _heads(q_bits, copies, 1), _heads(k_bits, copies, 1), _heads(v_bits, copies, 1), idx,
+                             _heads(gates, copies, 2 if channels else 1), _heads(dout_bits, copies, 1), window_mode=window_mode,
+                             block_count=cnt, group_offsets=goff)
+        for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+            n_heads = r.shape[1]
+            for c in range(1, copies):
+                assert np.array_equal(g[:, c * n_heads:(c + 1) * n_heads], g[:, :n_heads]), (tag, name, c)
+            g = g[:, :n_heads]
+            assert np.isfinite(g).all() and np.all(g[~active] == 0), (tag, name)
+            ma, rl = G.attention_errors(g, r)
+            _log(f"    {tag} {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} (|ref| max {np.abs(r).max():.3e})")
+            assert ma <= G.MAX_ABS_TOL and rl <= G.REL_L2_TOL, (tag, name, ma, rl)
+
+    check(cfg, idx, 1, "joint")
+    wide = 120
+    assert cfg.nb * wide > 16384
+    holes = np.full((cfg.nb, wide - cfg.topk), -1, dtype=np.int32)
+    check(dataclasses.replace(cfg, topk=wide), np.concatenate([idx[:, :2], holes, idx[:, 2:]], axis=1), 1, "general, five")
+    copies = -(-1281 // (cfg.nb * heads)) if d == 128 else -(-3073 // (cfg.nb * h_kv))
+    check(dataclasses.replace(cfg, heads=copies * heads, h_kv=copies * h_kv), idx, copies, "general, one")
+
+
+@pytest.mark.parametrize("n_groups,with_counts", [(511, True), (512, False), (513, True), (576, True), (641, False)])
+def test_backward_many_pairs_of_spatial_blocks(B, n_groups, with_counts):
+    """At d = 128 workgroups of 128 pooled keys from 512 on, here fewer pairs than blocks: the compressed branch alone (no
+    routed blocks, no window) against its formulas in float64."""
+    import torch
+    cfg = I.small_config(name=f"g-pairs{n_groups}", n_obj=64 * 699, n_views=1, grid=8, heads=2, d=128, topk=1, window=0, seed=98,
+                         h_kv=1)
+    assert cfg.nb == 700
+    rng = np.random.default_rng(n_groups)
+    goff = np.concatenate([[0], np.sort(rng.choice(np.arange(1, cfg.nb), size=n_groups - 1, replace=False)), [cfg.nb]]).astype(np.int32)
+    cnt = rng.integers(8, 65, size=cfg.nb).astype(np.int32) if with_counts else np.full(cfg.nb, 64, dtype=np.int32)
+    _log(f"[spatial blocks] {cfg.name}")
+    q_bits, k_bits, v_bits = I.make_qkv(cfg)
+    gates, dout_bits = I.make_gates(cfg), I.make_dout(cfg)
+    idx = np.full((cfg.nb, 1), -1, dtype=np.int32)
+    count = cnt if with_counts else None
+    _, _, kc, vc = G.run_compress(B, cfg, k_bits, v_bits, count, goff)
+    k_in, v_in, do_in = _poison(cfg, count, k_bits, v_bits, dout_bits)
+    got = G.run_backward(B, cfg, q_bits, k_in, v_in, idx, gates, do_in, block_count=count, group_offsets=goff)
+
+    active = torch.from_numpy((np.arange(cfg.n) % 64) < np.repeat(cnt, 64)).cuda()
+    group = torch.from_numpy(np.repeat(np.repeat(np.arange(n_groups), np.diff(goff)), 64)).cuda()
+    q, do = (torch.from_numpy(I.bf16_bits_to_f32(a)).cuda().double() for a in (q_bits, dout_bits))
+    gate = torch.from_numpy(gates[:, :, 0]).cuda().double()
+    kc, vc = kc[:, 0].double(), vc[:, 0].double()
+    scale = cfg.d ** -0.5
+    dq, dkc, dvc = torch.zeros_like(q), torch.zeros_like(kc), torch.zeros_like(vc)
+    for h in range(cfg.heads):
+        qh, doh = q[active][:, h], (do * gate[:, :, None])[active][:, h]
+        p = torch.softmax(qh @ kc.T * scale, dim=1)
+        dp = doh @ vc.T
+        ds = p * (dp - (p * dp).sum(1, keepdim=True)) * scale
+        dq[active, h] = ds @ kc
+        dkc += ds.T @ qh
+        dvc += p.T @ doh
+    n_tok = torch.zeros(n_groups, dtype=torch.float64, device="cuda").index_add_(0, group, active.double())
+    dk, dv = ((x / n_tok[:, None])[group] * active[:, None] for x in (dkc, dvc))
+    for name, g, r in zip(("dq", "dk", "dv"), got, (dq, dk[:, None], dv[:, None])):
+        r = r.cpu().numpy()
+        assert np.isfinite(g).all() and np.all(g[~active.cpu().numpy()] == 0), name
+        # (gradients of pairs are far below the absolute bar here: the relative one, and a tenth of the largest row's size)
+        ma, rl = G.attention_errors(g, r)
+        _log(f"    {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} (|ref| max {np.abs(r).max():.3e})")
+        assert rl <= G.REL_L2_TOL and ma <= 0.1 * np.abs(r).max(), (name, ma, rl)
 
 
 def test_group_arguments_are_checked(B):
