@@ -82,6 +82,7 @@ struct BwdArgs {
     // order / order_part [<= max_tasks] hold the tasks, longest first: the order the workgroups start in.  Where a block's
     // walk is dealt out, the workgroups leave fp32 sums [hsplit][max_slots][64][H_kv][d], those of block b's parts from slot
     // slot0[b] on, and a last pass adds them up in order: over all blocks if hsplit > 1, else over those in split_list.
+    // (In the launches of small problems every walk leaves sums, and the last pass goes over all blocks.)
     int hsplit, hpw, part_steps, max_slots, cut_window;
     float *hpart_k, *hpart_v;
     int32_t *order, *order_part, *slot0, *split_list, *task_n;  // task_n: number of tasks, length of split_list
@@ -1569,7 +1570,7 @@ __global__ __launch_bounds__(64 * WV, (D == 128 ? WV / 2 : 3)) void bwd_dkv_kern
 }
 
 // The three kinds of walks of a small problem in one launch: none of them fills the chip, and none needs another's results (the
-// gradients of the pooled pairs meet those of the token keys in finish_small).  Workgroups: token keys first, dQ, pooled keys; each
+// gradients of the pooled pairs meet those of the token keys in sum_walks<D, true>).  Workgroups: token keys first, dQ, pooled keys; each
 // kind's number is a multiple of 8 (XCDs).
 template <int D, bool WIDE>
 __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdArgs a, int n_tasks, int n_dkv, int n_dq_x, int n_dq) {
@@ -1680,8 +1681,8 @@ bool small_table(const Shape &s) {
     return s.topk > 0 && s.nb <= kTableBlocks && (int64_t)s.nb * s.topk <= kTableEntries && (int64_t)s.nb * s.h <= 1 << 20;
 }
 
-// Whether a backward goes through the launches of small problems.  They save eight of eleven launches and the ends of three
-// kernels; they cost fp32 sums of every walk and, at d = 128, dQ walks with one
+// Whether a backward goes through the launches of small problems.  They are three, bwd_prepare and the general kernels six (without
+// bwd_prepare ten), and the ends of three kernels become one; they cost fp32 sums of every walk and, at d = 128, dQ walks with one
 // wavefront per SIMD.  Backward, general / small (us), blocks x heads (on key/value heads):
 //   d = 32   96 x 4 95 / 51, 192 x 8 174 / 130, 548 x 4 353 / 311, 337 x 8 (2) 357 / 296, 160 x 32 (16) 400 / 343; 896 x 8 777 / 809,
 //            512 x 16 752 / 776

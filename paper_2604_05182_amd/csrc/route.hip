@@ -1,12 +1,13 @@
 // 3D-aware block routing on gfx950 (Sec. 3.3 of the paper, block-level reading).
 //
-// Two kernels:
+// Kernels:
 //   project_blocks  one workgroup per sixteen object blocks: centroid of their 64 positions, then
 //                   its pinhole projection (u, v) into every view.
 //   select_topk     one 256-thread workgroup per query block (object block or image
 //                   tile): evaluates the squared 2-D distance to every candidate once
 //                   (keys parked in LDS) and extracts the K smallest (distance, id)
 //                   keys: K rounds of a minimum per wave, then a merge of the four lists.
+//   select_topk_few the two in one, for few object blocks: a workgroup projects what its query needs.
 // and, for the four selection rules (volume/image query -> volume/image blocks):
 //   block_points    one workgroup per sixteen blocks of either modality: centroid of their 64 points.
 //   select_3d       one 256-thread workgroup per query block: a wave per view projects the
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(256) void select_topk_few(int nb_obj, int n_views, 
     const bool obj_row = row < nb_obj;
     const int b0 = obj_row ? row : 0, n = obj_row ? 1 : nb_obj;
     constexpr int NIT = kRouteFew * 3 * kBlock / 4 / 256;
-    // (a block's points are 768 bytes: sixteen-byte loads where the whole array allows them)
+    // (four floats in a row to a thread, loaded one by one: the array may start at any multiple of four bytes)
     float v[NIT][4];
     const float *src = pos + (size_t)b0 * kBlock * 3;
 #pragma unroll
