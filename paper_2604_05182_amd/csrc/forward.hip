@@ -2,14 +2,14 @@
 // each its own softmax, combined by the gated sum, in one kernel.
 //
 // Work decomposition
-//   One workgroup owns NP = 2 consecutive query blocks of one head and carries them through all
-//   three branches.  A wavefront holds 32 query rows, two wavefronts a query block.  Each of the
+//   One workgroup owns NP = 2 consecutive query blocks of one head (or, where query heads share key/value
+//   heads in pairs, one query block of two such heads) and carries them through all three branches.  A wavefront holds 32 query rows, two wavefronts a query block.  Each of the
 //   four wavefronts of a workgroup sits on its own SIMD, and as many workgroups share a CU as the
 //   registers of a wavefront allow: two at d = 128, three at d = 64, four at d = 32 (the LDS of a
 //   workgroup is sized for that).  They meet no common barrier, so one's start, epilogues, window
 //   edges and waits are filled by the others.  In the compressed branch every K/V tile is copied
 //   to LDS once and used by both query blocks; in the selected and the window branch each query
-//   block streams its own tiles.  Workgroups are numbered so that each of the 8 XCDs walks a
+//   block streams its own tiles (two heads share those too).  Workgroups are numbered so that each of the 8 XCDs walks a
 //   contiguous range of (head, query block) units: the L2 of an XCD then holds one head's pooled
 //   keys/values and the neighbouring windows / routed blocks.  With grouped-query heads the
 //   query heads that share a key/value head are consecutive, hence run back to back on the
@@ -414,8 +414,8 @@ __device__ __forceinline__ void end_phase() {
 // it lives in and who copies it is the business of a Tiles object:
 //   OwnTiles     selected and window branch: each query block streams its own tiles through NST slots of its own, its
 //                two wavefronts split the copies
-//   SharedTiles  compressed branch: both query blocks use the same tiles, which go through one ring of NSLOT slots,
-//                copied by all wavefronts together
+//   SharedTiles  compressed branch, and all branches of a workgroup of two heads: one list of tiles for all, which go
+//                through one ring of NSLOT slots, copied by all wavefronts together
 // Both have: n (tiles of this query block), NST (tile tau lives in slot tau mod NST), PER_STEP (copies a wavefront issues
 // per step), begin() (the first copies of the phase).  begin() is separate from run_tiles so that the epilogue of the previous
 // branch -- at the start of the kernel, the loads of the query rows and of the routing rows -- runs while the first
@@ -462,7 +462,7 @@ __device__ __forceinline__ OwnTiles<G, SrcFn> own_tiles(int n, SrcFn src, char *
     return OwnTiles<G, SrcFn>{n, src, lds, qbi, sub, lane16};
 }
 
-template <class G>
+template <class G, typename SrcFn>
 struct SharedTiles {
     static constexpr bool EXACT = false;
     static constexpr int NST = G::NSLOT, KN = G::K_BYTES / 1024, VN = G::V_BYTES / 1024;
@@ -473,25 +473,27 @@ struct SharedTiles {
     static_assert(KI == VI && KW == VW && (KW == G::WAVES || KW + VW == G::WAVES), "");
     static_assert(KW * KI == KN && VW * VI == VN, "");
     const int n;
-    const char *const base;
+    const SrcFn src;  // address of the image of tile tau
     char *const lds;
     const int wave;
     const uint32_t lane16;
     __device__ __forceinline__ char *stage(int tau) const { return lds + (tau & (NST - 1)) * G::TILE; }
     __device__ __forceinline__ void issue_k(int tau) const {
         if (KW < G::WAVES && wave >= KW) return;
+        const char *tile = src(tau);
 #pragma unroll
         for (int j = 0; j < KI; ++j) {
             const int i = wave + KW * j;
-            copy_kb_to_lds(base + (int64_t)tau * G::TILE + i * 1024, lane16, stage(tau) + i * 1024);
+            copy_kb_to_lds(tile + i * 1024, lane16, stage(tau) + i * 1024);
         }
     }
     __device__ __forceinline__ void issue_v(int tau) const {
         if (VW < G::WAVES && wave < G::WAVES - VW) return;
+        const char *tile = src(tau) + G::K_BYTES;
 #pragma unroll
         for (int j = 0; j < VI; ++j) {
             const int i = (VW < G::WAVES ? wave - (G::WAVES - VW) : wave) + VW * j;
-            copy_kb_to_lds(base + (int64_t)tau * G::TILE + G::K_BYTES + i * 1024, lane16, stage(tau) + G::K_BYTES + i * 1024);
+            copy_kb_to_lds(tile + i * 1024, lane16, stage(tau) + G::K_BYTES + i * 1024);
         }
     }
     __device__ __forceinline__ void begin() const {
@@ -503,6 +505,11 @@ struct SharedTiles {
             if (tau < n) issue_v(tau);
     }
 };
+
+template <class G, typename SrcFn>
+__device__ __forceinline__ SharedTiles<G, SrcFn> shared_tiles(int n, SrcFn src, char *lds, int wave, uint32_t lane16) {
+    return SharedTiles<G, SrcFn>{n, src, lds, wave, lane16};
+}
 
 // Three tiles are in flight in a wavefront: step t runs
 // mfma_block with QK of its tile t+1, the exponentials of tile t and PV of tile t-1, so every MFMA
@@ -631,7 +638,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
 // Optionally stores the un-gated branch output and its log-sum-exp.
 template <class G>
 __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, int branch, int64_t row0, int head,
-                                              int wave, int lane, char *lds) {
+                                              int64_t gtile, int wave, int lane, char *lds) {
     constexpr int D = G::D;
     const int r = lane & 31, hh = lane >> 5;
     char *tr = lds + wave * G::ROWS * G::OUT_ROW;  // output staging region of this wavefront
@@ -680,10 +687,8 @@ __device__ __forceinline__ void finish_branch(WaveCtx<G> &c, const FwdArgs &a, i
             } else {
                 // bf16 pairs in accumulator order: 8 bytes per lane and fragment, fully coalesced; in LDS for the
                 // first wavefronts of the workgroup (behind the ring), in the scratch buffer for the others
-                // (the scratch buffer holds the query tiles of wavefronts GSUM_LDS_WAVES .. WAVES - 1 only)
-                const int64_t gtile = (row0 / (32 * G::WAVES)) * (G::WAVES - G::GSUM_LDS_WAVES) + (wave - G::GSUM_LDS_WAVES);
-                uint2 *slot = reinterpret_cast<uint2 *>(a.gsum) +
-                              ((gtile * a.h + head) * (G::ND * 4) + dt * 4 + gq) * 64 + lane;
+                // (the scratch buffer holds the query tiles of wavefronts GSUM_LDS_WAVES .. WAVES - 1 only: number gtile)
+                uint2 *slot = reinterpret_cast<uint2 *>(a.gsum) + (gtile * (G::ND * 4) + dt * 4 + gq) * 64 + lane;
                 uint2 *slot_lds =
                     reinterpret_cast<uint2 *>(lds + G::LDS_BYTES + wave * G::GSUM_LDS_BYTES) + (dt * 4 + gq) * 64 + lane;
                 const bool in_lds = G::GSUM_LDS_WAVES == G::WAVES || wave < G::GSUM_LDS_WAVES;
@@ -773,9 +778,14 @@ __device__ __forceinline__ WinRange window_range(const FwdArgs &a, int qb) {
 
 // CNT: a.count is given (variable number of active tokens per block).
 // WIDE: routing rows of 65..128 entries (two per lane of the list holder instead of one).
-template <class G, bool CNT, bool WIDE>
+// HEADS: the workgroup has two query heads of one key/value head and one query block, instead of one head and two query
+// blocks: all three branches then read the same tiles, which are copied to LDS once for both, four stages deep.  A copy costs
+// a SIMD about 25 cycles of its MFMA rate, in time (it takes the LDS) and in the clock that is left (the chip is at its power limit: the
+// step of a wavefront at d = 32 alone, in nominal cycles per MFMA, without copies 96, with those of a tile shared by four wavefronts
+// 101, by two 106).
+template <class G, bool CNT, bool WIDE, bool HEADS>
 __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward_kernel(FwdArgs a) {
-    constexpr int D = G::D, NP = G::NP;
+    constexpr int D = G::D, NP = HEADS ? 1 : G::NP;  // query blocks of the workgroup
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     // XCD-aware numbering: hardware deals consecutive workgroups round-robin to the 8 XCDs
     // and runs them roughly in launch order.  All XCDs work on the same head at the same time (so the
@@ -783,12 +793,15 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
     // keys/values fit every L2), each XCD on its own contiguous eighth of the head's query blocks
     // (so neighbouring windows and routed blocks meet in its L2).
     const int xcd = blockIdx.x & 7, slot_id = blockIdx.x >> 3;
-    const int head = slot_id / a.groups_per_xcd;
+    const int unit = slot_id / a.groups_per_xcd;  // head, or pair of heads
     const int group = xcd * a.groups_per_xcd + slot_id % a.groups_per_xcd;
     if (group >= a.groups_per_head) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int qbi = wave / G::NW, sub = wave % G::NW;  // query block inside the group, wavefront inside the block
+    const int sub = wave % G::NW;              // wavefront inside the block
+    const int qbi = HEADS ? 0 : wave / G::NW;  // query block inside the group
+    const int head = HEADS ? 2 * unit + wave / G::NW : unit;
+    const int64_t gtile = (int64_t)(2 * group + wave - G::GSUM_LDS_WAVES) * (HEADS ? a.h / 2 : a.h) + unit;
     const int r = lane & 31, hh = lane >> 5;
     const int qb = group * NP + qbi;
     const bool active = qb < a.nb;  // a trailing group may have fewer than NP query blocks
@@ -804,7 +817,8 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
     // The first copies go out before anything else.  (Slots that no copy fills hold anything: run_tiles reads the tiles of
     // the phase only.)
     const int n_cmp = (a.nbc + 31) / 32;
-    const SharedTiles<G> cmp_tiles{n_cmp, a.kvc + head_kvc, lds, wave, c.lane16};
+    const char *const base_c = a.kvc + head_kvc;
+    const auto cmp_tiles = shared_tiles<G>(n_cmp, [=](int t) { return base_c + (int64_t)t * G::TILE; }, lds, wave, c.lane16);
     cmp_tiles.begin();
     {
         // (an inactive wavefront reads the rows of block 0: finite values, results discarded)
@@ -875,6 +889,12 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
         run_tiles<G>(c, n_cmp, cmp_tiles, mask_tile, sl2);
     }
 
+    auto tiles_of = [&](int n, auto src) {
+        if constexpr (HEADS)
+            return shared_tiles<G>(n, src, lds, wave, c.lane16);
+        else
+            return own_tiles<G>(n, src, lds, qbi, sub, c.lane16);
+    };
     // ---------------- selected branch: every token of the routed blocks
     {
         // entry u of the row / of the counts (wave-uniform u)
@@ -908,10 +928,10 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
                 }
             }
         };
-        const auto tiles = own_tiles<G>(2 * my_valid, src, lds, qbi, sub, c.lane16);
+        const auto tiles = tiles_of(2 * my_valid, src);
         end_phase();
         tiles.begin();
-        if (active) finish_branch<G>(c, a, 0, row0, head, wave, lane, lds);
+        if (active) finish_branch<G>(c, a, 0, row0, head, gtile, wave, lane, lds);
         reset_branch<G>(c);
         run_tiles<G>(c, 2 * max_valid, tiles, mask_tile, sl2);
     }
@@ -952,15 +972,15 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
                 mask_scores(lo, min(hi, cap), sc, j0, lane);
             }
         };
-        const auto tiles = own_tiles<G>(active ? mine.st1 - mine.st0 : 0, src, lds, qbi, sub, c.lane16);
+        const auto tiles = tiles_of(active ? mine.st1 - mine.st0 : 0, src);
         end_phase();
         tiles.begin();
-        if (active) finish_branch<G>(c, a, 1, row0, head, wave, lane, lds);
+        if (active) finish_branch<G>(c, a, 1, row0, head, gtile, wave, lane, lds);
         reset_branch<G>(c);
         run_tiles<G>(c, n_max, tiles, mask_tile, sl2);
         __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         wg_barrier();  // the tile slots are about to be reused for the output rows
-        if (active) finish_branch<G>(c, a, 2, row0, head, wave, lane, lds);
+        if (active) finish_branch<G>(c, a, 2, row0, head, gtile, wave, lane, lds);
     }
 }
 
@@ -1023,7 +1043,7 @@ struct TeamTiles {
     __device__ __forceinline__ int in_flight_first() const { return min(NST - 1, n - 1) + min(NST - 2, n); }
 };
 
-template <class G, class TM, bool CNT, bool WIDE>
+template <class G, bool CNT, bool WIDE, class TM>
 __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forward_teams(FwdArgs a) {
     constexpr int D = G::D, NB = TM::NB, NT = TM::NT;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -1446,29 +1466,33 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
             ++a.teams[most];
         }
     }
-    a.groups_per_head = nb_wg == 0 ? (s.nb + NP - 1) / NP : (s.nb + nb_wg - 1) / nb_wg;
+    // A workgroup of two heads wherever heads that share keys and values come in pairs.  Whole call, two query blocks / two heads:
+    // 196 K tokens, 32 heads of 32 on 2, rows of 80 10.61 / 10.21 ms; ragged spatial blocks, 8 heads of 64 on 2, training step 548 / 542 us.
+    const bool heads = nb_wg == 0 && a.group % 2 == 0;
+    const int per_wg = nb_wg > 0 ? nb_wg : heads ? 1 : NP;  // query blocks
+    a.groups_per_head = (s.nb + per_wg - 1) / per_wg;
     a.groups_per_xcd = nb_wg == 0 ? (a.groups_per_head + 7) / 8 : (a.groups_per_head * s.h + 7) / 8;
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern;
     int lds, threads;
-#define LSRM_KERNEL(...) \
-    (cnt ? (wide ? reinterpret_cast<const void *>(&__VA_ARGS__, true, true>) : reinterpret_cast<const void *>(&__VA_ARGS__, true, false>)) \
-         : (wide ? reinterpret_cast<const void *>(&__VA_ARGS__, false, true>) : reinterpret_cast<const void *>(&__VA_ARGS__, false, false>)))
+#define LSRM_KERNEL(NAME, ...) \
+    (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>)) \
+         : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
     if (nb_wg == 1) {
-        kern = LSRM_KERNEL(nsa_forward_teams<G, One);
+        kern = LSRM_KERNEL(nsa_forward_teams, One);
         lds = One::LDS_ALL, threads = One::THREADS;
     } else if (nb_wg == 2) {
-        kern = LSRM_KERNEL(nsa_forward_teams<G, Two);
+        kern = LSRM_KERNEL(nsa_forward_teams, Two);
         lds = Two::LDS_ALL, threads = Two::THREADS;
     } else {
-        kern = LSRM_KERNEL(nsa_forward_kernel<G);
+        kern = heads ? LSRM_KERNEL(nsa_forward_kernel, true) : LSRM_KERNEL(nsa_forward_kernel, false);
         lds = G::LDS_ALL, threads = G::THREADS;  // the tile slots, then the LDS part of the running gated sum
     }
 #undef LSRM_KERNEL
     // (set on every launch: cheap, and right whichever device is current and whichever thread calls)
     LSRM_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
-    const dim3 grid(8 * a.groups_per_xcd * (nb_wg == 0 ? s.h : 1));
+    const dim3 grid(8 * a.groups_per_xcd * (nb_wg > 0 ? 1 : heads ? s.h / 2 : s.h));
     void *kargs[] = {&a};
     LSRM_HIP_CHECK(hipLaunchKernel(kern, grid, dim3(threads), kargs, lds, st));
     LSRM_HIP_CHECK(hipGetLastError());

@@ -578,3 +578,27 @@ def test_forward_few_and_many_query_blocks(B, oracle_lib, d, nb, heads, h_kv, to
     _log(f"[forward] {cfg.name}")
     cnt = _block_counts(cfg, 12) if with_counts else None
     _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("nb,heads,h_kv,topk,window,with_counts,channels", [
+    (130, 6, 3, 6, 320, False, False),   # groups of two: one workgroup a group
+    (49, 12, 2, 5, 96, True, False),     # of six, an odd number of blocks
+    (49, 18, 2, 5, 96, True, False),     # of nine: the general kernel's workgroups of two blocks
+    (33, 32, 2, 80, 160, False, True),   # of sixteen, wide rows, a gate per channel
+    (33, 32, 2, 100, 160, True, False),
+    (9, 64, 32, 3, 66, False, False),    # fewer blocks than a tile of pooled pairs, XCDs without any
+])
+def test_forward_two_heads_to_a_workgroup(B, oracle_lib, d, nb, heads, h_kv, topk, window, with_counts, channels):
+    """Query heads that share a key/value head, two to a workgroup with one list of tiles for all branches: rows of every
+    length (none, one, full), so that branches of 0 .. 200 tiles go through the four slots."""
+    cfg = I.small_config(name=f"f-heads-d{d}-nb{nb}-h{heads}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=heads, d=d,
+                         topk=topk, window=window, seed=nb + 1, h_kv=h_kv, gate_channels=channels)
+    rng = np.random.default_rng(nb)
+    idx = np.full((nb, topk), -1, dtype=np.int32)
+    for r in range(nb):
+        n = (0, 1, 2, topk // 2, topk)[r % 5]
+        idx[r, np.sort(rng.choice(topk, size=n, replace=False))] = rng.integers(0, nb, size=n)
+    _log(f"[forward] {cfg.name}")
+    cnt = _block_counts(cfg, 14) if with_counts else None
+    _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
