@@ -79,6 +79,7 @@ struct FwdArgs {
     const int32_t *count;  // nullable [NB]: active tokens per block (its first count[b] slots)
     int groups_per_head, groups_per_xcd;  // query-block groups of one head, and the share of one XCD (nsa_forward_teams: of all heads)
     int teams[3];  // nsa_forward_teams: teams of each branch
+    const uint16_t *kc, *vc;  // nsa_forward_teams with PAIRS: the pooled pairs
     float scale_log2e, scale;
 };
 
@@ -560,7 +561,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         if (t + 1 < n) mask_tile(t + 1, s_next);
     };
     if constexpr (Tiles::EXACT)
-        wait_copies<Tiles::KI, Tiles::MOST>(n > 0 ? tiles.in_flight_first() : 0);
+        wait_copies<Tiles::KI, Tiles::MOST>(tiles.n_copied > 0 ? tiles.in_flight_first() : 0);
     else
         __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
     wg_barrier();
@@ -994,13 +995,19 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 // 3 K for each epilogue, on SIMDs with one wavefront or none.
 // Attention step, nsa_forward_kernel and this: that problem 19.9 -> 14.8 us; 43 blocks, 3 heads of 128, 9 routed blocks, window
 // 192: 33.8 -> 15.6 us (what remains is the copies' latency, two stages deep: 2000 cycles a step, 1400 without copies).
-template <class G, int NB_, int NT_, int NST_>
+// PAIRS: the workgroups make the images of the pooled pairs by themselves (FwdArgs::kc, vc), all of them, behind the slots.
+template <class G, int NB_, int NT_, int NST_, bool PAIRS_>
 struct Teams {
+    static constexpr bool PAIRS = PAIRS_;
     static constexpr int NB = NB_, NT = NT_, NST = NST_;  // query blocks of a workgroup; teams of one; stages of a team
     static constexpr int THREADS = 64 * G::NW * NT * NB;
     static constexpr int PITCH = G::D + 4;  // floats of a row of a team's result: 16-byte aligned, rows spread over the banks
     static constexpr int TILES_BYTES = NB * NT * NST * G::TILE, SUM_BYTES = NB * NT * kBlock * (PITCH + 2) * 4;
     static constexpr int LDS_ALL = TILES_BYTES > SUM_BYTES ? TILES_BYTES : SUM_BYTES;
+    // Tiles of pooled pairs that fit a CU's LDS behind the slots (what the teams add up at the end takes their place): 8 at d = 64, 2
+    // at d = 128.
+    static constexpr int MAX_PAIRS = (160 * 1024 - TILES_BYTES) / G::TILE;
+    static constexpr int lds_with_pairs(int tiles) { return tiles * G::TILE > LDS_ALL - TILES_BYTES ? TILES_BYTES + tiles * G::TILE : LDS_ALL; }
     static constexpr int WAVES_PER_SIMD = (THREADS / 64 + 3) / 4;  // (one workgroup per CU)
     static_assert(LDS_ALL <= 160 * 1024 && NT >= 3, "");
 };
@@ -1011,11 +1018,12 @@ struct TeamTiles {
     static constexpr bool EXACT = true;
     static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
     const int n;
+    const int n_copied;  // n, or 0: the tiles are there already, one behind the other from `lds` on
     const SrcFn src;
     char *const lds;  // the slots of the team
     const int sub;
     const uint32_t lane16;
-    __device__ __forceinline__ char *stage(int tau) const { return lds + (tau & (NST - 1)) * G::TILE; }
+    __device__ __forceinline__ char *stage(int tau) const { return lds + (!TM::PAIRS || n_copied > 0 ? tau & (NST - 1) : tau) * G::TILE; }
     __device__ __forceinline__ void issue_part(const char *tile, char *slot, int n_inst) const {
 #pragma unroll 8
         for (int j = 0; j < n_inst; ++j) {
@@ -1023,24 +1031,26 @@ struct TeamTiles {
             copy_kb_to_lds(tile + i * 1024, lane16, slot + i * 1024);
         }
     }
-    __device__ __forceinline__ void issue_k(int tau) const { issue_part(src(tau), stage(tau), KI); }
+    __device__ __forceinline__ void issue_k(int tau) const {
+        if (!TM::PAIRS || n_copied > 0) issue_part(src(tau), stage(tau), KI);
+    }
     __device__ __forceinline__ void issue_v(int tau) const {
-        issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
+        if (!TM::PAIRS || n_copied > 0) issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
     }
     // in the order K(0), K(1), V(0), K(2), V(1), ..
     __device__ __forceinline__ void begin() const {
 #pragma unroll
         for (int tau = 0; tau < NST; ++tau) {
-            if (tau < n) issue_k(tau);
-            if (tau >= 1 && tau < NST - 1 && tau - 1 < n) issue_v(tau - 1);
+            if (tau < n_copied) issue_k(tau);
+            if (tau >= 1 && tau < NST - 1 && tau - 1 < n_copied) issue_v(tau - 1);
         }
     }
     // Copies that may be in flight at barrier t, in units of KI instructions: behind K(t + 1) and V(t - 1) those of K(t + 2 ..) and
     // V(t ..) that were issued before it; ahead of the first step all but K(0).
     static constexpr int MOST = 2 * NST - 3;
     static_assert(KI == VI, "");
-    __device__ __forceinline__ int in_flight(int t) const { return min(NST - 2, max(0, n - 2 - t)) + min(NST - 2, max(0, n - t)); }
-    __device__ __forceinline__ int in_flight_first() const { return min(NST - 1, n - 1) + min(NST - 2, n); }
+    __device__ __forceinline__ int in_flight(int t) const { return min(NST - 2, max(0, n_copied - 2 - t)) + min(NST - 2, max(0, n_copied - t)); }
+    __device__ __forceinline__ int in_flight_first() const { return min(NST - 1, n_copied - 1) + min(NST - 2, n_copied); }
 };
 
 template <class G, bool CNT, bool WIDE, class TM>
@@ -1164,8 +1174,43 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
             mask_scores(lo, to, sc, j0, lane);
         }
     };
-    const TeamTiles<G, TM, decltype(src)> tiles{n, src, slots, sub, c.lane16};
+    const bool there = TM::PAIRS && cmp;
+    char *const pairs = lds + TM::TILES_BYTES;
+    const TeamTiles<G, TM, decltype(src)> tiles{n, there ? 0 : n, src, there ? pairs + t0 * G::TILE : slots, sub, c.lane16};
     tiles.begin();
+    if constexpr (TM::PAIRS) {
+        // The images of all pooled pairs of this key/value head (see pack_block), rows past the end as zeros: a launch of its own took 3 us
+        // and the time to enqueue it.  The first barrier of run_tiles publishes them.  A thread turns eight rows of V by eight channels.
+        constexpr int CHUNKS = D / 8;
+        auto chunk = [&](const uint16_t *from, int pair, int ch) {
+            return pair < a.nbc ? *reinterpret_cast<const uint4 *>(from + ((int64_t)pair * a.h_kv + kvh) * D + 8 * ch) : make_uint4(0, 0, 0, 0);
+        };
+        for (int e = threadIdx.x; e < n_cmp * 4 * CHUNKS; e += TM::THREADS) {
+            const int pair = e / CHUNKS * 8, ch = e % CHUNKS, r32 = pair % 32;
+            uint4 row[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) row[x] = chunk(a.vc, pair + x, ch);
+            char *vt = pairs + pair / 32 * G::TILE + G::K_BYTES + (r32 / 16 * G::ND + ch / 4) * 1024 + (r32 / 8 % 2 * 32 + ch % 4 * 8) * 16;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {  // channel 8 ch + x of the eight rows
+                uint32_t w[4];
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    const uint4 &r0 = row[2 * y], &r1 = row[2 * y + 1];
+                    const uint32_t lo = x / 2 == 0 ? r0.x : x / 2 == 1 ? r0.y : x / 2 == 2 ? r0.z : r0.w;
+                    const uint32_t hi = x / 2 == 0 ? r1.x : x / 2 == 1 ? r1.y : x / 2 == 2 ? r1.z : r1.w;
+                    w[y] = x % 2 == 0 ? (lo & 0xffffu) | hi << 16 : lo >> 16 | (hi & 0xffff0000u);
+                }
+                *reinterpret_cast<uint4 *>(vt + x * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+#pragma unroll 2
+        for (int e = threadIdx.x; e < n_cmp * 32 * CHUNKS; e += TM::THREADS) {
+            const int pair = e / CHUNKS, ch = e % CHUNKS, r32 = pair % 32;
+            *reinterpret_cast<uint4 *>(pairs + pair / 32 * G::TILE + ch * 512 + ((r32 & ~12) | ((r32 & 4) << 1) | ((r32 & 8) >> 1)) * 16) =
+                chunk(a.kc, pair, ch);
+        }
+    }
     // A thread finishes 8 channels of NIT rows: their gates are requested now.
     constexpr int CH = D / 8, NIT = (NB * kBlock * CH + TM::THREADS - 1) / TM::THREADS;
     const int n_rows = kBlock * min(NB, a.nb - group * NB);
@@ -1427,14 +1472,6 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
         if (rc != LSRM_OK) return rc;
         a.blk_seg = gt.blk_seg;
     }
-    const int pair_blocks = (s.nbc + 63) / 64;
-    if (!s.kv_packed)
-        hipLaunchKernelGGL(pack_both<D>, dim3(s.nb + pair_blocks, s.h_kv), dim3(256), 0, st, s.nb, s.nbc, d_k, d_v, ws + w.kv, d_kc,
-                           d_vc, ws + w.kvc, s.h_kv, a.count);
-    else
-        hipLaunchKernelGGL((pack_tiles<D>), dim3(pair_blocks, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
-                           (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
-    LSRM_HIP_CHECK(hipGetLastError());
     a.kv = ws + w.kv;
     a.kvc = ws + w.kvc;
     a.gsum = reinterpret_cast<uint16_t *>(ws + w.gsum);
@@ -1444,8 +1481,10 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // round of workgroups); 254 x 2: 28.4 and 34.1 / 26.5, 31.7 and 35.4 / 29.0; 258 x 2: 31.5 and 43.7 / 40.3, 36.8 and 46.1 / 45.6,
     // 59.4 and 67.9.  Workgroups are what counts, two query blocks or an odd one: 17 x 30 are 270.
     // (At d = 128 a wavefront's registers leave no room for the twelve of two query blocks.)
-    using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2>;
-    using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2>;
+    using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2, false>;
+    using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2, false>;
+    using OnePairs = Teams<G, 1, One::NT, One::NST, true>;
+    using TwoPairs = Teams<G, Two::NB, Two::NT, Two::NST, true>;
     const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
     const int64_t longest = std::max(tiles[0], std::max(tiles[1], tiles[2])), all = (int64_t)tiles[0] + tiles[1] + tiles[2];
     // Of two query blocks every branch has one team.  Where one is nearly all there is and long, the others' ends save less than
@@ -1472,6 +1511,19 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     const int per_wg = nb_wg > 0 ? nb_wg : heads ? 1 : NP;  // query blocks
     a.groups_per_head = (s.nb + per_wg - 1) / per_wg;
     a.groups_per_xcd = nb_wg == 0 ? (a.groups_per_head + 7) / 8 : (a.groups_per_head * s.h + 7) / 8;
+    // The workgroups make the images of the pooled pairs where a launch would do nothing else and their LDS holds them all.  A pass of packing
+    // and attention out of a graph, us, launch / own images: 16 blocks x 1 head of 32 14.6 / 13.1, 96 x 4 20.5 / 18.9, 300 x 1 24.2 / 22.9; of 64
+    // 96 x 4 25.4 / 23.4, 256 x 1 22.6 / 21.8; of 128 64 x 4 30.4 / 28.3.
+    const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? One::MAX_PAIRS : nb_wg == 2 ? Two::MAX_PAIRS : 0);
+    if (own_pairs) a.kc = d_kc, a.vc = d_vc;
+    const int pair_blocks = own_pairs ? 0 : (s.nbc + 63) / 64;
+    if (!s.kv_packed)
+        hipLaunchKernelGGL(pack_both<D>, dim3(s.nb + pair_blocks, s.h_kv), dim3(256), 0, st, s.nb, s.nbc, d_k, d_v, ws + w.kv, d_kc,
+                           d_vc, ws + w.kvc, s.h_kv, a.count);
+    else if (!own_pairs)
+        hipLaunchKernelGGL((pack_tiles<D>), dim3(pair_blocks, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
+                           (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
+    LSRM_HIP_CHECK(hipGetLastError());
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern;
     int lds, threads;
@@ -1479,11 +1531,11 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>)) \
          : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
     if (nb_wg == 1) {
-        kern = LSRM_KERNEL(nsa_forward_teams, One);
-        lds = One::LDS_ALL, threads = One::THREADS;
+        kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, OnePairs) : LSRM_KERNEL(nsa_forward_teams, One);
+        lds = own_pairs ? One::lds_with_pairs(tiles_c) : One::LDS_ALL, threads = One::THREADS;
     } else if (nb_wg == 2) {
-        kern = LSRM_KERNEL(nsa_forward_teams, Two);
-        lds = Two::LDS_ALL, threads = Two::THREADS;
+        kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, TwoPairs) : LSRM_KERNEL(nsa_forward_teams, Two);
+        lds = own_pairs ? Two::lds_with_pairs(tiles_c) : Two::LDS_ALL, threads = Two::THREADS;
     } else {
         kern = heads ? LSRM_KERNEL(nsa_forward_kernel, true) : LSRM_KERNEL(nsa_forward_kernel, false);
         lds = G::LDS_ALL, threads = G::THREADS;  // the tile slots, then the LDS part of the running gated sum

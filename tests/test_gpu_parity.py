@@ -602,3 +602,34 @@ def test_forward_two_heads_to_a_workgroup(B, oracle_lib, d, nb, heads, h_kv, top
     _log(f"[forward] {cfg.name}")
     cnt = _block_counts(cfg, 14) if with_counts else None
     _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
+
+
+@pytest.mark.parametrize("d,nb,heads,h_kv", [(32, 1, 3, 3), (32, 96, 4, 1), (32, 512, 1, 1), (64, 33, 4, 4), (64, 96, 4, 2),
+                                             (64, 256, 1, 1), (64, 257, 1, 1), (128, 31, 6, 2), (128, 64, 4, 4), (128, 65, 3, 1)])
+def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv):
+    """Small calls behind lsrm_nsa_compress_pack make the images of the pooled pairs in LDS, as many tiles as it holds: bit
+    for bit what the packing launch of the two-pass call gives, for whole and partly filled last tiles, for pairs that
+    are not the averages of k and v, in a workspace that holds anything."""
+    import torch
+    cfg = I.small_config(name=f"f-own-d{d}-nb{nb}-h{heads}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=heads, d=d, topk=4,
+                         window=96, seed=nb, h_kv=h_kv)
+    _log(f"[forward] {cfg.name}")
+    q, k, v = (G.bf16_dev(x) for x in I.make_qkv(cfg))
+    gates = torch.from_numpy(I.make_gates(cfg)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    idx = torch.randint(-1, nb, (nb, cfg.topk), generator=gen, device="cuda", dtype=torch.int32)
+    kc, vc = (torch.randn((nb, h_kv, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    p = G.params_for(B, cfg)
+    got = []
+    for packed in (1, 0):
+        ws = B.alloc_workspace(p, B.LSRM_WS_FORWARD)
+        ws.fill_(0xFF)
+        p.kv_packed = packed
+        if packed:
+            B.lsrm_nsa_compress_pack(p, k, v, torch.empty_like(kc), torch.empty_like(vc), ws)
+        res = [torch.empty_like(q), torch.empty((3, cfg.n, heads), device="cuda"),
+               torch.empty((3, cfg.n, heads, d), dtype=torch.bfloat16, device="cuda")]
+        B.lsrm_nsa_forward(p, q, k, v, kc, vc, idx, gates, *res, ws)
+        got.append(res)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
