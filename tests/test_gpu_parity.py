@@ -633,3 +633,12 @@ def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv):
         got.append(res)
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_calls_take_the_current_stream(B):
+    import torch
+    side = torch.cuda.Stream()
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream and B._stream(side) == side.cuda_stream
+    with torch.cuda.stream(side):
+        assert B._stream(None) == side.cuda_stream
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream != side.cuda_stream
