@@ -424,7 +424,7 @@ __device__ __forceinline__ void end_phase() {
 template <class G, typename SrcFn>
 struct OwnTiles {
     static constexpr int NP = G::NP, NST = G::NST;
-    static constexpr bool EXACT = false;
+    static constexpr bool EXACT = false, MEET = false;
     static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
     static_assert(G::NW == 2, "two wavefronts per query block");
     static_assert((NST & (NST - 1)) == 0 && NST >= 2, "");
@@ -465,7 +465,7 @@ __device__ __forceinline__ OwnTiles<G, SrcFn> own_tiles(int n, SrcFn src, char *
 
 template <class G, typename SrcFn>
 struct SharedTiles {
-    static constexpr bool EXACT = false;
+    static constexpr bool EXACT = false, MEET = false;
     static constexpr int NST = G::NSLOT, KN = G::K_BYTES / 1024, VN = G::V_BYTES / 1024;
     static constexpr int KI = (KN + G::WAVES - 1) / G::WAVES, VI = (VN + G::WAVES - 1) / G::WAVES;
     static constexpr int KW = KN / KI, VW = VN / VI;  // wavefronts that copy: the first KW the K part, the last VW the V part
@@ -541,7 +541,10 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
             wait_copies<Tiles::KI, Tiles::MOST>(tiles.in_flight(t));
         else
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
-        wg_barrier();
+        if constexpr (Tiles::MEET)
+            tiles.meet(t);
+        else
+            wg_barrier();
         if (t + NST < n) tiles.issue_k(t + NST);
         if (t + NST - 2 < n) tiles.issue_v(t + NST - 2);
     };
@@ -627,7 +630,7 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         pv_drain<G>(c, vq, P[0], v_last);
         done = 2;
     }
-    for (int t = done; t <= n_steps; ++t) {
+    for (int t = done; !Tiles::MEET && t <= n_steps; ++t) {
         __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
         wg_barrier();
     }
@@ -996,9 +999,13 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 // Attention step, nsa_forward_kernel and this: that problem 19.9 -> 14.8 us; 43 blocks, 3 heads of 128, 9 routed blocks, window
 // 192: 33.8 -> 15.6 us (what remains is the copies' latency, two stages deep: 2000 cycles a step, 1400 without copies).
 // PAIRS: the workgroups make the images of the pooled pairs by themselves (FwdArgs::kc, vc), all of them, behind the slots.
-template <class G, int NB_, int NT_, int NST_, bool PAIRS_>
+// MEET: the two wavefronts of a team wait for each other only in a step, not for all teams, by two numbers a team behind everything else
+// (TeamTiles::meet).  A barrier keeps all in step, copying and computing at the same times, as slow as the slowest: with packing, out of a graph,
+// us, 16 blocks x 1 head of 32 13.2 / 12.5, 128 x 2 19.2 / 18.3; of 64 33 x 4 16.6 / 15.8, 65 x 4 24.0 / 22.8, 200 x 1 26.8 / 25.6, 96 x 4 the
+// same.  Not at d = 128 (128 x 2 34.8 / 34.4, 33 x 4 22.4 / 22.7), nor where the pairs leave the numbers no room (8 tiles of d = 64).
+template <class G, int NB_, int NT_, int NST_, bool PAIRS_, bool MEET_ = (G::D <= 64)>
 struct Teams {
-    static constexpr bool PAIRS = PAIRS_;
+    static constexpr bool PAIRS = PAIRS_, MEET = MEET_;
     static constexpr int NB = NB_, NT = NT_, NST = NST_;  // query blocks of a workgroup; teams of one; stages of a team
     static constexpr int THREADS = 64 * G::NW * NT * NB;
     static constexpr int PITCH = G::D + 4;  // floats of a row of a team's result: 16-byte aligned, rows spread over the banks
@@ -1006,8 +1013,12 @@ struct Teams {
     static constexpr int LDS_ALL = TILES_BYTES > SUM_BYTES ? TILES_BYTES : SUM_BYTES;
     // Tiles of pooled pairs that fit a CU's LDS behind the slots (what the teams add up at the end takes their place): 8 at d = 64, 2
     // at d = 128.
-    static constexpr int MAX_PAIRS = (160 * 1024 - TILES_BYTES) / G::TILE;
-    static constexpr int lds_with_pairs(int tiles) { return tiles * G::TILE > LDS_ALL - TILES_BYTES ? TILES_BYTES + tiles * G::TILE : LDS_ALL; }
+    static constexpr int STEPS_BYTES = MEET ? NB * NT * 8 : 0;
+    static constexpr int MAX_PAIRS = (160 * 1024 - STEPS_BYTES - TILES_BYTES) / G::TILE;
+    static constexpr __host__ __device__ int steps_at(int tiles) {
+        return PAIRS && tiles * G::TILE > LDS_ALL - TILES_BYTES ? TILES_BYTES + tiles * G::TILE : LDS_ALL;
+    }
+    static constexpr int lds_bytes(int tiles) { return steps_at(tiles) + STEPS_BYTES; }
     static constexpr int WAVES_PER_SIMD = (THREADS / 64 + 3) / 4;  // (one workgroup per CU)
     static_assert(LDS_ALL <= 160 * 1024 && NT >= 3, "");
 };
@@ -1015,12 +1026,13 @@ struct Teams {
 template <class G, class TM, typename SrcFn>
 struct TeamTiles {
     static constexpr int NST = TM::NST;
-    static constexpr bool EXACT = true;
+    static constexpr bool EXACT = true, MEET = TM::MEET;
     static constexpr int KI = G::K_BYTES / 1024 / G::NW, VI = G::V_BYTES / 1024 / G::NW, PER_STEP = KI + VI;
     const int n;
     const int n_copied;  // n, or 0: the tiles are there already, one behind the other from `lds` on
     const SrcFn src;
     char *const lds;  // the slots of the team
+    int *const steps;  // [2] in LDS: steps that the team's wavefronts have come to
     const int sub;
     const uint32_t lane16;
     __device__ __forceinline__ char *stage(int tau) const { return lds + (!TM::PAIRS || n_copied > 0 ? tau & (NST - 1) : tau) * G::TILE; }
@@ -1036,6 +1048,16 @@ struct TeamTiles {
     }
     __device__ __forceinline__ void issue_v(int tau) const {
         if (!TM::PAIRS || n_copied > 0) issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
+    }
+    // The barrier of a team: a wavefront says that it has come to step t (its copies and reads are waited for) and looks until the
+    // other has, which runs as many steps.
+    __device__ __forceinline__ void meet(int t) const {
+        const uint32_t at = (uint32_t)(uintptr_t)steps;
+        asm volatile("ds_write_b32 %0, %1" ::"v"(at + 4 * sub), "v"(t + 1) : "memory");
+        int other;
+        do {
+            asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(other) : "v"(at + 4 * (1 - sub)) : "memory");
+        } while (__builtin_amdgcn_readfirstlane(other) <= t);
     }
     // in the order K(0), K(1), V(0), K(2), V(1), ..
     __device__ __forceinline__ void begin() const {
@@ -1176,7 +1198,9 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
     };
     const bool there = TM::PAIRS && cmp;
     char *const pairs = lds + TM::TILES_BYTES;
-    const TeamTiles<G, TM, decltype(src)> tiles{n, there ? 0 : n, src, there ? pairs + t0 * G::TILE : slots, sub, c.lane16};
+    int *const steps = reinterpret_cast<int *>(lds + TM::steps_at(n_cmp)) + 2 * (qbi * NT + team);
+    if (TM::MEET && lane == 0) steps[sub] = 0;
+    const TeamTiles<G, TM, decltype(src)> tiles{n, there ? 0 : n, src, there ? pairs + t0 * G::TILE : slots, steps, sub, c.lane16};
     tiles.begin();
     if constexpr (TM::PAIRS) {
         // The images of all pooled pairs of this key/value head (see pack_block), rows past the end as zeros: a launch of its own took 3 us
@@ -1484,6 +1508,7 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2, false>;
     using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2, false>;
     using OnePairs = Teams<G, 1, One::NT, One::NST, true>;
+    using OneFull = Teams<G, 1, One::NT, One::NST, true, false>;  // (as many pairs as there can be)
     using TwoPairs = Teams<G, Two::NB, Two::NT, Two::NST, true>;
     const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
     const int64_t longest = std::max(tiles[0], std::max(tiles[1], tiles[2])), all = (int64_t)tiles[0] + tiles[1] + tiles[2];
@@ -1514,7 +1539,7 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // The workgroups make the images of the pooled pairs where a launch would do nothing else and their LDS holds them all.  A pass of packing
     // and attention out of a graph, us, launch / own images: 16 blocks x 1 head of 32 14.6 / 13.1, 96 x 4 20.5 / 18.9, 300 x 1 24.2 / 22.9; of 64
     // 96 x 4 25.4 / 23.4, 256 x 1 22.6 / 21.8; of 128 64 x 4 30.4 / 28.3.
-    const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? One::MAX_PAIRS : nb_wg == 2 ? Two::MAX_PAIRS : 0);
+    const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? OneFull::MAX_PAIRS : nb_wg == 2 ? TwoPairs::MAX_PAIRS : 0);
     if (own_pairs) a.kc = d_kc, a.vc = d_vc;
     const int pair_blocks = own_pairs ? 0 : (s.nbc + 63) / 64;
     if (!s.kv_packed)
@@ -1531,11 +1556,14 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>)) \
          : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
     if (nb_wg == 1) {
-        kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, OnePairs) : LSRM_KERNEL(nsa_forward_teams, One);
-        lds = own_pairs ? One::lds_with_pairs(tiles_c) : One::LDS_ALL, threads = One::THREADS;
+        const bool full = tiles_c > OnePairs::MAX_PAIRS;
+        kern = !own_pairs ? LSRM_KERNEL(nsa_forward_teams, One)
+               : full     ? LSRM_KERNEL(nsa_forward_teams, OneFull)
+                          : LSRM_KERNEL(nsa_forward_teams, OnePairs);
+        lds = !own_pairs ? One::lds_bytes(tiles_c) : full ? OneFull::lds_bytes(tiles_c) : OnePairs::lds_bytes(tiles_c), threads = One::THREADS;
     } else if (nb_wg == 2) {
         kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, TwoPairs) : LSRM_KERNEL(nsa_forward_teams, Two);
-        lds = own_pairs ? Two::lds_with_pairs(tiles_c) : Two::LDS_ALL, threads = Two::THREADS;
+        lds = own_pairs ? TwoPairs::lds_bytes(tiles_c) : Two::lds_bytes(tiles_c), threads = Two::THREADS;
     } else {
         kern = heads ? LSRM_KERNEL(nsa_forward_kernel, true) : LSRM_KERNEL(nsa_forward_kernel, false);
         lds = G::LDS_ALL, threads = G::THREADS;  // the tile slots, then the LDS part of the running gated sum
