@@ -17,7 +17,7 @@
 //                    partial sums sum_parts adds in order); MODE 0: token keys, the query tiles
 //                    of the window and of the reverse routing list (query blocks in ascending order),
 //                    longest walks first -- accumulates dK^T and dV^T in registers, adds
-//                    the pooled gradients / 64.  Long walks, and the heads of a group, are dealt to several
+//                    the pooled gradients / 64.  Long walks, and the heads of large groups, are dealt to several
 //                    workgroups, whose sums sum_walks adds in order before finishing the rows.
 // Small problems go through three launches instead (bwd_prepare, bwd_walks_small, sum_walks): their walks run beside each
 // other, and all sums of token keys meet the pooled gradients in the last one.
@@ -32,6 +32,7 @@
 // nothing inside a loop may make the compiler wait for all memory operations (see tr_issue, run_segment).
 #include "lsrm_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -76,7 +77,7 @@ struct BwdArgs {
     int nt;               // query / key tiles of 32 tokens
     int nbp, tiles_per_split, n_split;  // pooled keys, rounded up; the query ranges of their walks
     // Token keys: a key block's walk -- the query tiles of its window, then two per entry of its reverse list -- is dealt to
-    // several workgroups where it is long.  With grouped-query heads the query heads of a group go to hsplit
+    // several workgroups where it is long.  The query heads of a large group go to hsplit
     // workgroups, hpw heads each; and a walk of more than part_steps tiles is cut into parts of that many (cut_window = 0:
     // the window, of unknown length, goes to the first part and is not counted).  A (key block, part) is a task;
     // order / order_part [<= max_tasks] hold the tasks, longest first: the order the workgroups start in.  Where a block's
@@ -1670,9 +1671,6 @@ __global__ __launch_bounds__(256) void sum_walks(BwdArgs a, int n_split) {
     *reinterpret_cast<uint2 *>(a.dv + dst) = wv;
 }
 
-// the shortest part a token-key walk is cut into, in query tiles
-constexpr int kMinPart = 16;
-
 // Whether bwd_prepare does what else takes five launches: few enough table entries to be counted by every block's workgroup, and a
 // grid that one direction holds.  Backward, five launches / bwd_prepare (us; blocks x heads, entries): 96 x 4, 768 118 / 99; 192 x 8 of
 // 128, 1536 430 / 412; 337 x 8 (2), 6740 532 / 511; 544 x 32 (2), 16320 3972 / 3935; 896 x 2, 14336 431 / 423; 896 x 8 1327 / 1319; 1020 x 4,
@@ -1761,13 +1759,22 @@ WsLayout ws_layout(const Shape &s) {
     }
     w.part_k = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
     w.part_v = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
-    // Token keys.  With grouped-query heads a workgroup would walk group x as many steps while there are group x
-    // fewer workgroups, so the heads of a group are dealt to up to 8 workgroups (as long as the fp32 sums stay within
-    // 2 GiB of workspace).  And no single walk may set the kernel's time: geometric routing makes some blocks popular,
-    // and a small problem has too few walks to fill the chip, which then waits for the latency of their steps (1 to 2 us
-    // each).  A walk is cut where it would take more than half of what an evenly filled chip needs for all of them --
-    // longest first, a shorter walk never ends last -- but not below kMinPart tiles: there a workgroup's start and its
-    // sums (32 KB at d = 64, written and read) cost more than the shorter walk gains.
+    // Token keys.  No single walk may set the kernel's time: geometric routing makes some blocks popular, and a small problem has too
+    // few walks to fill the chip, which then waits for the latency of their steps (1 to 2 us each).  A walk is cut where it would take more
+    // than a share of what an evenly filled chip needs for all of them -- longest first, a shorter walk never ends last: half
+    // of it, a quarter with grouped-query heads, where a cut is what spreads the heads of a group too -- but not below `least` steps:
+    // there a workgroup's start and its sums (32 KB at d = 64, written and read) cost more than the shorter walk gains.
+    // least, 16 to 64 steps (96 with grouped heads, where fewer workgroups are short of work): the less there is to do, the more every CU
+    // has to itself and the shorter a part may be.  Backward, 16 / with this, us: d = 64, 337 blocks x 8 heads (2) 364 / 352, 415 x 4 (2) 323 /
+    // 297, 150 x 1 110 / 103, 115 x 16 239 / 229, 455 x 1 89 / 84; d = 32, 591 x 1 120 / 101, 65 x 32 139 / 129; d = 128 in the joint launch, 71 x 4 (2)
+    // 107 / 97, 233 x 1 149 / 142; longer ones lose (d = 32, 169 x 12, 96 steps 154 for 145; d = 64, 96 x 4, 32 steps 52 for 47), and so does
+    // d = 128 in a launch of its own (278 x 1, 32 steps 121 for 114).
+    // With grouped-query heads a walk has group x as many steps.  The heads of a group used to be dealt to up to 8 workgroups; the sums
+    // that costs (8 times 64 KB a block, key/value head and part at d = 64) took more than it gave once walks were cut, except for large
+    // groups in large problems, where two workgroups' images of q and dout are nearer to each other in memory: there they are dealt to two (as
+    // long as the sums stay within 2 GiB of workspace).  8 workgroups and half a share / this, us: 2069 blocks, 6 heads on 2 of 128 9285 /
+    // 8120, 2553 x 6 (1) of 32 3190 / 3060, 297 x 8 (1) of 64 395 / 367, 3307 x 4 (2) of 128 8390 / 7790; 3072 x 32 (2) of 32 32024 / 31900,
+    // undealt 32900.
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp = s.h / s.h_kv;
@@ -1776,16 +1783,19 @@ WsLayout ws_layout(const Shape &s) {
         const int64_t reach = (((64 + (int64_t)s.window) / 32 + 2) + 1) & ~(int64_t)1;
         const int64_t win = s.group_window ? 0 : reach < (int64_t)nt ? reach : (int64_t)nt;
         const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);
-        for (int ranges = 8; ranges >= 1; --ranges) {
+        const int64_t half_share = steps * s.h / slots / 2;
+        const bool own_launch = s.d == 128 && !w.small;
+        const int64_t least = std::max<int64_t>(16, std::min<int64_t>(own_launch ? 16 : grp > 1 ? 96 : 64, (s.d == 128 ? 4 : 6) * half_share));
+        for (int ranges = !w.small && grp >= 8 ? 2 : 1; ranges >= 1; --ranges) {
             w.hpw = (grp + ranges - 1) / ranges;
             w.hsplit = (grp + w.hpw - 1) / w.hpw;
-            int64_t len = steps * s.h_kv * w.hsplit / slots / 2;
+            int64_t len = steps * s.h_kv * w.hsplit / slots / (grp > 1 && !w.small ? 4 : 2);
+            len = std::max(len, (least + w.hpw - 1) / w.hpw);
             len = (len + 1) & ~(int64_t)1;
-            if (len < kMinPart) len = kMinPart;
             if (len > 0x3ffffffe) len = 0x3ffffffe;
             w.part_steps = (int)len;
             // bounds whatever the table holds: parts beyond a block's first number at most steps / len in all, and
-            // so do the blocks that are cut (steps / len is below 4 slots, or 2^20 where len is at its largest: no
+            // so do the blocks that are cut (steps / len is below 8 slots, or 2^20 where len is at its largest: no
             // sum below leaves 32 bits)
             const int64_t more = steps / len;
             w.max_split = (int)(more < s.nb ? more : s.nb);

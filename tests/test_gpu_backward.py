@@ -294,7 +294,7 @@ def test_backward_full_size_is_deterministic(B, oracle_lib):
 
 @pytest.mark.parametrize("d,heads,h_kv", [(64, 2, 2), (32, 6, 2), (128, 1, 1)])
 def test_backward_lists_cut_into_parts(B, oracle_lib, d, heads, h_kv):
-    """Walks at the edges of the parts they are cut into (16 tiles at this size, 6 of them the window's away from the ends of
+    """Walks at the edges of the parts they are cut into (16 tiles at this size, 6 with three heads to a key/value head, 6 of them the window's away from the ends of
     the sequence): lists of 4, 5, 6 and 13, 14 entries and one of an entry per row, without grouped heads (only cut
     blocks take the summing pass) and with them (all do)."""
     cfg = I.small_config(name=f"b-parts-d{d}", n_obj=45 * 64, n_views=1, grid=16, heads=heads, d=d, topk=6, window=96,
@@ -324,7 +324,7 @@ def test_backward_unlimited_window(B, oracle_lib, d, heads, h_kv):
 
 @pytest.mark.parametrize("d,heads,h_kv,window", [(64, 1, 1, 1024), (128, 1, 1, 962), (32, 4, 2, 962)])
 def test_backward_walks_cut_inside_the_window(B, oracle_lib, d, heads, h_kv, window):
-    """Windows of two and more parts (at this size a walk is cut every 16 tiles): parts of window tiles only, one that
+    """Windows of two and more parts (at this size a walk is cut every 16 tiles, every 8 with two heads to a key/value head): parts of window tiles only, one that
     holds the window's end and list entries, and the odd tile by which a window of an odd number of tiles falls short of
     its even share.  Lists of 0, 1, 8 and 14 entries behind it; without grouped heads (only cut blocks take the summing
     pass) and with them (all do)."""
@@ -446,3 +446,28 @@ def test_backward_pooled_keys_at_the_edges_of_their_groups(B, oracle_lib, d, n_b
     ref = oracle_lib.nsa_backward_sampled(*args, blocks, blocks, some, kv_heads=kv)
     rows = (np.asarray(blocks)[:, None] * 64 + np.arange(64)[None]).reshape(-1)
     _assert_grads((got[0][rows][:, some], got[1][rows][:, kv], got[2][rows][:, kv]), ref, cfg.name)
+
+
+@pytest.mark.parametrize("d,heads,h_kv,channels", [(32, 9, 1, False), (64, 8, 1, False), (32, 7, 1, True), (128, 4, 2, False)])
+def test_backward_heads_of_a_group_dealt_to_two_or_to_one(B, oracle_lib, d, heads, h_kv, channels):
+    """Groups of eight and more heads in the general launches go to two workgroups (nine: five and four), smaller ones and the joint
+    launches of small problems keep theirs together; walks cut into parts of few tiles by many heads, the most popular into dozens.
+    Bar: 2e-2 plus 2^-7 of the largest reference value of the row, as for the other large sums over a group."""
+    n_blocks, topk, wide = 130, 4, 127
+    cfg = I.small_config(name=f"b-dealt-d{d}-h{heads}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
+                         window=224, seed=79, h_kv=h_kv, gate_channels=channels)
+    rng = np.random.default_rng(8)
+    idx = np.stack([rng.choice(cfg.nb // 2, size=topk, replace=False) for _ in range(cfg.nb)]).astype(np.int32)
+    idx[:, 0] = np.where(np.arange(cfg.nb) % 2, 5, 70)
+    idx[3] = -1
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    holes = np.full((cfg.nb, wide - topk), -1, dtype=np.int32)
+    ref = None
+    for what, c, table in (("small", cfg, idx), ("general", dataclasses.replace(cfg, topk=wide), np.concatenate([idx, holes], axis=1))):
+        got, args = _case(B, oracle_lib, c, idx=table)
+        ref = oracle_lib.nsa_backward(*args) if ref is None else ref
+        for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+            excess = np.abs(g - r) - (G.MAX_ABS_TOL + np.abs(r).max(axis=-1, keepdims=True) * 2.0 ** -7)
+            _, rl = G.attention_errors(g, r)
+            _log(f"[backward] {cfg.name} {what} {name}: worst excess over the bar {excess.max():.3e}, rel-L2 {rl:.3e}")
+            assert excess.max() <= 0.0 and rl <= G.REL_L2_TOL, (what, name, float(excess.max()), rl)
