@@ -1733,7 +1733,8 @@ WsLayout ws_layout(const Shape &s) {
     // allow), so the kernel takes ceil(workgroups / slots) rounds of (tiles per range) x (query heads per key/value
     // head) steps; every range also costs its partial sums, written here and read back by the token-key kernel.
     // n minimises that: e.g. at 848 workgroups per range and 512 slots, one range runs 2 rounds where 1.66 would
-    // do, three ranges run 5 rounds of a third of the length (17 % less).
+    // do, three ranges run 5 rounds of a third of the length (17 % less).  At most 96: 297 blocks x 8 heads (1) of 64, at most 64 / 96 / 128
+    // 370 / 356 / 352 us, 499 x 3 (1) of 128 610 / 595 / 592, 1740 x 1 of 32 214 / 208 / 208, but 337 x 8 (2) of 64 354 / 353 / 358.
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp_q = s.h / s.h_kv;
@@ -1741,7 +1742,7 @@ WsLayout ws_layout(const Shape &s) {
         const double step_seconds = wg_keys == 128 ? 1.9e-6 : 1.1e-6 * s.d / 128, range_steps = range_bytes / 4e12 / step_seconds;
         double best = 0;
         int best_n = 1;
-        for (int n = 1; n <= 64; ++n) {
+        for (int n = 1; n <= 96; ++n) {
             const int64_t tiles = ((int64_t)nt + n - 1) / n;
             if (tiles <= 0) break;
             const int64_t n_eff = ((int64_t)nt + tiles - 1) / tiles;
@@ -1766,7 +1767,7 @@ WsLayout ws_layout(const Shape &s) {
     // there a workgroup's start and its sums (32 KB at d = 64, written and read) cost more than the shorter walk gains.
     // least, 16 to 64 steps (96 with grouped heads, where fewer workgroups are short of work): the less there is to do, the more every CU
     // has to itself and the shorter a part may be.  Backward, 16 / with this, us: d = 64, 337 blocks x 8 heads (2) 364 / 352, 415 x 4 (2) 323 /
-    // 297, 150 x 1 110 / 103, 115 x 16 239 / 229, 455 x 1 89 / 84; d = 32, 591 x 1 120 / 101, 65 x 32 139 / 129; d = 128 in the joint launch, 71 x 4 (2)
+    // 297, 150 x 1 110 / 98, 115 x 16 239 / 229, 455 x 1 89 / 84; d = 32, 591 x 1 120 / 101, 65 x 32 139 / 129; d = 128 in the joint launch, 71 x 4 (2)
     // 107 / 97, 233 x 1 149 / 142; longer ones lose (d = 32, 169 x 12, 96 steps 154 for 145; d = 64, 96 x 4, 32 steps 52 for 47), and so does
     // d = 128 in a launch of its own (278 x 1, 32 steps 121 for 114).
     // With grouped-query heads a walk has group x as many steps.  The heads of a group used to be dealt to up to 8 workgroups; the sums
@@ -1785,7 +1786,7 @@ WsLayout ws_layout(const Shape &s) {
         const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);
         const int64_t half_share = steps * s.h / slots / 2;
         const bool own_launch = s.d == 128 && !w.small;
-        const int64_t least = std::max<int64_t>(16, std::min<int64_t>(own_launch ? 16 : grp > 1 ? 96 : 64, (s.d == 128 ? 4 : 6) * half_share));
+        const int64_t least = std::max<int64_t>(16, std::min<int64_t>(own_launch ? 16 : grp > 1 ? 96 : 64, (s.d == 128 ? 4 : 8) * half_share));
         for (int ranges = !w.small && grp >= 8 ? 2 : 1; ranges >= 1; --ranges) {
             w.hpw = (grp + ranges - 1) / ranges;
             w.hsplit = (grp + w.hpw - 1) / w.hpw;
