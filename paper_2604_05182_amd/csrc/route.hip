@@ -514,7 +514,8 @@ __global__ __launch_bounds__(256) void select_3d(Route3d a, const float4 *__rest
 // read, four queries a wavefront side by side.  select_3d gives a workgroup to a query: chains of minima over 64
 // lanes, most lanes with nothing of their own.  Bound by instructions issued (the vector pipe is busy all the time), as
 // that one is, with a fifth of them per query: what several queries have in common is done once.
-// 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query.
+// 57 K tokens, 8 of 512 volume blocks and 24 tiles of 6 views each: 322 -> 87 us, 3330 -> 680 vector instructions a query; with a lane for a
+// view's nearest tiles (tile_window) and four lanes for a tile's points, 570, the whole call 77.7 -> 71.8 us.
 constexpr int kManyQueries = 16;
 constexpr int kNearList = 128, kNearFrom = 48;  // listed blocks of a query, the largest volume budget that a list is made for
 constexpr int kCommonList = 256, kCommonFrom = 256;  // listed blocks of a workgroup, the fewest blocks it is made from
@@ -536,38 +537,68 @@ struct __attribute__((packed, aligned(4))) FourPoints {
     float v[12];
 };
 
-// The window of 4 x 4 tiles of a view around a projection in which its nearest tiles are looked for.  Squares and sums round
-// monotonically, so a tile outside the window is no nearer than `beside`, the smallest of the tiles just outside its four
+// The window of 4 x 4 tiles of a view around a projection in which its nearest tiles are looked for, by one lane.  Squares and sums
+// round monotonically, so a tile outside the window is no nearer than `beside`, the smallest of the tiles just outside its four
 // borders in the row or column of the window's smallest difference: tiles of the window that are strictly nearer than
-// that are the nearest of the view.  beside < 0: no tile of the view is a candidate.
+// that are the nearest of the view.
+// (A lane keeps the four nearest of the 16 in order, 20 instructions a tile for 64 projections; 16 lanes that took minima of one
+// projection's tiles needed as many for four of them.)
+constexpr int kNoTiles = -1, kLookAtAll = 0, kPicked = 1 << 16;
 struct TileWindow {
-    float u, v, beside;
+    float u, v;
     int first;  // first row << 16 | first column
+    int picks;  // kNoTiles: no tile of the view is a candidate; kLookAtAll; or kPicked and the nearest tiles, four bits each: row, column
 };
-__device__ __forceinline__ TileWindow tile_window(float2 uv, int tg) {
+__device__ __forceinline__ TileWindow tile_window(float2 uv, int tg, int prefilter) {
     TileWindow w;
     w.u = uv.x;
     w.v = uv.y;
-    w.beside = -1.0f;
     w.first = 0;
+    w.picks = kNoTiles;
     if (dist2(uv, 0, 0) == __builtin_inff()) return w;
+    w.picks = kLookAtAll;
+    if (prefilter > 4) return w;
     const int top = max(tg - 4, 0);
     const float fi = floorf((fminf(fmaxf(uv.y, -1.0e6f), 1.0e6f) - 4.0f) * 0.125f);
     const float fj = floorf((fminf(fmaxf(uv.x, -1.0e6f), 1.0e6f) - 4.0f) * 0.125f);
     const int i0 = min(max((int)fi - 1, 0), top), j0 = min(max((int)fj - 1, 0), top);
+    w.first = i0 << 16 | j0;
     auto du2_at = [&](int j) { const float du = uv.x - (float)(8 * j + 4); return du * du; };
     auto dv2_at = [&](int i) { const float dv = uv.y - (float)(8 * i + 4); return dv * dv; };
-    float du2 = du2_at(j0), dv2 = dv2_at(i0);
-    for (int t = 1; t < min(4, tg); ++t) {
-        du2 = fminf(du2, du2_at(j0 + t));
-        dv2 = fminf(dv2, dv2_at(i0 + t));
+    float du2[4], dv2[4], du2_min = __builtin_inff(), dv2_min = __builtin_inff();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        du2[t] = du2_at(j0 + t);
+        dv2[t] = dv2_at(i0 + t);
+        if (t < tg) {
+            du2_min = fminf(du2_min, du2[t]);
+            dv2_min = fminf(dv2_min, dv2[t]);
+        }
     }
-    w.beside = __builtin_inff();
-    if (i0 > 0) w.beside = fminf(w.beside, du2 + dv2_at(i0 - 1));
-    if (i0 + 4 < tg) w.beside = fminf(w.beside, du2 + dv2_at(i0 + 4));
-    if (j0 > 0) w.beside = fminf(w.beside, du2_at(j0 - 1) + dv2);
-    if (j0 + 4 < tg) w.beside = fminf(w.beside, du2_at(j0 + 4) + dv2);
-    w.first = i0 << 16 | j0;
+    float beside = __builtin_inff();
+    if (i0 > 0) beside = fminf(beside, du2_min + dv2_at(i0 - 1));
+    if (i0 + 4 < tg) beside = fminf(beside, du2_min + dv2_at(i0 + 4));
+    if (j0 > 0) beside = fminf(beside, du2_at(j0 - 1) + dv2_min);
+    if (j0 + 4 < tg) beside = fminf(beside, du2_at(j0 + 4) + dv2_min);
+    // the four smallest, equal ones in the order of the tiles
+    unsigned d[4], at[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) d[r] = 0xffffffffu, at[r] = 0;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const unsigned x = t / 4 < tg && t % 4 < tg ? __float_as_uint(du2[t % 4] + dv2[t / 4]) : 0xffffffffu;
+        bool less[4];  // (of the four in order, the first that x is less than and all behind it move on)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) less[r] = x < d[r];
+#pragma unroll
+        for (int r = 3; r >= 0; --r) {
+            const bool moved = r > 0 && less[r > 0 ? r - 1 : 0];
+            d[r] = moved ? d[r > 0 ? r - 1 : 0] : less[r] ? x : d[r];
+            at[r] = moved ? at[r > 0 ? r - 1 : 0] : less[r] ? (unsigned)t : at[r];
+        }
+    }
+    const unsigned last = prefilter == 1 ? d[0] : prefilter == 2 ? d[1] : prefilter == 3 ? d[2] : d[3];
+    if (last < __float_as_uint(beside)) w.picks = (int)(kPicked | at[0] | at[1] << 4 | at[2] << 8 | at[3] << 12);
     return w;
 }
 
@@ -610,7 +641,7 @@ __global__ __launch_bounds__(16 * Q) void select_3d_many(Route3d a, int n_querie
     for (int i = threadIdx.x; any_img && i < nq * a.n_views; i += 16 * Q) {
         const int q = i / a.n_views;
         const float4 p = points[q];
-        windows[i] = tile_window(project(cams[i - q * a.n_views], p.x, p.y, p.z), a.tg);
+        windows[i] = tile_window(project(cams[i - q * a.n_views], p.x, p.y, p.z), a.tg, a.prefilter);
     }
 
     // The volume blocks that any of the workgroup's queries can select.  With R the largest distance of a query from the
@@ -662,53 +693,35 @@ __global__ __launch_bounds__(16 * Q) void select_3d_many(Route3d a, int n_querie
         out_d2[g * a.width + at] = __uint_as_float((unsigned)(key >> 32));
     };
 
-    // image rule, first two steps: the prefilter nearest tiles of every view by 2-D distance, then their point sets (four
-    // points per lane)
+    // image rule, first two steps: the prefilter nearest tiles of every view by 2-D distance, then their point sets
     for (int m = 0; ki > 0 && m < a.n_views; ++m) {
         const TileWindow w = windows[g * a.n_views + m];
-        const float2 uv = make_float2(w.u, w.v);
         unsigned long long *out = keys + m * a.prefilter;
-        if (w.beside < 0.0f) {
+        if (w.picks == kNoTiles) {
             for (int c = l; c < a.prefilter; c += 16) out[c] = kNoKey;
             continue;
         }
-        auto point_set = [&](int tile) {
-            return *reinterpret_cast<const FourPoints *>(pos_img + ((size_t)tile * kBlock + 4 * l) * 3);
-        };
-        auto measure = [&](int c, int tile, const FourPoints &pts) {
+        // smallest distance of four points of a tile in a row
+        auto measure = [&](int tile, int point) {
+            const FourPoints pts = *reinterpret_cast<const FourPoints *>(pos_img + ((size_t)tile * kBlock + point) * 3);
             unsigned d = 0xffffffffu;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 d = min(d, __float_as_uint(sqdist3(p.x, p.y, p.z, pts.v[3 * i], pts.v[3 * i + 1], pts.v[3 * i + 2])));
-            d = row_min_u32(d);
-            if (l == 0) out[c] = ((unsigned long long)d << 32) | (unsigned)(a.nb_obj + tile);
+            return d;
         };
-        bool found = false;
-        if (a.prefilter <= 4) {
-            const int i0 = w.first >> 16, j0 = w.first & 0xffff, ti = i0 + (l >> 2), tj = j0 + (l & 3);
-            unsigned key = ti < a.tg && tj < a.tg ? __float_as_uint(dist2(uv, ti, tj)) : 0xffffffffu, last = 0;
-            int tile[4];
+        if (w.picks != kLookAtAll) {
+            // four lanes a tile, 16 points each, four in a row at a time
+            const int r = l >> 2, at = (w.picks >> (4 * (r < a.prefilter ? r : 0))) & 15;
+            const int tile = m * tpv + ((w.first >> 16) + (at >> 2)) * a.tg + (w.first & 0xffff) + (at & 3);
+            unsigned d = 0xffffffffu;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                tile[r] = 0;
-                if (r < a.prefilter) {
-                    last = row_min_u32(key);
-                    const int at = (int)row_min_u32(key == last ? (unsigned)l : 16u);  // (lanes are in the order of the tiles)
-                    tile[r] = m * tpv + (i0 + (at >> 2)) * a.tg + j0 + (at & 3);
-                    key = l == at ? 0xffffffffu : key;
-                }
-            }
-            found = last < __float_as_uint(w.beside);
-            if (found) {
-                FourPoints pts[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) pts[r] = point_set(tile[r]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r < a.prefilter) measure(r, tile[r], pts[r]);
-            }
-        }
-        if (!found) {
+            for (int k = 0; k < 4; ++k) d = min(d, measure(tile, 16 * k + 4 * (l & 3)));
+            d = min(d, (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0xB1, 0xF, 0xF, false));  // quad_perm [1,0,3,2]
+            d = min(d, (unsigned)__builtin_amdgcn_update_dpp(0, (int)d, 0x4E, 0xF, 0xF, false));  // quad_perm [2,3,0,1]
+            if ((l & 3) == 0 && r < a.prefilter) out[r] = ((unsigned long long)d << 32) | (unsigned)(a.nb_obj + tile);
+        } else {
+            const float2 uv = make_float2(w.u, w.v);
             auto tile_key = [&](int t) { return make_key(dist2(uv, t / a.tg, t % a.tg), (unsigned)t); };
             LaneKeys held;
             held.scan(l, 16, tpv, tile_key, false, 0);
@@ -716,7 +729,8 @@ __global__ __launch_bounds__(16 * Q) void select_3d_many(Route3d a, int n_querie
                 const unsigned long long best = row_min_u64(held.mine);
                 held.take(best, l, 16, tpv, tile_key);
                 const int tile = m * tpv + (int)(unsigned)(best & 0xffffffffu);
-                measure(c, tile, point_set(tile));
+                const unsigned d = row_min_u32(measure(tile, 4 * l));
+                if (l == 0) out[c] = ((unsigned long long)d << 32) | (unsigned)(a.nb_obj + tile);
             }
         }
     }

@@ -213,3 +213,27 @@ def test_route_3d_many_queries(B, oracle_lib, n_blocks, n_views, grid, pre, budg
     ref = oracle_lib.route_3d(pos, pimg, cams, cfg.grid, width, pre, *budgets, per_token=per_token, queries=pick)
     idx, d2 = G.run_route_3d(B, cfg, pos, pimg, cams, width, pre, *budgets, per_token=per_token)
     _same((idx[pick], d2[pick]), ref)
+
+
+@pytest.mark.parametrize("grid", [8, 16, 24, 48])
+@pytest.mark.parametrize("pre", [1, 2, 3, 4])
+def test_route_3d_many_queries_between_tiles(B, oracle_lib, grid, pre):
+    """Projections on the borders and corners of tiles, inside the image, on its edge and outside it: two and four tiles at the
+    same distance, of which the lower ids are candidates (all of a view's where it has fewer than a window's sixteen)."""
+    pre = min(pre, (grid // 8) ** 2)
+    n_blocks = 48
+    cfg = I.small_config(name="r3-lattice", n_obj=64 * n_blocks, n_views=2, grid=grid, seed=grid + pre)
+    rng = np.random.default_rng(grid)
+    pos = np.zeros((cfg.n_obj, 3), dtype=np.float32)   # u = 4 x + cx, v = 4 y + cy, exactly
+    pos[:, :2] = rng.integers(-4, grid // 4 + 5, size=(cfg.n_obj, 2))
+    cams = np.zeros((2, 16), dtype=np.float32)
+    cams[:, :9] = np.eye(3).reshape(-1)
+    cams[:, 11] = 3
+    cams[:, 12:] = (12, 12, 0, 0)
+    cams[1, 14:] = (4, 8)
+    pimg = pos[rng.integers(0, cfg.n_obj, size=cfg.n_img)] + rng.normal(size=(cfg.n_img, 3)).astype(np.float32)
+    budgets = (4, 2 * pre, 4, 2 * pre)
+    _log(f"[route3d] lattice grid {grid} B^i={pre}")
+    assert cfg.n >= 2048 + 2 * cfg.nb_obj
+    args = (B, cfg, pos, pimg, cams, 4 + 2 * pre, pre, *budgets)
+    _same(G.run_route_3d(*args, per_token=True), oracle_lib.route_3d(pos, pimg, cams, grid, 4 + 2 * pre, pre, *budgets, per_token=True))
