@@ -355,11 +355,13 @@ __device__ __forceinline__ void prep_rows(const BwdArgs &a, PrepStage<D> &stage,
         if (b == 0 || a.gate_channels) *reinterpret_cast<uint4 *>(const_cast<char *>(a.img_do[b]) + dst) = stage[b][src];
 }
 template <int D>
-__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a) {
+__global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prep(BwdArgs a, GroupTableArgs tables) {
     __shared__ PrepStage<D> stage;
-    // (the counters of the reverse lists, which the next kernel increments: there are more threads than blocks)
+    // (the counters of the reverse lists, which the next kernel increments, and the tables of spatial blocks: there are more threads than twice
+    // the blocks)
     const int64_t gid = (int64_t)blockIdx.x * PrepGeo<D>::THREADS + threadIdx.x;
     if (gid < a.nb) a.rev_cnt[gid] = 0;
+    if (gid < tables.n) group_table_entry((int)gid, tables.ng, tables.nb, tables.goff, tables.count, tables.tab);
     prep_rows<D>(a, stage, blockIdx.x);
 }
 
@@ -638,7 +640,7 @@ __global__ void rev_sort_serial(BwdArgs a) {
 constexpr int kTableBlocks = 768, kTableEntries = 16384;  // (see small_table)
 template <int D>
 __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare(BwdArgs a, int64_t n_prep, int64_t n_token_wg, int64_t n_pack,
-                                                                    int all_slots) {
+                                                                    int all_slots, GroupTableArgs tables) {
     constexpr int THREADS = PrepGeo<D>::THREADS, WAVES = THREADS / 64, DEEP = 8, SUMS = 6;
     __shared__ union {
         PrepStage<D> prep;
@@ -656,6 +658,11 @@ __global__ __launch_bounds__(PrepGeo<D>::THREADS) void bwd_prepare(BwdArgs a, in
         return;
     }
     const int kb = (int)(blockIdx.x - n_prep - n_pack), t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (kb >= a.nb) {
+        const int i = (kb - a.nb) * THREADS + t;
+        if (i < tables.n) group_table_entry(i, tables.ng, tables.nb, tables.goff, tables.count, tables.tab);
+        return;
+    }
     const int n_entries = a.nb * a.topk, per_wave = (n_entries + WAVES - 1) / WAVES;
     const int e0 = min(wave * per_wave, n_entries), e1 = min(e0 + per_wave, n_entries);
     // the entries [e0, e1) of this wavefront, 64 at a time: take(first entry, this lane's, -1 past the end)
@@ -1824,7 +1831,7 @@ WsLayout ws_layout(const Shape &s) {
 }
 
 template <int D>
-lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
+lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &tables, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
     constexpr int LDS_TOKENS = DKV_LDS<D, 2, false>;
     const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
@@ -1832,8 +1839,9 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     const bool table = small_table(s);
     if (ev_start != nullptr) LSRM_HIP_CHECK(hipEventRecord(ev_start, st));
     if (table) {
-        hipLaunchKernelGGL(bwd_prepare<D>, dim3((unsigned)(n_prep + n_wg + s.nb)), dim3(PrepGeo<D>::THREADS), 0, st, a, n_prep,
-                           n_token_wg, n_wg, w.small ? 1 : 0);
+        const int n_tables = (tables.n + PrepGeo<D>::THREADS - 1) / PrepGeo<D>::THREADS;
+        hipLaunchKernelGGL(bwd_prepare<D>, dim3((unsigned)(n_prep + n_wg + s.nb + n_tables)), dim3(PrepGeo<D>::THREADS), 0, st, a, n_prep,
+                           n_token_wg, n_wg, w.small ? 1 : 0, tables);
         LSRM_HIP_CHECK(hipGetLastError());
     }
     if (w.small) {
@@ -1855,7 +1863,7 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const WsLayout &w, char
     LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&bwd_dkv_kernel<D, 0>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_TOKENS));
     if (!table) {
-        hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a);
+        hipLaunchKernelGGL(bwd_prep<D>, dim3((unsigned)n_prep), dim3(PrepGeo<D>::THREADS), 0, st, a, tables);
         LSRM_HIP_CHECK(hipGetLastError());
         const int64_t n_pack = n_wg + ((int64_t)s.nb * s.topk + 255) / 256;
         const dim3 pack_grid((unsigned)(n_pack < kPackMaxGrid ? n_pack : kPackMaxGrid),
@@ -1956,10 +1964,10 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.nb = s.nb;
     a.nbc = s.nbc;
     a.blk_grp = a.blk_seg = a.grp_tok = nullptr;
+    GroupTableArgs tables{};
     if (s.ng > 0) {
-        GroupTables gt;
-        lsrm_status rc = launch_group_tables(s, reinterpret_cast<int32_t *>(ws + w.gtab), &gt, st);
-        if (rc != LSRM_OK) return rc;
+        tables = group_table_args(s, reinterpret_cast<int32_t *>(ws + w.gtab));  // (the first launch makes them)
+        const GroupTables gt = group_tables_in(s, tables.tab);
         a.blk_grp = gt.blk_grp;
         a.grp_tok = gt.grp_tok;
         if (s.group_window) a.blk_seg = gt.blk_seg;
@@ -1992,9 +2000,9 @@ lsrm_status launch_backward(const Shape &s, const int32_t *seg_host, int n_seg, 
     a.n_split = w.n_split;
     a.scale = s.scale;
     a.sl2 = s.scale * kLog2e;
-    if (s.d == 32) return launch_backward_d<32>(s, a, w, ws, st, ev_start, ev_stop);
-    if (s.d == 64) return launch_backward_d<64>(s, a, w, ws, st, ev_start, ev_stop);
-    return launch_backward_d<128>(s, a, w, ws, st, ev_start, ev_stop);
+    if (s.d == 32) return launch_backward_d<32>(s, a, tables, w, ws, st, ev_start, ev_stop);
+    if (s.d == 64) return launch_backward_d<64>(s, a, tables, w, ws, st, ev_start, ev_stop);
+    return launch_backward_d<128>(s, a, tables, w, ws, st, ev_start, ev_stop);
 }
 
 }  // namespace lsrm

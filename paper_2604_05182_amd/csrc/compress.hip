@@ -192,48 +192,7 @@ __global__ __launch_bounds__(256) void pool_groups(int ng, int row_chunks, const
     }
 }
 
-// The tables the attention kernels look blocks up in (see GroupTables): one thread per block, then one per group.
-// A block's group is the last one that starts at or before it; blocks that no group covers (offsets that do not
-// reach N / 64) get zero entries (an empty window).  Written by one kernel and no memset, which callers that
-// capture the stream cannot replay; nothing outside the tables is written, whatever the offsets hold.
-__global__ __launch_bounds__(256) void group_tables(int ng, int nb, const int32_t *__restrict__ goff,
-                                                    const int32_t *__restrict__ count, int32_t *__restrict__ blk_grp,
-                                                    int32_t *__restrict__ blk_seg, int32_t *__restrict__ grp_tok) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nb) {
-        int lo = 0, hi = ng;  // goff[lo] <= i, if any is
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) / 2;
-            if (goff[mid] <= i) lo = mid; else hi = mid;
-        }
-        const int b0 = max(goff[lo], 0), b1 = min(goff[lo + 1], nb);
-        const bool covered = b0 <= i && i < b1;
-        blk_grp[i] = covered ? lo : 0;
-        blk_seg[2 * i] = covered ? b0 * kBlock : 0;
-        blk_seg[2 * i + 1] = covered ? b1 * kBlock : 0;
-    } else if (i < nb + ng) {
-        const int g = i - nb;
-        const int b0 = min(max(goff[g], 0), nb), b1 = min(goff[g + 1], nb);
-        int tokens = 0;
-        for (int b = b0; b < b1; ++b) tokens += count != nullptr ? count[b] : kBlock;
-        grp_tok[g] = tokens > 0 ? tokens : 1;
-    }
-}
-
 }  // namespace
-
-lsrm_status launch_group_tables(const Shape &s, int32_t *tab, GroupTables *out, hipStream_t st) {
-    out->blk_grp = out->blk_seg = out->grp_tok = nullptr;
-    if (s.ng <= 0) return LSRM_OK;
-    int32_t *blk_grp = tab, *blk_seg = tab + s.nb, *grp_tok = tab + 3 * (size_t)s.nb;
-    hipLaunchKernelGGL(group_tables, dim3((s.nb + s.ng + 255) / 256), dim3(256), 0, st, s.ng, s.nb, s.goff, s.count, blk_grp,
-                       blk_seg, grp_tok);
-    LSRM_HIP_CHECK(hipGetLastError());
-    out->blk_grp = blk_grp;
-    out->blk_seg = blk_seg;
-    out->grp_tok = grp_tok;
-    return LSRM_OK;
-}
 
 lsrm_status launch_compress(const Shape &s, const uint16_t *d_k, const uint16_t *d_v, uint16_t *d_kc,
                             uint16_t *d_vc, hipStream_t st) {

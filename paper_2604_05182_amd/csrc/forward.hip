@@ -1450,15 +1450,23 @@ __global__ __launch_bounds__(256) void pack_tiles(const uint16_t *__restrict__ k
                                                   uint16_t *__restrict__ vc = nullptr) {
     pack_block<D, POOL>(blockIdx.x, k, v, img, n_rows, h, n_tiles, count, kc, vc);
 }
-// Keys and values and the pooled pairs in one launch: the workgroups behind the nb blocks take the pairs, nbc of them.
+// What the attention kernels read besides the images that lsrm_nsa_compress_pack leaves, in one launch: those of the nbc pooled pairs, and
+// the tables of spatial blocks; without that call the images of keys and values too.  Workgroups in x: nb_kv blocks of keys and
+// values, n_pairs of the pairs, then the tables.
 template <int D>
-__global__ __launch_bounds__(256) void pack_both(int nb, int nbc, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
+__global__ __launch_bounds__(256) void pack_both(int nb_kv, int n_pairs, int nbc, const uint16_t *__restrict__ k, const uint16_t *__restrict__ v,
                                                  char *__restrict__ img, const uint16_t *__restrict__ kc,
                                                  const uint16_t *__restrict__ vc, char *__restrict__ img_c, int h,
-                                                 const int32_t *__restrict__ count) {
-    const bool pairs = (int)blockIdx.x >= nb;
-    pack_block<D, false>(pairs ? blockIdx.x - nb : blockIdx.x, pairs ? kc : k, pairs ? vc : v, pairs ? img_c : img,
-                         pairs ? nbc : (int64_t)nb * kBlock, h, pairs ? (nbc + 31) / 32 : 2 * nb, pairs ? nullptr : count, nullptr,
+                                                 const int32_t *__restrict__ count, GroupTableArgs tables) {
+    const int x = blockIdx.x;
+    if (x >= nb_kv + n_pairs) {
+        const int i = (x - nb_kv - n_pairs) * 256 + threadIdx.x;
+        if (blockIdx.y == 0 && i < tables.n) group_table_entry(i, tables.ng, tables.nb, tables.goff, tables.count, tables.tab);
+        return;
+    }
+    const bool pairs = x >= nb_kv;
+    pack_block<D, false>(pairs ? x - nb_kv : x, pairs ? kc : k, pairs ? vc : v, pairs ? img_c : img,
+                         pairs ? nbc : (int64_t)nb_kv * kBlock, h, pairs ? (nbc + 31) / 32 : 2 * nb_kv, pairs ? nullptr : count, nullptr,
                          nullptr);
 }
 
@@ -1490,11 +1498,10 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     constexpr int D = G::D, NP = G::NP;
     for (int i = 0; i <= n_seg; ++i) a.seg[i] = seg_host[i];
     const int tiles_c = (s.nbc + 31) / 32;
+    GroupTableArgs tables{};
     if (s.group_window) {
-        GroupTables gt;
-        lsrm_status rc = launch_group_tables(s, reinterpret_cast<int32_t *>(ws + w.gtab), &gt, st);
-        if (rc != LSRM_OK) return rc;
-        a.blk_seg = gt.blk_seg;
+        tables = group_table_args(s, reinterpret_cast<int32_t *>(ws + w.gtab));
+        a.blk_seg = group_tables_in(s, tables.tab).blk_seg;
     }
     a.kv = ws + w.kv;
     a.kvc = ws + w.kvc;
@@ -1541,13 +1548,11 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     // 96 x 4 25.4 / 23.4, 256 x 1 22.6 / 21.8; of 128 64 x 4 30.4 / 28.3.
     const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? OneFull::MAX_PAIRS : nb_wg == 2 ? TwoPairs::MAX_PAIRS : 0);
     if (own_pairs) a.kc = d_kc, a.vc = d_vc;
-    const int pair_blocks = own_pairs ? 0 : (s.nbc + 63) / 64;
-    if (!s.kv_packed)
-        hipLaunchKernelGGL(pack_both<D>, dim3(s.nb + pair_blocks, s.h_kv), dim3(256), 0, st, s.nb, s.nbc, d_k, d_v, ws + w.kv, d_kc,
-                           d_vc, ws + w.kvc, s.h_kv, a.count);
-    else if (!own_pairs)
-        hipLaunchKernelGGL((pack_tiles<D>), dim3(pair_blocks, s.h_kv), dim3(256), 0, st, d_kc, d_vc, ws + w.kvc,
-                           (int64_t)s.nbc, s.h_kv, tiles_c, (const int32_t *)nullptr);
+    const int nb_kv = s.kv_packed ? 0 : s.nb, pair_blocks = own_pairs ? 0 : (s.nbc + 63) / 64;
+    const int n_pack = nb_kv + pair_blocks + (tables.n + 255) / 256;
+    if (n_pack > 0)
+        hipLaunchKernelGGL(pack_both<D>, dim3(n_pack, s.h_kv), dim3(256), 0, st, nb_kv, pair_blocks, s.nbc, d_k, d_v, ws + w.kv, d_kc, d_vc,
+                           ws + w.kvc, s.h_kv, a.count, tables);
     LSRM_HIP_CHECK(hipGetLastError());
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern;

@@ -81,7 +81,44 @@ struct GroupTables {
     const int32_t *blk_grp, *blk_seg, *grp_tok;
 };
 inline size_t group_tables_bytes(const Shape &s) { return s.ng > 0 ? align_up(((size_t)3 * s.nb + s.ng) * 4, 256) : 0; }
-lsrm_status launch_group_tables(const Shape &s, int32_t *tab, GroupTables *out, hipStream_t st);
+inline GroupTables group_tables_in(const Shape &s, const int32_t *tab) {
+    return s.ng > 0 ? GroupTables{tab, tab + s.nb, tab + 3 * (size_t)s.nb} : GroupTables{nullptr, nullptr, nullptr};
+}
+// Entry i of the nb + ng that the tables have, by one thread; a launch that prepares something else makes them beside it (a launch of their
+// own took 5 us, in the forward and in the backward of each step).  A block's group is the last one that starts at or before it; blocks that
+// no group covers (offsets that do not reach N / 64) get zero entries (an empty window).  Nothing outside the tables is
+// written, whatever the offsets hold.
+__device__ __forceinline__ void group_table_entry(int i, int ng, int nb, const int32_t *__restrict__ goff, const int32_t *__restrict__ count,
+                                                  int32_t *__restrict__ tab) {
+    if (i < nb) {
+        int lo = 0, hi = ng;  // goff[lo] <= i, if any is
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (goff[mid] <= i) lo = mid; else hi = mid;
+        }
+        const int b0 = max(goff[lo], 0), b1 = min(goff[lo + 1], nb);
+        const bool covered = b0 <= i && i < b1;
+        int32_t *blk_seg = tab + nb;
+        tab[i] = covered ? lo : 0;
+        blk_seg[2 * i] = covered ? b0 * kBlock : 0;
+        blk_seg[2 * i + 1] = covered ? b1 * kBlock : 0;
+    } else if (i < nb + ng) {
+        const int g = i - nb;
+        const int b0 = min(max(goff[g], 0), nb), b1 = min(goff[g + 1], nb);
+        int tokens = 0;
+        for (int b = b0; b < b1; ++b) tokens += count != nullptr ? count[b] : kBlock;
+        tab[3 * (size_t)nb + g] = tokens > 0 ? tokens : 1;
+    }
+}
+// What a kernel needs to make them: n entries, none where it is 0.
+struct GroupTableArgs {
+    int n, ng, nb;
+    const int32_t *goff, *count;
+    int32_t *tab;
+};
+inline GroupTableArgs group_table_args(const Shape &s, int32_t *tab) {
+    return {s.ng > 0 ? s.nb + s.ng : 0, s.ng, s.nb, s.goff, s.count, tab};
+}
 
 lsrm_status launch_compress(const Shape &s, const uint16_t *d_k, const uint16_t *d_v, uint16_t *d_kc,
                             uint16_t *d_vc, hipStream_t st);  // honours s.count
