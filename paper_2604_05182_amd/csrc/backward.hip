@@ -10,8 +10,8 @@
 // With grouped-query heads a key/value head walks the query tiles of every query head that reads it.
 //
 // No floating-point atomics: the work is split into passes that each own their output rows.
-//   bwd_dq_kernel    one workgroup per (query block, head): walks the same key tiles as the forward
-//                    (pooled, routed, window) and accumulates dQ^T in registers.
+//   bwd_dq_kernel    one workgroup per (query block, head, or two heads of one key/value head): walks the same key
+//                    tiles as the forward (pooled, routed, window) and accumulates dQ^T in registers.
 //   bwd_dkv_kernel   one workgroup per (key block, key/value head): walks the query tiles that attend it --
 //                    MODE 1: pooled keys, every query tile of the sequence (split into ranges whose
 //                    partial sums sum_parts adds in order); MODE 0: token keys, the query tiles
@@ -774,19 +774,21 @@ __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, flo
 }
 
 // ---------------------------------------------------------------------------------------------
-// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head)
+// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head), or (HEADS) four wavefronts for two heads of one key/value head,
+// which read the same tiles: a tile's copies then serve both.  (Copies and reads of LDS bound this kernel beside the clock, see HEADS in
+// forward.hip.)
 // WIDE: routing rows of 65..128 entries (two per lane of the list holder instead of one).
-// lds: DQ_LDS bytes.  wg, head: numbers of the workgroup.
-template <int D>
-constexpr int DQ_LDS = kBwdNbuf * 2 * BGeo<D>::ROW;
-template <int D, bool WIDE>
-__device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int head) {
+// lds: DQ_LDS bytes.  wg, unit: numbers of the workgroup; unit: head, or pair of heads.
+template <int D, bool HEADS = false>
+constexpr int DQ_LDS = HEADS && 4 * 32 * BGeo<D>::OUT_ROW > kBwdNbuf * 2 * BGeo<D>::ROW ? 4 * 32 * BGeo<D>::OUT_ROW : kBwdNbuf * 2 * BGeo<D>::ROW;
+template <int D, bool WIDE, bool HEADS>
+__device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int unit) {
     using G = BGeo<D>;
     constexpr int NS = G::NS, ND = G::ND;
     constexpr int TILE = 2 * G::ROW;     // K rows | V rows (K^T is read out of the K rows, see mfma_tr)
     constexpr int NBUF = kBwdNbuf;  // tile buffers: copies run NBUF - 1 tiles ahead
     static_assert((G::ROW / 1024) % 2 == 0, "");
-    static_assert(2 * 32 * G::OUT_ROW <= NBUF * TILE, "output staging fits in the tile buffers");
+    static_assert((HEADS ? 4 : 2) * 32 * G::OUT_ROW <= DQ_LDS<D, HEADS>, "output staging fits in the tile buffers");
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD a contiguous range of
     // blocks so that neighbouring blocks (overlapping windows, similar routed sets) share its L2
     const int per_xcd = (a.nb + 7) / 8;
@@ -794,9 +796,10 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     if (qb >= a.nb) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int head = HEADS ? 2 * unit + (wave >> 1) : unit;
     const int r = lane & 31, hh = lane >> 5;
     const uint32_t lane16 = (uint32_t)lane * 16u;
-    const int64_t row0 = (int64_t)qb * 64 + 32 * wave;
+    const int64_t row0 = (int64_t)qb * 64 + 32 * (wave & 1);
     const int half_w = a.window / 2;
     const int kvh = head / a.group;  // key/value head of this query head
     const uint32_t tr_off = tr_lane_offset(lane), row_off = row_lane_offset(lane);
@@ -900,8 +903,17 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     static_assert(NBUF == 2, "");
     auto issue_tile = [&](const char *kimg, const char *vimg, int tile, char *buf) {
         const int64_t off = (int64_t)((uint32_t)tile * (uint32_t)a.h_kv + (uint32_t)kvh) * G::IMG;
-        copy_kb<G::ROW / 1024>(kimg + off, buf, wave, lane16);
-        copy_kb<G::ROW / 1024>(vimg + off, buf + G::ROW, wave, lane16);
+        if constexpr (HEADS) {  // K rows and V rows, one behind the other, dealt to four wavefronts
+            constexpr int KB = G::ROW / 1024;
+#pragma unroll
+            for (int j = 0; j < 2 * KB; j += 4) {
+                const int i = j + wave;
+                copy_kb_to_lds((i < KB ? kimg : vimg - G::ROW) + off + i * 1024, lane16, buf + i * 1024);
+            }
+        } else {
+            copy_kb<G::ROW / 1024>(kimg + off, buf, wave, lane16);
+            copy_kb<G::ROW / 1024>(vimg + off, buf + G::ROW, wave, lane16);
+        }
     };
     // tile of step t of the whole walk (used at the branch boundaries only)
     auto issue_any = [&](int t, char *buf) {
@@ -1067,11 +1079,12 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
         for (int i = 0; i < 16; ++i) x[dt][i] = acc[dt][i] * a.scale;
     store_rows_transposed<D>(x, lds + wave * 32 * G::OUT_ROW, a.dq + (row0 * a.h + head) * D, (int64_t)a.h * D, lane);
 }
-template <int D, bool WIDE>
-__global__ __launch_bounds__(128, 2) void bwd_dq_kernel(BwdArgs a) {
-    // (at d = 128 the 256-register budget of two workgroups per SIMD still holds: 64 accumulator registers)
-    __shared__ __attribute__((aligned(1024))) char lds[DQ_LDS<D>];
-    dq_walk<D, WIDE>(a, lds, blockIdx.x, blockIdx.y);
+template <int D, bool WIDE, bool HEADS>
+__global__ __launch_bounds__((HEADS ? 256 : 128), (D == 128 ? 2 : D == 64 ? 3 : 4)) void bwd_dq_kernel(BwdArgs a) {
+    // (at d = 128 the 256-register budget of two workgroups per SIMD still holds: 64 accumulator registers; at d = 64 wide rows fit the 168
+    // of three wavefronts only if the compiler is told to: 1536 blocks, 4 heads, rows of 80 2869 -> 2793 us the whole backward)
+    __shared__ __attribute__((aligned(1024))) char lds[DQ_LDS<D, HEADS>];
+    dq_walk<D, WIDE, HEADS>(a, lds, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1595,7 +1608,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
     wg -= n_dkv;
     if (wg < n_dq) {
         const int y = uniform(wg / n_dq_x);
-        dq_walk<D, WIDE>(a, lds, wg - y * n_dq_x, y);
+        dq_walk<D, WIDE, false>(a, lds, wg - y * n_dq_x, y);
         return;
     }
     wg -= n_dq;
@@ -1884,10 +1897,12 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &t
             LSRM_HIP_CHECK(hipGetLastError());
         }
     }
-    if (s.topk > 64)
-        hipLaunchKernelGGL((bwd_dq_kernel<D, true>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
-    else
-        hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3((s.nb + 7) / 8 * 8, s.h), dim3(128), 0, st, a);
+    // Two heads to a workgroup wherever heads that share keys and values come in pairs.  Whole backward, one head / two, us: 1536 blocks, rows
+    // of 32, 16 heads on 2 of 64 6237 / 6070, 8 on 2 of 128 6175 / 5989; rows of 80, 8 on 4 of 64 5415 / 5096; 900 blocks, 4 on 2 of 64 696 / 684.
+    const bool heads = a.group % 2 == 0;
+    const auto dq = s.topk > 64 ? (heads ? &bwd_dq_kernel<D, true, true> : &bwd_dq_kernel<D, true, false>)
+                                : (heads ? &bwd_dq_kernel<D, false, true> : &bwd_dq_kernel<D, false, false>);
+    hipLaunchKernelGGL(dq, dim3((s.nb + 7) / 8 * 8, heads ? s.h / 2 : s.h), dim3(heads ? 256 : 128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     auto pooled = [&](auto *kernel, int lds) -> lsrm_status {
         LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
