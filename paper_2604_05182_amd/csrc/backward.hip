@@ -10,8 +10,8 @@
 // With grouped-query heads a key/value head walks the query tiles of every query head that reads it.
 //
 // No floating-point atomics: the work is split into passes that each own their output rows.
-//   bwd_dq_kernel    one workgroup per (query block, head, or two heads of one key/value head): walks the same key
-//                    tiles as the forward (pooled, routed, window) and accumulates dQ^T in registers.
+//   bwd_dq_kernel    one workgroup per (query block, head), or for two heads of one key/value head or two blocks of one head: walks
+//                    the same key tiles as the forward (pooled, routed, window) and accumulates dQ^T in registers.
 //   bwd_dkv_kernel   one workgroup per (key block, key/value head): walks the query tiles that attend it --
 //                    MODE 1: pooled keys, every query tile of the sequence (split into ranges whose
 //                    partial sums sum_parts adds in order); MODE 0: token keys, the query tiles
@@ -774,29 +774,36 @@ __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, flo
 }
 
 // ---------------------------------------------------------------------------------------------
-// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head), or (HEADS) four wavefronts for two heads of one key/value head,
-// which read the same tiles: a tile's copies then serve both.  (Copies and reads of LDS bound this kernel beside the clock, see HEADS in
-// forward.hip.)
+// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head), or four wavefronts that share the copies of tiles
+// (copies and reads of LDS bound this kernel beside the clock, see HEADS in forward.hip):
+//   HEADS   two heads of one key/value head, which read the same tiles in all branches
+//   BLOCKS  two query blocks of one head, which share the tiles of the pooled keys; the others' each block copies for itself, and
+//           the barriers are common: a block with fewer steps waits for the other at the end
 // WIDE: routing rows of 65..128 entries (two per lane of the list holder instead of one).
-// lds: DQ_LDS bytes.  wg, unit: numbers of the workgroup; unit: head, or pair of heads.
-template <int D, bool HEADS = false>
-constexpr int DQ_LDS = HEADS && 4 * 32 * BGeo<D>::OUT_ROW > kBwdNbuf * 2 * BGeo<D>::ROW ? 4 * 32 * BGeo<D>::OUT_ROW : kBwdNbuf * 2 * BGeo<D>::ROW;
-template <int D, bool WIDE, bool HEADS>
+// lds: DQ_LDS bytes.  wg, unit: numbers of the workgroup; wg: query block or pair of them, unit: head or pair of heads.
+enum Pair { ALONE, HEADS, BLOCKS };
+template <int D, Pair PAIR = ALONE>
+constexpr int DQ_LDS = PAIR == BLOCKS ? 2 * kBwdNbuf * 2 * BGeo<D>::ROW
+                       : PAIR == HEADS && 4 * 32 * BGeo<D>::OUT_ROW > kBwdNbuf * 2 * BGeo<D>::ROW ? 4 * 32 * BGeo<D>::OUT_ROW : kBwdNbuf * 2 * BGeo<D>::ROW;
+template <int D, bool WIDE, Pair PAIR>
 __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int unit) {
     using G = BGeo<D>;
     constexpr int NS = G::NS, ND = G::ND;
     constexpr int TILE = 2 * G::ROW;     // K rows | V rows (K^T is read out of the K rows, see mfma_tr)
     constexpr int NBUF = kBwdNbuf;  // tile buffers: copies run NBUF - 1 tiles ahead
     static_assert((G::ROW / 1024) % 2 == 0, "");
-    static_assert((HEADS ? 4 : 2) * 32 * G::OUT_ROW <= DQ_LDS<D, HEADS>, "output staging fits in the tile buffers");
+    static_assert((PAIR != ALONE ? 4 : 2) * 32 * G::OUT_ROW <= DQ_LDS<D, PAIR>, "output staging fits in the tile buffers");
     // consecutive workgroup ids go round-robin to the 8 XCDs: give each XCD a contiguous range of
     // blocks so that neighbouring blocks (overlapping windows, similar routed sets) share its L2
-    const int per_xcd = (a.nb + 7) / 8;
-    const int qb = (wg & 7) * per_xcd + (wg >> 3);
-    if (qb >= a.nb) return;
+    const int n_units = PAIR == BLOCKS ? (a.nb + 1) / 2 : a.nb, per_xcd = (n_units + 7) / 8;
+    const int place = (wg & 7) * per_xcd + (wg >> 3);
+    if (place >= n_units) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int head = HEADS ? 2 * unit + (wave >> 1) : unit;
+    const int head = PAIR == HEADS ? 2 * unit + (wave >> 1) : unit;
+    const int blk = PAIR == BLOCKS ? wave >> 1 : 0;             // query block inside the workgroup
+    const bool active = PAIR != BLOCKS || 2 * place + blk < a.nb;  // (without one: copies and barriers only)
+    const int qb = PAIR == BLOCKS ? min(2 * place + blk, a.nb - 1) : place;
     const int r = lane & 31, hh = lane >> 5;
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const int64_t row0 = (int64_t)qb * 64 + 32 * (wave & 1);
@@ -871,7 +878,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
             return __builtin_amdgcn_readlane(reg[0], u);
         }
     };
-    const int ts = 2 * n_valid;
+    const int ts = active ? 2 * n_valid : 0;
     int seg_lo = 0, seg_hi = 0;
     if (a.blk_seg != nullptr) {  // the query's spatial block
         seg_lo = a.blk_seg[2 * qb];
@@ -892,7 +899,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     // active tokens of the blocks of the window range, one per lane (a range of more than 64 blocks falls back to
     // loading the count inside the loop)
     const int wcount = a.count != nullptr && (st0 >> 1) + lane < a.nb ? a.count[(st0 >> 1) + lane] : 64;
-    const int tw = k_end > k_start ? (k_end - 1) / 32 + 1 - st0 : 0;
+    const int tw = active && k_end > k_start ? (k_end - 1) / 32 + 1 - st0 : 0;
     const int T = tc + ts + tw;
     const int wlo = max(seg_lo, (int)row0 + r - half_w), whi = min(seg_hi, (int)row0 + r + half_w);
 
@@ -901,9 +908,15 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     // branch (tile lookup, image, mask rule, table entries) is fixed inside a loop; the first tile of the next
     // branch is requested in the last step of the one before it, so the pipeline never drains.
     static_assert(NBUF == 2, "");
-    auto issue_tile = [&](const char *kimg, const char *vimg, int tile, char *buf) {
+    // Two query blocks: the tiles of the compressed branch in the first buffer of either block, shared; then each block's own, from
+    // its second buffer on.
+    auto buffer = [&](int t) {
+        if constexpr (PAIR != BLOCKS) return lds + (t & 1) * TILE;
+        return lds + (t < tc ? 2 * (t & 1) : 2 * blk + ((t - tc + 1) & 1)) * TILE;
+    };
+    auto issue_tile = [&](auto shared, const char *kimg, const char *vimg, int tile, char *buf) {
         const int64_t off = (int64_t)((uint32_t)tile * (uint32_t)a.h_kv + (uint32_t)kvh) * G::IMG;
-        if constexpr (HEADS) {  // K rows and V rows, one behind the other, dealt to four wavefronts
+        if constexpr (PAIR == HEADS || (PAIR == BLOCKS && decltype(shared)::value)) {  // K rows and V rows, one behind the other, dealt to four wavefronts
             constexpr int KB = G::ROW / 1024;
 #pragma unroll
             for (int j = 0; j < 2 * KB; j += 4) {
@@ -911,19 +924,19 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
                 copy_kb_to_lds((i < KB ? kimg : vimg - G::ROW) + off + i * 1024, lane16, buf + i * 1024);
             }
         } else {
-            copy_kb<G::ROW / 1024>(kimg + off, buf, wave, lane16);
-            copy_kb<G::ROW / 1024>(vimg + off, buf + G::ROW, wave, lane16);
+            copy_kb<G::ROW / 1024>(kimg + off, buf, wave & 1, lane16);
+            copy_kb<G::ROW / 1024>(vimg + off, buf + G::ROW, wave & 1, lane16);
         }
     };
     // tile of step t of the whole walk (used at the branch boundaries only)
     auto issue_any = [&](int t, char *buf) {
         if (t < tc) {
-            issue_tile(a.img_kc, a.img_vc, t, buf);
+            issue_tile(std::true_type{}, a.img_kc, a.img_vc, t, buf);
         } else if (t < tc + ts) {
             const int u = t - tc;
-            issue_tile(a.img_k, a.img_v, 2 * entry(packed, u >> 1) + (u & 1), buf);
+            issue_tile(std::false_type{}, a.img_k, a.img_v, 2 * entry(packed, u >> 1) + (u & 1), buf);
         } else {
-            issue_tile(a.img_k, a.img_v, st0 + (t - tc - ts), buf);
+            issue_tile(std::false_type{}, a.img_k, a.img_v, st0 + (t - tc - ts), buf);
         }
     };
     // steps [t0, t1) of the walk, all of branch BR.  tile_fn(u): image tile of the u-th step of the branch;
@@ -940,8 +953,8 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
             // with tile t-1, whose buffer takes tile t+1
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
             wg_barrier();
-            char *nbuf = lds + ((t + 1) & 1) * TILE;
-            const char *tile_k = lds + (t & 1) * TILE;
+            char *nbuf = buffer(t + 1);
+            const char *tile_k = buffer(t);
             const char *base = tile_k + row_off;
 
             // The pieces of the step in a fixed order (a wavefront issues in order: what is to overlap has to alternate
@@ -960,7 +973,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
             __builtin_amdgcn_sched_barrier(0);
             // the copies of the next tile: their address arithmetic runs while the first reads land
             if (t + 1 < t1)
-                issue_tile(kimg, vimg, tile_fn(t + 1 - t0), nbuf);
+                issue_tile(std::integral_constant<bool, BR == 0>{}, kimg, vimg, tile_fn(t + 1 - t0), nbuf);
             else if (t + 1 < T)
                 issue_any(t + 1, nbuf);
             int j0, lo, hi;
@@ -1032,6 +1045,13 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     auto valid_keys = [&](int cnt, int half) { return min(32, max(0, cnt - 32 * half)); };
 
     if (T > 0) issue_any(0, lds);
+    int t_all = T;  // steps of the workgroup
+    if constexpr (PAIR == BLOCKS) {
+        int *const steps = reinterpret_cast<int *>(lds + 3 * TILE);  // (a buffer that step tc - 1 is the first to fill)
+        if (lane == 0) steps[wave] = T;
+        __syncthreads();
+        t_all = __builtin_amdgcn_readfirstlane(max(T, steps[wave ^ 2]));
+    }
     // pooled keys: only the last tile can reach past the end
     run_branch(0, tc, std::integral_constant<int, 0>{}, a.img_kc, a.img_vc, [&](int u) { return u; },
                [&](int u, int *j0, int *lo, int *hi) {
@@ -1071,7 +1091,9 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
                    }
                    return need;
                });
+    for (int t = T; PAIR == BLOCKS && t < t_all; ++t) wg_barrier();  // (the other block's steps)
     __syncthreads();  // the tile buffers become the output staging
+    if (!active) return;
     float x[ND][16];
 #pragma unroll
     for (int dt = 0; dt < ND; ++dt)
@@ -1079,12 +1101,12 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
         for (int i = 0; i < 16; ++i) x[dt][i] = acc[dt][i] * a.scale;
     store_rows_transposed<D>(x, lds + wave * 32 * G::OUT_ROW, a.dq + (row0 * a.h + head) * D, (int64_t)a.h * D, lane);
 }
-template <int D, bool WIDE, bool HEADS>
-__global__ __launch_bounds__((HEADS ? 256 : 128), (D == 128 ? 2 : D == 64 ? 3 : 4)) void bwd_dq_kernel(BwdArgs a) {
+template <int D, bool WIDE, Pair PAIR>
+__global__ __launch_bounds__((PAIR != ALONE ? 256 : 128), (D == 128 ? 2 : D == 64 ? 3 : 4)) void bwd_dq_kernel(BwdArgs a) {
     // (at d = 128 the 256-register budget of two workgroups per SIMD still holds: 64 accumulator registers; at d = 64 wide rows fit the 168
     // of three wavefronts only if the compiler is told to: 1536 blocks, 4 heads, rows of 80 2869 -> 2793 us the whole backward)
-    __shared__ __attribute__((aligned(1024))) char lds[DQ_LDS<D, HEADS>];
-    dq_walk<D, WIDE, HEADS>(a, lds, blockIdx.x, blockIdx.y);
+    __shared__ __attribute__((aligned(1024))) char lds[DQ_LDS<D, PAIR>];
+    dq_walk<D, WIDE, PAIR>(a, lds, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1559,6 +1581,7 @@ __device__ __forceinline__ void dkv_walk(const BwdArgs &a, char *lds, int wg, in
 // 203 / 206, 64 groups of 256 x 8 469 / 481; 448 x 8 1103 / 1100, 512 x 2 339 / 345, 520 x 8 1314 / 1312, 700 x 8 1843 / 1802, 896 x 8
 // 2469 / 2391, 1500 x 4 2514 / 2405.
 constexpr int kPooledWide = 512;
+constexpr int kPooledMany = 2048;  // dQ, see launch_backward_d
 
 // Number of a workgroup among the walks of pooled keys -> group of 32 * WV keys, key/value head, range of query tiles; false: none left.
 // Equal shares of all walks for the XCDs, and to each the key groups of one (head, range) beside each other: they read the same
@@ -1608,7 +1631,7 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
     wg -= n_dkv;
     if (wg < n_dq) {
         const int y = uniform(wg / n_dq_x);
-        dq_walk<D, WIDE, false>(a, lds, wg - y * n_dq_x, y);
+        dq_walk<D, WIDE, ALONE>(a, lds, wg - y * n_dq_x, y);
         return;
     }
     wg -= n_dq;
@@ -1900,9 +1923,15 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &t
     // Two heads to a workgroup wherever heads that share keys and values come in pairs.  Whole backward, one head / two, us: 1536 blocks, rows
     // of 32, 16 heads on 2 of 64 6237 / 6070, 8 on 2 of 128 6175 / 5989; rows of 80, 8 on 4 of 64 5415 / 5096; 900 blocks, 4 on 2 of 64 696 / 684.
     const bool heads = a.group % 2 == 0;
-    const auto dq = s.topk > 64 ? (heads ? &bwd_dq_kernel<D, true, true> : &bwd_dq_kernel<D, true, false>)
-                                : (heads ? &bwd_dq_kernel<D, false, true> : &bwd_dq_kernel<D, false, false>);
-    hipLaunchKernelGGL(dq, dim3((s.nb + 7) / 8 * 8, heads ? s.h / 2 : s.h), dim3(heads ? 256 : 128), 0, st, a);
+    // Two query blocks to a workgroup for other heads where the pooled keys are many.  One block / two, us: d = 128, 6688 blocks x 16 heads
+    // 128.9 / 127.9 ms, 5121 x 4 16371 / 16177, 2176 x 8 9258 / 9218, 1536 x 8 6446 / 6445, 641 x 8 2300 / 2330, 257 x 8 870 / 902; d = 64, 4864 x 2
+    // 3693 / 3630, 2816 x 4 3727 / 3693, 2048 x 8 3959 / 3923, 1536 x 8 3192 / 3184, 897 x 8 1670 / 1680; d = 32, 4864 x 6 8082 / 8001, 641 x 4 424 / 427.
+    const bool blocks = !heads && s.nbc >= kPooledMany;
+#define LSRM_DQ(PAIR) (s.topk > 64 ? &bwd_dq_kernel<D, true, PAIR> : &bwd_dq_kernel<D, false, PAIR>)
+    const auto dq = heads ? LSRM_DQ(HEADS) : blocks ? LSRM_DQ(BLOCKS) : LSRM_DQ(ALONE);
+#undef LSRM_DQ
+    const int n_units = blocks ? (s.nb + 1) / 2 : s.nb;
+    hipLaunchKernelGGL(dq, dim3((n_units + 7) / 8 * 8, heads ? s.h / 2 : s.h), dim3(heads || blocks ? 256 : 128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());
     auto pooled = [&](auto *kernel, int lds) -> lsrm_status {
         LSRM_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));

@@ -471,3 +471,25 @@ def test_backward_heads_of_a_group_dealt_to_two_or_to_one(B, oracle_lib, d, head
             _, rl = G.attention_errors(g, r)
             _log(f"[backward] {cfg.name} {what} {name}: worst excess over the bar {excess.max():.3e}, rel-L2 {rl:.3e}")
             assert excess.max() <= 0.0 and rl <= G.REL_L2_TOL, (what, name, float(excess.max()), rl)
+
+
+@pytest.mark.parametrize("d,n_blocks,topk,channels", [(32, 2049, 4, True), (64, 2049, 65, False), (64, 2080, 4, True), (128, 2049, 4, False),
+                                                      (128, 2048, 66, True)])
+def test_backward_two_query_blocks_to_a_workgroup(B, oracle_lib, d, n_blocks, topk, channels):
+    """From 2048 pooled keys on a workgroup of the dQ pass has two query blocks of a head: an odd number of blocks, partners with
+    rows of very different numbers of valid entries, in narrow and wide tables; heads with key/value heads of their own."""
+    heads = 3
+    cfg = I.small_config(name=f"b-two-blocks{n_blocks}-{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
+                         window=224, seed=80, gate_channels=channels)
+    assert cfg.nb == n_blocks
+    rng = np.random.default_rng(14)
+    idx = rng.integers(0, cfg.nb // topk, size=(cfg.nb, topk)) * topk + np.arange(topk)  # (no block twice in a row)
+    idx = np.where(idx < cfg.nb, idx, -1).astype(np.int32)
+    idx[1::4, 1:] = -1
+    idx[2] = idx[-1] = -1
+    blocks = sorted({0, 1, 2, 3, 4, 5, cfg.nb - 2, cfg.nb - 1})
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+    got, args = _case(B, oracle_lib, cfg, idx=idx)
+    dq, _, _ = oracle_lib.nsa_backward_sampled(*args, blocks, [], [0, 2])
+    rows = (np.asarray(blocks)[:, None] * 64 + np.arange(64)[None]).reshape(-1)
+    _assert_grads((got[0][rows][:, [0, 2]],), (dq,), cfg.name)
