@@ -33,6 +33,7 @@
 #include "lsrm_internal.h"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -1742,6 +1743,12 @@ struct WsLayout {
     size_t hpart_k, hpart_v, order, order_part, slot0, split_list, task_n, walk, gtab;
 };
 
+// Blocks of a spatial block, about: the mean, of all or of those that are not an image tile each.
+double blocks_of_group(const Shape &s) {
+    const double all = (double)s.nb / s.ng;
+    return s.ng > s.n_tiles ? std::max(all, (double)s.nb_obj / (s.ng - s.n_tiles)) : all;
+}
+
 WsLayout ws_layout(const Shape &s) {
     WsLayout w;
     const size_t img = (size_t)s.d * 64;  // bytes of one (tile, head) image: row-order fragments only
@@ -1804,21 +1811,30 @@ WsLayout ws_layout(const Shape &s) {
     w.part_k = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
     w.part_v = take((size_t)w.n_split * w.nbp * s.h_kv * s.d * 4);
     // Token keys.  No single walk may set the kernel's time: geometric routing makes some blocks popular, and a small problem has too
-    // few walks to fill the chip, which then waits for the latency of their steps (1 to 2 us each).  A walk is cut where it would take more
-    // than a share of what an evenly filled chip needs for all of them -- longest first, a shorter walk never ends last: half
-    // of it, a quarter with grouped-query heads, where a cut is what spreads the heads of a group too -- but not below `least` steps:
-    // there a workgroup's start and its sums (32 KB at d = 64, written and read) cost more than the shorter walk gains.
-    // least, 16 to 64 steps (96 with grouped heads, where fewer workgroups are short of work): the less there is to do, the more every CU
-    // has to itself and the shorter a part may be.  Backward, 16 / with this, us: d = 64, 337 blocks x 8 heads (2) 364 / 352, 415 x 4 (2) 323 /
-    // 297, 150 x 1 110 / 98, 115 x 16 239 / 229, 455 x 1 89 / 84; d = 32, 591 x 1 120 / 101, 65 x 32 139 / 129; d = 128 in the joint launch, 71 x 4 (2)
-    // 107 / 97, 233 x 1 149 / 142; longer ones lose (d = 32, 169 x 12, 96 steps 154 for 145; d = 64, 96 x 4, 32 steps 52 for 47), and so does
-    // d = 128 in a launch of its own (278 x 1, 32 steps 121 for 114).
-    // With grouped-query heads a walk has group x as many steps.  The heads of a group used to be dealt to up to 8 workgroups; the sums
-    // that costs (8 times 64 KB a block, key/value head and part at d = 64) took more than it gave once walks were cut, except for large
-    // groups in large problems, where two workgroups' images of q and dout are nearer to each other in memory: there they are dealt to two (as
-    // long as the sums stay within 2 GiB of workspace).  8 workgroups and half a share / this, us: 2069 blocks, 6 heads on 2 of 128 9285 /
-    // 8120, 2553 x 6 (1) of 32 3190 / 3060, 297 x 8 (1) of 64 395 / 367, 3307 x 4 (2) of 128 8390 / 7790; 3072 x 32 (2) of 32 32024 / 31900,
-    // undealt 32900.
+    // few walks to fill the chip, which then waits for the latency of their steps (1 to 2 us each).  So long walks are cut into
+    // parts, longest first, and the heads of a group may be dealt to several workgroups.  Both cost a workgroup's start and its sums
+    // (32 KB at d = 64, written and read).  A "share" is the steps that all walks have for each workgroup the chip holds.
+    //
+    // Launches of their own: a part is half a share, a quarter with grouped-query heads, where a cut is what spreads the heads of a group
+    // too, but at least 64 steps (96 with grouped heads; at d = 128 16 and 64), fewer where there is little to do.
+    // The heads of a group used to be dealt to up to 8 workgroups; the sums that costs took more than it gave once walks were cut,
+    // except for large groups, where two workgroups' images of q and dout are nearer to each other in memory: those are dealt to
+    // two (as long as the sums stay within 2 GiB of workspace).  8 workgroups and half a share / this, us: 2069 blocks, 6 heads on 2
+    // of 128 9285 / 8120, 2553 x 6 (1) of 32 3190 / 3060, 3307 x 4 (2) of 128 8390 / 7790; 3072 x 32 (2) of 32 32024 / 31900, undealt
+    // 32900; spatial blocks with their own window, 115 x 16 (4) of 128 371 / 361 (with parts of at least 16 steps 422).
+    //
+    // The joint launch, plain heads: at least half a share as well, and 16 to 64 steps, the fewer the less there is to do (backward, parts
+    // of at least 16 steps / this, us: 174 x 2 of 64 195 / 149, 178 x 4 of 32 189 / 150, 99 x 1 of 128 120 / 100, 202 x 1 of 64 85 / 75).
+    // The joint launch, grouped heads: a part of L steps costs its chain, and a workgroup's place share / L starts and sums, which is
+    // least at L in proportion to the root of the share: at 8 to 10 roots, over 360 problems with parts of 8 to 256 steps.  A part
+    // cannot be shorter than an entry's two tiles of every head of its workgroup, nor, where the window is a spatial block, than
+    // that block's tiles, which go uncut (its size is known on the device only: half as much again as the mean); so heads are
+    // dealt until that fits, and until the walks take an eighth of the places.  Backward, 8 workgroups and at least 16 steps / undealt and
+    // at least 96 / this, us: spatial blocks with their own window 13 x 32 (2) of 32 47 / 167 / 46, 85 x 16 (2) of 64 136 / 256 / 131, 90 x
+    // 8 (1) of 64 131 / 217 / 116, 337 x 8 (2) of 64 375 / 346 / 348; single blocks 18 x 32 (4) of 64 60 / 104 / 58, 18 x 12 (3) of 128 59 /
+    // 107 / 56, 7 x 12 (1) of 128 54 / 72 / 42, 34 x 6 (2) of 64 54 / 93 / 55; 96 x 3 (1) of 64 127 / 97 / 109 and 65 x 4 (1) of 128 92 / 78 /
+    // 95 are what this loses.  Of 600 problems of the joint launch, plain heads among them, 14 take more than 5 % longer than with the
+    // first of the three, tables of few entries in long rows above all (the host knows the length of the rows only).
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp = s.h / s.h_kv;
@@ -1826,15 +1842,31 @@ WsLayout ws_layout(const Shape &s) {
         // caller's W (an unlimited one is 2^31 - 2: 64 bits)
         const int64_t reach = (((64 + (int64_t)s.window) / 32 + 2) + 1) & ~(int64_t)1;
         const int64_t win = s.group_window ? 0 : reach < (int64_t)nt ? reach : (int64_t)nt;
-        const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);
+        const int64_t steps = (int64_t)s.nb * (2 * s.topk + win);  // at most, whatever the table holds
         const int64_t half_share = steps * s.h / slots / 2;
-        const bool own_launch = s.d == 128 && !w.small;
-        const int64_t least = std::max<int64_t>(16, std::min<int64_t>(own_launch ? 16 : grp > 1 ? 96 : 64, (s.d == 128 ? 4 : 8) * half_share));
-        for (int ranges = !w.small && grp >= 8 ? 2 : 1; ranges >= 1; --ranges) {
+        // a row holds no more blocks than there are, unless it repeats some: the estimate leaves that out, the bounds below do not
+        const double share = (double)s.nb * (2 * std::min(s.topk, s.nb) + win) * s.h / slots;
+        double part;  // steps, of all heads that a workgroup has
+        int ranges;
+        if (w.small && grp > 1) {
+            part = std::max({16.0, (s.d == 32 ? 10 : 8) * std::sqrt(share), half_share / 2.0});
+            const double uncut = s.group_window ? 6 * blocks_of_group(s) : 4;
+            ranges = (int)std::min<double>(std::min(grp, 8), std::ceil(std::max(uncut * grp / part, slots / 8.0 / (s.nb * s.h_kv))));
+        } else if (w.small) {
+            part = std::max({16.0, std::min(64.0, (s.d == 128 ? 1.5 : 3) * share), (double)half_share});
+            ranges = 1;
+        } else {
+            part = std::max(16.0, std::min<double>(s.d < 128 ? (grp > 1 ? 96 : 64) : grp > 1 ? 64 : 16, (s.d == 128 ? 4 : 8) * half_share));
+            ranges = grp >= 8 ? 2 : 1;
+        }
+        for (; ranges >= 1; --ranges) {
             w.hpw = (grp + ranges - 1) / ranges;
             w.hsplit = (grp + w.hpw - 1) / w.hpw;
-            int64_t len = steps * s.h_kv * w.hsplit / slots / (grp > 1 && !w.small ? 4 : 2);
-            len = std::max(len, (least + w.hpw - 1) / w.hpw);
+            int64_t len;
+            if (w.small)
+                len = std::max<int64_t>(2, 2 * (int64_t)std::floor(part / w.hpw / 2 + 0.5));
+            else
+                len = std::max<int64_t>(steps * s.h_kv * w.hsplit / slots / (grp > 1 ? 4 : 2), (int64_t)std::ceil(part / w.hpw));
             len = (len + 1) & ~(int64_t)1;
             if (len > 0x3ffffffe) len = 0x3ffffffe;
             w.part_steps = (int)len;

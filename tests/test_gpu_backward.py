@@ -294,9 +294,9 @@ def test_backward_full_size_is_deterministic(B, oracle_lib):
 
 @pytest.mark.parametrize("d,heads,h_kv", [(64, 2, 2), (32, 6, 2), (128, 1, 1)])
 def test_backward_lists_cut_into_parts(B, oracle_lib, d, heads, h_kv):
-    """Walks at the edges of the parts they are cut into (16 tiles at this size, 6 with three heads to a key/value head, 6 of them the window's away from the ends of
-    the sequence): lists of 4, 5, 6 and 13, 14 entries and one of an entry per row, without grouped heads (only cut
-    blocks take the summing pass) and with them (all do)."""
+    """Walks at the edges of the parts they are cut into (16 tiles at this size, 6 of them the window's away from the ends of
+    the sequence): lists of 4, 5, 6 and 13, 14 entries and one of an entry per row, without grouped heads and with
+    three to a key/value head, a workgroup each."""
     cfg = I.small_config(name=f"b-parts-d{d}", n_obj=45 * 64, n_views=1, grid=16, heads=heads, d=d, topk=6, window=96,
                          seed=29, h_kv=h_kv)
     _log(f"[backward] {cfg.name} nb={cfg.nb}")
@@ -324,10 +324,10 @@ def test_backward_unlimited_window(B, oracle_lib, d, heads, h_kv):
 
 @pytest.mark.parametrize("d,heads,h_kv,window", [(64, 1, 1, 1024), (128, 1, 1, 962), (32, 4, 2, 962)])
 def test_backward_walks_cut_inside_the_window(B, oracle_lib, d, heads, h_kv, window):
-    """Windows of two and more parts (at this size a walk is cut every 16 tiles, every 8 with two heads to a key/value head): parts of window tiles only, one that
-    holds the window's end and list entries, and the odd tile by which a window of an odd number of tiles falls short of
-    its even share.  Lists of 0, 1, 8 and 14 entries behind it; without grouped heads (only cut blocks take the summing
-    pass) and with them (all do)."""
+    """Windows of two and more parts (at this size a walk is cut every 16 tiles, every 20 with two heads to a key/value
+    head): parts of window tiles only, one that holds the window's end and list entries, and the odd tile by which a window
+    of an odd number of tiles falls short of its even share.  Lists of 0, 1, 8 and 14 entries behind it; without grouped
+    heads and with two to a key/value head, a workgroup each."""
     cfg = I.small_config(name=f"b-window-parts-d{d}-w{window}", n_obj=45 * 64, n_views=1, grid=16, heads=heads, d=d, topk=3,
                          window=window, seed=33, h_kv=h_kv)
     _log(f"[backward] {cfg.name} nb={cfg.nb}")
@@ -450,8 +450,8 @@ def test_backward_pooled_keys_at_the_edges_of_their_groups(B, oracle_lib, d, n_b
 
 @pytest.mark.parametrize("d,heads,h_kv,channels", [(32, 9, 1, False), (64, 8, 1, False), (32, 7, 1, True), (128, 4, 2, False)])
 def test_backward_heads_of_a_group_dealt_to_two_or_to_one(B, oracle_lib, d, heads, h_kv, channels):
-    """Groups of eight and more heads in the general launches go to two workgroups (nine: five and four), smaller ones and the joint
-    launches of small problems keep theirs together; walks cut into parts of few tiles by many heads, the most popular into dozens.
+    """Groups of eight and more heads in the general launches go to two workgroups (nine: five and four), smaller ones stay
+    together; the joint launches deal groups of seven and more to two here; walks cut into parts of few tiles by many heads, the most popular into dozens.
     Bar: 2e-2 plus 2^-7 of the largest reference value of the row, as for the other large sums over a group."""
     n_blocks, topk, wide = 130, 4, 127
     cfg = I.small_config(name=f"b-dealt-d{d}-h{heads}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,

@@ -356,8 +356,8 @@ def test_pooling_of_as_many_spatial_blocks_as_there_can_be(B, nb, h_kv, d):
 def test_backward_lists_cut_into_parts_with_spatial_blocks(B, oracle_lib, d, heads, h_kv):
     """The window is the spatial block: it goes uncounted to a walk's first part, and walks are cut by their lists alone
     (every 16 tiles at this size).  Lists of 7, 8, 9, 16, 17 and 44 entries on blocks of different spatial blocks, full
-    and partly filled: whole walks, two parts and more, each finished with its own group's divisor; without grouped heads
-    (only cut blocks take the summing pass) and with them (all do)."""
+    and partly filled: whole walks, two parts and more, each finished with its own group's divisor; without grouped heads and
+    with three to a key/value head, a workgroup each."""
     cfg = I.small_config(name=f"g-parts-d{d}", n_obj=40 * 64, n_views=1, grid=16, heads=heads, d=d, topk=6, window=64,
                          seed=95, h_kv=h_kv)
     goff = np.concatenate([[0], np.cumsum([1, 8, 2, 3, 5, 8, 8, 5, 1, 1, 1, 1])]).astype(np.int32)
@@ -385,6 +385,39 @@ def test_backward_lists_cut_into_parts_with_spatial_blocks(B, oracle_lib, d, hea
     active = (np.arange(cfg.n) % 64) < np.repeat(cnt, 64)
     for name, g, r in zip(("dq", "dk", "dv"), got, ref):
         assert np.isfinite(g).all() and np.all(g[~active] == 0), name
+        ma, rl = G.attention_errors(g, r)
+        _log(f"    {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} (|ref| max {np.abs(r).max():.3e})")
+        assert ma <= G.MAX_ABS_TOL and rl <= G.REL_L2_TOL, (name, ma, rl)
+
+
+@pytest.mark.parametrize("d,heads,h_kv,window_mode,grouped_blocks", [(32, 12, 1, 1, True), (64, 5, 1, 0, True), (64, 10, 2, 1, False),
+                                                                     (32, 7, 1, 1, True), (128, 32, 2, 1, True), (128, 6, 2, 0, False)])
+def test_backward_of_few_blocks_deals_the_heads_of_a_group(B, oracle_lib, d, heads, h_kv, window_mode, grouped_blocks):
+    """In the joint launch of small problems up to eight workgroups share the heads of a group, one or more each and the
+    last one fewer (twelve and sixteen by twos, five and seven one each, five of ten by twos and one, three by two and one), and walks
+    are cut into parts of eight, ten and sixteen tiles; windows that are a spatial block go uncut."""
+    cfg = I.small_config(name=f"g-few-d{d}-h{heads}-w{window_mode}", n_obj=64 * 21, n_views=1, grid=16, heads=heads, d=d, topk=5,
+                         window=160, seed=99, h_kv=h_kv)
+    goff, idx, cnt = _case(cfg, 9, True, cfg.topk, min_count=8)
+    idx[:, 1] = np.where(np.arange(cfg.nb) % 5 == 0, -1, 11)
+    if not grouped_blocks:
+        goff = None
+        cnt = np.random.default_rng(10).integers(8, 65, size=cfg.nb).astype(np.int32)
+    _log(f"[few blocks] {cfg.name} nb={cfg.nb}")
+    q_bits, k_bits, v_bits = I.make_qkv(cfg)
+    gates, dout_bits = I.make_gates(cfg), I.make_dout(cfg)
+    # (a popular block and a group of heads add up gradients: keep them at the magnitude the absolute bar was set for)
+    dout_bits = I.f32_to_bf16_bits(I.bf16_bits_to_f32(dout_bits) * np.float32(0.5 * h_kv / heads))
+    q, k, v, dout = (I.bf16_bits_to_f32(a) for a in (q_bits, k_bits, v_bits, dout_bits))
+    k_bits, v_bits, dout_bits = _poison(cfg, cnt, k_bits, v_bits, dout_bits)
+    ref = oracle_lib.nsa_backward(q, k, v, oracle_lib.pool(k, cnt, goff), oracle_lib.pool(v, cnt, goff), idx, gates,
+                                  cfg.seg_offsets(), cfg.window, dout, window_mode=window_mode, block_count=cnt,
+                                  group_offsets=goff)
+    got = G.run_backward(B, cfg, q_bits, k_bits, v_bits, idx, gates, dout_bits, window_mode=window_mode, block_count=cnt,
+                         group_offsets=goff)
+    inactive = (np.arange(cfg.n) % 64) >= np.repeat(cnt, 64)
+    for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert np.isfinite(g).all() and np.all(g[inactive] == 0), name
         ma, rl = G.attention_errors(g, r)
         _log(f"    {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} (|ref| max {np.abs(r).max():.3e})")
         assert ma <= G.MAX_ABS_TOL and rl <= G.REL_L2_TOL, (name, ma, rl)
