@@ -1537,9 +1537,12 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
             ++a.teams[most];
         }
     }
-    // A workgroup of two heads wherever heads that share keys and values come in pairs.  Whole call, two query blocks / two heads:
-    // 196 K tokens, 32 heads of 32 on 2, rows of 80 10.61 / 10.21 ms; ragged spatial blocks, 8 heads of 64 on 2, training step 548 / 542 us.
-    const bool heads = nb_wg == 0 && a.group % 2 == 0;
+    // A workgroup of two heads where heads that share keys and values come in pairs; at d = 32 from 600 workgroups on, short of which too few
+    // share a CU to fill one another's waits.  Packing and attention, two query blocks / two heads, mean (and extremes) of drawn problems by
+    // the number of workgroups: d = 32 up to 600 0.990 (0.973 to 1.039, 31 problems), to 1100 1.014, to 5000 1.019, above 1.028; d = 64 up to
+    // 400 1.002 (0.990 to 1.021), to 800 1.021, to 5000 1.033, above 1.038; d = 128 up to 400 1.064 (1.030 to 1.219), to 5000 1.072, above
+    // 1.059.  196 K tokens, 32 heads of 32 on 2, rows of 80 10.61 / 10.21 ms.
+    const bool heads = nb_wg == 0 && a.group % 2 == 0 && (D > 32 || (int64_t)s.nb * s.h >= 1200);
     const int per_wg = nb_wg > 0 ? nb_wg : heads ? 1 : NP;  // query blocks
     a.groups_per_head = (s.nb + per_wg - 1) / per_wg;
     a.groups_per_xcd = nb_wg == 0 ? (a.groups_per_head + 7) / 8 : (a.groups_per_head * s.h + 7) / 8;

@@ -588,6 +588,10 @@ def test_forward_few_and_many_query_blocks(B, oracle_lib, d, nb, heads, h_kv, to
     (33, 32, 2, 80, 160, False, True),   # of sixteen, wide rows, a gate per channel
     (33, 32, 2, 100, 160, True, False),
     (9, 64, 32, 3, 66, False, False),    # fewer blocks than a tile of pooled pairs, XCDs without any
+    (299, 4, 2, 6, 320, True, False),    # the last one and
+    (300, 4, 2, 6, 320, False, True),    # the first one of d = 32
+    (38, 32, 2, 80, 160, True, True),    # wide rows of d = 32
+    (9, 144, 72, 3, 66, False, False),
 ])
 def test_forward_two_heads_to_a_workgroup(B, oracle_lib, d, nb, heads, h_kv, topk, window, with_counts, channels):
     """Query heads that share a key/value head, two to a workgroup with one list of tiles for all branches: rows of every
