@@ -999,26 +999,27 @@ __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward
 // Attention step, nsa_forward_kernel and this: that problem 19.9 -> 14.8 us; 43 blocks, 3 heads of 128, 9 routed blocks, window
 // 192: 33.8 -> 15.6 us (what remains is the copies' latency, two stages deep: 2000 cycles a step, 1400 without copies).
 // PAIRS: the workgroups make the images of the pooled pairs by themselves (FwdArgs::kc, vc), all of them, behind the slots.
-// MEET: the two wavefronts of a team wait for each other only in a step, not for all teams, by two numbers a team behind everything else
-// (TeamTiles::meet).  A barrier keeps all in step, copying and computing at the same times, as slow as the slowest: with packing, out of a graph,
-// us, 16 blocks x 1 head of 32 13.2 / 12.5, 128 x 2 19.2 / 18.3; of 64 33 x 4 16.6 / 15.8, 65 x 4 24.0 / 22.8, 200 x 1 26.8 / 25.6, 96 x 4 the
-// same.  Not at d = 128 (128 x 2 34.8 / 34.4, 33 x 4 22.4 / 22.7), nor where the pairs leave the numbers no room (8 tiles of d = 64).
-template <class G, int NB_, int NT_, int NST_, bool PAIRS_, bool MEET_ = (G::D <= 64)>
+// MEET: the two wavefronts of a team wait for each other only in a step, not for all teams, by two numbers a team (TeamTiles::meet).
+// A barrier keeps all in step, copying and computing at the same times, as slow as the slowest: with packing, out of a graph, us, 16
+// blocks x 1 head of 32 13.2 / 12.5, 128 x 2 19.2 / 18.3; of 64 33 x 4 16.6 / 15.8, 65 x 4 24.0 / 22.8, 200 x 1 26.8 / 25.6, 96 x 4 the
+// same.  Not at d = 128 (128 x 2 34.8 / 34.4, 33 x 4 22.4 / 22.7).
+template <class G, int NB_, int NT_, int NST_, bool PAIRS_>
 struct Teams {
-    static constexpr bool PAIRS = PAIRS_, MEET = MEET_;
+    static constexpr bool PAIRS = PAIRS_, MEET = G::D <= 64;
     static constexpr int NB = NB_, NT = NT_, NST = NST_;  // query blocks of a workgroup; teams of one; stages of a team
     static constexpr int THREADS = 64 * G::NW * NT * NB;
     static constexpr int PITCH = G::D + 4;  // floats of a row of a team's result: 16-byte aligned, rows spread over the banks
     static constexpr int TILES_BYTES = NB * NT * NST * G::TILE, SUM_BYTES = NB * NT * kBlock * (PITCH + 2) * 4;
     static constexpr int LDS_ALL = TILES_BYTES > SUM_BYTES ? TILES_BYTES : SUM_BYTES;
-    // Tiles of pooled pairs that fit a CU's LDS behind the slots (what the teams add up at the end takes their place): 8 at d = 64, 2
-    // at d = 128.
-    static constexpr int STEPS_BYTES = MEET ? NB * NT * 8 : 0;
-    static constexpr int MAX_PAIRS = (160 * 1024 - STEPS_BYTES - TILES_BYTES) / G::TILE;
-    static constexpr __host__ __device__ int steps_at(int tiles) {
-        return PAIRS && tiles * G::TILE > LDS_ALL - TILES_BYTES ? TILES_BYTES + tiles * G::TILE : LDS_ALL;
+    // Tiles of pooled pairs that fit a CU's LDS behind the slots (what the teams add up at the end takes their place): 16 at d = 32, 8
+    // at d = 64, 2 at d = 128.
+    static constexpr int MAX_PAIRS = (160 * 1024 - TILES_BYTES) / G::TILE;
+    // Where the numbers of MEET are: behind everything else, or, with PAIRS, in the slots of team 0, a team of the pooled pairs, which
+    // copies nothing there.
+    static constexpr int STEPS_AT = PAIRS ? 0 : LDS_ALL;
+    static constexpr int lds_bytes(int tiles) {
+        return PAIRS ? (tiles * G::TILE > LDS_ALL - TILES_BYTES ? TILES_BYTES + tiles * G::TILE : LDS_ALL) : LDS_ALL + (MEET ? NB * NT * 8 : 0);
     }
-    static constexpr int lds_bytes(int tiles) { return steps_at(tiles) + STEPS_BYTES; }
     static constexpr int WAVES_PER_SIMD = (THREADS / 64 + 3) / 4;  // (one workgroup per CU)
     static_assert(LDS_ALL <= 160 * 1024 && NT >= 3, "");
 };
@@ -1198,7 +1199,7 @@ __global__ __launch_bounds__((TM::THREADS), (TM::WAVES_PER_SIMD)) void nsa_forwa
     };
     const bool there = TM::PAIRS && cmp;
     char *const pairs = lds + TM::TILES_BYTES;
-    int *const steps = reinterpret_cast<int *>(lds + TM::steps_at(n_cmp)) + 2 * (qbi * NT + team);
+    int *const steps = reinterpret_cast<int *>(lds + TM::STEPS_AT) + 2 * (qbi * NT + team);
     if (TM::MEET && lane == 0) steps[sub] = 0;
     const TeamTiles<G, TM, decltype(src)> tiles{n, there ? 0 : n, src, there ? pairs + t0 * G::TILE : slots, steps, sub, c.lane16};
     tiles.begin();
@@ -1515,7 +1516,6 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     using One = Teams<G, 1, D == 128 ? 4 : 6, D == 32 ? 4 : 2, false>;
     using Two = Teams<G, D == 128 ? 1 : 2, D == 128 ? 4 : 3, 2, false>;
     using OnePairs = Teams<G, 1, One::NT, One::NST, true>;
-    using OneFull = Teams<G, 1, One::NT, One::NST, true, false>;  // (as many pairs as there can be)
     using TwoPairs = Teams<G, Two::NB, Two::NT, Two::NST, true>;
     const int tiles[3] = {tiles_c, 2 * s.topk, (int)std::min<int64_t>(s.window / 32 + 2, 2 * s.nb)};
     const int64_t longest = std::max(tiles[0], std::max(tiles[1], tiles[2])), all = (int64_t)tiles[0] + tiles[1] + tiles[2];
@@ -1548,8 +1548,8 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     a.groups_per_xcd = nb_wg == 0 ? (a.groups_per_head + 7) / 8 : (a.groups_per_head * s.h + 7) / 8;
     // The workgroups make the images of the pooled pairs where a launch would do nothing else and their LDS holds them all.  A pass of packing
     // and attention out of a graph, us, launch / own images: 16 blocks x 1 head of 32 14.6 / 13.1, 96 x 4 20.5 / 18.9, 300 x 1 24.2 / 22.9; of 64
-    // 96 x 4 25.4 / 23.4, 256 x 1 22.6 / 21.8; of 128 64 x 4 30.4 / 28.3.
-    const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? OneFull::MAX_PAIRS : nb_wg == 2 ? TwoPairs::MAX_PAIRS : 0);
+    // 96 x 4 25.4 / 23.4; of 128 64 x 4 30.4 / 28.3.  240 x 1 of 64, not out of a graph, 25.4 / 24.2.
+    const bool own_pairs = s.kv_packed && tiles_c <= (nb_wg == 1 ? OnePairs::MAX_PAIRS : nb_wg == 2 ? TwoPairs::MAX_PAIRS : 0);
     if (own_pairs) a.kc = d_kc, a.vc = d_vc;
     const int nb_kv = s.kv_packed ? 0 : s.nb, pair_blocks = own_pairs ? 0 : (s.nbc + 63) / 64;
     const int n_pack = nb_kv + pair_blocks + (tables.n + 255) / 256;
@@ -1564,11 +1564,8 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>)) \
          : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
     if (nb_wg == 1) {
-        const bool full = tiles_c > OnePairs::MAX_PAIRS;
-        kern = !own_pairs ? LSRM_KERNEL(nsa_forward_teams, One)
-               : full     ? LSRM_KERNEL(nsa_forward_teams, OneFull)
-                          : LSRM_KERNEL(nsa_forward_teams, OnePairs);
-        lds = !own_pairs ? One::lds_bytes(tiles_c) : full ? OneFull::lds_bytes(tiles_c) : OnePairs::lds_bytes(tiles_c), threads = One::THREADS;
+        kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, OnePairs) : LSRM_KERNEL(nsa_forward_teams, One);
+        lds = own_pairs ? OnePairs::lds_bytes(tiles_c) : One::lds_bytes(tiles_c), threads = One::THREADS;
     } else if (nb_wg == 2) {
         kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, TwoPairs) : LSRM_KERNEL(nsa_forward_teams, Two);
         lds = own_pairs ? TwoPairs::lds_bytes(tiles_c) : Two::lds_bytes(tiles_c), threads = Two::THREADS;

@@ -609,7 +609,7 @@ def test_forward_two_heads_to_a_workgroup(B, oracle_lib, d, nb, heads, h_kv, top
 
 
 @pytest.mark.parametrize("d,nb,heads,h_kv", [(32, 1, 3, 3), (32, 96, 4, 1), (32, 512, 1, 1), (64, 33, 4, 4), (64, 96, 4, 2),
-                                             (64, 256, 1, 1), (64, 257, 1, 1), (128, 31, 6, 2), (128, 64, 4, 4), (128, 65, 3, 1)])
+                                             (64, 225, 1, 1), (64, 256, 1, 1), (64, 257, 1, 1), (128, 31, 6, 2), (128, 64, 4, 4), (128, 65, 3, 1)])
 def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv):
     """Small calls behind lsrm_nsa_compress_pack make the images of the pooled pairs in LDS, as many tiles as it holds: bit
     for bit what the packing launch of the two-pass call gives, for whole and partly filled last tiles, for pairs that
