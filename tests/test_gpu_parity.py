@@ -608,22 +608,35 @@ def test_forward_two_heads_to_a_workgroup(B, oracle_lib, d, nb, heads, h_kv, top
     _assert_forward(*_forward_case(B, oracle_lib, cfg, idx=idx, block_count=cnt), cfg.name)
 
 
-@pytest.mark.parametrize("d,nb,heads,h_kv", [(32, 1, 3, 3), (32, 96, 4, 1), (32, 512, 1, 1), (64, 33, 4, 4), (64, 96, 4, 2),
-                                             (64, 225, 1, 1), (64, 256, 1, 1), (64, 257, 1, 1), (128, 31, 6, 2), (128, 64, 4, 4), (128, 65, 3, 1)])
-def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv):
+@pytest.mark.parametrize("d,nb,heads,h_kv,topk,with_counts,channels", [
+    (32, 1, 3, 3, 4, False, False), (32, 96, 4, 1, 4, False, False), (32, 512, 1, 1, 4, False, False), (64, 33, 4, 4, 4, False, False),
+    (64, 96, 4, 2, 4, False, False), (64, 225, 1, 1, 4, False, False), (64, 256, 1, 1, 4, False, False), (64, 257, 1, 1, 4, False, False),
+    (128, 31, 6, 2, 4, False, False), (128, 64, 4, 4, 4, False, False), (128, 65, 3, 1, 4, False, False),
+    # long rows, active counts and a gate per channel: one query block to a workgroup, two, as many tiles of pairs as there can be
+    (32, 64, 4, 2, 100, True, True), (32, 96, 4, 1, 80, True, False), (32, 512, 1, 1, 66, True, True), (64, 51, 5, 5, 128, True, False),
+    (64, 96, 4, 2, 70, True, True), (64, 256, 1, 1, 66, True, False), (64, 256, 2, 1, 80, False, True), (64, 193, 2, 2, 5, True, False),
+    (128, 64, 4, 4, 128, True, False), (128, 33, 7, 1, 65, False, True), (128, 63, 4, 2, 6, True, True),
+])
+def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv, topk, with_counts, channels):
     """Small calls behind lsrm_nsa_compress_pack make the images of the pooled pairs in LDS, as many tiles as it holds: bit
     for bit what the packing launch of the two-pass call gives, for whole and partly filled last tiles, for pairs that
-    are not the averages of k and v, in a workspace that holds anything."""
+    are not the averages of k and v, in a workspace that holds anything, with anything in padding slots."""
     import torch
-    cfg = I.small_config(name=f"f-own-d{d}-nb{nb}-h{heads}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=heads, d=d, topk=4,
-                         window=96, seed=nb, h_kv=h_kv)
-    _log(f"[forward] {cfg.name}")
+    cfg = I.small_config(name=f"f-own-d{d}-nb{nb}-h{heads}-k{topk}", n_obj=64 * (nb - 1), n_views=1, grid=8, heads=heads, d=d,
+                         topk=topk, window=640 if topk > 64 else 96, seed=nb, h_kv=h_kv, gate_channels=channels)
+    _log(f"[forward] {cfg.name}")   # (a long row beside a short window would go to the general kernel)
     q, k, v = (G.bf16_dev(x) for x in I.make_qkv(cfg))
     gates = torch.from_numpy(I.make_gates(cfg)).cuda()
     gen = torch.Generator(device="cuda").manual_seed(nb)
     idx = torch.randint(-1, nb, (nb, cfg.topk), generator=gen, device="cuda", dtype=torch.int32)
     kc, vc = (torch.randn((nb, h_kv, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
-    p = G.params_for(B, cfg)
+    cnt, active = None, torch.ones(cfg.n, dtype=torch.bool, device="cuda")
+    if with_counts:
+        cnt = _block_counts(cfg, 16)
+        active = torch.from_numpy((np.arange(cfg.n) % 64) < np.repeat(cnt, 64)).cuda()
+        k[~active] = float("nan")
+        v[~active] = float("nan")
+    p = G.params_for(B, cfg, block_count=cnt)
     got = []
     for packed in (1, 0):
         ws = B.alloc_workspace(p, B.LSRM_WS_FORWARD)
@@ -634,9 +647,9 @@ def test_forward_own_images_of_pairs(B, d, nb, heads, h_kv):
         res = [torch.empty_like(q), torch.empty((3, cfg.n, heads), device="cuda"),
                torch.empty((3, cfg.n, heads, d), dtype=torch.bfloat16, device="cuda")]
         B.lsrm_nsa_forward(p, q, k, v, kc, vc, idx, gates, *res, ws)
-        got.append(res)
+        got.append((res[0][active], res[1][:, active], res[2][:, active]))
     for a, b in zip(*got):
-        assert torch.equal(a, b)
+        assert not torch.isnan(a).any() and torch.equal(a, b)
 
 
 def test_calls_take_the_current_stream(B):
