@@ -803,7 +803,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int head = PAIR == HEADS ? 2 * unit + (wave >> 1) : unit;
     const int blk = PAIR == BLOCKS ? wave >> 1 : 0;             // query block inside the workgroup
-    const bool active = PAIR != BLOCKS || 2 * place + blk < a.nb;  // (without one: copies and barriers only)
+    const bool active = PAIR != BLOCKS || 2 * place + blk < a.nb;  // (without one: the pooled keys for the last block once more, not stored)
     const int qb = PAIR == BLOCKS ? min(2 * place + blk, a.nb - 1) : place;
     const int r = lane & 31, hh = lane >> 5;
     const uint32_t lane16 = (uint32_t)lane * 16u;
@@ -950,7 +950,7 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
 #pragma unroll
         for (int i = 0; i < 16; ++i) dp0[i] = dl[BR];
         for (int t = t0; t < t1; ++t) {
-            // tile t has landed (this wavefront's share; the barrier covers the other's); both wavefronts are done
+            // tile t has landed (this wavefront's share; the barrier covers the others'); all wavefronts are done
             // with tile t-1, whose buffer takes tile t+1
             __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
             wg_barrier();
@@ -1954,14 +1954,23 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &t
     }
     // Two heads to a workgroup wherever heads that share keys and values come in pairs.  Whole backward, one head / two, us: 1536 blocks, rows
     // of 32, 16 heads on 2 of 64 6237 / 6070, 8 on 2 of 128 6175 / 5989; rows of 80, 8 on 4 of 64 5415 / 5096; 900 blocks, 4 on 2 of 64 696 / 684.
+    // From 641 blocks on (257 at d = 128) 1 to 3 % in each of 126 problems but two, 257 and 300 blocks x 2 (1) of 128, 1.5 % the other way.
     const bool heads = a.group % 2 == 0;
-    // Two query blocks to a workgroup for other heads where the pooled keys are many.  One block / two, us: d = 128, 6688 blocks x 16 heads
-    // 128.9 / 127.9 ms, 5121 x 4 16371 / 16177, 2176 x 8 9258 / 9218, 1536 x 8 6446 / 6445, 641 x 8 2300 / 2330, 257 x 8 870 / 902; d = 64, 4864 x 2
-    // 3693 / 3630, 2816 x 4 3727 / 3693, 2048 x 8 3959 / 3923, 1536 x 8 3192 / 3184, 897 x 8 1670 / 1680; d = 32, 4864 x 6 8082 / 8001, 641 x 4 424 / 427.
-    const bool blocks = !heads && s.nbc >= kPooledMany;
-#define LSRM_DQ(PAIR) (s.topk > 64 ? &bwd_dq_kernel<D, true, PAIR> : &bwd_dq_kernel<D, false, PAIR>)
-    const auto dq = heads ? LSRM_DQ(HEADS) : blocks ? LSRM_DQ(BLOCKS) : LSRM_DQ(ALONE);
-#undef LSRM_DQ
+    // Two query blocks to a workgroup for other heads where the pooled keys are many, at d >= 64.  One block / two, us: d = 128, 6688 blocks x
+    // 16 heads 128.9 / 127.9 ms, 5121 x 4 16371 / 16177, 2176 x 8 9258 / 9218, 1536 x 8 6446 / 6445, 641 x 8 2300 / 2330, 257 x 8 870 / 902;
+    // d = 64, 4864 x 2 3693 / 3630, 2816 x 4 3727 / 3693, 2048 x 8 3959 / 3923, 1536 x 8 3192 / 3184, 897 x 8 1670 / 1680.
+    // It is little: over 46 problems of 2048 to 6700 blocks each (rows of 16 and 80; 1, 3 and 8 heads, and 3 on 1) one block takes, of two's time, at d =
+    // 128 0.8 % more (-1.6 to 2.6, one of them below -0.3: 3128 x 1, rows of 80), at d = 64 0.6 % (-0.7 to 3.3, five below -0.3), at d = 32
+    // 0.3 % (-1.0 to 2.6, ten below -0.3).
+    const bool blocks = D >= 64 && !heads && s.nbc >= kPooledMany;
+    auto choose = [&](auto wide) {
+        constexpr bool WIDE = decltype(wide)::value;
+        if (heads) return &bwd_dq_kernel<D, WIDE, HEADS>;
+        if constexpr (D >= 64)
+            if (blocks) return &bwd_dq_kernel<D, WIDE, BLOCKS>;
+        return &bwd_dq_kernel<D, WIDE, ALONE>;
+    };
+    const auto dq = s.topk > 64 ? choose(std::true_type{}) : choose(std::false_type{});
     const int n_units = blocks ? (s.nb + 1) / 2 : s.nb;
     hipLaunchKernelGGL(dq, dim3((n_units + 7) / 8 * 8, heads ? s.h / 2 : s.h), dim3(heads || blocks ? 256 : 128), 0, st, a);
     LSRM_HIP_CHECK(hipGetLastError());

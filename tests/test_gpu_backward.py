@@ -476,8 +476,8 @@ def test_backward_heads_of_a_group_dealt_to_two_or_to_one(B, oracle_lib, d, head
 @pytest.mark.parametrize("d,n_blocks,topk,channels", [(32, 2049, 4, True), (64, 2049, 65, False), (64, 2080, 4, True), (128, 2049, 4, False),
                                                       (128, 2048, 66, True)])
 def test_backward_two_query_blocks_to_a_workgroup(B, oracle_lib, d, n_blocks, topk, channels):
-    """From 2048 pooled keys on a workgroup of the dQ pass has two query blocks of a head: an odd number of blocks, partners with
-    rows of very different numbers of valid entries, in narrow and wide tables; heads with key/value heads of their own."""
+    """From 2048 pooled keys on a workgroup of the dQ pass has two query blocks of a head (at d = 32 one): an odd number of blocks,
+    partners with rows of very different numbers of valid entries, in narrow and wide tables; heads with key/value heads of their own."""
     heads = 3
     cfg = I.small_config(name=f"b-two-blocks{n_blocks}-{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
                          window=224, seed=80, gate_channels=channels)
@@ -493,3 +493,47 @@ def test_backward_two_query_blocks_to_a_workgroup(B, oracle_lib, d, n_blocks, to
     dq, _, _ = oracle_lib.nsa_backward_sampled(*args, blocks, [], [0, 2])
     rows = (np.asarray(blocks)[:, None] * 64 + np.arange(64)[None]).reshape(-1)
     _assert_grads((got[0][rows][:, [0, 2]],), (dq,), cfg.name)
+
+
+@pytest.mark.parametrize("d,heads,h_kv,n_blocks,n_groups,topk,window,window_mode,with_counts,channels", [
+    (64, 1, 1, 2049, 0, 4, 224, 1, True, False),     # the window is the query's own block
+    (128, 3, 1, 2051, 0, 66, 224, 0, True, True),
+    (64, 3, 1, 2500, 2049, 5, 224, 1, True, False),  # the window is the spatial block: partners of very different lengths
+    (128, 1, 1, 2701, 2048, 3, 160, 1, True, True),
+    (128, 5, 1, 2048, 0, 1, 0, 0, False, False),     # half of the blocks have the pooled keys only
+    (64, 3, 3, 2047, 0, 4, 224, 0, True, False),     # one pooled key too few
+])
+def test_backward_two_query_blocks_and_two_heads_to_a_workgroup(B, d, heads, h_kv, n_blocks, n_groups, topk, window, window_mode,
+                                                                with_counts, channels):
+    """The dQ pass with two query blocks to a workgroup and, every query head given twice, with two heads to one: the same
+    bits in every row, and again in a second run.  Active counts, both windows, spatial blocks, groups of three and five."""
+    cfg = I.small_config(name=f"b-both-pairs{n_blocks}-{d}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
+                         window=window, seed=81, h_kv=h_kv, gate_channels=channels)
+    rng = np.random.default_rng(15)
+    goff = None
+    if n_groups:   # (the last spatial block of more than one block and an image tile of its own)
+        ends = np.sort(rng.choice(np.arange(1, n_blocks - 1), size=n_groups - 2, replace=False))
+        goff = np.concatenate([[0], ends, [n_blocks - 1, n_blocks]]).astype(np.int32)
+    cnt = rng.integers(1, 65, size=n_blocks).astype(np.int32) if with_counts else None
+    idx = rng.integers(0, cfg.nb, size=(cfg.nb, topk)).astype(np.int32)
+    idx[1::4, 1:] = -1
+    idx[::2] = np.where(rng.random(idx[::2].shape) < 0.5, -1, idx[::2])
+    idx[2] = idx[-1] = -1
+    if topk == 1:
+        idx[1::2] = -1
+    q, k, v = I.make_qkv(cfg)
+    gates, dout = I.make_gates(cfg), I.make_dout(cfg)
+    twice = dataclasses.replace(cfg, heads=2 * heads)
+    _log(f"[backward] {cfg.name} nb={cfg.nb}")
+
+    def run(c, copies):
+        def of(x, axis):
+            return np.ascontiguousarray(np.repeat(x, copies, axis=axis))
+        return G.run_backward(B, c, of(q, 1), k, v, idx, of(gates, 2 if channels else 1), of(dout, 1), window_mode=window_mode,
+                              block_count=cnt, group_offsets=goff)
+
+    runs, pairs = [run(cfg, 1) for _ in range(2)], [run(twice, 2) for _ in range(2)]
+    for one, other in (runs, pairs):
+        for x, y in zip(one, other):
+            assert np.isfinite(x).all() and np.array_equal(x, y)
+    assert np.array_equal(pairs[0][0], np.repeat(runs[0][0], 2, axis=1))
