@@ -95,3 +95,21 @@ def test_backward_workspace_does_not_follow_the_window_beyond_the_sequence():
         # the window over the own block or the spatial block has no W
         assert size(2147483646, window_mode=1) == size(128, window_mode=1)
         assert size(2147483646, B.LSRM_WS_FORWARD) == size(128, B.LSRM_WS_FORWARD)
+
+
+def test_current_stream_without_the_functions_behind_it(monkeypatch):
+    """The handle of the current stream comes from functions that torch does not promise to keep; a torch without either of
+    them makes the stream object instead."""
+    import importlib.util
+    import types
+    import torch
+    from paper_2604_05182_amd import binding as B
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4660))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.delattr(torch._C, name, raising=False)
+            spec = importlib.util.spec_from_file_location("binding_without_" + name, B.__file__)
+            other = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(other)
+            assert other._stream(None) == 4660
+    assert B._stream(types.SimpleNamespace(cuda_stream=22136)) == 22136
