@@ -38,7 +38,8 @@
 #include <utility>
 
 constexpr int kBwdNbuf = 2;         // tile buffers of the dQ kernel
-constexpr int kBwdDkvNbuf = 2;      // tile buffers of the dK/dV kernels (three, copies two steps ahead: slower, 51 -> 65 ms on the pooled keys at d = 128)
+// tile buffers of the dK/dV kernels (three, copies two steps ahead: slower, 51 -> 65 ms on the pooled keys at d = 128)
+constexpr int kBwdDkvNbuf = 2;
 
 namespace lsrm {
 
@@ -78,7 +79,7 @@ struct BwdArgs {
     int nt;               // query / key tiles of 32 tokens
     int nbp, tiles_per_split, n_split;  // pooled keys, rounded up; the query ranges of their walks
     // Token keys: a key block's walk -- the query tiles of its window, then two per entry of its reverse list -- is dealt to
-    // several workgroups where it is long.  The query heads of a large group go to hsplit
+    // several workgroups where it is long.  The query heads of a group go to hsplit
     // workgroups, hpw heads each; and a walk of more than part_steps tiles is cut into parts of that many (cut_window = 0:
     // the window, of unknown length, goes to the first part and is not counted).  A (key block, part) is a task;
     // order / order_part [<= max_tasks] hold the tasks, longest first: the order the workgroups start in.  Where a block's
@@ -775,8 +776,7 @@ __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, flo
 }
 
 // ---------------------------------------------------------------------------------------------
-// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head), or four wavefronts that share the copies of tiles
-// (copies and reads of LDS bound this kernel beside the clock, see HEADS in forward.hip):
+// dQ: one workgroup (2 wavefronts x 32 query rows) per (query block, head), or four wavefronts that share the copies of tiles:
 //   HEADS   two heads of one key/value head, which read the same tiles in all branches
 //   BLOCKS  two query blocks of one head, which share the tiles of the pooled keys; the others' each block copies for itself, and
 //           the barriers are common: a block with fewer steps waits for the other at the end
@@ -784,8 +784,9 @@ __global__ __launch_bounds__(256) void sum_parts(float *__restrict__ part_k, flo
 // lds: DQ_LDS bytes.  wg, unit: numbers of the workgroup; wg: query block or pair of them, unit: head or pair of heads.
 enum Pair { ALONE, HEADS, BLOCKS };
 template <int D, Pair PAIR = ALONE>
-constexpr int DQ_LDS = PAIR == BLOCKS ? 2 * kBwdNbuf * 2 * BGeo<D>::ROW
-                       : PAIR == HEADS && 4 * 32 * BGeo<D>::OUT_ROW > kBwdNbuf * 2 * BGeo<D>::ROW ? 4 * 32 * BGeo<D>::OUT_ROW : kBwdNbuf * 2 * BGeo<D>::ROW;
+constexpr int DQ_LDS = PAIR == BLOCKS  ? 2 * kBwdNbuf * 2 * BGeo<D>::ROW
+                       : PAIR == HEADS ? std::max(4 * 32 * BGeo<D>::OUT_ROW, kBwdNbuf * 2 * BGeo<D>::ROW)
+                                       : kBwdNbuf * 2 * BGeo<D>::ROW;
 template <int D, bool WIDE, Pair PAIR>
 __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int unit) {
     using G = BGeo<D>;
@@ -917,7 +918,8 @@ __device__ __forceinline__ void dq_walk(const BwdArgs &a, char *lds, int wg, int
     };
     auto issue_tile = [&](auto shared, const char *kimg, const char *vimg, int tile, char *buf) {
         const int64_t off = (int64_t)((uint32_t)tile * (uint32_t)a.h_kv + (uint32_t)kvh) * G::IMG;
-        if constexpr (PAIR == HEADS || (PAIR == BLOCKS && decltype(shared)::value)) {  // K rows and V rows, one behind the other, dealt to four wavefronts
+        if constexpr (PAIR == HEADS || (PAIR == BLOCKS && decltype(shared)::value)) {
+            // K rows and V rows, one behind the other, dealt to four wavefronts
             constexpr int KB = G::ROW / 1024;
 #pragma unroll
             for (int j = 0; j < 2 * KB; j += 4) {
@@ -1643,8 +1645,8 @@ __global__ __launch_bounds__(128, (D == 128 ? 1 : 3)) void bwd_walks_small(BwdAr
 // The rows of the key blocks whose walks were dealt out: the sums of the parts of each head range, added in order, then
 // what the token-key kernel does at the end of a walk of its own (pooled gradient, scale, rounding).  One workgroup per
 // (block, key/value head, 256 groups of four channels of a token), one such group per thread, four sums of each of dk and dv in flight:
-// bound by memory at size (196 K tokens, 2 key/value heads of 32, 8 ranges: 805 MB of sums), by its chain of loads
-// below.
+// bound by memory at size (196 K tokens, 2 key/value heads of 32, two head ranges: 201 MB of sums and those of cut walks in 71 us), by
+// its chain of loads below.
 // SMALL (behind bwd_walks_small): the rows of all blocks; the pooled gradient is still in n_split parts, which a workgroup adds up first,
 // 256 / (D / 2) threads to a group of four channels.
 template <int D, bool SMALL>
@@ -1726,11 +1728,14 @@ bool small_table(const Shape &s) {
 // Whether a backward goes through the launches of small problems.  They are three, bwd_prepare and the general kernels six (without
 // bwd_prepare ten), and the ends of three kernels become one; they cost fp32 sums of every walk and, at d = 128, dQ walks with one
 // wavefront per SIMD.  Backward, general / small (us), blocks x heads (on key/value heads):
-//   d = 32   96 x 4 95 / 51, 192 x 8 174 / 130, 548 x 4 353 / 311, 337 x 8 (2) 357 / 296, 160 x 32 (16) 400 / 343; 896 x 8 777 / 809,
-//            512 x 16 752 / 776
-//   d = 64   96 x 4 119 / 65, 192 x 8 260 / 224, 548 x 4 533 / 507, 337 x 8 (2) 532 / 471, 160 x 32 (16) 662 / 614; 896 x 2 410 / 420,
-//            512 x 16 1249 / 1323
-//   d = 128  96 x 4 181 / 135, 132 x 1 134 / 93, 192 x 6 430 / 402; 192 x 8 425 / 431, 512 x 2 404 / 434, 160 x 32 (2) 1995 / 2098
+//   d = 32   96 x 4 74 / 51, 192 x 8 147 / 116, 548 x 4 273 / 235, 337 x 8 (2) 287 / 241, 640 x 2 193 / 156, 160 x 32 (16) 515 / 478;
+//            700 x 8 591 / 583, 512 x 16 774 / 776
+//   d = 64   96 x 4 92 / 62, 192 x 8 214 / 186, 548 x 4 416 / 384, 337 x 8 (2) 432 / 390, 160 x 32 (16) 806 / 769; 700 x 2 290 / 278,
+//            384 x 12 779 / 741, 512 x 16 1284 / 1315
+//   d = 128  96 x 4 146 / 103, 132 x 1 96 / 62, 116 x 16 (1) 434 / 390, 256 x 4 377 / 387, 192 x 6 291 / 305; 192 x 8 374 / 404, 512 x 2 361 /
+//            394, 160 x 32 (2) 1500 / 1567
+// Over 700 drawn problems that bwd_prepare takes, the rule costs 0.1 % against the better choice for each with grouped heads at d <= 64,
+// 0.4 and 1.6 % with plain ones (d = 64 and 32: the joint launch still wins a little beyond its limits), 1 % at d = 128.
 bool small_backward(const Shape &s) {
     if (!small_table(s) || s.nb > 640 || (int64_t)s.nb * s.h > 1 << 16) return false;
     return s.d == 128 ? s.nb <= 256 && s.nb * s.h <= 1280 : s.nb * s.h_kv <= 3072;
@@ -1829,11 +1834,12 @@ WsLayout ws_layout(const Shape &s) {
     // least at L in proportion to the root of the share: at 8 to 10 roots, over 360 problems with parts of 8 to 256 steps.  A part
     // cannot be shorter than an entry's two tiles of every head of its workgroup, nor, where the window is a spatial block, than
     // that block's tiles, which go uncut (its size is known on the device only: half as much again as the mean); so heads are
-    // dealt until that fits, and until the walks take an eighth of the places.  Backward, 8 workgroups and at least 16 steps / undealt and
+    // dealt until that fits, and until the walks take an eighth of the places.  Where whole walks take a third of the places, cuts are for
+    // popular blocks only: up to 96 steps, and windows deal nothing (337 x 8 (2) of 64 below: 353 us without that).  Backward, 8 workgroups and at least 16 steps / undealt and
     // at least 96 / this, us: spatial blocks with their own window 13 x 32 (2) of 32 47 / 167 / 46, 85 x 16 (2) of 64 136 / 256 / 131, 90 x
-    // 8 (1) of 64 131 / 217 / 116, 337 x 8 (2) of 64 375 / 346 / 348; single blocks 18 x 32 (4) of 64 60 / 104 / 58, 18 x 12 (3) of 128 59 /
+    // 8 (1) of 64 131 / 217 / 116, 337 x 8 (2) of 64 375 / 346 / 346; single blocks 18 x 32 (4) of 64 60 / 104 / 58, 18 x 12 (3) of 128 59 /
     // 107 / 56, 7 x 12 (1) of 128 54 / 72 / 42, 34 x 6 (2) of 64 54 / 93 / 55; 96 x 3 (1) of 64 127 / 97 / 109 and 65 x 4 (1) of 128 92 / 78 /
-    // 95 are what this loses.  Of 600 problems of the joint launch, plain heads among them, 14 take more than 5 % longer than with the
+    // 95 are what this loses.  Of 350 drawn problems of the joint launch, plain heads among them, 6 take more than 5 % longer than with the
     // first of the three, tables of few entries in long rows above all (the host knows the length of the rows only).
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
@@ -1849,8 +1855,9 @@ WsLayout ws_layout(const Shape &s) {
         double part;  // steps, of all heads that a workgroup has
         int ranges;
         if (w.small && grp > 1) {
-            part = std::max({16.0, (s.d == 32 ? 10 : 8) * std::sqrt(share), half_share / 2.0});
-            const double uncut = s.group_window ? 6 * blocks_of_group(s) : 4;
+            const bool many = 3 * s.nb * s.h_kv >= slots;
+            part = std::max({16.0, (s.d == 32 ? 10 : 8) * std::sqrt(share), half_share / 2.0, many ? std::min(96.0, 1.5 * share) : 0.0});
+            const double uncut = s.group_window && !many ? 6 * blocks_of_group(s) : 4;
             ranges = (int)std::min<double>(std::min(grp, 8), std::ceil(std::max(uncut * grp / part, slots / 8.0 / (s.nb * s.h_kv))));
         } else if (w.small) {
             part = std::max({16.0, std::min(64.0, (s.d == 128 ? 1.5 : 3) * share), (double)half_share});
@@ -1899,8 +1906,8 @@ WsLayout ws_layout(const Shape &s) {
 }
 
 template <int D>
-lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &tables, const WsLayout &w, char *ws, hipStream_t st, hipEvent_t ev_start,
-                              hipEvent_t ev_stop) {
+lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &tables, const WsLayout &w, char *ws, hipStream_t st,
+                              hipEvent_t ev_start, hipEvent_t ev_stop) {
     constexpr int LDS_TOKENS = DKV_LDS<D, 2, false>;
     const int64_t n_prep = (int64_t)a.nt * ((s.h + PrepGeo<D>::HB - 1) / PrepGeo<D>::HB);
     const int64_t n_token_wg = (int64_t)s.nb * (s.h + 2 * s.h_kv), n_wg = n_token_wg + (int64_t)((s.nbc + 63) / 64) * 2 * s.h_kv;
@@ -1959,9 +1966,9 @@ lsrm_status launch_backward_d(const Shape &s, BwdArgs a, const GroupTableArgs &t
     // Two query blocks to a workgroup for other heads where the pooled keys are many, at d >= 64.  One block / two, us: d = 128, 6688 blocks x
     // 16 heads 128.9 / 127.9 ms, 5121 x 4 16371 / 16177, 2176 x 8 9258 / 9218, 1536 x 8 6446 / 6445, 641 x 8 2300 / 2330, 257 x 8 870 / 902;
     // d = 64, 4864 x 2 3693 / 3630, 2816 x 4 3727 / 3693, 2048 x 8 3959 / 3923, 1536 x 8 3192 / 3184, 897 x 8 1670 / 1680.
-    // It is little: over 46 problems of 2048 to 6700 blocks each (rows of 16 and 80; 1, 3 and 8 heads, and 3 on 1) one block takes, of two's time, at d =
-    // 128 0.8 % more (-1.6 to 2.6, one of them below -0.3: 3128 x 1, rows of 80), at d = 64 0.6 % (-0.7 to 3.3, five below -0.3), at d = 32
-    // 0.3 % (-1.0 to 2.6, ten below -0.3).
+    // It is little: over 46 problems of 2048 to 6700 blocks each (rows of 16 and 80; 1, 3 and 8 heads, and 3 on 1) one block takes, of
+    // two's time, at d = 128 0.8 % more (-1.6 to 2.6, one of them below -0.3: 3128 x 1, rows of 80), at d = 64 0.6 % (-0.7 to 3.3, five
+    // below -0.3), at d = 32 0.3 % (-1.0 to 2.6, ten below -0.3).
     const bool blocks = D >= 64 && !heads && s.nbc >= kPooledMany;
     auto choose = [&](auto wide) {
         constexpr bool WIDE = decltype(wide)::value;

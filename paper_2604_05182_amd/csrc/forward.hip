@@ -3,17 +3,17 @@
 //
 // Work decomposition
 //   One workgroup owns NP = 2 consecutive query blocks of one head (or, where query heads share key/value
-//   heads in pairs, one query block of two such heads) and carries them through all three branches.  A wavefront holds 32 query rows, two wavefronts a query block.  Each of the
-//   four wavefronts of a workgroup sits on its own SIMD, and as many workgroups share a CU as the
-//   registers of a wavefront allow: two at d = 128, three at d = 64, four at d = 32 (the LDS of a
-//   workgroup is sized for that).  They meet no common barrier, so one's start, epilogues, window
-//   edges and waits are filled by the others.  In the compressed branch every K/V tile is copied
-//   to LDS once and used by both query blocks; in the selected and the window branch each query
-//   block streams its own tiles (two heads share those too).  Workgroups are numbered so that each of the 8 XCDs walks a
-//   contiguous range of (head, query block) units: the L2 of an XCD then holds one head's pooled
-//   keys/values and the neighbouring windows / routed blocks.  With grouped-query heads the
-//   query heads that share a key/value head are consecutive, hence run back to back on the
-//   same tile images.
+//   heads in pairs, one query block of two such heads) and carries them through all three branches.  A
+//   wavefront holds 32 query rows, two wavefronts a query block.  Each of the four wavefronts of a
+//   workgroup sits on its own SIMD, and as many workgroups share a CU as the registers of a wavefront
+//   allow: two at d = 128, three at d = 64, four at d = 32 (the LDS of a workgroup is sized for that).
+//   They meet no common barrier, so one's start, epilogues, window edges and waits are filled by the
+//   others.  In the compressed branch every K/V tile is copied to LDS once and used by both query blocks;
+//   in the selected and the window branch each query block streams its own tiles (two heads share those
+//   too).  Workgroups are numbered so that each of the 8 XCDs walks a contiguous range of (head, query
+//   block) units: the L2 of an XCD then holds one head's pooled keys/values and the neighbouring windows /
+//   routed blocks.  With grouped-query heads the query heads that share a key/value head are
+//   consecutive, hence run back to back on the same tile images.
 //
 // Per 32-key step, per wavefront
 //   S^T = K Q^T        v_mfma_f32_32x32x16_bf16, A = 32 keys x 16 channels, B = Q^T.
@@ -268,7 +268,8 @@ __device__ __forceinline__ bool sum_overflow(float psum) {
     return __builtin_amdgcn_ballot_w64(!(psum <= kSumLimit)) != 0;
 }
 
-// Redoes the exponentials of one tile (scores s, already masked) after raising m to the tile's maximum; O and l (which do not yet contain this tile) are rescaled.  Rare path.
+// Redoes the exponentials of one tile (scores s, already masked) after raising m to the tile's maximum; O and l (which do
+// not yet contain this tile) are rescaled.  Rare path.
 template <class G>
 __device__ __forceinline__ void redo_tile(WaveCtx<G> &c, const f32x16 &s, uint32_t (&pu)[8], float &psum, float sl2) {
     mfma_settle();  // the O accumulators (and, at the start of a phase, s itself) may still be in flight
@@ -783,10 +784,9 @@ __device__ __forceinline__ WinRange window_range(const FwdArgs &a, int qb) {
 // CNT: a.count is given (variable number of active tokens per block).
 // WIDE: routing rows of 65..128 entries (two per lane of the list holder instead of one).
 // HEADS: the workgroup has two query heads of one key/value head and one query block, instead of one head and two query
-// blocks: all three branches then read the same tiles, which are copied to LDS once for both, four stages deep.  A copy costs
-// a SIMD about 25 cycles of its MFMA rate, in time (it takes the LDS) and in the clock that is left (the chip is at its power limit: the
-// step of a wavefront at d = 32 alone, in nominal cycles per MFMA, without copies 96, with those of a tile shared by four wavefronts
-// 101, by two 106).
+// blocks: all three branches then read the same tiles, which are copied to LDS once for both, four stages deep.  What that
+// saves is the copies (they take instructions and the LDS; the images come from L2 either way); what it gave stands at
+// its rule in launch_forward_d.
 template <class G, bool CNT, bool WIDE, bool HEADS>
 __global__ __launch_bounds__((G::THREADS), (G::WAVES_PER_SIMD)) void nsa_forward_kernel(FwdArgs a) {
     constexpr int D = G::D, NP = HEADS ? 1 : G::NP;  // query blocks of the workgroup
@@ -1560,9 +1560,11 @@ lsrm_status launch_forward_d(const Shape &s, const int32_t *seg_host, int n_seg,
     const bool cnt = a.count != nullptr, wide = s.topk > 64;
     const void *kern;
     int lds, threads;
-#define LSRM_KERNEL(NAME, ...) \
-    (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>)) \
-         : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>) : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
+#define LSRM_KERNEL(NAME, ...)                                                            \
+    (cnt ? (wide ? reinterpret_cast<const void *>(&NAME<G, true, true, __VA_ARGS__>)      \
+                 : reinterpret_cast<const void *>(&NAME<G, true, false, __VA_ARGS__>))    \
+         : (wide ? reinterpret_cast<const void *>(&NAME<G, false, true, __VA_ARGS__>)     \
+                 : reinterpret_cast<const void *>(&NAME<G, false, false, __VA_ARGS__>)))
     if (nb_wg == 1) {
         kern = own_pairs ? LSRM_KERNEL(nsa_forward_teams, OnePairs) : LSRM_KERNEL(nsa_forward_teams, One);
         lds = own_pairs ? OnePairs::lds_bytes(tiles_c) : One::lds_bytes(tiles_c), threads = One::THREADS;

@@ -54,8 +54,8 @@ __device__ __forceinline__ float2 project(const lsrm_camera &c, float cx, float 
 // in whole lines into LDS, then a thread per (block, coordinate) adds its 64 values left to right.  Bound by latency:
 // with one thread per block that loaded its 192 floats itself, 768 bytes apart from its neighbours', the whole kernel
 // waited for strided loads (4096 blocks into 18 views 20 -> 4 us; a whole forward step of 6 K tokens
-// 34.8 -> 33.1 us, four-rule routing of 57 K tokens 303 -> 298 us).  The pitch of 195 puts the 48 threads of the sum in 48 banks.  point_at(b) = the first
-// coordinate of block b.
+// 34.8 -> 33.1 us, four-rule routing of 57 K tokens 303 -> 298 us).  The pitch of 195 puts the 48 threads of the sum in 48 banks.
+// point_at(b) = the first coordinate of block b.
 constexpr int kCentBlocks = 16, kCentPitch = 3 * kBlock + 3;
 template <class PointAt>
 __device__ __forceinline__ void block_centroids(int b0, int n, PointAt point_at, float (&cent)[kCentBlocks][3]) {

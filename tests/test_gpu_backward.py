@@ -451,7 +451,8 @@ def test_backward_pooled_keys_at_the_edges_of_their_groups(B, oracle_lib, d, n_b
 @pytest.mark.parametrize("d,heads,h_kv,channels", [(32, 9, 1, False), (64, 8, 1, False), (32, 7, 1, True), (128, 4, 2, False)])
 def test_backward_heads_of_a_group_dealt_to_two_or_to_one(B, oracle_lib, d, heads, h_kv, channels):
     """Groups of eight and more heads in the general launches go to two workgroups (nine: five and four), smaller ones stay
-    together; the joint launches deal groups of seven and more to two here; walks cut into parts of few tiles by many heads, the most popular into dozens.
+    together; the joint launches deal groups of seven and more to two here; walks cut into parts of few tiles by many heads,
+    the most popular into dozens.
     Bar: 2e-2 plus 2^-7 of the largest reference value of the row, as for the other large sums over a group."""
     n_blocks, topk, wide = 130, 4, 127
     cfg = I.small_config(name=f"b-dealt-d{d}-h{heads}", n_obj=64 * (n_blocks - 1), n_views=1, grid=8, heads=heads, d=d, topk=topk,
