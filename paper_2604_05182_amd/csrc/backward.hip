@@ -1826,7 +1826,7 @@ WsLayout ws_layout(const Shape &s) {
     // except for large groups, where two workgroups' images of q and dout are nearer to each other in memory: those are dealt to
     // two (as long as the sums stay within 2 GiB of workspace).  8 workgroups and half a share / this, us: 2069 blocks, 6 heads on 2
     // of 128 9285 / 8120, 2553 x 6 (1) of 32 3190 / 3060, 3307 x 4 (2) of 128 8390 / 7790; 3072 x 32 (2) of 32 32024 / 31900, undealt
-    // 32900; spatial blocks with their own window, 115 x 16 (4) of 128 371 / 361 (with parts of at least 16 steps 422).
+    // 32900; spatial blocks with their own window, 115 x 16 (4) of 128 381 / 364 (with parts of at least 16 steps 430).
     //
     // The joint launch, plain heads: at least half a share as well, and 16 to 64 steps, the fewer the less there is to do (backward, parts
     // of at least 16 steps / this, us: 174 x 2 of 64 195 / 149, 178 x 4 of 32 189 / 150, 99 x 1 of 128 120 / 100, 202 x 1 of 64 85 / 75).
@@ -1835,12 +1835,14 @@ WsLayout ws_layout(const Shape &s) {
     // cannot be shorter than an entry's two tiles of every head of its workgroup, nor, where the window is a spatial block, than
     // that block's tiles, which go uncut (its size is known on the device only: half as much again as the mean); so heads are
     // dealt until that fits, and until the walks take an eighth of the places.  Where whole walks take a third of the places, cuts are for
-    // popular blocks only: up to 96 steps, and windows deal nothing (337 x 8 (2) of 64 below: 353 us without that).  Backward, 8 workgroups and at least 16 steps / undealt and
-    // at least 96 / this, us: spatial blocks with their own window 13 x 32 (2) of 32 47 / 167 / 46, 85 x 16 (2) of 64 136 / 256 / 131, 90 x
-    // 8 (1) of 64 131 / 217 / 116, 337 x 8 (2) of 64 375 / 346 / 346; single blocks 18 x 32 (4) of 64 60 / 104 / 58, 18 x 12 (3) of 128 59 /
-    // 107 / 56, 7 x 12 (1) of 128 54 / 72 / 42, 34 x 6 (2) of 64 54 / 93 / 55; 96 x 3 (1) of 64 127 / 97 / 109 and 65 x 4 (1) of 128 92 / 78 /
-    // 95 are what this loses.  Of 350 drawn problems of the joint launch, plain heads among them, 6 take more than 5 % longer than with the
-    // first of the three, tables of few entries in long rows above all (the host knows the length of the rows only).
+    // popular blocks only: up to 96 steps, and windows deal nothing (337 x 8 (2) of 64 below: 353 us without that).  Backward, 8
+    // workgroups and at least 16 steps / undealt and up to 96 / this, us: spatial blocks with their own window 13 x 32 (2) of 32 48 / 167 /
+    // 46, 85 x 16 (2) of 64 139 / 257 / 133, 90 x 8 (1) of 64 131 / 219 / 116, 337 x 8 (2) of 64 375 / 346 / 346; single blocks 18 x 32 (4)
+    // of 64 60 / 104 / 58, 18 x 12 (3) of 128 59 / 108 / 56, 7 x 12 (1) of 128 54 / 72 / 44, 34 x 6 (2) of 64 53 / 93 / 54; 96 x 3 (1) of 64
+    // 126 / 96 / 109 and 65 x 4 (1) of 128 91 / 78 / 94 are what this loses.  Of 800 drawn problems of the joint launch, plain heads among
+    // them, the second takes more than 5 % longer than the first in 122 (20 % in 65), this in 25 (20 % in one), tables of few entries in long
+    // rows above all: the host knows the length of the rows only.  On average this is 4.5 % faster than the first, 4 % than the second.
+    // (Walks cut only where they are a quarter or a half longer than a part: slower.)
     {
         const int slots = 256 * (s.d == 128 ? 2 : s.d == 64 ? 6 : 8);  // workgroups the chip holds
         const int grp = s.h / s.h_kv;
