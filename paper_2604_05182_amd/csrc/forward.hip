@@ -631,9 +631,13 @@ __device__ __forceinline__ void run_tiles(WaveCtx<G> &c, int n_steps, const Tile
         pv_drain<G>(c, vq, P[0], v_last);
         done = 2;
     }
-    for (int t = done; !Tiles::MEET && t <= n_steps; ++t) {
-        __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
-        wg_barrier();
+    if constexpr (Tiles::MEET) {
+        tiles.leave();
+    } else {
+        for (int t = done; t <= n_steps; ++t) {
+            __builtin_amdgcn_s_waitcnt(vm_lgkm_imm(0));
+            wg_barrier();
+        }
     }
 }
 
@@ -1051,10 +1055,15 @@ struct TeamTiles {
         if (!TM::PAIRS || n_copied > 0) issue_part(src(tau) + G::K_BYTES, stage(tau) + G::K_BYTES, VI);
     }
     // The barrier of a team: a wavefront says that it has come to step t (its copies and reads are waited for) and looks until the
-    // other has, which runs as many steps.
+    // other has, which runs as many steps.  After its last it says so for all: each has read the routing row for itself, and if a
+    // caller lets the table be written meanwhile, the rows may differ and the result is worthless, but no wavefront may wait for ever.
+    __device__ __forceinline__ void say(int t) const {
+        asm volatile("ds_write_b32 %0, %1" ::"v"((uint32_t)(uintptr_t)steps + 4 * sub), "v"(t) : "memory");
+    }
+    __device__ __forceinline__ void leave() const { say(0x7fffffff); }
     __device__ __forceinline__ void meet(int t) const {
         const uint32_t at = (uint32_t)(uintptr_t)steps;
-        asm volatile("ds_write_b32 %0, %1" ::"v"(at + 4 * sub), "v"(t + 1) : "memory");
+        say(t + 1);
         int other;
         do {
             asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(other) : "v"(at + 4 * (1 - sub)) : "memory");
